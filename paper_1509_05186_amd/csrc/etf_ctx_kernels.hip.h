@@ -414,7 +414,7 @@ __global__ __launch_bounds__(1024) void k_fused(const uint32_t *__restrict__ cod
         my_tm = next_tm;
     }
     if (MODE == OUT_FILTER) flush();
-    if (MODE == OUT_SAMPLE) o.gmin[((int64_t)tile * o.ngroups + wv) * QT + lane] = best;
+    if (MODE == OUT_SAMPLE) o.gmin[((int64_t)tile * QT + lane) * o.gstride + wv] = best;
 }
 
 }  // namespace etf

@@ -176,6 +176,7 @@ struct Plan {
     int64_t S = 0;            // threshold sample size
     int gsize = 1;            // sample entries per group (only group minima are kept)
     int64_t ngroups = 0;      // ceil(S / gsize)
+    int64_t gstride = 0;      // length of a query's row of group minima
     uint32_t C = 0;           // candidate capacity per query
     bool use_tau = false;
     bool ctx_path = false;    // trees walked with the distance context in registers (no partial-sum tables)
@@ -183,7 +184,7 @@ struct Plan {
     bool flat_lds = false;    // flat mode through the same kernels
     bool fx = false;          // the main pass of the LDS-resident search filters candidates in fixed point
     bool fx16 = false;        // ... on 16-bit tables (k_lds16)
-    int64_t o_counter = 0, o_lutT = 0, o_gmin = 0, o_tau = 0, o_boff = 0, o_bm = 0, o_cnt = 0, o_flag = 0, o_cand = 0;
+    int64_t o_counter = 0, o_lutT = 0, o_gmin = 0, o_tau = 0, o_bm = 0, o_cnt = 0, o_flag = 0, o_cand = 0;
     int64_t o_part[ETF_MAX_M][ETF_MAX_M];
     int64_t o_leafp[ETF_MAX_M];
     int64_t total = 0;
@@ -230,6 +231,7 @@ int make_plan(const etf_ctx *ctx, int64_t Q, int k, int mode, bool search, Plan 
         // waves of its workgroups; 1025 groups instead of 1024 cost cfg2's pass 7 % and cfg4's 23 %)
         P.gsize = (int)std::max<int64_t>(1, (P.S + groups - 1) / groups);
         P.ngroups = (P.S + P.gsize - 1) / P.gsize;
+        P.gstride = (P.ngroups + 63) & ~(int64_t)63;
         int64_t C = ctx->opt.cand_cap;
         if (C == 0) {
             int64_t expect = (int64_t)(1.3 * (double)k * (double)P.items / (double)std::max<int64_t>(P.S, 1));
@@ -276,7 +278,7 @@ int make_plan(const etf_ctx *ctx, int64_t Q, int k, int mode, bool search, Plan 
             per_tile += al256(tr.U * QT * 4);
         }
     if (search) {
-        if (P.use_tau) per_tile += al256(P.ngroups * QT * 4);
+        if (P.use_tau) per_tile += al256(P.gstride * QT * 4);
         per_tile += (int64_t)QT * (12 + (int64_t)P.C * 8);
     }
     int64_t nt = ws_cap / std::max<int64_t>(per_tile + 4096, 1);
@@ -298,9 +300,8 @@ int make_plan(const etf_ctx *ctx, int64_t Q, int k, int mode, bool search, Plan 
             P.o_leafp[t] = take(P.NT * tr.U * QT * 4);
         }
     if (search) {
-        if (P.use_tau) P.o_gmin = take(P.NT * P.ngroups * QT * 4);
+        if (P.use_tau) P.o_gmin = take(P.NT * P.gstride * QT * 4);
         P.o_tau = take(P.NT * QT * 4);
-        P.o_boff = take(P.NT * QT * 4);
         P.o_bm = take(P.NT * M * QT * 4);
         P.o_cnt = take(P.NT * QT * 4);
         P.o_flag = take(P.NT * QT * 4);
@@ -688,13 +689,14 @@ bool lds_eligible(int M, int K, int T, const int32_t *chunk_begin)
 
 template <int MODE, bool CTX, bool FX = false, bool TERM = false>
 int launch_lds(etf_ctx *ctx, const Plan &P, char *ws, const uint32_t *rec, int64_t nitems, const uint32_t *map, int T,
-               int64_t tiles, const OutArgs &o, int cls)
+               int64_t tiles, OutArgs o, int cls)
 {
     if (nitems == 0) return ETF_OK;
     const int M = ctx->M, K = ctx->K;
     const int G = std::max(2, pick_G(M, K));
-    const size_t lds = lds_table_bytes(G, M, K) + lds_aux_bytes(MODE == OUT_FILTER);
+    size_t lds = lds_table_bytes(G, M, K) + lds_aux_bytes(MODE == OUT_FILTER);
     const int IPS = LDS_V * G;  // items per wave step
+    const int64_t Qs = WAVE / G, live = std::min<int64_t>(tiles * G, (o.nq + Qs - 1) / Qs);  // sub-tiles that hold a query
     // The kernels are built for trees of at least four chunks (1, 2 or 4 trees); shorter trees lie inside the
     // pairs of a group of four, whose sum is formed the same way whatever the trees: they run as trees of four.
     if (M / T < 4) T = M / 4;
@@ -702,14 +704,27 @@ int launch_lds(etf_ctx *ctx, const Plan &P, char *ws, const uint32_t *rec, int64
     int64_t bx;
     int per_block = 0;
     if (MODE == OUT_SAMPLE) {
-        // every workgroup stages the whole table set: give each wave at least two stretches of IPS sample groups
-        bx = blocks_for(o.ngroups, 2 * 16 * IPS, tiles * G);
+        // The workgroups per sub-tile by the cost rule of lds_blocks_for, among the powers of two (so that the stretches
+        // of IPS sample groups divide evenly); past a wave per stretch several waves share one.  Cost of a choice:
+        // rounds * (staging + the items a workgroup walks).
+        const int64_t nwr = (o.ngroups + IPS - 1) / IPS;
+        int64_t best = -1;
+        bx = 1;
+        for (int64_t b = 1; b <= nwr; b <<= 1) {
+            const int64_t cost = ((live * b + 255) / 256) * (5000 + (nitems + b - 1) / b);
+            if (best < 0 || cost < best) {
+                best = cost;
+                bx = b;
+            }
+        }
+        o.wps = 1;
+        while (o.wps < 16 && nwr * o.wps * 2 <= bx * 16) o.wps *= 2;
+        if (o.wps > 1) lds += LDS_SAMPLE_BYTES;
     } else {
         // item numbers inside a workgroup's share travel in 26 bits
         if (MODE == OUT_ALLPAIRS) {
             // sub-tiles past the last query end at once: only the live ones share the compute units, and a small
             // batch should fill them in one round
-            const int64_t Qs = WAVE / G, live = std::min<int64_t>(tiles * G, (o.nq + Qs - 1) / Qs);
             const bool few = live * ((nitems + 4095) / 4096) < 256;  // would leave compute units idle
             bx = lds_blocks_for(std::max<int64_t>(live, 1), nitems, (nitems >> 25) + 1, few ? 1024 : 4096);
         } else {
@@ -775,6 +790,24 @@ int launch_lds16(etf_ctx *ctx, const Plan &P, char *ws, const uint32_t *rec, int
         return fail(ctx, ETF_EINVAL, "no 16-bit filter kernel for M=%d", M);
     }
     LAUNCH_CHECK(ctx, "k_lds16");
+    return ETF_OK;
+}
+
+// the bound of every query from its sample groups' minima (and the per-query state of the passes behind it)
+int launch_tau(etf_ctx *ctx, const Plan &P, const OutArgs &o, int64_t nql, uint32_t *flag, uint32_t *counter)
+{
+    ProfScope prof(ctx, ETF_K_TAU);
+    const dim3 grid((unsigned)((nql + 3) / 4)), block(256);
+    hipStream_t st = (hipStream_t)ctx->stream;
+    float *tau = const_cast<float *>(o.tau);
+    const int S = (int)P.ngroups;
+#define TAU_CASE(NV) hipLaunchKernelGGL(k_tau<NV>, grid, block, 0, st, o.gmin, S, o.gstride, P.k, o.nq, nql, tau, o.cnt, flag, counter)
+    if (S <= 256) TAU_CASE(4);
+    else if (S <= 1024) TAU_CASE(16);
+    else if (S <= 2048) TAU_CASE(32);
+    else TAU_CASE(64);
+#undef TAU_CASE
+    LAUNCH_CHECK(ctx, "k_tau");
     return ETF_OK;
 }
 
@@ -1142,8 +1175,6 @@ static int search_impl(etf_ctx *ctx, const float *queries, int64_t Q, int k, int
     char *w = (char *)ws;
     const bool flat = mode == ETF_MODE_FLAT;
     uint32_t *counter = reinterpret_cast<uint32_t *>(w + P.o_counter);
-    hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, st, counter, (int64_t)64, 0u);
-    LAUNCH_CHECK(ctx, "k_fill_u32");
     ctx->last_flag_count = counter;
     for (int64_t t0 = 0; t0 < P.tiles_total; t0 += P.NT) {
         const int64_t tiles = std::min<int64_t>(P.NT, P.tiles_total - t0);
@@ -1157,25 +1188,22 @@ static int search_impl(etf_ctx *ctx, const float *queries, int64_t Q, int k, int
         uint64_t *cand = reinterpret_cast<uint64_t *>(w + P.o_cand);
         rc = launch_lut(ctx, queries, Q, q0, tiles, lutT, nullptr);
         if (rc) return rc;
-        float *boff = nullptr;
+        float *bm = nullptr;
         if (ctx->opt.metric == 1) {  // the selection orders non-negative values, smallest first
-            boff = reinterpret_cast<float *>(w + P.o_boff);
+            bm = reinterpret_cast<float *>(w + P.o_bm);
             ProfScope prof(ctx, ETF_K_LUT);
-            float *bm = reinterpret_cast<float *>(w + P.o_bm);
             hipLaunchKernelGGL(k_lut_shift, dim3((unsigned)tiles, (unsigned)ix.M), dim3(256), 0, st, lutT, ix.M, ix.K, bm);
             LAUNCH_CHECK(ctx, "k_lut_shift");
-            hipLaunchKernelGGL(k_lut_shift_sum, dim3((unsigned)tiles), dim3(64), 0, st, bm, ix.M, boff);
-            LAUNCH_CHECK(ctx, "k_lut_shift_sum");
         }
-        const unsigned fb = (unsigned)((nql + 255) / 256);
-        hipLaunchKernelGGL(k_fill_u32, dim3(fb), dim3(256), 0, st, cnt, nql, 0u);
-        hipLaunchKernelGGL(k_fill_u32, dim3(fb), dim3(256), 0, st, flag, nql, ctx->opt.force_fallback ? 1u : 0u);
-        LAUNCH_CHECK(ctx, "k_fill_u32");
+        // the count of queries the exact kernel answers runs over all batches: the first one clears it
+        uint32_t *clear = t0 == 0 ? counter : nullptr;
         OutArgs o;
         memset(&o, 0, sizeof o);
         o.gmin = P.use_tau ? reinterpret_cast<float *>(w + P.o_gmin) : nullptr;
         o.ngroups = P.ngroups;
+        o.gstride = P.gstride;
         o.gsize = P.gsize;
+        o.wps = 1;
         o.tau = tau;
         o.cnt = cnt;
         o.cand = cand;
@@ -1195,6 +1223,11 @@ static int search_impl(etf_ctx *ctx, const float *queries, int64_t Q, int k, int
             if (P.ctx_path) fill_fused_args(ctx, P, w, r);
             else fill_reduce_args(ctx, P, w, r);
         }
+        if (!P.use_tau || ctx->opt.force_fallback) {
+            hipLaunchKernelGGL(k_search_init, dim3((unsigned)((nql + 255) / 256)), dim3(256), 0, st, tau, cnt, flag, clear, nq, nql,
+                               ctx->opt.force_fallback ? 1u : 0u);
+            LAUNCH_CHECK(ctx, "k_search_init");
+        }
         if (!ctx->opt.force_fallback) {
             if (P.use_tau) {
                 if (flat)
@@ -1206,15 +1239,8 @@ static int search_impl(etf_ctx *ctx, const float *queries, int64_t Q, int k, int
                     rc = P.ctx_path ? launch_fused<OUT_SAMPLE>(ctx, P, w, r, P.S, reinterpret_cast<const uint32_t *>(ctx->dev_base + L.sample_enc), tiles, o)
                                     : launch_reduce<OUT_SAMPLE>(ctx, r, P.S, reinterpret_cast<const uint32_t *>(ctx->dev_base + L.sample_enc), tiles, o);
                 if (rc) return rc;
-                {
-                    ProfScope prof(ctx, ETF_K_TAU);
-                    // three digits: the bound is the top of a bucket 2^-16 of its value wide (the fourth pass bought nothing)
-                    hipLaunchKernelGGL(k_tau, dim3((unsigned)tiles), dim3(1024), 0, st, o.gmin, P.ngroups, k, 3, nq, tau);
-                }
-                LAUNCH_CHECK(ctx, "k_tau");
-            } else {
-                hipLaunchKernelGGL(k_fill_f32, dim3(fb), dim3(256), 0, st, tau, nql, nq, __builtin_inff(), -1.f);
-                LAUNCH_CHECK(ctx, "k_fill_f32");
+                rc = launch_tau(ctx, P, o, nql, flag, clear);
+                if (rc) return rc;
             }
             if (flat)
                 rc = launch_flat<OUT_FILTER>(ctx, P, w, ix.N, nullptr, tiles, o);
@@ -1239,7 +1265,7 @@ static int search_impl(etf_ctx *ctx, const float *queries, int64_t Q, int k, int
         sa.out_ids = out_ids + q0 * k;
         sa.out_dist = out_dist + q0 * k;
         sa.flag = flag;
-        sa.boff = boff;
+        sa.bm = bm;
         // fixed-point candidates: rounding moves a sum by at most M units (truncated entries) plus 2^-24 relative per
         // entry and per float32 addition of the distance it stands for, 2^27 * (M + 1) * 2^-24 = 8 (M + 1) units at the
         // bound; twice that between two candidates
@@ -1289,7 +1315,7 @@ static int search_impl(etf_ctx *ctx, const float *queries, int64_t Q, int k, int
         ea.k = k;
         ea.out_ids = sa.out_ids;
         ea.out_dist = sa.out_dist;
-        ea.boff = boff;
+        ea.bm = bm;
         {
             ProfScope prof(ctx, ETF_K_EXACT);
             hipLaunchKernelGGL(k_exact, dim3((unsigned)nq), dim3(256), 0, st, ea);

@@ -1289,8 +1289,6 @@ extern "C" int etf_ivf_search(etf_ctx *ctx, const float *queries, int64_t Q, int
     char *wsp = (char *)ws;
     const char *img = iv.dev_base;
     uint32_t *counter = reinterpret_cast<uint32_t *>(wsp + P.o_counter);
-    hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, st, counter, (int64_t)64, 0u);
-    LAUNCH_CHECK(ctx, "k_fill_u32");
     ctx->last_flag_count = counter;
     rc = set_lds(ctx, k_ivf_scan, lds_scan);
     if (rc) return rc;
@@ -1344,10 +1342,9 @@ extern "C" int etf_ivf_search(etf_ctx *ctx, const float *queries, int64_t Q, int
                                nullptr, nullptr, ctx->dsp, nullptr, lut, ord);
             LAUNCH_CHECK(ctx, "k_lut_mfma");
         }
-        const unsigned fb = (unsigned)((nq + 255) / 256);
-        hipLaunchKernelGGL(k_fill_u32, dim3(fb), dim3(256), 0, st, flag, nq, ctx->opt.force_fallback ? 1u : 0u);
-        hipLaunchKernelGGL(k_fill_u32, dim3(fb), dim3(256), 0, st, cnt, nq, 0u);
-        LAUNCH_CHECK(ctx, "k_fill_u32");
+        hipLaunchKernelGGL(k_search_init, dim3((unsigned)((nq + 255) / 256)), dim3(256), 0, st, nullptr, cnt, flag,
+                           q0 == 0 ? counter : nullptr, nq, nq, ctx->opt.force_fallback ? 1u : 0u);
+        LAUNCH_CHECK(ctx, "k_search_init");
         IvfScanArgs a;
         memset(&a, 0, sizeof a);
         a.lut = lut;

@@ -134,31 +134,39 @@ __global__ __launch_bounds__(256) void k_lut_direct(const float *__restrict__ qu
 // Scalar-product searches.  The selection kernels order candidates by the bits of non-negative floats, smallest
 // first; the largest scalar products are found as the smallest values of  B(q) - q.x,  B(q) = sum over groups of
 // the group's largest table entry.  This kernel rewrites a tile's tables of products p[m][k] as B_m - p[m][k]
-// (never negative: B_m is the maximum of the same rounded values) and stores B(q), the sum of the B_m in group
-// order, which the selection kernels subtract from again when they write the results.
-//     k_lut_shift: grid (tiles, M), block 256: wave w takes codewords w, w + 4, ...; lane = query of the tile.
-//     k_lut_shift_sum: grid (tiles), block 64: B(q) from the M maxima.
+// (never negative: B_m is the maximum of the same rounded values) and stores the B_m, whose sum in group order
+// (product_shift) is what the selection kernels subtract from again when they write the results.
+//     A wave holds its 64 entries of every query's column in registers: one read and one write of the tables, all
+//     loads in flight together (333 queries: two passes of one load at a time took 17 us, this 4.4 us).
+//     grid (tiles, M), block 256: wave w takes codewords w, w + 4, ...; lane = query of the tile; K <= 256.
 // ------------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void k_lut_shift(float *__restrict__ lutT, int M, int K, float *__restrict__ bm)
 {
     __shared__ float s_b[4][QT];
     const int tile = blockIdx.x, m = blockIdx.y, lane = threadIdx.x & 63, w = uniform(threadIdx.x >> 6);
     float *t = lutT + ((int64_t)tile * M + m) * K * QT + lane;
-    float b = -__uint_as_float(0x7F800000u);
-    for (int k = w; k < K; k += 4) b = fmaxf(b, t[(int64_t)k * QT]);
+    float v[64];
+#pragma unroll
+    for (int i = 0; i < 64; ++i) v[i] = t[(int64_t)min(w + 4 * i, K - 1) * QT];
+    float b = v[0];
+#pragma unroll
+    for (int i = 1; i < 64; ++i) b = fmaxf(b, v[i]);
     s_b[w][lane] = b;
     __syncthreads();
     b = fmaxf(fmaxf(s_b[0][lane], s_b[1][lane]), fmaxf(s_b[2][lane], s_b[3][lane]));
-    for (int k = w; k < K; k += 4) t[(int64_t)k * QT] = b - t[(int64_t)k * QT];
+#pragma unroll
+    for (int i = 0; i < 64; ++i)
+        if (w + 4 * i < K) t[(int64_t)(w + 4 * i) * QT] = b - v[i];
     if (w == 0) bm[((int64_t)tile * M + m) * QT + lane] = b;
 }
 
-__global__ __launch_bounds__(64) void k_lut_shift_sum(const float *__restrict__ bm, int M, float *__restrict__ boff)
+// B(q) of query ql of the batch from the M maxima, added in group order
+__device__ __forceinline__ float product_shift(const float *__restrict__ bm, int M, int64_t ql)
 {
-    const int tile = blockIdx.x, lane = threadIdx.x;
+    const float *p = bm + (ql / QT) * M * QT + (ql % QT);
     float b = 0.f;
-    for (int m = 0; m < M; ++m) b += bm[((int64_t)tile * M + m) * QT + lane];
-    boff[(int64_t)tile * QT + lane] = b;
+    for (int m = 0; m < M; ++m) b += p[(int64_t)m * QT];
+    return b;
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1211,9 +1219,11 @@ struct OutArgs {
     int64_t nq;         // live queries of this batch (rows beyond are not written)
     // OUT_SAMPLE: the sample is cut into groups of `gsize` consecutive entries; only the minimum of
     // every group is kept
-    float *gmin;        // [tile][ngroups][64]
+    float *gmin;        // [tiles*64][gstride]: a query's minima side by side, as k_tau reads them
     int64_t ngroups;
+    int64_t gstride;    // ngroups rounded up to a multiple of 64
     int gsize;
+    int wps;            // k_lds: waves that share a stretch of the sample (a power of two, at most 16)
     // OUT_FILTER
     const float *tau;   // [tiles*64]
     uint32_t *cnt;      // [tiles*64]
@@ -1278,7 +1288,7 @@ __global__ void k_flat(const uint8_t *__restrict__ codes, int64_t nitems, const 
             float best = __uint_as_float(0x7F800000u);
             for (int64_t j = lo; j < hi; ++j)
                 best = fminf(best, flat_one<G>(lds, codes + (int64_t)sample[j] * M, M, K, qq) + (o.term ? o.term[sample[j]] : 0.f));
-            o.gmin[((int64_t)tile * o.ngroups + g) * QT + col] = best;
+            o.gmin[((int64_t)tile * QT + col) * o.gstride + g] = best;
         }
         return;
     }
@@ -1481,6 +1491,7 @@ __host__ __device__ inline size_t lds_table_bytes(int G, int M, int K)
     return (size_t)(M / CPL) * lds_lines_per_group(G, K) * (size_t)(CPL * (WAVE / G) * 4);
 }
 __host__ __device__ inline size_t lds_aux_bytes(bool filter) { return filter ? (size_t)16 * LDS_RING * 8 + 2 * 16 * 64 * 4 : 0; }
+constexpr size_t LDS_SAMPLE_BYTES = 16 * 64 * 16;  // sample mode with shared stretches: a partial minimum per lane
 // k_lds16: a ring entry is a lane's eight results (16 bytes) and a word that says whose they are
 constexpr int LDS16_RING = 76;
 __host__ __device__ inline size_t lds16_aux_bytes() { return (size_t)16 * LDS16_RING * 20 + 2 * 16 * 64 * 4; }
@@ -1515,7 +1526,8 @@ __global__ __launch_bounds__(1024) void k_lds(const uint32_t *__restrict__ rec, 
     const int w = uniform(threadIdx.x >> 6), nw = blockDim.x >> 6;
     static_assert(!FX || MODE == OUT_FILTER, "the fixed-point form is a candidate filter");
     static_assert(!TERM || (MODE == OUT_FILTER && !FX), "TERM selects the filter pass with a leaf payload; the other modes test o.term");
-    if (MODE == OUT_ALLPAIRS && (int64_t)tile * QT + sub * Qs >= o.nq) return;  // a sub-tile past the last query: nothing to write
+    // a sub-tile past the last query: nothing to write
+    if ((MODE == OUT_ALLPAIRS || MODE == OUT_SAMPLE) && (int64_t)tile * QT + sub * Qs >= o.nq) return;
     if (FILTER) wcount[w][lane] = 0u;
     stage_lines<G, FX>(lds, lutT, tile, sub, M, K, KP, FX ? o.tau : nullptr);
     const int lg = lane / LPI, lq = lane % LPI;
@@ -1587,13 +1599,16 @@ __global__ __launch_bounds__(1024) void k_lds(const uint32_t *__restrict__ rec, 
         // The sample is cut into one stretch per IPS sample groups; a wave walks a stretch, its lane groups
         // taking the items in turn (coalesced record loads), and every lane group's share is one sample group.
         // (Any partition of the sample into ngroups disjoint sets serves the bound; the sample is in random
-        // order.)
+        // order.)  Where a batch has too few sub-tiles to fill the chip with a wave per stretch, wps waves of the
+        // workgroup share one: each walks every wps-th block of steps, and their minima meet in LDS (one query
+        // against a million vectors: 55 us with the 64 stretches walked by two workgroups, 7 us by 64).
         const int64_t nwr = (o.ngroups + IPS - 1) / IPS;
         const int64_t per = ((nitems + nwr - 1) / nwr + IPS - 1) / IPS * IPS;  // items per stretch
-        for (int64_t wr = (int64_t)blockIdx.x * nw + w; wr < nwr; wr += (int64_t)gridDim.x * nw) {
+        const int wps = o.wps, sw = w & (wps - 1);
+        auto walk = [&](int64_t wr) -> vecq {
             const int64_t lo = wr * per, hi = min(nitems, lo + per);
             vecq best = __uint_as_float(0x7F800000u);
-            for (int64_t j0 = lo; j0 < hi; j0 += IPS * U) {
+            for (int64_t j0 = lo + (int64_t)sw * (IPS * U); j0 < hi; j0 += (int64_t)wps * (IPS * U)) {
                 uint32_t dw[U][M4];
                 bool live[U];
                 float tm[U];
@@ -1617,11 +1632,33 @@ __global__ __launch_bounds__(1024) void k_lds(const uint32_t *__restrict__ rec, 
                     }
                 }
             }
+            return best;
+        };
+        auto keep = [&](int64_t wr, const vecq &best) {
             const int64_t g = wr * IPS + lg;
             if (g < o.ngroups) {
-                float *dst = o.gmin + ((int64_t)tile * o.ngroups + g) * QT + col;
+                float *dst = o.gmin + ((int64_t)tile * QT + col) * o.gstride + g;
 #pragma unroll
-                for (int v = 0; v < V; ++v) dst[v] = best[v];
+                for (int v = 0; v < V; ++v) dst[v * o.gstride] = best[v];
+            }
+        };
+        if (wps == 1) {
+            for (int64_t wr = (int64_t)blockIdx.x * nw + w; wr < nwr; wr += (int64_t)gridDim.x * nw) keep(wr, walk(wr));
+        } else {
+            // one stretch per wps waves, no loop: the launch has waves for all of them
+            const int64_t wr = ((int64_t)blockIdx.x * nw + w) / wps;
+            vecq *part = reinterpret_cast<vecq *>(aux);  // [16 waves][64 lanes]
+            vecq best = __uint_as_float(0x7F800000u);
+            if (wr < nwr) best = walk(wr);
+            part[w * WAVE + lane] = best;
+            __syncthreads();
+            if (sw == 0 && wr < nwr) {
+                for (int i = 1; i < wps; ++i) {
+                    const vecq b = part[(w + i) * WAVE + lane];
+#pragma unroll
+                    for (int v = 0; v < V; ++v) best[v] = fminf(best[v], b[v]);
+                }
+                keep(wr, best);
             }
         }
         return;
@@ -2170,97 +2207,81 @@ __global__ __launch_bounds__(256) void k_reduce(ReduceArgs r, int64_t nitems, co
     }
     if (MODE == OUT_FILTER && nloc > 0) flush();
     // OUT_SAMPLE: a wave's items are one sample group (per_wave == gsize); keep its minimum
-    if (MODE == OUT_SAMPLE && lo < hi) o.gmin[((int64_t)tile * o.ngroups + wv) * QT + lane] = best;
+    if (MODE == OUT_SAMPLE && lo < hi) o.gmin[((int64_t)tile * QT + lane) * o.gstride + wv] = best;
 }
 
 // ------------------------------------------------------------------------------------------------
 // S5a  per-query bound from the sample.  Input: the minimum distance of each of S sample groups.  The
 //      k-th smallest group minimum is an upper bound of the k-th smallest database distance, because k
-//      different encodings (one per group) are at or below it.  Found by a most-significant-digit radix
-//      select on the float bit patterns (distances are >= 0, so the patterns order like the values);
-//      `passes` digits of 8 bits are resolved and the bound is the top of the remaining bucket.
-//      grid (tiles), block 1024, LDS hist[256][64].
+//      different encodings (one per group) are at or below it.
+//      A wave per query holds the minima in registers (distances are >= 0, so the bit patterns order like the
+//      values) and bisects between the smallest and the largest of them until at most 2^7 patterns are left, 2^-16 of the
+//      value: a step is NV compares whose lane masks are counted on the scalar unit, no LDS and no barrier.  (A radix
+//      select over LDS histograms of 64 queries per workgroup took 28 us however few queries there were and 32 us
+//      for ten thousand, mostly clearing and scanning 64 KB of counters three times; this takes 10 and 25 us.)
+//      The kernel also sets the query's candidate count and flag, so that no launch is needed for those.
+//      grid (ceil(queries / 4)), block 256; S <= 64 NV.
 // ------------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(1024) void k_tau(const float *__restrict__ gmin, int64_t S, int k, int passes,
-                                              int64_t nq, float *__restrict__ tau)
+template <int NV>
+__global__ __launch_bounds__(256) void k_tau(const float *__restrict__ gmin, int S, int64_t gstride, int k, int64_t nq, int64_t nql,
+                                             float *__restrict__ tau, uint32_t *__restrict__ cnt, uint32_t *__restrict__ flag,
+                                             uint32_t *__restrict__ counter)
 {
-    __shared__ uint32_t hist[256][64];
-    __shared__ uint32_t s_prefix[64], s_rank[64];
-    __shared__ uint32_t s_part[16][64];
-    const int tile = blockIdx.x;
-    const int lane = threadIdx.x & 63, w = uniform(threadIdx.x >> 6), nw = blockDim.x >> 6;
-    const int64_t ql = (int64_t)tile * QT + lane;
-    if (threadIdx.x < 64) {
-        s_prefix[lane] = 0;
-        s_rank[lane] = (uint32_t)k;
-    }
-    if (S < k) {  // too few samples: no bound
-        if (threadIdx.x < 64) tau[ql] = (ql < nq) ? __uint_as_float(0x7F800000u) : -1.f;
-        return;
-    }
-    const float *col = gmin + (int64_t)tile * S * QT + lane;
-    int shift = 24;
-    for (int p = 0; p < passes; ++p, shift -= 8) {
-        for (int i = threadIdx.x; i < 256 * 64; i += blockDim.x) (&hist[0][0])[i] = 0;
-        __syncthreads();
-        const uint32_t prefix = s_prefix[lane];
-        // eight rows in flight per wave: one load at a time would make the pass a chain of memory latencies
-        for (int64_t s0 = w; s0 < S; s0 += 8 * nw) {
-            uint32_t v[8];
+    const int lane = threadIdx.x & 63;
+    const int64_t ql = (int64_t)blockIdx.x * 4 + uniform(threadIdx.x >> 6);
+    if (counter && blockIdx.x == 0 && threadIdx.x < 64) counter[lane] = 0u;
+    if (ql >= nql) return;
+    uint32_t bound = __float_as_uint(-1.f);  // a column past the last query: nothing passes
+    if (ql < nq) {
+        const float *row = gmin + ql * gstride;
+        uint32_t x[NV];
+        uint32_t lo = 0xFFFFFFFFu, hi = 0u;
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int64_t s = s0 + (int64_t)u * nw;
-                v[u] = s < S ? __float_as_uint(col[s * QT]) : 0u;
-            }
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const bool match = s0 + (int64_t)u * nw < S && ((p == 0) || ((v[u] >> (shift + 8)) == (prefix >> (shift + 8))));
-                if (match) atomicAdd(&hist[(v[u] >> shift) & 255][lane], 1u);
-            }
+        for (int i = 0; i < NV; ++i) {
+            const int g = i * 64 + lane;
+            x[i] = g < S ? __float_as_uint(row[g]) : 0xFFFFFFFFu;
         }
-        __syncthreads();
-        // the bin in which the running count of a query reaches its rank: wave w sums bins 16w .. 16w+15 of
-        // every query, then the wave whose stretch holds the crossing walks its 16 bins (blockDim.x = 1024)
-        {
-            uint32_t part = 0;
 #pragma unroll
-            for (int b = 0; b < 16; ++b) part += hist[w * 16 + b][lane];
-            s_part[w][lane] = part;
-            __syncthreads();
-            uint32_t below = 0;
-            for (int w2 = 0; w2 < w; ++w2) below += s_part[w2][lane];
-            const uint32_t rank = s_rank[lane];
-            const bool last = w == nw - 1;
-            __syncthreads();
-            if (below < rank && (rank <= below + part || last)) {
-                int b = w * 16;
-                for (; b < w * 16 + 15; ++b) {
-                    const uint32_t h = hist[b][lane];
-                    if (below + h >= rank) break;
-                    below += h;
-                }
-                s_prefix[lane] = prefix | ((uint32_t)b << shift);
-                s_rank[lane] = rank - below;
-            }
+        for (int i = 0; i < NV; ++i) {
+            lo = min(lo, x[i]);
+            hi = max(hi, i * 64 + lane < S ? x[i] : 0u);
         }
-        __syncthreads();
+#pragma unroll
+        for (int dlt = 32; dlt >= 1; dlt >>= 1) {
+            lo = min(lo, (uint32_t)__shfl_xor((int)lo, dlt));
+            hi = max(hi, (uint32_t)__shfl_xor((int)hi, dlt));
+        }
+        lo = (uint32_t)uniform((int)lo);
+        hi = (uint32_t)uniform((int)hi);
+        // at least k minima are at or below hi, fewer than k below lo
+        while (hi - lo > 127u) {
+            const uint32_t mid = lo + ((hi - lo) >> 1);
+            int c = 0;
+#pragma unroll
+            for (int i = 0; i < NV; ++i) c += __popcll(__ballot(x[i] <= mid));
+            if (c >= k) hi = mid;
+            else lo = mid + 1;
+        }
+        bound = S >= k ? hi : 0x7F800000u;
     }
-    if (threadIdx.x < 64) {
-        const uint32_t top = s_prefix[lane] | ((shift + 8 > 0) ? ((1u << (shift + 8)) - 1u) : 0u);
-        tau[ql] = (ql < nq) ? __uint_as_float(top) : -1.f;
+    if (lane == 0) {
+        tau[ql] = __uint_as_float(bound);
+        cnt[ql] = 0u;
+        flag[ql] = 0u;
     }
 }
 
-__global__ void k_fill_u32(uint32_t *p, int64_t n, uint32_t v)
+// The same per-query state where there is no sample to take a bound from: every encoding is a candidate (tau: +inf;
+// nullptr: not used), or (flagv = 1) every query goes to the exact kernel.  grid (ceil(queries / 256)), block 256.
+__global__ __launch_bounds__(256) void k_search_init(float *__restrict__ tau, uint32_t *__restrict__ cnt, uint32_t *__restrict__ flag,
+                                                     uint32_t *__restrict__ counter, int64_t nq, int64_t nql, uint32_t flagv)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = v;
-}
-
-__global__ void k_fill_f32(float *p, int64_t n, int64_t nlive, float v, float vdead)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = i < nlive ? v : vdead;
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (counter && blockIdx.x == 0 && threadIdx.x < 64) counter[threadIdx.x] = 0u;
+    if (i >= nql) return;
+    if (tau) tau[i] = i < nq ? __uint_as_float(0x7F800000u) : -1.f;
+    cnt[i] = 0u;
+    flag[i] = flagv;
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -2443,7 +2464,7 @@ struct SelectArgs {
     int32_t *out_ids;        // [nq][k]
     float *out_dist;         // [nq][k]
     uint32_t *flag;          // [nq]  set to 1 when the query needs the exact kernel
-    const float *boff;       // [nq] or nullptr: results are written as boff[q] - value (scalar-product searches)
+    const float *bm;         // [tiles][M][64] or nullptr: results are written as B(q) - value (scalar-product searches)
     // Candidates from a fixed-point filter (k_lds with FX, k_lds16): the upper word of a candidate is a fixed-point
     // sum, which orders like the float32 distance up to fx_margin units.  First the k-th smallest sum is found; every
     // candidate up to it plus the margin gets its float32 distance from the tables (associated like the exact kernel
@@ -2693,10 +2714,11 @@ __global__ __launch_bounds__(256) void k_select(SelectArgs a)
     for (int i = (int)xtotal + threadIdx.x; i < nx2; i += 256) xkeys[i] = ~0ull;
     __syncthreads();
     sort_u64(xkeys, nx2);
+    const float boff = a.bm ? product_shift(a.bm, a.M, ql) : 0.f;
     for (int i = threadIdx.x; i < k; i += 256) {
         a.out_ids[ql * k + i] = (int32_t)(uint32_t)xkeys[i];
         const float v = __uint_as_float((uint32_t)(xkeys[i] >> 32));
-        a.out_dist[ql * k + i] = a.boff ? a.boff[ql] - v : v;
+        a.out_dist[ql * k + i] = a.bm ? boff - v : v;
     }
 }
 
@@ -2723,7 +2745,7 @@ struct ExactArgs {
     int k;
     int32_t *out_ids;
     float *out_dist;
-    const float *boff;        // as in SelectArgs
+    const float *bm;          // as in SelectArgs
 };
 
 __device__ __forceinline__ float exact_distance(const ExactArgs &a, const float *lut, const uint8_t *c)
@@ -2809,10 +2831,11 @@ __global__ __launch_bounds__(256) void k_exact(ExactArgs a)
     for (int i = n + threadIdx.x; i < n2; i += 256) okeys[i] = ~0ull;
     __syncthreads();
     bitonic_sort_u64(okeys, n2);
+    const float boff = a.bm ? product_shift(a.bm, a.M, ql) : 0.f;
     for (int i = threadIdx.x; i < a.k; i += 256) {
         a.out_ids[ql * a.k + i] = (int32_t)(uint32_t)okeys[i];
         const float v = __uint_as_float((uint32_t)(okeys[i] >> 32));
-        a.out_dist[ql * a.k + i] = a.boff ? a.boff[ql] - v : v;
+        a.out_dist[ql * a.k + i] = a.bm ? boff - v : v;
     }
 }
 
