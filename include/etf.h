@@ -135,10 +135,10 @@ const char *etf_last_error(const etf_ctx *ctx);
  *                     chunks of every group of four in pairs and agrees with them to rounding.
  *   "encode_kernel"   etf_pq_encode_device (and the residual encoding of etf_ivf_assign_device).  0 (default): the
  *                     K distance evaluations of every (vector, group) on the matrix cores as ||c||^2 - 2 x.c;
- *                     where the smallest is not clearly below the second smallest (by twice a bound on the
- *                     rounding of either form) the float32 rule is evaluated for all K codewords.  1: the float32
+ *                     where the smallest is not clearly below the others (by twice a bound on the rounding of
+ *                     either form) the float32 rule is evaluated for those in question.  1: the float32
  *                     rule for every codeword (needs d/M <= 128).  Both return the same codes, bit for bit
- *   "encode_wide"     1 (default): groups of more than 64 dimensions with aligned rows take the matrix-core kernel
+ *   "encode_wide"     1 (default): groups of more than 128 dimensions with aligned rows take the matrix-core kernel
  *                     that stages both operands through LDS; 0: the general one (operands streamed per lane)
  *   "ivf_coarse_kernel"  etf_ivf_search, distances between queries and centroids.  0 (default): all of them on the
  *                     matrix cores as ||c||^2 - 2 q.c; the cells that can be among the w nearest, given a bound on

@@ -57,6 +57,7 @@ struct ProfScope {
 static void lookup_scratch(int device);
 
 static constexpr int64_t LDS_BUDGET = 128 * 1024;  // bytes of table slices a workgroup may stage
+static constexpr int64_t LDS_BYTES = 160 * 1024;   // LDS of a compute unit
 static constexpr int CUB = 4;                       // items per batch of the register-context kernels (measured best)
 
 // =============================================================================================
@@ -1086,31 +1087,44 @@ extern "C" int etf_pq_encode_device(etf_ctx *ctx, const float *x, int64_t n, uin
     const float *cb = reinterpret_cast<const float *>(ws);
     if (mfma) {
         ProfScope prof(ctx, ETF_K_ENCODE);
-        const bool aligned = (ds & 3) == 0 && (d & 3) == 0 && (reinterpret_cast<uintptr_t>(x) & 15) == 0;
-        if (aligned && ds <= 64 && K <= 256) {
-            float *cc2 = reinterpret_cast<float *>((char *)ws + ((ctx->codebooks.size() * sizeof(float) + 255) & ~(size_t)255));
-            hipLaunchKernelGGL(k_encode_norms, dim3((unsigned)M), dim3(256), 0, st, cb, ds, K, M, cc2);
-            // operands staged in LDS in instruction order; stretches of 128 vectors per workgroup, as many as leave
-            // about eight workgroups per compute unit
-            const int64_t chunks = (n + 127) / 128;
-            const int reps = (int)std::max<int64_t>(1, std::min<int64_t>(16, chunks * M / 2048));
-            const dim3 grid((unsigned)((chunks + reps - 1) / reps), (unsigned)M);
-#define TC_CASE(RL, NB)                                                                                        \
+        if (ds <= 128 && K <= 256) {
+            // one workgroup per compute unit (the operands of as many groups as fit fill its LDS); a small call gives a
+            // workgroup fewer groups, so that its chunks still reach every compute unit
+            const int NB = ds <= 64 ? (ds + 15) / 16 : ds <= 96 ? 6 : 8, NW = NB <= 2 ? 12 : 8;
+            const int fit = (int)((LDS_BYTES - NW * ENC_QUEUE_BYTES) / encode_bf_group_bytes(NB));
+            const int64_t chunks = (n + 31) / 32;
+            const int most = (int)std::max<int64_t>(1, std::min<int64_t>(std::min(fit, M), (M * chunks + 255) / 256));
+            const int gy = (M + most - 1) / most, gs = (M + gy - 1) / gy;
+            const dim3 grid((unsigned)std::min<int64_t>(chunks, std::max(1, 256 / gy)), (unsigned)gy);
+            const size_t lds = encode_bf_lds(NB, gs, NW);
+            const bool wide = (ds & 3) == 0 && (d & 3) == 0 && (reinterpret_cast<uintptr_t>(x) & 15) == 0;
+#define BF_LAUNCH(NB_, W_, NW_)                                                                                \
     {                                                                                                         \
-        const size_t lds = (size_t)256 * NB * 2 * RL * 4;                                                     \
-        int rc2 = set_lds(ctx, k_encode_tc<RL, NB>, lds);                                                     \
+        int rc2 = set_lds(ctx, k_encode_bf<NB_, W_, NW_>, lds);                                               \
         if (rc2) return rc2;                                                                                  \
-        hipLaunchKernelGGL((k_encode_tc<RL, NB>), grid, dim3(256), lds, st, x, n, d, ds, K, M, cb, cc2, codes_out, reps); \
+        hipLaunchKernelGGL((k_encode_bf<NB_, W_, NW_>), grid, dim3(NW_ * 64), lds, st, x, n, d, ds, K, M, cb, codes_out, gs); \
     }
-            if (ds <= 8) TC_CASE(4, 1)
-            else if (ds <= 16) TC_CASE(8, 1)
-            else if (ds <= 32) TC_CASE(8, 2)
-            else TC_CASE(8, 4)
-#undef TC_CASE
-            LAUNCH_CHECK(ctx, "k_encode_tc");
+#define BF_CASE(NB_, NW_)                                                                                      \
+    case NB_:                                                                                                 \
+        if (wide) BF_LAUNCH(NB_, true, NW_)                                                                   \
+        else BF_LAUNCH(NB_, false, NW_)                                                                       \
+        break;
+            switch (NB) {
+                BF_CASE(1, 12)
+                BF_CASE(2, 12)
+                BF_CASE(3, 8)
+                BF_CASE(4, 8)
+                BF_CASE(6, 8)
+                BF_CASE(8, 8)
+                default: return fail(ctx, ETF_EINVAL, "no encoder for %d dimensions per group", ds);
+            }
+#undef BF_LAUNCH
+#undef BF_CASE
+            LAUNCH_CHECK(ctx, "k_encode_bf");
             return ETF_OK;
         }
-        if (aligned && ds > 64 && K <= 256 && (int64_t)127 * d < ((int64_t)1 << 31) && ctx->opt.encode_wide != 0) {
+        const bool aligned = (ds & 3) == 0 && (d & 3) == 0 && (reinterpret_cast<uintptr_t>(x) & 15) == 0;
+        if (aligned && K <= 256 && (int64_t)127 * d < ((int64_t)1 << 31) && ctx->opt.encode_wide != 0) {
             // wide groups: both operands through LDS
             float *cc2 = reinterpret_cast<float *>((char *)ws + ((ctx->codebooks.size() * sizeof(float) + 255) & ~(size_t)255));
             hipLaunchKernelGGL(k_encode_norms, dim3((unsigned)M), dim3(256), 0, st, cb, ds, K, M, cc2);

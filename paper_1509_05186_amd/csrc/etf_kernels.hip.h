@@ -886,19 +886,405 @@ __global__ __launch_bounds__(256, 2) void k_encode_mfma(const float *__restrict_
 }
 
 // ------------------------------------------------------------------------------------------------
-// The matrix-core assignment again, laid out for the instruction rather than for the arrays (aligned rows, groups of at
-//     most 64 dimensions; everything else takes k_encode_mfma).  A workgroup stages its group's codewords in LDS once,
-//     already in operand order: for every tile of 32 codewords and every block of 2 RL dimensions, lane (codeword,
-//     half) finds its RL consecutive values side by side (one or two 16-byte reads).  A wave then takes 32 vectors at a
-//     time, loads their values of the group once (the other operand, NB x RL registers), and walks the 8 tiles with
-//     one accumulator block, which starts at -||c||^2 / 2: the largest x.c - ||c||^2 / 2 is the smallest
-//     ||c||^2 - 2 x.c, exactly (a factor of -2), so the two largest values and the index of the largest are kept with
-//     four instructions per value and the bound of k_encode_mfma applies to the difference of the two largest as E.
-//     Near-ties go through the float32 rule as there; the codes are k_encode's, bit for bit.
-//     cc2: from k_encode_norms.  grid (ceil(n / (128 reps)), M), block 256, dynamic LDS 256 * NB * 2 RL * 4 bytes.
+// The same assignment on the bf16 matrix cores (groups of at most 128 dimensions, any alignment; wider groups take
+//     k_encode_wide or k_encode_mfma).  Only a decision is wanted, and only its rounding has to be proved harmless, so
+//     every float32 value goes in as a sum of two bf16 numbers, a = a_h + a_l + r with |r| <= 2^-18 |a|, and x.c as
+//     x_l.c_h + x_h.c_l + x_h.c_h: three bf16 instructions of 32 cycles for 16 dimensions where the float32 instruction
+//     takes eight of 64.  Vectors and codewords are taken relative to a point mu near the group's codewords (their
+//     mean, roughly), which changes no distance and makes the values, and with them every rounding, smaller.
+//     For a (vector, group) the accumulators hold x.c - ||c||^2 / 2 of all codewords (largest = nearest).  -||c||^2 / 2
+//     enters last, as the sum of three bf16 numbers against ones in an instruction of its own (as a starting value it
+//     would take four LDS reads per tile and make every rounding one of the larger sum); the small products are first.  With S = ||x||^2 + max ||c||^2, in units of 2^-24 S a value is off by at
+//     most: 99.2 (split: 3.1 2^-18 sum |x c|), 1.03 ds (sum of x_h.c_h and of the small products, one unit in the last
+//     place per product), 6 (the three norm slots), 0.5 ds (the norm), 2 (x - mu, c - mu); the float32 rule's distance
+//     (halved) by ds + 2.  Two values together: less than 6 ds + 224 (from 6 blocks of 16 dimensions on the small products
+//     come first in either half of the blocks, for want of registers: 1.03 ds more per value, 8 ds + 224).  So with E = (6 ds + 224) 2^-24 S every codeword
+//     the rule might choose has a value of at least the largest minus E.  Where that is one codeword it is the code;
+//     otherwise (a few vectors in a thousand) the float32 rule is evaluated for exactly those codewords (usually two),
+//     pairs (vector, codeword) of a wave collected in LDS until they fill its lanes.  The codes are k_encode's, bit
+//     for bit.
+//     Which values are at or above a threshold takes no index per value: a lane keeps the maximum of every tile
+//     of 32 codewords (over its 16 accumulator registers) and of every register (over the 8 tiles), one v_max3 per
+//     value for both, and compares 8 + 16 maxima in the end; the codewords in question lie in marked tiles x
+//     marked registers.  (Largest, second largest and index per value took four instructions a value and bound the
+//     kernel once the products were cheap.)
+//     A workgroup keeps the operands of as many groups as fit its LDS (16 KB per 16 dimensions, in instruction order)
+//     and walks the vectors, 32 per wave and step, whole rows at a time where all groups fit.
+//     What bounds it: vector and matrix issue together (about 300 vector instructions and 32 matrix instructions for 32
+//     vectors of a group of 16 dimensions; a matrix instruction takes the issue slot of about two others), the matrix
+//     cores for wide groups.  Kernel time against the float32 matrix instruction with three values tracked per codeword:
+//     a million vectors, 8 groups of 16, 0.81 -> 0.26 ms; 250 001 vectors, 8 groups of 120, 1.63 -> 0.36 ms.
+//     grid (vector chunks, ceil(M / gs)), block NW * 64, dynamic LDS encode_bf_lds().
+// ------------------------------------------------------------------------------------------------
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x8 __attribute__((ext_vector_type(8)));
+constexpr int ENC_PAIRS = 64;  // (vector, codeword) pairs a wave collects
+constexpr size_t ENC_QUEUE_BYTES = 64 * 8 + 64 * 8 + ENC_PAIRS * 4;
+__host__ __device__ constexpr size_t encode_bf_group_bytes(int NB) { return (size_t)NB * 16384 + 2048 + (size_t)NB * 64 + 16; }  // (the last 16: the largest norm, the turn)
+__host__ __device__ constexpr size_t encode_bf_lds(int NB, int gs, int NW) { return gs * encode_bf_group_bytes(NB) + NW * ENC_QUEUE_BYTES; }
+
+// eight float32 values as the sum of two bf16 numbers each
+__device__ __forceinline__ void split_bf16(const f32x8 &v, bf16x8 &h, bf16x8 &l)
+{
+    typedef uint32_t u32x4v __attribute__((ext_vector_type(4)));
+    h = __builtin_convertvector(v, bf16x8);
+    const u32x4v b = __builtin_bit_cast(u32x4v, h);
+    f32x8 r;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        r[2 * i] = v[2 * i] - __uint_as_float(b[i] << 16);
+        r[2 * i + 1] = v[2 * i + 1] - __uint_as_float(b[i] & 0xFFFF0000u);
+    }
+    l = __builtin_convertvector(r, bf16x8);
+}
+
+// WIDE: rows that can be read 16 bytes at a time
+template <int NB, bool WIDE, int NW>
+__global__ __launch_bounds__(NW * 64, NW / 4) void k_encode_bf(const float *__restrict__ x, int64_t n, int d, int ds, int K, int M,
+                                                               const float *__restrict__ cb, uint8_t *__restrict__ codes, int gs)
+{
+    constexpr int DSP = NB * 16, NT = NW * 64;
+    constexpr int TS = 2;          // codeword tiles at a time
+    constexpr bool AHEAD = NB < 6;  // registers for the next step's values (else its lines are only drawn into the cache)
+    extern __shared__ __align__(16) char enc_raw[];
+    const int lane = threadIdx.x & 63, w = uniform(threadIdx.x >> 6);
+    const int col = lane & 31, half = lane >> 5;
+    const int m0 = (int)blockIdx.y * gs, gl = min(gs, M - m0);
+    bf16x8 *ops = reinterpret_cast<bf16x8 *>(enc_raw);                      // [gs][8 tiles][NB][high, low][64 lanes]
+    char *behind = enc_raw + (size_t)gs * NB * 16384;
+    uint64_t *hbest = reinterpret_cast<uint64_t *>(behind) + w * 64;        // per open vector: smallest (distance, codeword)
+    behind += NW * 64 * 8;
+    uint64_t *hvec = reinterpret_cast<uint64_t *>(behind) + w * 64;         // ... and whose it is: vector << 8 | group
+    behind += NW * 64 * 8;
+    uint2 *nrm = reinterpret_cast<uint2 *>(behind);                         // [gs][256]: four bf16 (the last is zero)
+    behind += (size_t)gs * 2048;
+    float *mu = reinterpret_cast<float *>(behind);                          // [gs][DSP]
+    behind += (size_t)gs * DSP * 4;
+    uint32_t *ccm = reinterpret_cast<uint32_t *>(behind);                   // [gs] largest ||c||^2 (bits)
+    uint32_t *turn = ccm + gs;                                              // work handed out so far
+    behind += (size_t)gs * 16;
+    uint32_t *pairs = reinterpret_cast<uint32_t *>(behind) + w * ENC_PAIRS;  // slot << 8 | codeword
+
+    // ---- the point the group is taken relative to: the mean of up to 16 codewords
+    if ((int)threadIdx.x <= gl) (threadIdx.x == 0 ? turn : ccm + threadIdx.x - 1)[0] = 0u;
+    for (int idx = threadIdx.x; idx < gl * DSP; idx += NT) {
+        const int ml = idx / DSP, j = idx % DSP;
+        float s = 0.f;
+        if (j < ds) {
+            const float *c = cb + (int64_t)(m0 + ml) * K * ds + j;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) s += c[(int64_t)((i * K) >> 4) * ds];
+        }
+        mu[idx] = s * 0.0625f;
+    }
+    __syncthreads();
+    // ---- codewords as operands
+    for (int idx = threadIdx.x; idx < gl * 256; idx += NT) {
+        const int ml = idx >> 8, k = idx & 255;
+        const float *c = cb + ((int64_t)(m0 + ml) * K + min(k, K - 1)) * ds;
+        bf16x8 *dst = ops + (size_t)(ml * 8 + (k >> 5)) * NB * 128 + (k & 31);
+        float cc = 0.f;
+#pragma unroll 2
+        for (int p = 0; p < 2 * NB; ++p) {
+            f32x8 v;
+            if (WIDE) {
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    const int j = 8 * p + 4 * q;
+                    float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
+                    if (j < ds) t = *reinterpret_cast<const float4 *>(c + j);
+                    v[4 * q] = t.x; v[4 * q + 1] = t.y; v[4 * q + 2] = t.z; v[4 * q + 3] = t.w;
+                }
+            } else {
+#pragma unroll
+                for (int i = 0; i < 8; ++i) v[i] = 8 * p + i < ds ? c[8 * p + i] : 0.f;
+            }
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const float u = mu[ml * DSP + 8 * p + i];
+                v[i] = (k < K && 8 * p + i < ds) ? v[i] - u : 0.f;
+                cc = fmaf(v[i], v[i], cc);
+            }
+            bf16x8 h, l;
+            split_bf16(v, h, l);
+            dst[(p >> 1) * 128 + (p & 1) * 32] = h;
+            dst[(p >> 1) * 128 + 64 + (p & 1) * 32] = l;
+        }
+        // -||c||^2 / 2 as three bf16 numbers; far below every value beyond K
+        const float h0 = k < K ? -0.5f * cc : -3.0e38f;
+        const __bf16 n0 = (__bf16)h0;
+        const float h1 = h0 - (float)n0;
+        const __bf16 n1 = (__bf16)h1;
+        const __bf16 n2 = (__bf16)(h1 - (float)n1);
+        const uint32_t b0 = __builtin_bit_cast(uint16_t, n0), b1 = __builtin_bit_cast(uint16_t, n1), b2 = __builtin_bit_cast(uint16_t, n2);
+        nrm[ml * 256 + k] = make_uint2(b0 | (b1 << 16), b2);
+        if (k < K) atomicMax(&ccm[ml], __float_as_uint(cc) & 0x7FFFFFFFu);  // non-negative floats order like their bits, NaN above all
+    }
+    __syncthreads();
+
+    const float eps = (float)((NB >= 6 ? 8 : 6) * ds + 224) * 5.9604645e-8f;
+    const float inf = __uint_as_float(0x7F800000u);
+    int hcount = 0, pcount = 0;
+    // the float32 rule for the collected pairs, a lane each
+    auto evaluate = [&]() {
+        __builtin_amdgcn_wave_barrier();
+        for (int i = lane; i < pcount; i += 64) {
+            const uint32_t p = pairs[i];
+            const int slot = (int)(p >> 8), k = (int)(p & 255u);
+            if (k >= K) continue;
+            const uint64_t hv = hvec[slot];
+            const int m = (int)(hv & 255u);
+            const float *xv = x + (int64_t)(hv >> 8) * d + (int64_t)m * ds;
+            const float *c = cb + ((int64_t)m * K + k) * ds;
+            float s = 0.f;
+            if (WIDE) {
+#pragma unroll 4
+                for (int j = 0; j < ds; j += 4) {
+                    const float4 xq = *reinterpret_cast<const float4 *>(xv + j), cq = *reinterpret_cast<const float4 *>(c + j);
+                    s = encode_rule_term(s, xq.x, cq.x);
+                    s = encode_rule_term(s, xq.y, cq.y);
+                    s = encode_rule_term(s, xq.z, cq.z);
+                    s = encode_rule_term(s, xq.w, cq.w);
+                }
+            } else {
+                for (int j = 0; j < ds; ++j) s = encode_rule_term(s, xv[j], c[j]);
+            }
+            if (s < 3.402823466e+38f) atomicMin(reinterpret_cast<unsigned long long *>(&hbest[slot]), ((unsigned long long)__float_as_uint(s) << 32) | (uint32_t)k);
+        }
+        __builtin_amdgcn_wave_barrier();
+        pcount = 0;
+    };
+    auto settle = [&]() {
+        evaluate();
+        if (lane < hcount) {
+            const uint64_t hv = hvec[lane];
+            codes[(int64_t)(hv >> 8) * M + (int64_t)(hv & 255u)] = (uint8_t)hbest[lane];
+        }
+        __builtin_amdgcn_wave_barrier();
+        hcount = 0;
+    };
+
+    // A unit of work is a chunk of 32 vectors and up to four groups; the waves of the workgroup take the units of its
+    // chunks in turn (dealt out beforehand, the last waves worked alone for a sixth of the time).
+    const int64_t chunks = (n + 31) / 32;
+    const int parts = (gl + 3) / 4;
+    int64_t chunk = 0;
+    int ml = 0, mlend = 0;
+    auto take = [&]() {
+        uint32_t u = 0;
+        if (lane == 0) u = atomicAdd(turn, 1u);
+        u = (uint32_t)uniform((int)u);
+        const uint32_t i = u / (uint32_t)parts;
+        ml = 4 * (int)(u - i * (uint32_t)parts);
+        mlend = min(ml + 4, gl);
+        chunk = blockIdx.x + (int64_t)gridDim.x * i;
+    };
+    // The values of a step, one step ahead: lane (col, half) has dimensions 16 nb + 8 half .. + 7 of vector col.  Through
+    // a buffer over the step's rows, whose end turns what lies beyond the group (or the last vector) into zeros.
+    f32x8 raw[NB];
+    const uint32_t voff = (uint32_t)(col * d + 8 * half) * 4u;
+    auto fetch = [&](int64_t chunk, int ml) {
+        const int64_t v0 = chunk * 32;
+        const rsrc_t rr = make_rsrc(x + v0 * d, (uint32_t)min<int64_t>(32, n - v0) * (uint32_t)d * 4u);
+        const int so = (m0 + ml) * ds * 4;
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+            for (int i = 0; i < 8; i += WIDE ? 4 : 1) {
+                const int j = 16 * nb + i;
+                const uint32_t vo = (nb < NB - 2 || j + 8 * half < ds) ? voff + (uint32_t)j * 4u : 0x7FFFFFFFu;
+                if (WIDE) {
+                    const auto t = __builtin_amdgcn_raw_buffer_load_b128(rr, (int)vo, so, 0);
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) raw[nb][i + q] = __uint_as_float(t[q]);
+                } else {
+                    raw[nb][i] = buf_load(rr, (int)vo, so);
+                }
+            }
+    };
+    // the codes of a step leave through a buffer as well: lanes without one store past its end, without a branch (behind a
+    // branch the wait for the next step's values also waits for the store)
+    auto put = [&](int64_t chunk, int m, bool write, uint32_t code) {
+        const rsrc_t rc = make_rsrc(codes + chunk * 32 * M, (uint32_t)min<int64_t>(32, n - chunk * 32) * (uint32_t)M);
+        __builtin_amdgcn_raw_buffer_store_b8((uint8_t)code, rc, write ? col * M + m : 0x7FFFFFFF, 0, 0);
+    };
+    const uint32_t one = half == 0 ? 0x3F80u : 0u;  // bf16 1.0 in the lower half's first three slots
+    const bf16x8 ones = __builtin_bit_cast(bf16x8, make_uint4(one | (one << 16), one, 0u, 0u));
+    // operand of a tile's codewords; narrow groups have registers to read those of the next tiles ahead
+    auto operand = [&](int g, int tile, int nb, int low) -> bf16x8 { return ops[((g * 8 + tile) * NB + nb) * 128 + low * 64 + lane]; };
+    bf16x8 next_h[TS][NB <= 2 ? NB : 1], next_l[TS][NB <= 2 ? NB : 1];
+    uint2 next_n[TS];
+    auto preload = [&](int g, int tp) {
+#pragma unroll
+        for (int q = 0; q < TS; ++q) {
+#pragma unroll
+            for (int nb = 0; nb < (NB <= 2 ? NB : 1); ++nb) {
+                next_l[q][nb] = operand(g, TS * tp + q, nb, 1);
+                next_h[q][nb] = operand(g, TS * tp + q, nb, 0);
+            }
+            next_n[q] = nrm[g * 256 + (TS * tp + q) * 32 + col];
+        }
+    };
+    // a word of every 128 bytes of a step's values: what is loaded one step later comes from the near cache
+    uint32_t drawn[2] = {0u, 0u};
+    auto draw_in = [&](int64_t chunk, int ml) {
+        const rsrc_t rr = make_rsrc(x + chunk * 32 * d, (uint32_t)min<int64_t>(32, n - chunk * 32) * (uint32_t)d * 4u);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) drawn[i] = __builtin_amdgcn_raw_buffer_load_b32(rr, col * d * 4 + half * 128 + i * 256, (m0 + ml) * ds * 4, 0);
+    };
+    take();
+    if (AHEAD && chunk < chunks) fetch(chunk, ml);
+    while (chunk < chunks) {
+        if (!AHEAD) {
+            asm volatile("" ::"v"(drawn[0]), "v"(drawn[1]));
+            fetch(chunk, ml);
+        }
+        // ---- this step's operand
+        bf16x8 bh[NB], bl[NB];
+        float xx = 0.f;
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+            const int j = ml * DSP + 16 * nb + 8 * half;
+            const float4 u0 = *reinterpret_cast<const float4 *>(&mu[j]), u1 = *reinterpret_cast<const float4 *>(&mu[j + 4]);
+            const f32x8 u = {u0.x, u0.y, u0.z, u0.w, u1.x, u1.y, u1.z, u1.w};
+            const f32x8 v = raw[nb] - u;  // both are zero beyond the group
+#pragma unroll
+            for (int i = 0; i < 8; ++i) xx = fmaf(v[i], v[i], xx);
+            split_bf16(v, bh[nb], bl[nb]);
+        }
+        const int64_t now = chunk;
+        const int mlc = ml;
+        if (++ml == mlend) take();
+        if (NB <= 2) preload(mlc, 0);
+        if (chunk < chunks) {
+            if (AHEAD) fetch(chunk, ml);
+            else draw_in(chunk, ml);
+        }
+        __builtin_amdgcn_sched_barrier(0);  // the loads stay ahead of the matrix instructions
+        // ---- all codewords, TS tiles at a time
+        float tmax[8], rmax[16];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) tmax[i] = -3.4e38f;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) rmax[r] = -3.4e38f;
+#pragma unroll
+        for (int tp = 0; tp < 8 / TS; ++tp) {
+            if (tp == 2 && K <= 128) break;
+            floatx16 acc[TS];
+#pragma unroll
+            for (int q = 0; q < TS; ++q) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[q][r] = 0.f;
+                constexpr int HB = NB >= 6 ? NB / 2 : NB;  // blocks whose small products come first (registers)
+#pragma unroll
+                for (int n0 = 0; n0 < NB; n0 += HB) {
+                    bf16x8 ah[HB];
+#pragma unroll
+                    for (int i = 0; i < HB; ++i) {
+                        ah[i] = NB <= 2 ? next_h[q][NB <= 2 ? i : 0] : operand(mlc, TS * tp + q, n0 + i, 0);
+                        const bf16x8 al = NB <= 2 ? next_l[q][NB <= 2 ? i : 0] : operand(mlc, TS * tp + q, n0 + i, 1);
+                        acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al, bh[n0 + i], acc[q], 0, 0, 0);
+                        acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[i], bl[n0 + i], acc[q], 0, 0, 0);
+                    }
+#pragma unroll
+                    for (int i = 0; i < HB; ++i) acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[i], bh[n0 + i], acc[q], 0, 0, 0);
+                }
+                // (the upper half's ones are zeros)
+                const uint2 nn = NB <= 2 ? next_n[q] : nrm[mlc * 256 + (TS * tp + q) * 32 + col];
+                acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, make_uint4(nn.x, nn.y, 0u, 0u)), ones, acc[q], 0, 0, 0);
+            }
+            if (NB <= 2 && tp < 3) preload(mlc, tp + 1);  // while the matrix cores work
+#pragma unroll
+            for (int r = 0; r < 16; ++r) rmax[r] = fmaxf(fmaxf(rmax[r], acc[0][r]), acc[1][r]);
+#pragma unroll
+            for (int q = 0; q < TS; ++q) {
+                float t = acc[q][0];
+#pragma unroll
+                for (int r = 1; r < 15; r += 2) t = fmaxf(fmaxf(t, acc[q][r]), acc[q][r + 1]);
+                tmax[TS * tp + q] = fmaxf(t, acc[q][15]);
+                asm volatile("" : "+v"(tmax[TS * tp + q]));
+            }
+            // the maxima are taken here: put off until they are needed (as the compiler likes to), they keep the
+            // accumulators of all tiles alive
+#pragma unroll
+            for (int r = 0; r < 16; ++r) asm volatile("" : "+v"(rmax[r]));
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        // ---- decide.  Accumulator register r of lane l: codeword 32 tile + 8 (r / 4) + 4 (l / 32) + r % 4, vector l % 32
+        {
+            // the two halves of the wave hold different codewords of the same vectors: both halves' values in every lane
+            auto halves = [](uint32_t a) { return __builtin_amdgcn_permlane32_swap(a, a, false, false); };
+            float top = tmax[0];
+#pragma unroll
+            for (int i = 1; i < 8; ++i) top = fmaxf(top, tmax[i]);
+            const auto tops = halves(__float_as_uint(top)), sums = halves(__float_as_uint(xx));
+            top = fmaxf(__uint_as_float(tops[0]), __uint_as_float(tops[1]));
+            const float norm = __uint_as_float(sums[0]) + __uint_as_float(sums[1]) + __uint_as_float(ccm[mlc]);
+            const float E = eps * norm, th = top - E;
+            // bits 16..23: tiles, 0..15: registers; the sign of maximum - threshold shifted in, one by one
+            uint32_t mark = 0;
+#pragma unroll
+            for (int i = 7; i >= 0; --i) mark = __builtin_amdgcn_alignbit(mark, __float_as_uint(tmax[i] - th), 31);
+#pragma unroll
+            for (int r = 15; r >= 0; --r) mark = __builtin_amdgcn_alignbit(mark, __float_as_uint(rmax[r] - th), 31);
+            mark = ~mark & 0x00FFFFFFu;
+            // not finite, or so small that products vanish: every codeword goes through the rule
+            if (!(E < inf) || norm < 1.0e-30f) mark = 0x00FFFFFFu;
+            const int64_t v = now * 32 + col;
+            const bool live = v < n;
+            const auto marks = halves(mark);
+            const uint32_t sel = marks[0] | marks[1];
+            const bool hard = live && ((marks[0] && marks[1]) || __popc(sel) != 2);
+            const int r = __ffs((int)(sel & 0xFFFFu)) - 1, tile = __ffs((int)(sel >> 16)) - 1;
+            put(now, m0 + mlc, half == 0 && !hard, (uint32_t)(32 * tile + 8 * (r >> 2) + (marks[0] ? 0 : 4) + (r & 3)));
+            const uint64_t hb = __ballot(hard);
+            if (hb != 0ull) {
+                const uint32_t lowm = (uint32_t)hb;  // both halves of the wave agree on which vectors are open
+                const int nh = __popc(lowm);
+                if (hcount + nh > 64) settle();
+                const int slot = hcount + __popc(lowm & ((1u << col) - 1u));
+                hcount += nh;
+                if (hard && half == 0) {
+                    hvec[slot] = ((uint64_t)v << 8) | (uint32_t)(m0 + mlc);
+                    hbest[slot] = ((uint64_t)0x7F7FFFFFu << 32) | 0xFFFFFFFFu;
+                }
+                uint32_t tm = hard ? mark >> 16 : 0u, rm = mark & 0xFFFFu;
+                for (;;) {
+                    const uint64_t pb = __ballot(tm != 0u);
+                    if (pb == 0ull) break;
+                    const int np = __popcll(pb);
+                    if (pcount + np > ENC_PAIRS) evaluate();
+                    if (tm != 0u) {
+                        const int rr = __ffs((int)rm) - 1, tt = __ffs((int)tm) - 1;
+                        const int at = pcount + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(pb >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)pb, 0u));
+                        pairs[at] = ((uint32_t)slot << 8) | (uint32_t)(32 * tt + 8 * (rr >> 2) + 4 * half + (rr & 3));
+                        rm &= rm - 1u;
+                        if (rm == 0u) {
+                            tm &= tm - 1u;
+                            rm = mark & 0xFFFFu;
+                        }
+                    }
+                    pcount += np;
+                }
+            }
+        }
+    }
+    settle();
+}
+
+// ------------------------------------------------------------------------------------------------
+// The matrix-core assignment for wide groups (more than 64 dimensions per group, aligned rows): both operands go
+//     through LDS 32 dimensions at a time, fetched with coalesced 16-byte loads (eight threads per row) into registers
+//     while the previous stage is multiplied, as in k_ivf_coarse_tc; k_encode_mfma's per-lane loads of 16 bytes from
+//     64 different rows keep the matrix cores waiting for the cache's tag look-ups.  A workgroup owns 128 vectors
+//     and the group's 256 codewords: wave (wk, wv) multiplies codewords 128 wk .. by vectors 64 wv .. (A = codewords,
+//     4 x 2 accumulator blocks that start at -||c||^2 / 2), keeps largest, second largest and index per vector as
+//     k_encode_tc does, the two waves of a vector set merge through LDS, and near-ties go through the float32 rule.
+//     The codes are k_encode's, bit for bit.
+//     cc2: from k_encode_norms.  grid (ceil(n / 128), M), block 256; ds and d multiples of 4, K <= 256.
 // ------------------------------------------------------------------------------------------------
 // -0.5 ||c||^2 of every codeword (-3e38 beyond K) as cc2[M][256], and the largest ||c||^2 of every group as
-// cc2[M * 256 + m]: what k_encode_tc starts its accumulators from.  grid (M), block 256.
+// cc2[M * 256 + m]: what k_encode_wide starts its accumulators from.  grid (M), block 256.
 __global__ __launch_bounds__(256) void k_encode_norms(const float *__restrict__ cb, int ds, int K, int M, float *__restrict__ cc2)
 {
     __shared__ float s_mx[4];
@@ -916,135 +1302,6 @@ __global__ __launch_bounds__(256) void k_encode_norms(const float *__restrict__ 
     if (t == 0) cc2[M * 256 + m] = fmaxf(fmaxf(s_mx[0], s_mx[1]), fmaxf(s_mx[2], s_mx[3]));
 }
 
-template <int RL, int NB>
-__global__ __launch_bounds__(256, 2) void k_encode_tc(const float *__restrict__ x, int64_t n, int d, int ds, int K, int M,
-                                                      const float *__restrict__ cb, const float *__restrict__ cc2, uint8_t *__restrict__ codes, int reps)
-{
-    extern __shared__ float enc_lds[];  // [8 tiles][NB][64 lanes][RL]
-    __shared__ __align__(16) float s_cc2[256];
-    constexpr int DSP = NB * 2 * RL;
-    const int m = blockIdx.y;
-    const int lane = threadIdx.x & 63, w = uniform(threadIdx.x >> 6);
-    const int col = lane & 31, half = lane >> 5;
-    const float *cbm = cb + (int64_t)m * K * ds;
-    for (int idx = threadIdx.x; idx < 256 * DSP; idx += 256) {
-        const int k = idx / DSP, j = idx % DSP;
-        const int blk = j / (2 * RL), hf = (j / RL) & 1, i = j % RL;
-        enc_lds[((((k >> 5) * NB + blk) * 64) + hf * 32 + (k & 31)) * RL + i] = (k < K && j < ds) ? cbm[(int64_t)k * ds + j] : 0.f;
-    }
-    s_cc2[threadIdx.x] = cc2[m * 256 + threadIdx.x];
-    __syncthreads();
-    const float ccmax = cc2[M * 256 + m];
-    const float eps = 8.f * (float)(ds + 2) * 5.9604645e-8f;
-    const int tiles = (K + 31) >> 5;
-    for (int rep = 0; rep < reps; ++rep) {
-        const int64_t v0 = ((int64_t)blockIdx.x * reps + rep) * 128 + w * 32;
-        if (v0 >= n) return;
-        const int64_t v = v0 + col;
-        const bool live = v < n;
-        const float *xrow = x + (live ? v : 0) * d + (int64_t)m * ds;
-        float b[NB][RL];
-        float xx = 0.f;
-#pragma unroll
-        for (int blk = 0; blk < NB; ++blk)
-#pragma unroll
-            for (int q4 = 0; q4 < RL / 4; ++q4) {
-                const int j = blk * 2 * RL + half * RL + 4 * q4;
-                float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
-                if (live && j + 4 <= ds) t = *reinterpret_cast<const float4 *>(xrow + j);
-                b[blk][4 * q4 + 0] = t.x;
-                b[blk][4 * q4 + 1] = t.y;
-                b[blk][4 * q4 + 2] = t.z;
-                b[blk][4 * q4 + 3] = t.w;
-                xx = fmaf(t.x, t.x, fmaf(t.y, t.y, fmaf(t.z, t.z, fmaf(t.w, t.w, xx))));
-            }
-        // the largest value so far, the second largest, and where the largest is: tile and accumulator register
-        float v1 = -3.0e38f, v2 = -3.0e38f;
-        int k1t = 0, k1r = 0;
-        const float inf = __uint_as_float(0x7F800000u);
-        auto start = [&](int tile, floatx16 &acc) {
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const float4 c4 = *reinterpret_cast<const float4 *>(&s_cc2[tile * 32 + 8 * g + 4 * half]);
-                acc[4 * g + 0] = c4.x;
-                acc[4 * g + 1] = c4.y;
-                acc[4 * g + 2] = c4.z;
-                acc[4 * g + 3] = c4.w;
-            }
-            const float *ap = enc_lds + ((int64_t)tile * NB * 64 + lane) * RL;
-#pragma unroll
-            for (int blk = 0; blk < NB; ++blk) {
-                float a[RL];
-#pragma unroll
-                for (int q4 = 0; q4 < RL / 4; ++q4) {
-                    const float4 t = *reinterpret_cast<const float4 *>(ap + blk * 64 * RL + 4 * q4);
-                    a[4 * q4 + 0] = t.x;
-                    a[4 * q4 + 1] = t.y;
-                    a[4 * q4 + 2] = t.z;
-                    a[4 * q4 + 3] = t.w;
-                }
-#pragma unroll
-                for (int i = 0; i < RL; ++i) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[blk][i], acc, 0, 0, 0);
-            }
-        };
-        auto finish = [&](int tile, const floatx16 &acc) {
-            const float before = v1;
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const float val = acc[r];
-                k1r = val > v1 ? r : k1r;
-                v2 = __builtin_amdgcn_fmed3f(val, v1, v2);   // v1 >= v2: the median is the new second largest
-                v1 = __builtin_amdgcn_fmed3f(val, v1, inf);  // the larger of the two
-            }
-            k1t = v1 != before ? tile : k1t;
-        };
-        // (taking turns between two accumulator blocks, with the vector work on one tile's values scheduled between the
-        // matrix instructions of the next, gained 4 % on a million vectors per call and lost 8 % on 131 072: float32
-        // matrix instructions and vector instructions share the SIMD's issue, so there is little to overlap)
-        for (int tile = 0; tile < tiles; ++tile) {
-            floatx16 acc;
-            start(tile, acc);
-            finish(tile, acc);
-        }
-        // accumulator register r of lane l: codeword 32 tile + 8 (r / 4) + 4 (l / 32) + r % 4, vector l % 32
-        int k1 = k1t * 32 + 8 * (k1r >> 2) + 4 * half + (k1r & 3);
-        // the two halves of the wave saw different codewords of the same vectors
-        {
-            const float o1 = __shfl_xor(v1, 32), o2 = __shfl_xor(v2, 32);
-            const int ok = __shfl_xor(k1, 32);
-            xx += __shfl_xor(xx, 32);
-            const float lo = fminf(v1, o1);
-            if (o1 > v1 || (o1 == v1 && ok < k1)) k1 = ok;
-            v1 = fmaxf(v1, o1);
-            v2 = fmaxf(lo, fmaxf(v2, o2));
-        }
-        const float E = eps * (xx + ccmax);
-        // (values so small that products are subnormal: the matrix instruction flushes them, E does not cover that)
-        const bool hard = live && (!(v1 - v2 > E) || xx + ccmax < 1.0e-30f);
-        if (half == 0 && live && !hard) codes[v * M + m] = (uint8_t)k1;
-        // near-ties: the float32 rule itself for every codeword, the wave's lanes taking codewords lane, lane + 64, ...
-        uint64_t todo = __ballot(hard && half == 0);
-        while (todo != 0ull) {
-            const int src = __ffsll((unsigned long long)todo) - 1;
-            todo &= todo - 1;
-            const int64_t vh = v0 + src;
-            const int best = encode_rule_wave(x + vh * d + (int64_t)m * ds, cbm, ds, K, lane, true);
-            if (lane == 0) codes[vh * M + m] = (uint8_t)best;
-        }
-    }
-}
-
-// ------------------------------------------------------------------------------------------------
-// The matrix-core assignment for wide groups (more than 64 dimensions per group, aligned rows): both operands go
-//     through LDS 32 dimensions at a time, fetched with coalesced 16-byte loads (eight threads per row) into registers
-//     while the previous stage is multiplied, as in k_ivf_coarse_tc; k_encode_mfma's per-lane loads of 16 bytes from
-//     64 different rows keep the matrix cores waiting for the cache's tag look-ups.  A workgroup owns 128 vectors
-//     and the group's 256 codewords: wave (wk, wv) multiplies codewords 128 wk .. by vectors 64 wv .. (A = codewords,
-//     4 x 2 accumulator blocks that start at -||c||^2 / 2), keeps largest, second largest and index per vector as
-//     k_encode_tc does, the two waves of a vector set merge through LDS, and near-ties go through the float32 rule.
-//     The codes are k_encode's, bit for bit.
-//     cc2: from k_encode_norms.  grid (ceil(n / 128), M), block 256; ds and d multiples of 4, K <= 256.
-// ------------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(256, 2) void k_encode_wide(const float *__restrict__ x, int64_t n, int d, int ds, int K, int M,
                                                         const float *__restrict__ cb, const float *__restrict__ cc2, uint8_t *__restrict__ codes)
 {

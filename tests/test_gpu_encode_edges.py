@@ -1,0 +1,72 @@
+"""The bf16 matrix-core encoder at the sizes where it can go wrong: every number of 16-dimension blocks and both sides of
+their edges, aligned and unaligned rows, codebooks that end inside a tile, chunks of 32 vectors and their remainders,
+values that are not finite or far from the origin.  Codes are whole numbers: exact, against the float32 oracle."""
+import numpy as np
+import pytest
+
+import oracle
+from workload import near_tie_vectors
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+import paper_1509_05186_amd as etf  # noqa: E402
+
+
+def encoder(cb):
+    c = etf.Context(device=0, stream=torch.cuda.current_stream().cuda_stream)
+    c.pq_set_codebooks(cb)
+    return c
+
+
+def encode(c, x):
+    got = c.pq_encode_device(torch.from_numpy(x).cuda())
+    torch.cuda.synchronize()
+    return got.cpu().numpy()
+
+
+@pytest.mark.parametrize("ds,M,K,n", [
+    (1, 3, 256, 33), (6, 4, 100, 1000), (13, 4, 256, 31), (16, 8, 128, 4097), (16, 16, 256, 700), (17, 2, 129, 65),
+    (25, 4, 64, 333), (32, 8, 256, 1025), (33, 2, 33, 97), (48, 5, 256, 640), (61, 1, 31, 100), (64, 3, 256, 257),
+    (65, 2, 256, 95), (80, 2, 200, 160), (96, 2, 256, 64), (97, 1, 256, 129), (120, 3, 256, 300), (126, 2, 256, 40),
+    (128, 2, 256, 1), (12, 1, 1, 50),
+])
+def test_edges_of_blocks_tiles_and_chunks(ds, M, K, n):
+    print("encoder edges: ds", ds, "M", M, "K", K, "n", n, flush=True)
+    rng = np.random.default_rng(ds * 1000 + M)
+    cb = rng.normal(size=(M, K, ds)).astype(np.float32)
+    c = encoder(cb)
+    x = rng.normal(size=(n, M * ds)).astype(np.float32)
+    assert np.array_equal(encode(c, x), oracle.encode_f32(x, cb))
+    ties = near_tie_vectors(cb, n, seed=ds) if K > 1 else x
+    assert np.array_equal(encode(c, ties), oracle.encode_f32(ties, cb))
+
+
+@pytest.mark.parametrize("ds", [16, 120])
+def test_most_vectors_take_the_rule(ds):
+    print("encoder: values far from the origin and spread codebooks, ds", ds, flush=True)
+    rng = np.random.default_rng(ds)
+    cb = rng.normal(size=(4, 256, ds)).astype(np.float32)
+    cb[:, 1::2] = cb[:, ::2] * np.float32(1 + 2.0 ** -22)  # pairs that only the rule tells apart
+    cb[2] += 300.0
+    cb[3, 7] *= 1e6                                        # one codeword makes every bound loose
+    c = encoder(cb)
+    x = np.concatenate([cb[m][rng.integers(0, 256, 3000)] + rng.normal(size=(3000, ds)) * 0.1 for m in range(4)], 1).astype(np.float32)
+    assert np.array_equal(encode(c, x), oracle.encode_f32(x, cb))
+
+
+def test_values_that_are_not_finite_stay_their_own():
+    print("encoder: NaN and infinities in some groups", flush=True)
+    rng = np.random.default_rng(8)
+    cb = rng.normal(size=(4, 256, 16)).astype(np.float32)
+    c = encoder(cb)
+    x = rng.normal(size=(500, 64)).astype(np.float32)
+    bad = np.zeros((500, 4), dtype=bool)
+    for i, v in ((3, np.nan), (77, np.inf), (78, -np.inf), (499, 3e38)):
+        x[i, 16 * (i % 4) + 5] = v
+        bad[i, i % 4] = True
+    got = encode(c, x)
+    clean = np.where(np.isfinite(x) & (np.abs(x) < 1e30), x, 0).astype(np.float32)
+    want = oracle.encode_f32(clean, cb)
+    assert np.array_equal(got[~bad], want[~bad])
+    assert (got[bad] == 255).all()  # no codeword has a finite distance below the largest float
