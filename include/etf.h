@@ -103,6 +103,9 @@ const char *etf_last_error(const etf_ctx *ctx);
  *                     (a wave whose lane groups all stay inside their two-chunk prefix skips those two lookups).
  *                     0: every chunk of every encoding is looked up (same results; measured 3 to 6 % slower at M = 8
  *                     and 4 % faster at M = 16, where the two skipped reads leave a bank-conflict pattern behind)
+ *   "matrix_filter"   the 16-bit filter pass runs on the matrix cores where chunks have at most 8 dimensions, the batch
+ *                     fills its blocks of 128 queries and has at least this many (query, distinct encoding) pairs
+ *                     (default 2^29, twice that at M = 8; -1: never).  Same results
  *   "lds_blocks"      workgroups per sub-tile of queries in the LDS-resident kernels (0 = chosen by the
  *                     library from the number of sub-tiles and items; for experiments)
  *   "metric"          0 (default): squared Euclidean distance.  1: scalar product (the paper notes, after

@@ -794,15 +794,68 @@ int launch_lds16(etf_ctx *ctx, const Plan &P, char *ws, const uint32_t *rec, int
     return ETF_OK;
 }
 
+// The filter pass on the matrix cores (see k_mm16) where it is the cheaper one: chunks of at most 8 dimensions (at 16, M = 8, it took
+// 1.73 ms where k_lds16 takes 1.43), and a batch that fills its blocks of 128 queries well enough beside the sub-tiles of
+// k_lds16 (32 queries at M = 8, 16 at M = 16).  k_lds16 takes 0.33 ps per pair of query and encoding at M = 16, 0.2 ps at
+// M = 8, k_mm16 0.22 and 0.16; the empty one of the two launches costs 3 to 5 us, 2 % of the pass at the fewest pairs
+// taken here (2^29, 2^30).
+bool mm_wanted(const etf_ctx *ctx, const Plan &P, int64_t nq)
+{
+    if (!P.fx16 || ctx->opt.metric != 0 || ctx->ds > 8 || ctx->opt.matrix_filter < 0) return false;
+    const int64_t Qs = ctx->M == 8 ? 32 : 16;
+    const int64_t padded = (nq + MM_Q - 1) / MM_Q * MM_Q;
+    return padded * 2 <= (nq + Qs - 1) / Qs * Qs * 3 && (double)padded * (double)ctx->idx.Nd >= (double)ctx->opt.matrix_filter * (ctx->M == 8 ? 2.0 : 1.0);
+}
+
+int launch_mm16(etf_ctx *ctx, const float *queries, const uint32_t *rec, int64_t nitems, int64_t nql, const OutArgs &o, uint32_t *margin,
+                uint32_t *mode)
+{
+    const int M = ctx->M;
+    MmArgs a;
+    memset(&a, 0, sizeof a);
+    a.queries = queries;
+    a.nq = o.nq;
+    a.nql = nql;
+    a.d = ctx->d;
+    a.ds = ctx->ds;
+    a.dsp = ctx->dsp;
+    a.K = ctx->K;
+    a.cbc = reinterpret_cast<const float *>(ctx->dev_base + ctx->lay.cb_centered);
+    a.cbnorm = reinterpret_cast<const float *>(ctx->dev_base + ctx->lay.cb_norm);
+    a.cbmean = reinterpret_cast<const float *>(ctx->dev_base + ctx->lay.cb_mean);
+    for (int j = 0; j < ETF_MAX_M; ++j) a.ord.src[j] = (uint8_t)((size_t)j < ctx->idx.order.size() ? ctx->idx.order[j] : j);
+    a.margin = margin;
+    a.loose = margin + nql;
+    a.mode = mode;
+    const int64_t W = (nql + MM_Q - 1) / MM_Q;
+    int64_t bx = lds_blocks_for(W, nitems, (nitems >> 25) + 1);
+    if (ctx->opt.lds_blocks > 0) bx = std::max<int64_t>(ctx->opt.lds_blocks, (nitems >> 25) + 1);
+    const int per_block = (int)(((nitems + bx - 1) / bx + 31) / 32 * 32);
+    const dim3 grid((unsigned)((nitems + per_block - 1) / per_block), (unsigned)W);
+    hipStream_t st = (hipStream_t)ctx->stream;
+    ProfScope prof(ctx, ETF_K_LDS16);
+    const size_t lds = mm_lds_bytes(M);
+    int rc;
+    if (M == 8) {
+        if ((rc = set_lds(ctx, k_mm16<8>, lds))) return rc;
+        hipLaunchKernelGGL(k_mm16<8>, grid, dim3(512), lds, st, rec, nitems, per_block, o, a);
+    } else {
+        if ((rc = set_lds(ctx, k_mm16<16>, lds))) return rc;
+        hipLaunchKernelGGL(k_mm16<16>, grid, dim3(512), lds, st, rec, nitems, per_block, o, a);
+    }
+    LAUNCH_CHECK(ctx, "k_mm16");
+    return ETF_OK;
+}
+
 // the bound of every query from its sample groups' minima (and the per-query state of the passes behind it)
-int launch_tau(etf_ctx *ctx, const Plan &P, const OutArgs &o, int64_t nql, uint32_t *flag, uint32_t *counter)
+int launch_tau(etf_ctx *ctx, const Plan &P, const OutArgs &o, int64_t nql, uint32_t *flag, uint32_t *counter, const LooseArgs &la)
 {
     ProfScope prof(ctx, ETF_K_TAU);
     const dim3 grid((unsigned)((nql + 3) / 4)), block(256);
     hipStream_t st = (hipStream_t)ctx->stream;
     float *tau = const_cast<float *>(o.tau);
     const int S = (int)P.ngroups;
-#define TAU_CASE(NV) hipLaunchKernelGGL(k_tau<NV>, grid, block, 0, st, o.gmin, S, o.gstride, P.k, o.nq, nql, tau, o.cnt, flag, counter)
+#define TAU_CASE(NV) hipLaunchKernelGGL(k_tau<NV>, grid, block, 0, st, o.gmin, S, o.gstride, P.k, o.nq, nql, tau, o.cnt, flag, counter, la)
     if (S <= 256) TAU_CASE(4);
     else if (S <= 1024) TAU_CASE(16);
     else if (S <= 2048) TAU_CASE(32);
@@ -1229,6 +1282,19 @@ static int search_impl(etf_ctx *ctx, const float *queries, int64_t Q, int k, int
             o.term = term;
             o.term_map = reinterpret_cast<const uint32_t *>(ctx->dev_base + (flat ? L.sample_pos : L.sample_enc));
         }
+        // the matrix filter's margins and the blocks that it has taken lie where the product searches keep their shifts
+        const bool mm = mm_wanted(ctx, P, nq);
+        uint32_t *margins = mm ? reinterpret_cast<uint32_t *>(w + P.o_bm) : nullptr;
+        LooseArgs la;
+        memset(&la, 0, sizeof la);
+        if (mm) {
+            la.loose = margins + nql;
+            la.queries = queries + q0 * ctx->d;
+            la.mean = reinterpret_cast<const float *>(ctx->dev_base + L.cb_mean);
+            la.d = ctx->d;
+            la.most = ctx->cb_norm_most;
+        }
+        o.done = mm ? margins + 2 * nql : nullptr;
         ReduceArgs r;
         const uint32_t *ecodes = reinterpret_cast<const uint32_t *>(ctx->dev_base + L.ecodes);
         if (!flat && !P.lds_path) {
@@ -1253,7 +1319,11 @@ static int search_impl(etf_ctx *ctx, const float *queries, int64_t Q, int k, int
                     rc = P.ctx_path ? launch_fused<OUT_SAMPLE>(ctx, P, w, r, P.S, reinterpret_cast<const uint32_t *>(ctx->dev_base + L.sample_enc), tiles, o)
                                     : launch_reduce<OUT_SAMPLE>(ctx, r, P.S, reinterpret_cast<const uint32_t *>(ctx->dev_base + L.sample_enc), tiles, o);
                 if (rc) return rc;
-                rc = launch_tau(ctx, P, o, nql, flag, clear);
+                rc = launch_tau(ctx, P, o, nql, flag, clear, la);
+                if (rc) return rc;
+            }
+            if (mm) {
+                rc = launch_mm16(ctx, queries + q0 * ctx->d, ecodes, ix.Nd, nql, o, margins, const_cast<uint32_t *>(o.done));
                 if (rc) return rc;
             }
             if (flat)
@@ -1286,6 +1356,7 @@ static int search_impl(etf_ctx *ctx, const float *queries, int64_t Q, int k, int
         sa.fx_margin = P.fx ? (uint32_t)(2 * (ix.M + 8 * (ix.M + 1)) + 16) : 0u;
         // 16-bit tables: truncation makes a sum too small by at most M units, everything else is far below one unit
         if (P.fx16) sa.fx_margin = (uint32_t)(ix.M + 2);
+        sa.margins = margins;
         sa.fx_first_pass = P.fx16 ? 2 : 0;
         sa.lutT = lutT;
         sa.codes = reinterpret_cast<const uint8_t *>(ctx->dev_base + (flat ? L.codes : L.ecodes));

@@ -208,7 +208,9 @@ void prepare_centered(etf_ctx *ctx)
     ctx->cb_mean.assign((size_t)M * ds, 0.f);
     ctx->cb_centered.assign((size_t)M * K * ctx->dsp, 0.f);
     ctx->cb_norm.assign((size_t)M * K, 0.f);
+    ctx->cb_norm_most = 0.f;
     for (int m = 0; m < M; ++m) {
+        float most = 0.f;
         for (int j = 0; j < ds; ++j) {
             double s = 0.0;
             for (int k = 0; k < K; ++k) s += ctx->codebooks[((size_t)m * K + k) * ds + j];
@@ -222,7 +224,9 @@ void prepare_centered(etf_ctx *ctx)
                 nn += (double)c * (double)c;
             }
             ctx->cb_norm[(size_t)m * K + k] = (float)nn;
+            most = std::max(most, (float)nn);
         }
+        ctx->cb_norm_most += most;
     }
 }
 
@@ -410,6 +414,9 @@ extern "C" int etf_set_option(etf_ctx *ctx, const char *name, int64_t value)
     } else if (n == "lds16_context") {
         if (value < 0 || value > 1) return fail(ctx, ETF_EINVAL, "lds16_context is 0 or 1");
         ctx->opt.lds16_context = (int)value;
+    } else if (n == "matrix_filter") {
+        if (value < -1) return fail(ctx, ETF_EINVAL, "matrix_filter is a number of pairs, or -1");
+        ctx->opt.matrix_filter = value;
     } else if (n == "lds_blocks") {
         if (value < 0 || value > 65535) return fail(ctx, ETF_EINVAL, "lds_blocks out of range");
         ctx->opt.lds_blocks = value;

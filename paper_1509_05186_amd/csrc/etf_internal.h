@@ -123,6 +123,7 @@ struct Options {
     int64_t sample_scale = 120; // sample size = max(sample_min, sample_scale * sqrt(n))
     int64_t cand_cap = 0;
     int64_t traversal = 2;  // 0: distance context in registers, 1: level-synchronous kernels, 2: searches with all tables in LDS
+    int64_t matrix_filter = (int64_t)1 << 29;  // (query, encoding) pairs from which k_mm16 filters (-1: never)
     int lds16_context = 1;  // k_lds16 keeps a distance context of two levels (1) or looks every chunk up (0)
     int64_t lds_blocks = 0; // workgroups per sub-tile of queries in the LDS-resident search kernel (0: chosen by the library)
     int64_t metric = 0;     // 0: squared Euclidean distance (smallest first), 1: scalar product (largest first)
@@ -160,6 +161,7 @@ struct etf_ctx {
     std::vector<float> cb_centered;         // [M][K][dsp]
     std::vector<float> cb_norm;             // [M][K]
     std::vector<float> cb_mean;             // [M][ds]
+    float cb_norm_most = 0.f;               // sum over the groups of the largest squared norm of a centred codeword
     // index
     etf::HostIndex idx;
     etf::IvfIndex ivf;

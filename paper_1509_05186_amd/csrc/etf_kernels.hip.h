@@ -1480,6 +1480,7 @@ struct OutArgs {
     int64_t ngroups;
     int64_t gstride;    // ngroups rounded up to a multiple of 64
     int gsize;
+    const uint32_t *done;  // k_lds16: per 128 queries, not zero where k_mm16 has filtered them; or nullptr
     int wps;            // k_lds: waves that share a stretch of the sample (a power of two, at most 16)
     // OUT_FILTER
     const float *tau;   // [tiles*64]
@@ -2155,6 +2156,7 @@ __global__ __launch_bounds__(1024) void k_lds16(const uint32_t *__restrict__ rec
     uint32_t(*wcount)[64] = reinterpret_cast<uint32_t(*)[64]>(aux + 16 * RING * 20);
     uint32_t(*wpos)[64] = reinterpret_cast<uint32_t(*)[64]>(aux + 16 * RING * 20 + 16 * 64 * 4);
     const int tile = blockIdx.z, sub = blockIdx.y;
+    if (o.done && o.done[tile >> 1] != 0u) return;
     const int lane = threadIdx.x & 63;
     const int w = uniform(threadIdx.x >> 6), nw = blockDim.x >> 6;
     wcount[w][lane] = 0u;
@@ -2357,6 +2359,414 @@ __global__ __launch_bounds__(1024) void k_lds16(const uint32_t *__restrict__ rec
 }
 
 // ------------------------------------------------------------------------------------------------
+// The filter pass of the search on the matrix cores (few dimensions per chunk).
+//     For the decision "can this encoding be among the k nearest" the distance may also be taken as what it is, the
+//     distance to the encoding's reconstruction r: ||q - r||^2 = ||q||^2 - 2 (q.r - ||r||^2 / 2), a contraction over the
+//     dimensions in 16-bit floats.  A lane's operand for 8 dimensions of an encoding is a 16-byte piece of a codeword,
+//     read from LDS at the code: no tables, no staged reconstruction, and one read serves 128 queries.  All codewords
+//     in 16 bits (32 dpad bytes per code value: 64 KB at 128 dimensions) are staged once per workgroup; a wave keeps the
+//     operands of 128 queries in registers and walks 32 encodings per step.  The walk then costs dpad / 16 matrix
+//     instructions per 32 x 32 distances however many chunks an encoding has, where k_lds16 reads M table entries.
+//     Exactness.  Queries and codewords are taken relative to the codebooks' means, scaled by powers of two (codewords
+//     by one for all, queries by one per workgroup).  With q = q^ + e, c = c^ + f (q^, c^ the 16-bit values; nothing is
+//     assumed of the conversion: e and f are computed) the error of a chunk's product is e.c^ + q^.f + e.f.  The
+//     first two are evaluated here for every (query, chunk, codeword), on the matrix cores again, and the largest of a chunk
+//     taken: their sum over the chunks is half of what sqrt(sum ||e||^2) sqrt(sum ||c||^2) and its like would give.
+//     Everything else is float32 rounding: in units of 2^-24
+//     (||q||^2 + C^2), C^2 the sum of the largest ||c||^2, the contraction (one unit in the last place per product)
+//     4 dpad + 16, ||q||^2 d, the table entries that the float32 distance is summed from 4 ds + 10, the sums of M terms
+//     3 M, the centring 4: below 6 dpad + 4 ds + 4 M + 64.  E bounds the difference between the value here and the float32
+//     distance of the tables, and everything with a value of at most tau + E passes.  Its candidates carry a 16-bit fixed-point
+//     value; k_select takes everything within margin = 2 E of the k-th smallest and recomputes those from the tables.
+//     Where E is not small against the bound (tight clusters far from the mean) too many would pass: a block of 128 queries
+//     with such a query, as estimated by k_tau or found here, is left to k_lds16 (`mode`), which is launched behind and
+//     otherwise ends at once.
+//     What bounds it: the matrix cores under the card's power limit.  Ten million encodings of 16 chunks (128 dimensions),
+//     10 000 queries: 13.1 ms = 1.29 PFLOP/s, against 1.55 of the bare instruction on random operands and 1.16 to 1.21 of a large
+//     library product here; k_lds16 19.7 ms.
+//     Candidates: a lane that finds one among its 16 values parks all 16 in the wave's ring; a full ring is taken apart by
+//     all lanes (as in k_lds16).
+//     MC: chunks, each of at most 8 dimensions (a lane's operand is one chunk's codeword).
+//     grid (blocks, ceil(nql / 128)), block 512, dynamic LDS mm_lds_bytes(MC).
+// ------------------------------------------------------------------------------------------------
+typedef float floatx4_t __attribute__((ext_vector_type(4)));
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+constexpr int MM_Q = 128, MM_RING = 128, MM_WAVES = 8;
+__host__ __device__ constexpr size_t mm_lds_bytes(int MC)
+{
+    return (size_t)MC * 5120 + (size_t)MM_WAVES * MM_RING * 68 + (size_t)MM_WAVES * MM_Q * 8 + MM_Q * 16 + 2 * 64 + 64;
+}
+
+struct MmArgs {
+    const float *queries;  // rows of this batch
+    int64_t nq, nql;       // live queries, queries with state (multiple of 64)
+    int d, ds, dsp, K;
+    const float *cbc, *cbnorm, *cbmean;  // centred codewords [M][K][dsp], their squared norms, the means [M][ds]
+    ChunkOrder ord;
+    const uint32_t *loose; // [nql] from k_tau
+    uint32_t *margin;      // [nql] for k_select
+    uint32_t *mode;        // [ceil(nql / 128)] 1: this kernel filtered the block, 0: left to k_lds16
+};
+
+template <int MC>
+__global__ __launch_bounds__(512, 2) void k_mm16(const uint32_t *__restrict__ rec, int64_t nitems, int per_block, OutArgs o, MmArgs a)
+{
+    constexpr int M4 = MC / 4, KS = MC / 2, NB = MM_Q / 32, RING = MM_RING, NW = MM_WAVES;
+    extern __shared__ __align__(16) char mm_raw[];
+    f16x8 *piece = reinterpret_cast<f16x8 *>(mm_raw);                                     // [MC][256]
+    float *hn = reinterpret_cast<float *>(mm_raw + (size_t)MC * 4096);                    // [MC][256] -||c||^2 / 2, scaled
+    char *behind = mm_raw + (size_t)MC * 4096 + (size_t)MC * 1024;
+    f16x8 *bstage = reinterpret_cast<f16x8 *>(behind);                                    // [NB][KS][64], before the ring is in use
+    f16x8 *estage = bstage + NB * KS * 64;                                                // ... and what the conversion lost, times 2^11
+    static_assert((size_t)2 * NB * KS * 64 * 16 <= (size_t)NW * RING * 68, "the staging area lies where the rings will");
+    floatx4_t(*ringx)[4][RING] = reinterpret_cast<floatx4_t(*)[4][RING]>(behind);
+    uint32_t(*ringm)[RING] = reinterpret_cast<uint32_t(*)[RING]>(behind + NW * RING * 64);
+    behind += NW * RING * 68;
+    uint32_t(*wcount)[MM_Q] = reinterpret_cast<uint32_t(*)[MM_Q]>(behind);
+    uint32_t(*wpos)[MM_Q] = reinterpret_cast<uint32_t(*)[MM_Q]>(behind + NW * MM_Q * 4);
+    float(*part)[MM_Q] = reinterpret_cast<float(*)[MM_Q]>(behind);                        // partial sums, before the counters are in use
+    behind += NW * MM_Q * 8;
+    float4 *qc = reinterpret_cast<float4 *>(behind);                                      // [MM_Q] threshold, offset, factor
+    uint32_t *cmax = reinterpret_cast<uint32_t *>(behind + MM_Q * 16);                    // [MC] largest ||c||^2, then of ||f||^2
+    uint32_t *fmaxs = cmax + 16, *shared = cmax + 32;                  // shared: max |q|, blocks too loose
+    const int lane = threadIdx.x & 63, w = uniform(threadIdx.x >> 6);
+    const int col = lane & 31, half = lane >> 5;
+    const int qb = blockIdx.y;
+    const int K = a.K, ds = a.ds;
+    const float inf = __uint_as_float(0x7F800000u);
+
+    auto decline = [&]() {
+        if (blockIdx.x == 0) {
+            if (threadIdx.x < MM_Q && (int64_t)qb * MM_Q + threadIdx.x < a.nql) a.margin[(int64_t)qb * MM_Q + threadIdx.x] = (uint32_t)(MC + 2);
+            if (threadIdx.x == 0) a.mode[qb] = 0u;
+        }
+    };
+    if (__syncthreads_or(threadIdx.x < MM_Q && (int64_t)qb * MM_Q + threadIdx.x < a.nql ? (int)a.loose[(int64_t)qb * MM_Q + threadIdx.x] : 0)) {
+        decline();
+        return;
+    }
+    // ---- the largest norms
+    if (threadIdx.x < 48) cmax[threadIdx.x] = 0u;
+    __syncthreads();
+    for (int idx = threadIdx.x; idx < MC * 256; idx += 512) {
+        const int m = idx >> 8, k = idx & 255;
+        if (k < K) atomicMax(&cmax[m], __float_as_uint(a.cbnorm[(int64_t)a.ord.src[m] * K + k]) & 0x7FFFFFFFu);
+    }
+    // ---- this wave's share of the queries: block w % 4, one half of the contraction
+    static_assert(NB == 4 && NW == 8, "eight waves prepare four blocks of 32 queries");
+    const int pbk = w & 3, s0 = (w >> 2) * (KS / 2);
+    float qv[KS / 2][8];
+    {
+        const int64_t ql = (int64_t)qb * MM_Q + pbk * 32 + col;
+        const bool live = ql < a.nq;
+        const float *row = a.queries + (live ? ql : 0) * a.d;
+        const bool wide = (ds & 3) == 0 && (a.d & 3) == 0 && ((reinterpret_cast<uintptr_t>(a.queries) | reinterpret_cast<uintptr_t>(a.cbmean)) & 15) == 0;
+        float mx = 0.f, nn = 0.f;
+#pragma unroll
+        for (int s = 0; s < KS / 2; ++s) {
+            const int src = a.ord.src[2 * (s0 + s) + half];
+            if (wide) {
+#pragma unroll
+                for (int i = 0; i < 8; i += 4) {
+                    float4 v = make_float4(0.f, 0.f, 0.f, 0.f), u = v;
+                    if (live && i < ds) {
+                        v = *reinterpret_cast<const float4 *>(row + src * ds + i);
+                        u = *reinterpret_cast<const float4 *>(a.cbmean + src * ds + i);
+                    }
+                    qv[s][i] = v.x - u.x;
+                    qv[s][i + 1] = v.y - u.y;
+                    qv[s][i + 2] = v.z - u.z;
+                    qv[s][i + 3] = v.w - u.w;
+                }
+            } else {
+#pragma unroll
+                for (int i = 0; i < 8; ++i) qv[s][i] = (live && i < ds) ? row[src * ds + i] - a.cbmean[src * ds + i] : 0.f;
+            }
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                mx = fmaxf(mx, fabsf(qv[s][i]));
+                nn = fmaf(qv[s][i], qv[s][i], nn);
+            }
+        }
+        atomicMax(&shared[0], __float_as_uint(mx));
+        part[(w >> 2) * 2 + half][pbk * 32 + col] = nn;
+    }
+    __syncthreads();
+    float call = 0.f;
+#pragma unroll
+    for (int m = 0; m < MC; ++m) call = fmaxf(call, __uint_as_float(cmax[m]));
+    // powers of two that bring the largest values to at most 2^14 (values from 2^-14 on keep 11 bits)
+    auto scale_for = [](float largest) {
+        int e = 0;
+        frexpf(fmaxf(largest, 1e-18f), &e);
+        return ldexpf(1.f, min(14 - e, 60));
+    };
+    const float sc = scale_for(sqrtf(call)), sq = scale_for(__uint_as_float(shared[0]));
+    const float sigma = sc * sq;
+    auto to16 = [](float v) -> _Float16 { return (_Float16)(fabsf(v) < 6.1035156e-5f ? 0.f : v); };  // no subnormal operands
+    // ---- codewords as operands
+    for (int idx = threadIdx.x; idx < MC * 256; idx += 512) {
+        const int m = idx >> 8, k = idx & 255;
+        const int64_t src = (int64_t)a.ord.src[m] * K + min(k, K - 1);
+        const float *c = a.cbc + src * a.dsp;
+        float ff = 0.f;
+        f16x8 h;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const float v = i < ds ? c[i] : 0.f;
+            h[i] = to16(v * sc);
+            const float f = v - (float)h[i] / sc;
+            ff = fmaf(f, f, ff);
+        }
+        piece[m * 256 + k] = h;
+        hn[m * 256 + k] = -0.5f * sigma * a.cbnorm[src];
+        atomicMax(&fmaxs[m], __float_as_uint(ff) & 0x7FFFFFFFu);
+    }
+    {
+        float ee = 0.f;
+#pragma unroll
+        for (int s = 0; s < KS / 2; ++s) {
+            f16x8 h, l;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                h[i] = to16(qv[s][i] * sq);
+                const float e = qv[s][i] - (float)h[i] / sq;
+                l[i] = to16(e * (2048.f * sq));
+                ee = fmaf(e, e, ee);
+            }
+            bstage[(pbk * KS + s0 + s) * 64 + lane] = h;
+            estage[(pbk * KS + s0 + s) * 64 + lane] = l;
+        }
+        part[4 + (w >> 2) * 2 + half][pbk * 32 + col] = ee;
+    }
+    __syncthreads();
+    // ---- the largest |e.c^ + q^.f| (times 2^11 sigma) of every (query, chunk): wave w takes chunks w and w + 8
+    {
+        float sum[NB] = {0.f, 0.f, 0.f, 0.f};
+        for (int m = w; m < MC; m += NW) {
+            const bool mine = half == (m & 1);  // the other half of the contraction is the neighbouring chunk: zeros
+            float most[NB] = {0.f, 0.f, 0.f, 0.f};
+            for (int t = 0; t * 32 < K; ++t) {
+                const int k = t * 32 + col;
+                f16x8 h = piece[m * 256 + k], l;
+                const float *c = a.cbc + ((int64_t)a.ord.src[m] * K + min(k, K - 1)) * a.dsp;
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    const float v = i < ds ? c[i] : 0.f;
+                    l[i] = mine ? to16((v - (float)h[i] / sc) * (2048.f * sc)) : (_Float16)0.f;
+                    if (!mine) h[i] = (_Float16)0.f;
+                }
+#pragma unroll
+                for (int b = 0; b < NB; ++b) {
+                    floatx16 acc;
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(h, estage[(b * KS + (m >> 1)) * 64 + lane], acc, 0, 0, 0);
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(l, bstage[(b * KS + (m >> 1)) * 64 + lane], acc, 0, 0, 0);
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) most[b] = fmaxf(most[b], fabsf(acc[r]));
+                }
+            }
+#pragma unroll
+            for (int b = 0; b < NB; ++b) sum[b] += fmaxf(most[b], __shfl_xor(most[b], 32));
+        }
+        if (half == 0)
+#pragma unroll
+            for (int b = 0; b < NB; ++b) part[8 + w][b * 32 + col] = sum[b];
+    }
+    __syncthreads();
+    // ---- per query: error bound, threshold, fixed-point form
+    if (threadIdx.x < MM_Q) {
+        const int t = threadIdx.x;
+        const int64_t ql = (int64_t)qb * MM_Q + t;
+        const float nq = (part[0][t] + part[1][t]) + (part[2][t] + part[3][t]);
+        const float ee = (part[4][t] + part[5][t]) + (part[6][t] + part[7][t]);
+        float F = 0.f, C = 0.f, L = 0.f;
+        for (int m = 0; m < MC; ++m) {
+            F += __uint_as_float(fmaxs[m]);
+            C += __uint_as_float(cmax[m]);
+        }
+#pragma unroll
+        for (int i = 0; i < NW; ++i) L += part[8 + i][t];
+        // (1.01: the rounding of e and f themselves; MC / 32: what to16 dropped of them, two units of 2^-14 per dimension)
+        const float G = (float)(6 * 8 * MC + 4 * ds + 4 * MC + 64) * 5.9604645e-8f;
+        const float E = 1.01f * (2.f * L * 4.8828125e-4f + (float)MC * 0.03125f) / sigma + 2.02f * sqrtf(ee * F) + G * (nq + C);
+        const float tau = ql < a.nql ? o.tau[ql] : -1.f;
+        float thr = inf, c0 = 0.f, c1 = 0.f;
+        uint32_t margin = 0u;
+        if (ql < a.nq && tau >= 0.f) {
+            if (!(E * 24.f <= tau) || !(tau < inf) || !(sigma * (nq + C) < 1e37f)) atomicMax(&shared[1], 1u);
+            const float S = 32000.f / (tau + 2.f * E);
+            thr = sigma * (0.5f * (nq - tau) - 0.5f * E);
+            c0 = (nq + E) * S;
+            c1 = 2.f * S / sigma;
+            margin = (uint32_t)fminf(2.002f * E * S + c0 * 9.5367432e-7f + 6.f, 60000.f);
+        }
+        qc[t] = make_float4(thr, c0, c1, __uint_as_float(margin));
+    }
+    __syncthreads();
+    if (shared[1] != 0u) {
+        decline();
+        return;
+    }
+    if (blockIdx.x == 0) {
+        if (threadIdx.x < MM_Q && (int64_t)qb * MM_Q + threadIdx.x < a.nql) a.margin[(int64_t)qb * MM_Q + threadIdx.x] = __float_as_uint(qc[threadIdx.x].w);
+        if (threadIdx.x == 0) a.mode[qb] = 1u;
+    }
+    f16x8 B[NB][KS];
+    float thr[NB];
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+#pragma unroll
+        for (int s = 0; s < KS; ++s) B[b][s] = bstage[(b * KS + s) * 64 + lane];
+        thr[b] = qc[b * 32 + col].x;
+    }
+    __syncthreads();  // the staging area becomes the rings and counters
+    for (int i = lane; i < MM_Q; i += 64) wcount[w][i] = 0u;
+    const int64_t blo = (int64_t)blockIdx.x * per_block, bhi = min(nitems, blo + per_block);
+    if (blo >= bhi) return;
+    const int live_items = (int)(bhi - blo);
+    int held = 0;
+    // A full ring: which of an entry's 16 values pass (a mask), how many per query (LDS atomics, which also hand every entry
+    // its place among them), one global reservation per query, then the values, nearly always one per entry.
+    auto flush = [&]() {
+        constexpr int PASS = (RING + 63) / 64;
+        uint32_t mask[PASS], at[PASS], meta[PASS];
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int u = 0; u < PASS; ++u) {
+            const int i = u * 64 + lane;
+            mask[u] = 0u;
+            if (i < held) {
+                meta[u] = ringm[w][i];
+                const int q = (int)((meta[u] >> 26) & 31u) + 32 * (int)((meta[u] >> 24) & 3u);
+                const int left = live_items - (int)(meta[u] & 0xFFFFFFu) * 32 - 4 * (int)(meta[u] >> 31);  // items from the entry's first on
+                const float t = qc[q].x;
+                uint32_t below = 0u;
+#pragma unroll
+                for (int g = 3; g >= 0; --g) {
+                    const floatx4_t x = ringx[w][g][i];
+#pragma unroll
+                    for (int r = 3; r >= 0; --r) below = (below << 1) | (x[r] >= t && 8 * g + r < left ? 0u : 1u);
+                }
+                mask[u] = ~below & 0xFFFFu;
+                if (mask[u]) at[u] = atomicAdd(&wcount[w][q], (uint32_t)__popc(mask[u]));
+            }
+        }
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int i = 0; i < MM_Q / 64; ++i) {
+            const int q = i * 64 + lane;
+            const uint32_t n = wcount[w][q];
+            wpos[w][q] = n ? atomicAdd(&o.cnt[(int64_t)qb * MM_Q + q], n) : 0u;
+            wcount[w][q] = 0u;
+        }
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int u = 0; u < PASS; ++u) {
+            const int i = u * 64 + lane;
+            if (mask[u]) {
+                const int q = (int)((meta[u] >> 26) & 31u) + 32 * (int)((meta[u] >> 24) & 3u);
+                const uint32_t item0 = (uint32_t)blo + (meta[u] & 0xFFFFFFu) * 32u + 4u * (meta[u] >> 31);
+                const float4 c = qc[q];
+                uint32_t pos = wpos[w][q] + at[u];
+                uint64_t *list = o.cand + ((int64_t)qb * MM_Q + q) * o.C;
+                while (mask[u]) {
+                    const int r = __ffs((int)mask[u]) - 1;
+                    mask[u] &= mask[u] - 1u;
+                    const float x = reinterpret_cast<const float *>(&ringx[w][r >> 2][i])[r & 3];
+                    const uint32_t v = (uint32_t)fminf(fmaxf(c.y - c.z * x, 0.f), 65535.f);
+                    if (pos < o.C) list[pos] = ((uint64_t)v << 32) | (item0 + 8u * (uint32_t)(r >> 2) + (uint32_t)(r & 3));
+                    ++pos;
+                }
+            }
+        }
+        __builtin_amdgcn_wave_barrier();
+        held = 0;
+    };
+    // ---- the walk: 32 encodings per wave and step, the records one step ahead
+    const rsrc_t rr = make_rsrc(rec + blo * M4, (uint32_t)live_items * (M4 * 4));
+    uint32_t nextw[M4];
+    auto fetch = [&](int step) {
+#pragma unroll
+        for (int i = 0; i < M4; ++i)
+            nextw[i] = __builtin_amdgcn_raw_buffer_load_b32(rr, (int)((uint32_t)col * (M4 * 4) + 4u * i), step * (32 * M4 * 4), 0);
+    };
+    const char *abase = mm_raw + half * 4096;                                     // piece `half` of a pair
+    const char *nbase = reinterpret_cast<const char *>(hn) + half * 1024;         // chunk `half` of a pair
+    const int steps = (live_items + 31) / 32;
+    // -||r||^2 / 2: this half's chunks summed here, the two halves by the matrix instruction, for every column
+    uint32_t rot[M4];  // the codes, shifted so that this half's chunk of a pair is in an even byte
+    float part_n = 0.f;
+    auto ready = [&]() {
+        part_n = 0.f;
+#pragma unroll
+        for (int i = 0; i < M4; ++i) rot[i] = nextw[i] >> (8 * half);
+#pragma unroll
+        for (int j = 0; j < MC / 2; ++j) part_n += *reinterpret_cast<const float *>(nbase + j * 2048 + __builtin_amdgcn_ubfe(rot[j >> 1], 16 * (j & 1), 8) * 4);
+    };
+    // the encodings' operands, AHEAD of them on their way: a read takes longer than the four matrix instructions of one
+    constexpr int AHEAD = 2;
+    f16x8 av[AHEAD];
+    auto operand = [&](int s) -> f16x8 {
+        return *reinterpret_cast<const f16x8 *>(abase + s * 8192 + __builtin_amdgcn_ubfe(rot[s >> 1], 16 * (s & 1), 8) * 16);
+    };
+    if (w < steps) {
+        fetch(w);
+        ready();
+#pragma unroll
+        for (int s = 0; s < AHEAD; ++s) av[s] = operand(s);
+    }
+    for (int step = w; step < steps; step += NW) {
+        if (step + NW < steps) fetch(step + NW);
+        floatx16 zero;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) zero[r] = 0.f;
+        const floatx16 norm = __builtin_amdgcn_mfma_f32_32x32x2f32(part_n, 1.f, zero, 0, 0, 0);
+        floatx16 acc[NB];
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+#pragma unroll
+            for (int b = 0; b < NB; ++b) acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(av[s % AHEAD], B[b][s], s == 0 ? norm : acc[b], 0, 0, 0);
+            if (s + AHEAD < KS) av[s % AHEAD] = operand(s + AHEAD);
+            __builtin_amdgcn_sched_barrier(0);  // in this order
+        }
+        ready();  // the next step's, beside the matrix instructions and the tests
+#pragma unroll
+        for (int s = 0; s < AHEAD; ++s) av[s] = operand(s);
+        __builtin_amdgcn_sched_barrier(0);
+        float t[NB];
+        uint64_t bal[NB];
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            t[b] = fmaxf(acc[b][0], acc[b][15]);
+#pragma unroll
+            for (int r = 1; r < 15; r += 2) t[b] = fmaxf(fmaxf(t[b], acc[b][r]), acc[b][r + 1]);
+        }
+#pragma unroll
+        for (int b = 0; b < NB; ++b) bal[b] = __ballot(t[b] >= thr[b]);
+        for (uint32_t todo = (1u << NB) - 1u;;) {
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+                const int n = __popcll(bal[b]);
+                if ((todo >> b & 1u) == 0u || held + n > RING) continue;
+                if (t[b] >= thr[b]) {
+                    const int slot = held + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(bal[b] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal[b], 0u));
+#pragma unroll
+                    for (int g = 0; g < 4; ++g) ringx[w][g][slot] = floatx4_t{acc[b][4 * g], acc[b][4 * g + 1], acc[b][4 * g + 2], acc[b][4 * g + 3]};
+                    ringm[w][slot] = ((uint32_t)lane << 26) | ((uint32_t)b << 24) | (uint32_t)step;
+                }
+                held += n;
+                todo &= ~(1u << b);
+            }
+            if (todo == 0u) break;
+            flush();
+        }
+    }
+    flush();
+}
+
+// ------------------------------------------------------------------------------------------------
 // S4  forest reduction (paper "Encoding Forests": per-tree result arrays summed per vector):
 //     dist(e) = leafp[0][leaf_of[0][e]] + leafp[1][leaf_of[1][e]] + ...   (tree order).
 //     Lane = query; a wave walks consecutive items, each item is T coalesced row reads.
@@ -2476,13 +2886,23 @@ __global__ __launch_bounds__(256) void k_reduce(ReduceArgs r, int64_t nitems, co
 //      value: a step is NV compares whose lane masks are counted on the scalar unit, no LDS and no barrier.  (A radix
 //      select over LDS histograms of 64 queries per workgroup took 28 us however few queries there were and 32 us
 //      for ten thousand, mostly clearing and scanning 64 KB of counters three times; this takes 10 and 25 us.)
-//      The kernel also sets the query's candidate count and flag, so that no launch is needed for those.
+//      The kernel also sets the query's candidate count and flag, so that no launch is needed for those, and says
+//      (LooseArgs) for which queries the error bound of k_mm16 will not be small against this bound: about
+//      4.4e-4 ||q|| C there, more than a thirty-second of tau.  Only the choice of the filter hangs on it.
 //      grid (ceil(queries / 4)), block 256; S <= 64 NV.
 // ------------------------------------------------------------------------------------------------
+struct LooseArgs {
+    uint32_t *loose;       // [nql] or nullptr: not asked for
+    const float *queries;  // [nq][d]
+    const float *mean;     // [d]
+    int d;
+    float most;            // sum over the chunks of the largest squared norm of a centred codeword
+};
+
 template <int NV>
 __global__ __launch_bounds__(256) void k_tau(const float *__restrict__ gmin, int S, int64_t gstride, int k, int64_t nq, int64_t nql,
                                              float *__restrict__ tau, uint32_t *__restrict__ cnt, uint32_t *__restrict__ flag,
-                                             uint32_t *__restrict__ counter)
+                                             uint32_t *__restrict__ counter, LooseArgs la)
 {
     const int lane = threadIdx.x & 63;
     const int64_t ql = (int64_t)blockIdx.x * 4 + uniform(threadIdx.x >> 6);
@@ -2520,6 +2940,17 @@ __global__ __launch_bounds__(256) void k_tau(const float *__restrict__ gmin, int
             else lo = mid + 1;
         }
         bound = S >= k ? hi : 0x7F800000u;
+    }
+    if (la.loose) {
+        float nn = 0.f;
+        if (ql < nq)
+            for (int j = lane; j < la.d; j += 64) {
+                const float v = la.queries[ql * la.d + j] - la.mean[j];
+                nn = fmaf(v, v, nn);
+            }
+#pragma unroll
+        for (int dlt = 32; dlt >= 1; dlt >>= 1) nn += __shfl_xor(nn, dlt);
+        if (lane == 0) la.loose[ql] = ql < nq && !(1.4e-2f * sqrtf(nn * la.most) <= __uint_as_float(bound)) ? 1u : 0u;
     }
     if (lane == 0) {
         tau[ql] = __uint_as_float(bound);
@@ -2730,6 +3161,7 @@ struct SelectArgs {
     int allow_short;         // 1: a query with fewer than k vectors among its candidates is complete (they are all
                              // there are): its row is filled up with id -1 and +inf; 0: such a query goes to the exact kernel
     uint32_t fx_margin;      // 0: the upper word is the float32 distance itself
+    const uint32_t *margins; // [nq] a margin for every query in place of fx_margin, or nullptr
     int fx_first_pass;       // 2: the fixed-point sums are below 2^16 (see block_radix_select), else 0
     const float *lutT;       // [tiles][M][K][64] tables of this batch
     const uint8_t *codes;    // [items][M]
@@ -2816,7 +3248,8 @@ __global__ __launch_bounds__(256) void k_select(SelectArgs a)
             block_radix_select(
                 c, (uint32_t)k, [&](int i, uint32_t &v) { v = (uint32_t)(cand[i] >> 32); return true; }, hist, sel_sh, cut, r2, n2,
                 a.fx_first_pass);
-            cut = cut < 0xFFFFFFFFu - a.fx_margin ? cut + a.fx_margin : 0xFFFFFFFFu;
+            const uint32_t margin = a.margins ? a.margins[ql] : a.fx_margin;
+            cut = cut < 0xFFFFFFFFu - margin ? cut + margin : 0xFFFFFFFFu;
         }
         const float *lq = a.lutT + (int64_t)(ql / QT) * a.M * a.K * QT + (ql % QT);
         auto lut = [&](int m, int code) -> float { return lq[((int64_t)m * a.K + code) * QT]; };
