@@ -277,19 +277,23 @@ __global__ __launch_bounds__(256) void k_ivf_coarse_mfma(const float *__restrict
 }
 
 // ------------------------------------------------------------------------------------------------
-// The same matrix with both operands staged through LDS, for d a multiple of 32 and 16-byte aligned rows: a workgroup
-// owns 128 queries x 256 cells and walks the dimensions 32 at a time; the 384 rows of a stage (one 128-byte line each)
-// are fetched with coalesced 16-byte loads, eight threads per row, held in registers while the previous stage is
-// multiplied, and written to LDS rows of 36 floats (16 lanes reading one column of 16 rows hit 16 different bank
-// quartets).  Same tiles per wave, same operand order and so the same values as k_ivf_coarse_mfma, whose per-lane
-// loads of 16 bytes from 64 different lines keep the matrix cores waiting for the cache's tag look-ups.
-//     grid (ceil(nq / 128), ceil(Kc / 256)), block 256, static LDS 384 * 36 * 4 bytes.
+// The same matrix on the bf16 matrix cores with both operands staged through LDS, for d a multiple of 32 and 16-byte
+// aligned rows: a workgroup owns 128 queries x 256 cells and walks the dimensions 32 at a time; the 384 rows of a stage
+// (one 128-byte line each) are fetched with coalesced 16-byte loads, eight threads per row, held in registers while the
+// previous stage is multiplied, and written to LDS as the sum of two bf16 numbers each (rows of 32 high and 32 low parts
+// and 16 bytes of padding: 16 lanes reading one column of 16 rows hit 16 different bank quartets).  q.c is taken as
+// q_l.c_h + q_h.c_l + q_h.c_h: what is left out is at most 3.1 2^-18 sum |q c|, 99 2^-24 (||q|| + ||c||)^2 of the value,
+// and the three products per dimension round like 3 d (same unit); the selection's bound allows for both.
+// Bound by its results: 10 000 x 8192 cells of 128 dimensions, 328 MB written, 0.27 -> 0.15 ms against the float32 matrix
+// instruction (whose 0.15 ms of matrix time came on top of the stores).
+//     grid (ceil(nq / 128), ceil(Kc / 256)), block 256, static LDS 384 * 144 bytes.
 // ------------------------------------------------------------------------------------------------
+constexpr int IVF_SPLIT_UNITS = 128;  // what the split adds to the selection's bound (99, and the third product's rounding at small d)
 __global__ __launch_bounds__(256, 2) void k_ivf_coarse_tc(const float *__restrict__ x, int64_t n, int d, const float *__restrict__ cent,
                                                        const float *__restrict__ cnorm, int Kc, float *__restrict__ approx)
 {
-    constexpr int RS = 36;  // floats per LDS row
-    __shared__ __attribute__((aligned(16))) float tile[384 * RS];
+    constexpr int RS = 144;  // bytes per LDS row
+    __shared__ __attribute__((aligned(16))) char tile[384 * RS];
     const int t = threadIdx.x, lane = t & 63, w = uniform(t >> 6);
     const int col = lane & 31, half = lane >> 5;
     const int64_t q0 = (int64_t)blockIdx.x * 128;
@@ -307,7 +311,7 @@ __global__ __launch_bounds__(256, 2) void k_ivf_coarse_tc(const float *__restric
     for (int i = 0; i < 4; ++i) off[i] = (uint32_t)(min(r0 + 32 * i, qrows - 1) * d + 4 * c4);
 #pragma unroll
     for (int i = 4; i < 12; ++i) off[i] = (uint32_t)(min(r0 + 32 * (i - 4), crows - 1) * d + 4 * c4);
-    const int dst0 = r0 * RS + 4 * c4;  // LDS position of piece i: dst0 + 32 i RS
+    const int dst0 = r0 * RS + 8 * c4;  // LDS position of piece i's high parts: dst0 + 32 i RS; the low parts 64 bytes on
     floatx16 acc[2][4];
 #pragma unroll
     for (int rb = 0; rb < 2; ++rb)
@@ -323,7 +327,15 @@ __global__ __launch_bounds__(256, 2) void k_ivf_coarse_tc(const float *__restric
     for (int j0 = 0; j0 < d; j0 += 32) {
         __syncthreads();  // the previous stage has been read
 #pragma unroll
-        for (int i = 0; i < 12; ++i) *reinterpret_cast<vf4 *>(tile + dst0 + 32 * i * RS) = st[i];
+        for (int i = 0; i < 12; ++i) {
+            typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+            const bf16x4 h = __builtin_convertvector(st[i], bf16x4);
+            const uint2 hb = __builtin_bit_cast(uint2, h);
+            const vf4 up = {__uint_as_float(hb.x << 16), __uint_as_float(hb.x & 0xFFFF0000u), __uint_as_float(hb.y << 16),
+                            __uint_as_float(hb.y & 0xFFFF0000u)};
+            *reinterpret_cast<bf16x4 *>(tile + dst0 + 32 * i * RS) = h;
+            *reinterpret_cast<bf16x4 *>(tile + dst0 + 32 * i * RS + 64) = __builtin_convertvector(st[i] - up, bf16x4);
+        }
         __syncthreads();
         {
             const int jn = min(j0 + 32, d - 32);  // after the last stage: the last again (not used)
@@ -336,29 +348,25 @@ __global__ __launch_bounds__(256, 2) void k_ivf_coarse_tc(const float *__restric
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int blk = 0; blk < 2; ++blk) {
-            const int j = 16 * blk + 8 * half;
-            float a[2][8], b[4][8];
+            const int j = (16 * blk + 8 * half) * 2;
+            bf16x8 ah[2], al[2];
 #pragma unroll
             for (int rb = 0; rb < 2; ++rb) {
-                const float *p = tile + (arow + rb * 32 + col) * RS + j;
-                const float4 lo = *reinterpret_cast<const float4 *>(p), hi = *reinterpret_cast<const float4 *>(p + 4);
-                a[rb][0] = lo.x; a[rb][1] = lo.y; a[rb][2] = lo.z; a[rb][3] = lo.w;
-                a[rb][4] = hi.x; a[rb][5] = hi.y; a[rb][6] = hi.z; a[rb][7] = hi.w;
+                const char *p = tile + (arow + rb * 32 + col) * RS + j;
+                ah[rb] = *reinterpret_cast<const bf16x8 *>(p);
+                al[rb] = *reinterpret_cast<const bf16x8 *>(p + 64);
             }
 #pragma unroll
             for (int cb = 0; cb < 4; ++cb) {
-                const float *p = tile + (brow + cb * 32 + col) * RS + j;
-                const float4 lo = *reinterpret_cast<const float4 *>(p), hi = *reinterpret_cast<const float4 *>(p + 4);
-                b[cb][0] = lo.x; b[cb][1] = lo.y; b[cb][2] = lo.z; b[cb][3] = lo.w;
-                b[cb][4] = hi.x; b[cb][5] = hi.y; b[cb][6] = hi.z; b[cb][7] = hi.w;
+                const char *p = tile + (brow + cb * 32 + col) * RS + j;
+                const bf16x8 bh = *reinterpret_cast<const bf16x8 *>(p), bl = *reinterpret_cast<const bf16x8 *>(p + 64);
+#pragma unroll
+                for (int rb = 0; rb < 2; ++rb) acc[rb][cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al[rb], bh, acc[rb][cb], 0, 0, 0);
+#pragma unroll
+                for (int rb = 0; rb < 2; ++rb) acc[rb][cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[rb], bl, acc[rb][cb], 0, 0, 0);
+#pragma unroll
+                for (int rb = 0; rb < 2; ++rb) acc[rb][cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[rb], bh, acc[rb][cb], 0, 0, 0);
             }
-#pragma unroll
-            for (int i = 0; i < 8; ++i)
-#pragma unroll
-                for (int rb = 0; rb < 2; ++rb)
-#pragma unroll
-                    for (int cb = 0; cb < 4; ++cb)
-                        acc[rb][cb] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[rb][i], b[cb][i], acc[rb][cb], 0, 0, 0);
         }
     }
     const int64_t qb = q0 + (w & 1) * 64;
@@ -415,7 +423,7 @@ __device__ __forceinline__ float ivf_rule_distance(const float *q, const float *
 // ------------------------------------------------------------------------------------------------
 // Probe selection on the approximate matrix of k_ivf_coarse_mfma, with the result of the float32 rule.
 //     With a = ||c||^2 - 2 <q, c> as computed there and r the rule's distance, |a + ||q||^2 - r| <= E for
-//     E = (8 d + 16) 2^-24 (||q|| + max ||c||)^2: the centroid's norm, the contraction (d products, accumulated in
+//     E = units 2^-24 (||q|| + max ||c||)^2, units = 8 d + 16, and 128 more for the split products of k_ivf_coarse_tc: the centroid's norm, the contraction (d products, accumulated in
 //     float32, taken at twice the unit roundoff), the last operation and the rule's own d + 2 roundings are each at
 //     most their count times 2^-24 (||q|| + ||c||)^2, together (6 d + 7) of them.  So a cell among the w smallest
 //     by the rule has a <= a_w + 2 E, a_w the w-th smallest a of the row, and so a <= t + 2 E for any t with at
@@ -469,7 +477,7 @@ __device__ __forceinline__ void ivf_for_row(const float *__restrict__ row, int K
     }
 }
 
-__global__ __launch_bounds__(256) void k_ivf_probe_mfma(const float *__restrict__ x, int d, const float *__restrict__ cent, float cmax, float slack,
+__global__ __launch_bounds__(256) void k_ivf_probe_mfma(const float *__restrict__ x, int d, const float *__restrict__ cent, float cmax, int units, float slack,
                                                         float *__restrict__ approx, int Kc, int w, int cap,
                                                         int32_t *__restrict__ probes, float *__restrict__ base)
 {
@@ -496,7 +504,7 @@ __global__ __launch_bounds__(256) void k_ivf_probe_mfma(const float *__restrict_
     __syncthreads();
     const float qq = (s_red[0] + s_red[1]) + (s_red[2] + s_red[3]);
     const float S = sqrtf(qq) * 1.001f + cmax;
-    const float E2 = 2.f * (float)(8 * d + 16) * 5.9604645e-8f * 1.01f * S * S * slack;
+    const float E2 = 2.f * (float)units * 5.9604645e-8f * 1.01f * S * S * slack;
     // A bound at or above the w-th smallest a of the row, without sorting anything: the row's range in 1024 equal bins,
     // the first bin at which the running count reaches w, its upper edge.  (A radix select on the float bits finds the
     // w-th itself, but its first digits are the same for nearly all cells: every count lands on one LDS word.)
@@ -1170,16 +1178,19 @@ extern "C" int etf_ivf_upload(etf_ctx *ctx, void *dev_buf, int64_t bytes)
 }
 
 // ---- database side on the device: cell, residual, residual encoding ------------------------------------------
-// the approximate distance matrix of n vectors: operands through LDS where the rows allow it
-static void ivf_launch_coarse(etf_ctx *ctx, const float *x, int64_t n, const float *cent, const float *cnorm, float *matrix)
+// the approximate distance matrix of n vectors: operands through LDS where the rows allow it; returns the units of the
+// selection's bound (see k_ivf_probe_mfma)
+static int ivf_launch_coarse(etf_ctx *ctx, const float *x, int64_t n, const float *cent, const float *cnorm, float *matrix)
 {
     const int d = ctx->d, Kc = ctx->ivf.Kc;
     const dim3 grid((unsigned)((n + 127) / 128), (unsigned)((Kc + 255) / 256));
     hipStream_t st = (hipStream_t)ctx->stream;
-    if ((d & 31) == 0 && (reinterpret_cast<uintptr_t>(x) & 15) == 0 && (reinterpret_cast<uintptr_t>(cent) & 15) == 0 && ctx->opt.ivf_coarse_tile != 0)
+    if ((d & 31) == 0 && (reinterpret_cast<uintptr_t>(x) & 15) == 0 && (reinterpret_cast<uintptr_t>(cent) & 15) == 0 && ctx->opt.ivf_coarse_tile != 0) {
         hipLaunchKernelGGL(k_ivf_coarse_tc, grid, dim3(256), 0, st, x, n, d, cent, cnorm, Kc, matrix);
-    else
-        hipLaunchKernelGGL(k_ivf_coarse_mfma, grid, dim3(256), 0, st, x, n, d, cent, cnorm, Kc, matrix);
+        return 8 * d + 16 + IVF_SPLIT_UNITS;
+    }
+    hipLaunchKernelGGL(k_ivf_coarse_mfma, grid, dim3(256), 0, st, x, n, d, cent, cnorm, Kc, matrix);
+    return 8 * d + 16;
 }
 
 // vectors per batch of the coarse assignment: their distance matrix stays within 256 MiB
@@ -1241,9 +1252,9 @@ extern "C" int etf_ivf_assign_device(etf_ctx *ctx, const float *x, int64_t n, in
             if (rc) return rc;
             for (int64_t v0 = 0; v0 < n; v0 += nb) {
                 const int64_t nv = std::min<int64_t>(nb, n - v0);
-                ivf_launch_coarse(ctx, x + v0 * d, nv, cent, cnorm, matrix);
+                const int units = ivf_launch_coarse(ctx, x + v0 * d, nv, cent, cnorm, matrix);
                 LAUNCH_CHECK(ctx, "k_ivf_coarse_mfma");
-                hipLaunchKernelGGL(k_ivf_probe_mfma, dim3((unsigned)nv), dim3(256), lds_probe, st, x + v0 * d, d, cent, iv.cmax,
+                hipLaunchKernelGGL(k_ivf_probe_mfma, dim3((unsigned)nv), dim3(256), lds_probe, st, x + v0 * d, d, cent, iv.cmax, units,
                                    (float)ctx->opt.ivf_probe_slack, matrix, iv.Kc, 1, cap, cells_out + v0, nearest);
                 LAUNCH_CHECK(ctx, "k_ivf_probe_mfma");
             }
@@ -1316,9 +1327,9 @@ extern "C" int etf_ivf_search(etf_ctx *ctx, const float *queries, int64_t Q, int
             ProfScope prof(ctx, ETF_K_IVF_COARSE);
             if (ctx->opt.ivf_coarse_kernel == 0) {
                 const float *cnorm = reinterpret_cast<const float *>(img + iv.o_cnorm);
-                ivf_launch_coarse(ctx, qb, nq, cent, cnorm, coarse);
+                const int units = ivf_launch_coarse(ctx, qb, nq, cent, cnorm, coarse);
                 LAUNCH_CHECK(ctx, "k_ivf_coarse_mfma");
-                hipLaunchKernelGGL(k_ivf_probe_mfma, dim3((unsigned)nq), dim3(256), lds_probe, st, qb, d, cent, iv.cmax, (float)ctx->opt.ivf_probe_slack, coarse, iv.Kc, w, P.cap, probes,
+                hipLaunchKernelGGL(k_ivf_probe_mfma, dim3((unsigned)nq), dim3(256), lds_probe, st, qb, d, cent, iv.cmax, units, (float)ctx->opt.ivf_probe_slack, coarse, iv.Kc, w, P.cap, probes,
                                    pbase);
                 LAUNCH_CHECK(ctx, "k_ivf_probe_mfma");
             } else {
