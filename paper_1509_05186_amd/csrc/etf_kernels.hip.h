@@ -180,6 +180,9 @@ __device__ __forceinline__ float product_shift(const float *__restrict__ bm, int
 //     fixed r the lanes 0..31 hold 32 consecutive queries of one codeword: a 128-byte piece of a table row.
 //     Entries that are small against the norms are recomputed exactly (see below).
 //     IP: the tables hold the scalar products q_m . c themselves: the contraction on the unshifted vectors.
+//     PUB (with IP): only lut_public is written, [q][M][K].  The operands change places, so that the lanes of a result
+//     register hold 32 codewords of one query, 128 bytes of a row (the lanes' queries lie M K floats apart:
+//     a store instruction was 64 pieces of 4 bytes; the tables of 10 000 queries, 8 KB each, 0.10 -> 0.03 ms).
 //     RB = 2: grid (tiles, M), block 256 (wave w: codewords 64w .. 64w+63).  RB = 1 (the default launch): grid
 //     (tiles, M, ceil(K / 32)), block 64 (one wave per workgroup, its 32 codewords given by blockIdx.z): eight times
 //     the workgroups, each with an eighth of the entries to sweep and to recompute and a queue of 4 KB instead of
@@ -188,7 +191,7 @@ __device__ __forceinline__ float product_shift(const float *__restrict__ bm, int
 // ------------------------------------------------------------------------------------------------
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 
-template <bool IP, int RB>
+template <bool IP, int RB, bool PUB = false>
 __global__ __launch_bounds__(256) void k_lut_mfma(const float *__restrict__ queries, int64_t Q, int64_t q0, int d, int M,
                                                   int K, const float *__restrict__ cb, const float *__restrict__ cbc,
                                                   const float *__restrict__ cbnorm, const float *__restrict__ cbmean,
@@ -265,7 +268,22 @@ __global__ __launch_bounds__(256) void k_lut_mfma(const float *__restrict__ quer
             for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
                 for (int cb2 = 0; cb2 < 2; ++cb2)
-                    acc[rb][cb2] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[rb][i], b[cb2][i], acc[rb][cb2], 0, 0, 0);
+                    acc[rb][cb2] = PUB ? __builtin_amdgcn_mfma_f32_32x32x2f32(b[cb2][i], a[rb][i], acc[rb][cb2], 0, 0, 0)
+                                       : __builtin_amdgcn_mfma_f32_32x32x2f32(a[rb][i], b[cb2][i], acc[rb][cb2], 0, 0, 0);
+    }
+    if constexpr (PUB) {
+#pragma unroll
+        for (int cb2 = 0; cb2 < 2; ++cb2)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int64_t q = q0 + (int64_t)tile * QT + cb2 * 32 + 8 * (r / 4) + 4 * half + (r % 4);
+#pragma unroll
+                for (int rb = 0; rb < RB; ++rb) {
+                    const int k = kbase + rb * 32 + col;
+                    if (q < Q && k < K) lut_public[(q * M + ms) * K + k] = acc[rb][cb2][r];
+                }
+            }
+        return;
     }
     // the two halves of the wave summed the even and the odd dimensions of the same query
 #pragma unroll
