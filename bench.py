@@ -325,7 +325,13 @@ class Workload:
             lps = kd["launches_per_step"]
             achieved = kd["alg_GBps"] or 0.0
             traffic, traffic_note = (None, "scaled run") if not self.valid else measured_traffic(cfg.name, dom, TRAVERSAL_NAMES[traversal])
-            if dom in ("lds", "lds16"):
+            if dom == "lds16" and cfg.M in (8, 16) and cfg.d <= 8 * cfg.M and \
+                    (cfg.query_batch or self.Q) * stats["n_distinct"] >= (1 << 29) * (2 if cfg.M == 8 else 1):
+                # chunks of at most 8 dimensions: the filter runs on the matrix cores (k_mm16), a contraction over the dimensions
+                tflops = 2.0 * self.Q * stats["n_distinct"] * cfg.d / (kd["ms_per_step"] / 1e3) / 1e12
+                roofline = {"bound": "alu", "resource": "16-bit matrix cores", "kernel": "k_mm16", "achieved": tflops, "peak": 2500.0,
+                            "unit": "TFLOP/s", "frac": tflops / 2500.0, "traffic": None, "traffic_note": "not counted for this kernel"}
+            elif dom in ("lds", "lds16"):
                 # bound by the LDS pipe and the vector adds behind it: algorithmic bytes are the table entries this kernel
                 # reads from LDS per query, 4 bytes each in k_lds, 2 bytes each in k_lds16
                 eb = 4 if dom == "lds" else 2
