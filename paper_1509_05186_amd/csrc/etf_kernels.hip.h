@@ -906,17 +906,19 @@ __global__ __launch_bounds__(256, 2) void k_encode_mfma(const float *__restrict_
 // ------------------------------------------------------------------------------------------------
 // The same assignment on the bf16 matrix cores (groups of at most 128 dimensions, any alignment; wider groups take
 //     k_encode_wide or k_encode_mfma).  Only a decision is wanted, and only its rounding has to be proved harmless, so
-//     every float32 value goes in as a sum of two bf16 numbers, a = a_h + a_l + r with |r| <= 2^-18 |a|, and x.c as
-//     x_l.c_h + x_h.c_l + x_h.c_h: three bf16 instructions of 32 cycles for 16 dimensions where the float32 instruction
-//     takes eight of 64.  Vectors and codewords are taken relative to a point mu near the group's codewords (their
+//     every float32 value goes in as a sum of two bf16 numbers, a = a_h + a_l + r, and x.c as x_l.c_h + x_h.c_l + x_h.c_h:
+//     three bf16 instructions of 32 cycles for 16 dimensions where the float32 instruction takes eight of 64.  bf16 has 8
+//     significant bits, so |a_l| <= 2^-8 |a| and |r| <= 2^-17 |a|; a product lacks x_l c_l and two such rests, at most
+//     2^-16 + 2 2^-17 = 2^-15 of |x c|.  Vectors and codewords are taken relative to a point mu near the group's codewords (their
 //     mean, roughly), which changes no distance and makes the values, and with them every rounding, smaller.
 //     For a (vector, group) the accumulators hold x.c - ||c||^2 / 2 of all codewords (largest = nearest).  -||c||^2 / 2
 //     enters last, as the sum of three bf16 numbers against ones in an instruction of its own (as a starting value it
-//     would take four LDS reads per tile and make every rounding one of the larger sum); the small products are first.  With S = ||x||^2 + max ||c||^2, in units of 2^-24 S a value is off by at
-//     most: 99.2 (split: 3.1 2^-18 sum |x c|), 1.03 ds (sum of x_h.c_h and of the small products, one unit in the last
-//     place per product), 6 (the three norm slots), 0.5 ds (the norm), 2 (x - mu, c - mu); the float32 rule's distance
-//     (halved) by ds + 2.  Two values together: less than 6 ds + 224 (from 6 blocks of 16 dimensions on the small products
-//     come first in either half of the blocks, for want of registers: 1.03 ds more per value, 8 ds + 224).  So with E = (6 ds + 224) 2^-24 S every codeword
+//     would take four LDS reads per tile and make every rounding one of the larger sum); the small products are first.
+//     With S = ||x||^2 + max ||c||^2, sum |x c| <= S / 2, in units of 2^-24 S a value is off by at most: 256 (split), 1.03 ds
+//     (sum of x_h.c_h and of the small products, one unit in the last place per product), 6 (the three norm slots), 0.5 ds
+//     (the norm), 2 (x - mu, c - mu); the float32 rule's distance (halved) by ds + 2.  Two values together: less than
+//     6 ds + 544 (from 6 blocks of 16 dimensions on the small products come first in either half of the blocks, for want of
+//     registers: 1.03 ds more per value, 8 ds + 544).  So with E = (6 ds + 544) 2^-24 S every codeword
 //     the rule might choose has a value of at least the largest minus E.  Where that is one codeword it is the code;
 //     otherwise (a few vectors in a thousand) the float32 rule is evaluated for exactly those codewords (usually two),
 //     pairs (vector, codeword) of a wave collected in LDS until they fill its lanes.  The codes are k_encode's, bit
@@ -1040,7 +1042,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void k_encode_bf(const float *__re
     }
     __syncthreads();
 
-    const float eps = (float)((NB >= 6 ? 8 : 6) * ds + 224) * 5.9604645e-8f;
+    const float eps = (float)((NB >= 6 ? 8 : 6) * ds + 544) * 5.9604645e-8f;
     const float inf = __uint_as_float(0x7F800000u);
     int hcount = 0, pcount = 0;
     // the float32 rule for the collected pairs, a lane each

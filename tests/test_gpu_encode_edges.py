@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 
 import oracle
-from workload import near_tie_vectors
+from workload import aligned_low_parts, near_tie_vectors
 
 pytestmark = pytest.mark.gpu
 
@@ -53,6 +53,20 @@ def test_most_vectors_take_the_rule(ds):
     c = encoder(cb)
     x = np.concatenate([cb[m][rng.integers(0, 256, 3000)] + rng.normal(size=(3000, ds)) * 0.1 for m in range(4)], 1).astype(np.float32)
     assert np.array_equal(encode(c, x), oracle.encode_f32(x, cb))
+
+
+@pytest.mark.parametrize("ds", [4, 7, 8, 12, 16, 17, 20, 25, 40, 64, 96, 128])
+def test_split_errors_that_point_the_same_way(ds):
+    """What two bf16 numbers leave out of a value makes the farther of two codewords look the nearer one by as much as the
+    split can; random values stay a factor of ten below (see tests/test_split_bounds.py for the sizes)."""
+    print("encoder: aligned low parts, ds", ds, flush=True)
+    made = [aligned_low_parts(ds, f) for f in (0.3, 0.6, 0.8, 0.85, 0.9, 0.95, 0.98, 0.99)]
+    cb = np.stack([m[0] for m in made])
+    x = np.concatenate([m[1] for m in made])[None].repeat(33, 0)
+    x[1::2] = -x[1::2]                                     # the other half: ordinary vectors of the same codebooks
+    want = oracle.encode_f32(x, cb)
+    assert (want[::2] == 1).all()
+    assert np.array_equal(encode(encoder(cb), x), want)
 
 
 def test_values_that_are_not_finite_stay_their_own():

@@ -142,3 +142,23 @@ def near_tie_vectors(codebooks: np.ndarray, n: int, seed: int, spread: float = 3
     scale = np.abs(cb).max()
     x = mid + rng.uniform(-spread, spread, size=mid.shape) * scale
     return np.ascontiguousarray(x.reshape(n, M * ds), dtype=np.float32)
+
+
+def aligned_low_parts(ds: int, fraction: float, K: int = 256):
+    """A codebook [K][ds] and a vector [ds] on which everything that a sum of two bf16 numbers leaves out of a float32
+    points the same way: codeword 1 is h + l and codeword 2 is h - l in all dimensions but the first, the vector lies
+    above h by half a unit in the last place (2^-8) less its own last bits.  In dimension 0 codeword 1 has what makes up
+    the given fraction of the amount by which codeword 2 is the farther one in the others, so codeword 1 stays the
+    nearest.  All other codewords are +-p with p alternating in sign, such that those at the multiples of 16 cancel.
+    Draws nothing and evaluates no nearest codeword."""
+    h, low = 1 + 2.0 ** -7, 2.0 ** -8 - 2.0 ** -16 + 2.0 ** -17 - 2.0 ** -23
+    k = np.arange(K)
+    sign = np.where(k % 16 == 0, np.where(k % 32 == 0, -1.0, 1.0), np.where(k % 2 == 0, 1.0, -1.0))
+    cb = (sign[:, None] * np.where(np.arange(ds) % 2 == 0, 1.0, -1.0)[None, :]).astype(np.float32)
+    x = np.zeros(ds, dtype=np.float32)
+    x[1:] = h + 2.0 ** -8 - 2.0 ** -17
+    cb[1:3, 0] = 0.0
+    cb[1, 1:], cb[2, 1:] = h + low, h - low
+    farther = (x[1:].astype(np.float64) - cb[2, 1:]) ** 2 - (x[1:].astype(np.float64) - cb[1, 1:]) ** 2
+    cb[1, 0] = np.sqrt(fraction * farther.sum())
+    return cb, x
