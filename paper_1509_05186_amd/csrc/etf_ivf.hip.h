@@ -282,13 +282,14 @@ __global__ __launch_bounds__(256) void k_ivf_coarse_mfma(const float *__restrict
 // (one 128-byte line each) are fetched with coalesced 16-byte loads, eight threads per row, held in registers while the
 // previous stage is multiplied, and written to LDS as the sum of two bf16 numbers each (rows of 32 high and 32 low parts
 // and 16 bytes of padding: 16 lanes reading one column of 16 rows hit 16 different bank quartets).  q.c is taken as
-// q_l.c_h + q_h.c_l + q_h.c_h: what is left out is at most 3.1 2^-18 sum |q c|, 99 2^-24 (||q|| + ||c||)^2 of the value,
-// and the three products per dimension round like 3 d (same unit); the selection's bound allows for both.
+// q_l.c_h + q_h.c_l + q_h.c_h.  bf16 has 8 significant bits: what is left out is at most (2^-16 + 2 2^-17) sum |q c|, which is
+// 2^-16 (||q|| + ||c||)^2 of the value or 256 units of 2^-24 (||q|| + ||c||)^2, and the three products per dimension round
+// like 3 d such units; the selection's bound allows for both.
 // Bound by its results: 10 000 x 8192 cells of 128 dimensions, 328 MB written, 0.27 -> 0.15 ms against the float32 matrix
 // instruction (whose 0.15 ms of matrix time came on top of the stores).
 //     grid (ceil(nq / 128), ceil(Kc / 256)), block 256, static LDS 384 * 144 bytes.
 // ------------------------------------------------------------------------------------------------
-constexpr int IVF_SPLIT_UNITS = 128;  // what the split adds to the selection's bound (99, and the third product's rounding at small d)
+constexpr int IVF_SPLIT_UNITS = 272;  // what the split adds to the selection's bound (256, and room for the rounding at the smallest d)
 __global__ __launch_bounds__(256, 2) void k_ivf_coarse_tc(const float *__restrict__ x, int64_t n, int d, const float *__restrict__ cent,
                                                        const float *__restrict__ cnorm, int Kc, float *__restrict__ approx)
 {
@@ -423,9 +424,10 @@ __device__ __forceinline__ float ivf_rule_distance(const float *q, const float *
 // ------------------------------------------------------------------------------------------------
 // Probe selection on the approximate matrix of k_ivf_coarse_mfma, with the result of the float32 rule.
 //     With a = ||c||^2 - 2 <q, c> as computed there and r the rule's distance, |a + ||q||^2 - r| <= E for
-//     E = units 2^-24 (||q|| + max ||c||)^2, units = 8 d + 16, and 128 more for the split products of k_ivf_coarse_tc: the centroid's norm, the contraction (d products, accumulated in
-//     float32, taken at twice the unit roundoff), the last operation and the rule's own d + 2 roundings are each at
-//     most their count times 2^-24 (||q|| + ||c||)^2, together (6 d + 7) of them.  So a cell among the w smallest
+//     E = units 2^-24 (||q|| + max ||c||)^2: the centroid's norm (d units), the contraction (one per product, each rounded to
+//     a unit in the last place: d, or 3 d for k_ivf_coarse_tc), the last operation, the bin edge below and the rule's own
+//     d + 2 roundings stay below 3 d + 16 (5 d + 16); units = 8 d + 16 allows for them, and IVF_SPLIT_UNITS more for what the split
+//     products of k_ivf_coarse_tc leave out.  So a cell among the w smallest
 //     by the rule has a <= a_w + 2 E, a_w the w-th smallest a of the row, and so a <= t + 2 E for any t with at
 //     least w cells at or below it (t: a bin edge of the row's range, see below).  Those cells are collected (a few
 //     more than w), their distances computed by the rule, and the w smallest (distance, cell) of them are the probes:

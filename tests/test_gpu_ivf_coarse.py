@@ -6,6 +6,7 @@ import numpy as np
 import pytest
 
 import oracle
+from workload import aligned_low_parts
 
 pytestmark = pytest.mark.gpu
 
@@ -58,3 +59,14 @@ def test_queries_that_are_not_finite():
     q = rng.normal(size=(140, 32)).astype(np.float32)
     q[3, 4], q[77, 0], q[139, 31] = np.inf, 3.4e38, -1e25
     both(cent, x, q, 8, 5)
+
+
+@pytest.mark.parametrize("d", [32, 64])
+def test_split_errors_that_point_the_same_way(d):
+    """The farther of two centroids looks the nearer one by as much as the split can (tests/test_split_bounds.py)."""
+    print("split coarse distances: aligned low parts, d", d, flush=True)
+    for fraction in (0.6, 0.9, 0.99):
+        cent, x = aligned_low_parts(d, fraction)
+        v = np.tile(x, (40, 1))
+        v[1::2] = -x
+        both(cent, v, v[:33], 1, 5)
