@@ -692,7 +692,7 @@ __device__ __forceinline__ float encode_rule_term(float s, float x, float c)
 
 // The float32 rule for one vector, evaluated by a whole wave (the near-ties of the matrix-core encoders): lane l takes
 // codewords l, l + 64, l + 128, l + 192 (K <= 256), each distance the sum of its terms in dimension order; returns
-// the codeword with the smallest (distance, index) in every lane.  xv: the vector's values of the group, cbm: the
+// the codeword with the smallest (distance, index) in every lane, 0 where no distance is below the largest float (as k_encode).  xv: the vector's values of the group, cbm: the
 // group's codewords [K][ds].  rows16: ds is a multiple of 4 and both rows are 16-byte aligned; then the four sums
 // advance together on 16-byte loads, two steps in flight (one value per load and iteration is a memory latency per
 // dimension and codeword: 0.1 ms for a single vector with 120 dimensions per group).
@@ -746,7 +746,7 @@ __device__ __forceinline__ int encode_rule_wave(const float *__restrict__ xv, co
             best = ob;
         }
     }
-    return best;
+    return best == 0x7FFFFFFF ? 0 : best;
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1266,7 +1266,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void k_encode_bf(const float *__re
                 hcount += nh;
                 if (hard && half == 0) {
                     hvec[slot] = ((uint64_t)v << 8) | (uint32_t)(m0 + mlc);
-                    hbest[slot] = ((uint64_t)0x7F7FFFFFu << 32) | 0xFFFFFFFFu;
+                    hbest[slot] = (uint64_t)0x7F7FFFFFu << 32;  // codeword 0 where no distance is below the largest float
                 }
                 uint32_t tm = hard ? mark >> 16 : 0u, rm = mark & 0xFFFFu;
                 for (;;) {

@@ -69,18 +69,23 @@ def test_split_errors_that_point_the_same_way(ds):
     assert np.array_equal(encode(encoder(cb), x), want)
 
 
-def test_values_that_are_not_finite_stay_their_own():
-    print("encoder: NaN and infinities in some groups", flush=True)
+@pytest.mark.parametrize("ds,K", [(16, 256), (16, 40), (6, 256), (132, 256), (130, 100)])
+@pytest.mark.parametrize("wide", [0, 1])
+def test_values_that_are_not_finite_stay_their_own(ds, K, wide):
+    """A vector without a distance below the largest float in a group gets codeword 0 there, as by the rule for every codeword;
+    its other groups and the other vectors keep their codes."""
+    print("encoder: NaN and infinities in some groups, ds", ds, "K", K, flush=True)
     rng = np.random.default_rng(8)
-    cb = rng.normal(size=(4, 256, 16)).astype(np.float32)
+    cb = rng.normal(size=(4, K, ds)).astype(np.float32)
     c = encoder(cb)
-    x = rng.normal(size=(500, 64)).astype(np.float32)
+    c.set_option("encode_wide", wide)
+    x = rng.normal(size=(500, 4 * ds)).astype(np.float32)
     bad = np.zeros((500, 4), dtype=bool)
     for i, v in ((3, np.nan), (77, np.inf), (78, -np.inf), (499, 3e38)):
-        x[i, 16 * (i % 4) + 5] = v
+        x[i, ds * (i % 4) + 5] = v
         bad[i, i % 4] = True
     got = encode(c, x)
-    clean = np.where(np.isfinite(x) & (np.abs(x) < 1e30), x, 0).astype(np.float32)
-    want = oracle.encode_f32(clean, cb)
-    assert np.array_equal(got[~bad], want[~bad])
-    assert (got[bad] == 255).all()  # no codeword has a finite distance below the largest float
+    with np.errstate(all="ignore"):
+        want = oracle.encode_f32(x, cb)
+    assert (want[bad] == 0).all()
+    assert np.array_equal(got, want)
