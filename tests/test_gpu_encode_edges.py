@@ -1,6 +1,7 @@
-"""The bf16 matrix-core encoder at the sizes where it can go wrong: every number of 16-dimension blocks and both sides of
+"""The matrix-core encoders at the sizes where they can go wrong: every number of 16-dimension blocks and both sides of
 their edges, aligned and unaligned rows, codebooks that end inside a tile, chunks of 32 vectors and their remainders,
-values that are not finite or far from the origin.  Codes are whole numbers: exact, against the float32 oracle."""
+groups beyond 128 dimensions (the float32 matrix instruction, through LDS or streamed per lane), values that are not finite
+or far from the origin.  Codes are whole numbers: exact, against the float32 oracle."""
 import numpy as np
 import pytest
 
@@ -40,6 +41,40 @@ def test_edges_of_blocks_tiles_and_chunks(ds, M, K, n):
     assert np.array_equal(encode(c, x), oracle.encode_f32(x, cb))
     ties = near_tie_vectors(cb, n, seed=ds) if K > 1 else x
     assert np.array_equal(encode(c, ties), oracle.encode_f32(ties, cb))
+
+
+@pytest.mark.parametrize("ds,M,K,n", [
+    (129, 2, 256, 300), (130, 3, 100, 257), (131, 2, 50, 333), (132, 3, 256, 129), (132, 2, 100, 65), (160, 2, 33, 128),
+    (164, 1, 256, 1), (250, 2, 200, 97), (256, 2, 256, 255), (340, 1, 7, 513),
+])
+@pytest.mark.parametrize("wide", [1, 0])
+def test_groups_beyond_128_dimensions(ds, M, K, n, wide):
+    """Aligned rows take the kernel through LDS with encode_wide = 1, unaligned ones and encode_wide = 0 the streaming one."""
+    print("encoder, wide groups: ds", ds, "M", M, "K", K, "n", n, "encode_wide", wide, flush=True)
+    rng = np.random.default_rng(ds * 1000 + M)
+    cb = rng.normal(size=(M, K, ds)).astype(np.float32)
+    c = encoder(cb)
+    c.set_option("encode_wide", wide)
+    x = rng.normal(size=(n, M * ds)).astype(np.float32)
+    assert np.array_equal(encode(c, x), oracle.encode_f32(x, cb))
+    ties = near_tie_vectors(cb, n, seed=ds)
+    assert np.array_equal(encode(c, ties), oracle.encode_f32(ties, cb))
+    far = (cb[np.arange(M)[None, :], rng.integers(0, K, (n, M))].reshape(n, M * ds) + np.float32(50)).astype(np.float32)
+    assert np.array_equal(encode(c, far), oracle.encode_f32(far, cb))
+
+
+def test_rows_that_are_not_aligned():
+    """The same vectors at a 4-byte offset: the streaming kernel beyond 128 dimensions, single words up to there."""
+    print("encoder: rows at an odd address", flush=True)
+    rng = np.random.default_rng(12)
+    for ds in (16, 120, 132):
+        cb = rng.normal(size=(2, 256, ds)).astype(np.float32)
+        x = near_tie_vectors(cb, 301, seed=ds)
+        flat = torch.empty(x.size + 1, dtype=torch.float32, device="cuda")
+        flat[1:] = torch.from_numpy(x.ravel()).cuda()
+        got = encoder(cb).pq_encode_device(flat[1:].view(x.shape))
+        torch.cuda.synchronize()
+        assert np.array_equal(got.cpu().numpy(), oracle.encode_f32(x, cb))
 
 
 @pytest.mark.parametrize("ds", [16, 120])
