@@ -411,6 +411,10 @@ int etf_search_static(etf_ctx *ctx, const float *queries, int64_t Q, int k, int 
  * search has run since the index was built or uploaded. */
 int etf_last_fallback_count(etf_ctx *ctx, int64_t *out);
 
+/* Number of blocks of 128 queries whose candidates the most recent search on this context filtered on the matrix
+ * cores (option "matrix_filter"; diagnostic).  The count lies beside the one above and the same holds for it. */
+int etf_last_matrix_blocks(etf_ctx *ctx, int64_t *out);
+
 /* ---- IVFADC on the merged, sorted encodings -------------------------------- */
 
 /* The paper's application experiment ("Application on related algorithms", Table 1): an inverted file with a coarse

@@ -808,7 +808,7 @@ bool mm_wanted(const etf_ctx *ctx, const Plan &P, int64_t nq)
 }
 
 int launch_mm16(etf_ctx *ctx, const float *queries, const uint32_t *rec, int64_t nitems, int64_t nql, const OutArgs &o, uint32_t *margin,
-                uint32_t *mode)
+                uint32_t *mode, uint32_t *taken)
 {
     const int M = ctx->M;
     MmArgs a;
@@ -827,6 +827,7 @@ int launch_mm16(etf_ctx *ctx, const float *queries, const uint32_t *rec, int64_t
     a.margin = margin;
     a.loose = margin + nql;
     a.mode = mode;
+    a.taken = taken;
     const int64_t W = (nql + MM_Q - 1) / MM_Q;
     int64_t bx = lds_blocks_for(W, nitems, (nitems >> 25) + 1);
     if (ctx->opt.lds_blocks > 0) bx = std::max<int64_t>(ctx->opt.lds_blocks, (nitems >> 25) + 1);
@@ -1323,7 +1324,7 @@ static int search_impl(etf_ctx *ctx, const float *queries, int64_t Q, int k, int
                 if (rc) return rc;
             }
             if (mm) {
-                rc = launch_mm16(ctx, queries + q0 * ctx->d, ecodes, ix.Nd, nql, o, margins, const_cast<uint32_t *>(o.done));
+                rc = launch_mm16(ctx, queries + q0 * ctx->d, ecodes, ix.Nd, nql, o, margins, const_cast<uint32_t *>(o.done), counter + 1);
                 if (rc) return rc;
             }
             if (flat)
@@ -1468,7 +1469,8 @@ extern "C" int etf_search_static(etf_ctx *ctx, const float *queries, int64_t Q, 
     return rc;
 }
 
-extern "C" int etf_last_fallback_count(etf_ctx *ctx, int64_t *out)
+// word `word` of the counts that the last search left in the first 256 bytes of its workspace
+static int last_count(etf_ctx *ctx, int word, int64_t *out)
 {
     int rc = need_device(ctx);
     if (rc) return rc;
@@ -1477,9 +1479,13 @@ extern "C" int etf_last_fallback_count(etf_ctx *ctx, int64_t *out)
     HIP_TRY(ctx, hipSetDevice(ctx->device));
     HIP_TRY(ctx, hipStreamSynchronize((hipStream_t)ctx->stream));
     uint32_t v = 0;
-    HIP_TRY(ctx, hipMemcpy(&v, ctx->last_flag_count, sizeof v, hipMemcpyDeviceToHost));
+    HIP_TRY(ctx, hipMemcpy(&v, static_cast<const uint32_t *>(ctx->last_flag_count) + word, sizeof v, hipMemcpyDeviceToHost));
     *out = v;
     return ETF_OK;
 }
+
+extern "C" int etf_last_fallback_count(etf_ctx *ctx, int64_t *out) { return last_count(ctx, 0, out); }
+
+extern "C" int etf_last_matrix_blocks(etf_ctx *ctx, int64_t *out) { return last_count(ctx, 1, out); }
 
 #include "etf_ivf.hip.h"

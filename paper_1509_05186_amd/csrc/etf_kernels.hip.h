@@ -2426,6 +2426,7 @@ struct MmArgs {
     const uint32_t *loose; // [nql] from k_tau
     uint32_t *margin;      // [nql] for k_select
     uint32_t *mode;        // [ceil(nql / 128)] 1: this kernel filtered the block, 0: left to k_lds16
+    uint32_t *taken;       // count of the blocks that it filtered (etf_last_matrix_blocks)
 };
 
 template <int MC>
@@ -2631,7 +2632,10 @@ __global__ __launch_bounds__(512, 2) void k_mm16(const uint32_t *__restrict__ re
     }
     if (blockIdx.x == 0) {
         if (threadIdx.x < MM_Q && (int64_t)qb * MM_Q + threadIdx.x < a.nql) a.margin[(int64_t)qb * MM_Q + threadIdx.x] = __float_as_uint(qc[threadIdx.x].w);
-        if (threadIdx.x == 0) a.mode[qb] = 1u;
+        if (threadIdx.x == 0) {
+            a.mode[qb] = 1u;
+            atomicAdd(a.taken, 1u);
+        }
     }
     f16x8 B[NB][KS];
     float thr[NB];

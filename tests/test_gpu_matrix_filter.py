@@ -10,13 +10,17 @@ from test_gpu_parity import FOREST, TREE, Problem, etf, say, torch
 pytestmark = pytest.mark.gpu
 
 
-def check(c, q, k, mode, fallback=0):
+def check(c, q, k, mode, fallback=0, taken=None):
+    """taken: blocks of 128 queries that k_mm16 must have filtered (all of them unless given)."""
     qd = torch.from_numpy(q).cuda()
     ids, dist = c.search(qd, k, mode)
     torch.cuda.synchronize()
     assert c.last_fallback_count() == fallback
+    assert c.last_matrix_blocks() == ((len(q) + 127) // 128 if taken is None else taken)
     c.set_option("lds_filter", 0)
     ids0, dist0 = c.search(qd, k, mode)
+    torch.cuda.synchronize()
+    assert c.last_matrix_blocks() == 0
     c.set_option("force_fallback", 1)
     wi, wd = c.search(qd, k, mode)
     torch.cuda.synchronize()
@@ -27,13 +31,21 @@ def check(c, q, k, mode, fallback=0):
     assert torch.equal(dist, wd) and torch.equal(ids, wi)
 
 
-@pytest.mark.parametrize("M,ds,T,N", [(16, 8, 4, 30001), (16, 5, 1, 29999), (16, 1, 2, 20031), (8, 8, 2, 40000), (8, 3, 1, 33333)])
-def test_shapes_and_block_edges(M, ds, T, N):
+def filled(M, Q):
+    """Blocks of a batch of ordinary queries that k_mm16 takes: all, where the batch fills them beside sub-tiles of 32 (M = 8) or
+    16 queries to at most half as much again."""
+    sub, blocks = (32 if M == 8 else 16), (Q + 127) // 128
+    return blocks if 2 * 128 * blocks <= 3 * sub * ((Q + sub - 1) // sub) else 0
+
+
+@pytest.mark.parametrize("M,ds,T,N,k", [(16, 8, 4, 30001, 20), (16, 5, 1, 29999, 20), (16, 1, 2, 20031, 200), (8, 8, 2, 40000, 20),
+                                        (8, 3, 1, 33333, 200)])
+def test_shapes_and_block_edges(M, ds, T, N, k):
     say("matrix filter M", M, "ds", ds, "T", T, "N", N)
     p = Problem(d=M * ds, M=M, K=256, N=N, Q=400, ntrain=3000, seed=M + ds)
     c = p.ctx(matrix_filter=0, T=T, sample_min=1 << 13, cand_cap=8192)
-    for Q in (86, 96, 127, 128, 129, 400):  # the smallest batches that take it, and the edges of its blocks
-        check(c, p.q[:Q], 20, TREE if T == 1 else FOREST)
+    for Q in (86, 96, 127, 128, 129, 192, 257, 400):  # the smallest batches that take it, and the edges of its blocks
+        check(c, p.q[:Q], k, TREE if T == 1 else FOREST, taken=filled(M, Q))
 
 
 @pytest.mark.parametrize("k", [1, 100, 900])
@@ -51,15 +63,34 @@ def test_k_and_chunk_order(k):
     check(c, p.q, k, FOREST)
 
 
-def test_clusters_far_from_the_mean_and_outliers():
-    say("matrix filter: blocks left to the table kernel, beside blocks that are not")
+def with_a_tight_cluster(M, ds, N, Q, seed):
+    """A problem whose first two codewords of every chunk nearly coincide and of whose database a sixth is made of them:
+    a query at such a reconstruction has distances far below the matrix filter's error bound."""
+    p = Problem(d=M * ds, M=M, K=256, N=N, Q=Q, ntrain=3000, seed=seed)
+    rng = np.random.default_rng(seed)
+    p.cb[:, 1] = p.cb[:, 0] * np.float32(1 + 1e-4)
+    p.codes[:N // 6] = rng.integers(0, 2, (N // 6, M))
+    return p, p.cb[:, 0].reshape(-1)
+
+
+@pytest.mark.parametrize("M,T", [(16, 4), (8, 2)])
+def test_blocks_left_to_the_table_filter(M, T):
+    say("matrix filter: blocks left to the table kernel, beside blocks that are not, M", M)
+    p, tight = with_a_tight_cluster(M, 8, 30000, 700, 51)
+    c = p.ctx(matrix_filter=0, T=T, sample_min=1 << 14, cand_cap=8192)
+    for at in ([], [0], [699], [130, 131, 200], [5, 300, 650], [0, 130, 260, 390, 600], range(0, 700, 100), range(0, 700, 64)):
+        q = p.q.copy()
+        q[list(at)] = tight
+        check(c, q, 10, FOREST, taken=6 - len({i // 128 for i in at}))
+
+
+def test_outliers():
+    say("matrix filter: one query far out (the scale of its block), one at the origin")
     p = Problem(d=128, M=16, K=256, N=30000, Q=384, ntrain=3000, seed=51)
     q = p.q.copy()
-    q[128:256] = p.xb[:128]                 # distances near zero: no bound is small against them
-    q[300] *= 1000.0                        # one query far out: the block's scale, and a bound of its own
+    q[300] *= 1000.0
     q[301] = 0.0
-    c = p.ctx(matrix_filter=0, T=4, sample_min=1 << 14, cand_cap=8192)
-    check(c, q, 10, FOREST)
+    check(p.ctx(matrix_filter=0, T=4, sample_min=1 << 14, cand_cap=8192), q, 10, FOREST)
 
 
 def test_queries_that_are_not_finite():
