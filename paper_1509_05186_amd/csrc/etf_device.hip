@@ -2,6 +2,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 #include <cstring>
 #include <functional>
 #include <mutex>
@@ -825,7 +826,7 @@ int launch_mm16(etf_ctx *ctx, const float *queries, const uint32_t *rec, int64_t
     a.cbmean = reinterpret_cast<const float *>(ctx->dev_base + ctx->lay.cb_mean);
     for (int j = 0; j < ETF_MAX_M; ++j) a.ord.src[j] = (uint8_t)((size_t)j < ctx->idx.order.size() ? ctx->idx.order[j] : j);
     a.margin = margin;
-    a.loose = margin + nql;
+    a.room = reinterpret_cast<const float *>(margin + nql);
     a.mode = mode;
     a.taken = taken;
     const int64_t W = (nql + MM_Q - 1) / MM_Q;
@@ -1289,10 +1290,14 @@ static int search_impl(etf_ctx *ctx, const float *queries, int64_t Q, int k, int
         LooseArgs la;
         memset(&la, 0, sizeof la);
         if (mm) {
-            la.loose = margins + nql;
+            la.room = reinterpret_cast<float *>(margins + nql);
             la.queries = queries + q0 * ctx->d;
             la.mean = reinterpret_cast<const float *>(ctx->dev_base + L.cb_mean);
             la.d = ctx->d;
+            // an expected two thirds of the candidate list, in encodings of the sample and in groups that hold one of them (a third
+            // is left for the spread of the sample and of its duplicates, as in make_plan)
+            const double fit = (double)P.C / 1.5 * (double)P.S / ((double)P.items * std::min(8.0, (double)ix.N / (double)ix.Nd));
+            la.groups = (int)((double)P.ngroups * -std::expm1(-fit / (double)P.ngroups));
             la.most = ctx->cb_norm_most;
         }
         o.done = mm ? margins + 2 * nql : nullptr;

@@ -2398,9 +2398,9 @@ __global__ __launch_bounds__(1024) void k_lds16(const uint32_t *__restrict__ rec
 //     3 M, the centring 4: below 6 dpad + 4 ds + 4 M + 64.  E bounds the difference between the value here and the float32
 //     distance of the tables, and everything with a value of at most tau + E passes.  Its candidates carry a 16-bit fixed-point
 //     value; k_select takes everything within margin = 2 E of the k-th smallest and recomputes those from the tables.
-//     Where E is not small against the bound (tight clusters far from the mean) too many would pass: a block of 128 queries
-//     with such a query, as estimated by k_tau or found here, is left to k_lds16 (`mode`), which is launched behind and
-//     otherwise ends at once.
+//     Where E is not small against the bound (tight clusters far from the mean), or the sample has so many encodings just above
+//     the bound that those up to tau + E would not fit the candidate list (`room`, from k_tau), a block of 128 queries with
+//     such a query is left to k_lds16 (`mode`), which is launched behind and otherwise ends at once.
 //     What bounds it: the matrix cores under the card's power limit.  Ten million encodings of 16 chunks (128 dimensions),
 //     10 000 queries: 13.1 ms = 1.29 PFLOP/s, against 1.55 of the bare instruction on random operands and 1.16 to 1.21 of a large
 //     library product here; k_lds16 19.7 ms.
@@ -2423,7 +2423,7 @@ struct MmArgs {
     int d, ds, dsp, K;
     const float *cbc, *cbnorm, *cbmean;  // centred codewords [M][K][dsp], their squared norms, the means [M][ds]
     ChunkOrder ord;
-    const uint32_t *loose; // [nql] from k_tau
+    const float *room;     // [nql] from k_tau: the largest error bound with which the candidates still fit, negative: none
     uint32_t *margin;      // [nql] for k_select
     uint32_t *mode;        // [ceil(nql / 128)] 1: this kernel filtered the block, 0: left to k_lds16
     uint32_t *taken;       // count of the blocks that it filtered (etf_last_matrix_blocks)
@@ -2462,7 +2462,7 @@ __global__ __launch_bounds__(512, 2) void k_mm16(const uint32_t *__restrict__ re
             if (threadIdx.x == 0) a.mode[qb] = 0u;
         }
     };
-    if (__syncthreads_or(threadIdx.x < MM_Q && (int64_t)qb * MM_Q + threadIdx.x < a.nql ? (int)a.loose[(int64_t)qb * MM_Q + threadIdx.x] : 0)) {
+    if (__syncthreads_or(threadIdx.x < MM_Q && (int64_t)qb * MM_Q + threadIdx.x < a.nql && a.room[(int64_t)qb * MM_Q + threadIdx.x] < 0.f)) {
         decline();
         return;
     }
@@ -2616,7 +2616,7 @@ __global__ __launch_bounds__(512, 2) void k_mm16(const uint32_t *__restrict__ re
         float thr = inf, c0 = 0.f, c1 = 0.f;
         uint32_t margin = 0u;
         if (ql < a.nq && tau >= 0.f) {
-            if (!(E * 24.f <= tau) || !(tau < inf) || !(sigma * (nq + C) < 1e37f)) atomicMax(&shared[1], 1u);
+            if (!(E <= a.room[ql]) || !(E * 24.f <= tau) || !(tau < inf) || !(sigma * (nq + C) < 1e37f)) atomicMax(&shared[1], 1u);
             const float S = 32000.f / (tau + 2.f * E);
             thr = sigma * (0.5f * (nq - tau) - 0.5f * E);
             c0 = (nq + E) * S;
@@ -2911,15 +2911,19 @@ __global__ __launch_bounds__(256) void k_reduce(ReduceArgs r, int64_t nitems, co
 //      select over LDS histograms of 64 queries per workgroup took 28 us however few queries there were and 32 us
 //      for ten thousand, mostly clearing and scanning 64 KB of counters three times; this takes 10 and 25 us.)
 //      The kernel also sets the query's candidate count and flag, so that no launch is needed for those, and says
-//      (LooseArgs) for which queries the error bound of k_mm16 will not be small against this bound: about
-//      4.4e-4 ||q|| C there, more than a thirty-second of tau.  Only the choice of the filter hangs on it.
+//      (LooseArgs) how large the error bound E of k_mm16 may be: everything up to tau + E becomes a candidate there, and
+//      where a query's neighbourhood has many dimensions the count grows fast.  At most `groups` of the sample's
+//      minima may lie up to there (the number at which the list's capacity is expected to be two thirds full), found by a
+//      second bisection of the same registers.  A query whose E, about 4.4e-4 ||q|| C or more, will exceed that or a
+//      thirty-second of tau gets -1.  Only the choice of the filter hangs on it.
 //      grid (ceil(queries / 4)), block 256; S <= 64 NV.
 // ------------------------------------------------------------------------------------------------
 struct LooseArgs {
-    uint32_t *loose;       // [nql] or nullptr: not asked for
+    float *room;           // [nql] or nullptr: not asked for
     const float *queries;  // [nq][d]
     const float *mean;     // [d]
     int d;
+    int groups;            // sample groups whose minima may be at or below tau + E
     float most;            // sum over the chunks of the largest squared norm of a centred codeword
 };
 
@@ -2933,6 +2937,7 @@ __global__ __launch_bounds__(256) void k_tau(const float *__restrict__ gmin, int
     if (counter && blockIdx.x == 0 && threadIdx.x < 64) counter[lane] = 0u;
     if (ql >= nql) return;
     uint32_t bound = __float_as_uint(-1.f);  // a column past the last query: nothing passes
+    float room = 0.f;
     if (ql < nq) {
         const float *row = gmin + ql * gstride;
         uint32_t x[NV];
@@ -2954,18 +2959,37 @@ __global__ __launch_bounds__(256) void k_tau(const float *__restrict__ gmin, int
         }
         lo = (uint32_t)uniform((int)lo);
         hi = (uint32_t)uniform((int)hi);
+        const uint32_t largest = hi;
+        auto count = [&](uint32_t upto) {
+            int c = 0;
+#pragma unroll
+            for (int i = 0; i < NV; ++i) c += __popcll(__ballot(x[i] <= upto));
+            return c;
+        };
         // at least k minima are at or below hi, fewer than k below lo
         while (hi - lo > 127u) {
             const uint32_t mid = lo + ((hi - lo) >> 1);
-            int c = 0;
-#pragma unroll
-            for (int i = 0; i < NV; ++i) c += __popcll(__ballot(x[i] <= mid));
-            if (c >= k) hi = mid;
+            if (count(mid) >= k) hi = mid;
             else lo = mid + 1;
         }
         bound = S >= k ? hi : 0x7F800000u;
+        if (la.room) {
+            if (la.groups >= S) {
+                room = __uint_as_float(0x7F800000u);
+            } else if (count(bound) <= la.groups) {
+                // at most la.groups minima are at or below lo, more at or below hi (to 2^-10 of the value)
+                lo = bound;
+                hi = largest;
+                while (hi - lo > 8191u) {
+                    const uint32_t mid = lo + ((hi - lo) >> 1);
+                    if (count(mid) <= la.groups) lo = mid;
+                    else hi = mid;
+                }
+                room = __uint_as_float(lo) - __uint_as_float(bound);
+            }
+        }
     }
-    if (la.loose) {
+    if (la.room) {
         float nn = 0.f;
         if (ql < nq)
             for (int j = lane; j < la.d; j += 64) {
@@ -2974,7 +2998,8 @@ __global__ __launch_bounds__(256) void k_tau(const float *__restrict__ gmin, int
             }
 #pragma unroll
         for (int dlt = 32; dlt >= 1; dlt >>= 1) nn += __shfl_xor(nn, dlt);
-        if (lane == 0) la.loose[ql] = ql < nq && !(1.4e-2f * sqrtf(nn * la.most) <= __uint_as_float(bound)) ? 1u : 0u;
+        const float least = 4.4e-4f * sqrtf(nn * la.most);
+        if (lane == 0) la.room[ql] = ql < nq && !(least <= room && 32.f * least <= __uint_as_float(bound)) ? -1.f : room;
     }
     if (lane == 0) {
         tau[ql] = __uint_as_float(bound);

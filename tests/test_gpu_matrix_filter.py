@@ -5,6 +5,7 @@ selection, bit for bit, and no query may need that selection."""
 import numpy as np
 import pytest
 
+from workload import GaussianMixture
 from test_gpu_parity import FOREST, TREE, Problem, etf, say, torch
 
 pytestmark = pytest.mark.gpu
@@ -104,3 +105,31 @@ def test_queries_that_are_not_finite():
     torch.cuda.synchronize()
     keep = torch.from_numpy(np.isfinite(q).all(1)).cuda()
     assert torch.equal(got[0][keep], want[0][keep]) and torch.equal(got[1][keep], want[1][keep])
+
+
+@pytest.mark.parametrize("M,T", [(16, 4), (8, 2)])
+def test_candidates_fit_where_those_of_the_table_filter_do(M, T):
+    """k_mm16 lets everything up to tau + E through.  With lists from far too short to the default length, no more queries may
+    need the exact selection than with the table filter; with room for them all, the blocks are taken."""
+    say("matrix filter: candidate lists, M", M)
+    gm = GaussianMixture(8 * M, 64, 1.1, (0.2, 1.0), (-4.0, 4.0), seed=60)
+    c = etf.Context(device=0, stream=torch.cuda.current_stream().cuda_stream)
+    c.pq_train(gm.sample(4000, 1), M, 256, 3, 1)
+    N, Q, k = 300_000, 512, 100
+    c.index_build_device(c.pq_encode_device(torch.from_numpy(gm.sample(N, 2)).cuda()), T=T)
+    q = torch.from_numpy(gm.sample(Q, 3)).cuda()
+    over = {}
+    for cap in (256, 384, 512, 640, 768, 1024, 1280, 1536, 2048, 0):
+        c.set_option("cand_cap", cap)
+        for pairs in (-1, 0):
+            c.set_option("matrix_filter", pairs)
+            c.search(q, k, FOREST)
+            torch.cuda.synchronize()
+            over[cap, pairs] = c.last_fallback_count()
+        say("  cap", cap, "exact selections: table", over[cap, -1], "matrix", over[cap, 0])
+    assert all(over[cap, 0] <= over[cap, -1] for cap, _ in over)
+    assert over[0, 0] == 0 and c.last_matrix_blocks() == Q // 128
+    c.set_option("cand_cap", 256)
+    c.search(q, k, FOREST)
+    torch.cuda.synchronize()
+    assert c.last_matrix_blocks() == 0
