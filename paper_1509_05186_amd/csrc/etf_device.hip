@@ -769,8 +769,9 @@ int launch_lds16(etf_ctx *ctx, const Plan &P, char *ws, const uint32_t *rec, int
     const size_t lds = lds_table_bytes(G, M, K) + lds16_aux_bytes();
     int64_t bx = lds_blocks_for(tiles * (G / 2), nitems, (nitems >> 25) + 1);
     if (ctx->opt.lds_blocks > 0) bx = std::max<int64_t>(ctx->opt.lds_blocks, (nitems >> 25) + 1);
-    const int per_block = (int)((nitems + bx - 1) / bx);
-    dim3 grid((unsigned)bx, (unsigned)(G / 2), (unsigned)tiles);
+    // behind k_mm16 the workgroups divide the sub-tiles that it has left among themselves
+    const int per_block = o.done ? (int)(ctx->opt.lds_blocks > 0 ? bx : 0) : (int)((nitems + bx - 1) / bx);
+    const dim3 grid = o.done ? dim3((unsigned)(bx * (G / 2) * tiles)) : dim3((unsigned)bx, (unsigned)(G / 2), (unsigned)tiles);
     hipStream_t st = (hipStream_t)ctx->stream;
     const float *lutT = reinterpret_cast<const float *>(ws + P.o_lutT);
     ProfScope prof(ctx, ETF_K_LDS16);
@@ -808,8 +809,8 @@ bool mm_wanted(const etf_ctx *ctx, const Plan &P, int64_t nq)
     return padded * 2 <= (nq + Qs - 1) / Qs * Qs * 3 && (double)padded * (double)ctx->idx.Nd >= (double)ctx->opt.matrix_filter * (ctx->M == 8 ? 2.0 : 1.0);
 }
 
-int launch_mm16(etf_ctx *ctx, const float *queries, const uint32_t *rec, int64_t nitems, int64_t nql, const OutArgs &o, uint32_t *margin,
-                uint32_t *mode, uint32_t *taken)
+int launch_mm16(etf_ctx *ctx, const float *queries, const uint32_t *rec, int64_t nitems, int64_t nql, const OutArgs &o, const LooseArgs &la,
+                uint32_t *taken)
 {
     const int M = ctx->M;
     MmArgs a;
@@ -825,25 +826,26 @@ int launch_mm16(etf_ctx *ctx, const float *queries, const uint32_t *rec, int64_t
     a.cbnorm = reinterpret_cast<const float *>(ctx->dev_base + ctx->lay.cb_norm);
     a.cbmean = reinterpret_cast<const float *>(ctx->dev_base + ctx->lay.cb_mean);
     for (int j = 0; j < ETF_MAX_M; ++j) a.ord.src[j] = (uint8_t)((size_t)j < ctx->idx.order.size() ? ctx->idx.order[j] : j);
-    a.margin = margin;
-    a.room = reinterpret_cast<const float *>(margin + nql);
-    a.mode = mode;
+    a.margin = la.margin;
+    a.room = la.room;
+    a.loose = la.loose;
     a.taken = taken;
-    const int64_t W = (nql + MM_Q - 1) / MM_Q;
-    int64_t bx = lds_blocks_for(W, nitems, (nitems >> 25) + 1);
-    if (ctx->opt.lds_blocks > 0) bx = std::max<int64_t>(ctx->opt.lds_blocks, (nitems >> 25) + 1);
-    const int per_block = (int)(((nitems + bx - 1) / bx + 31) / 32 * 32);
-    const dim3 grid((unsigned)((nitems + per_block - 1) / per_block), (unsigned)W);
+    int64_t bx = lds_blocks_for(o.blocks, nitems, (nitems >> 25) + 1);
+    if (ctx->opt.lds_blocks > 0) {
+        bx = std::max<int64_t>(ctx->opt.lds_blocks, (nitems >> 25) + 1);
+        a.shares = (int)bx;
+    }
+    const dim3 grid((unsigned)(bx * o.blocks));
     hipStream_t st = (hipStream_t)ctx->stream;
     ProfScope prof(ctx, ETF_K_LDS16);
     const size_t lds = mm_lds_bytes(M);
     int rc;
     if (M == 8) {
         if ((rc = set_lds(ctx, k_mm16<8>, lds))) return rc;
-        hipLaunchKernelGGL(k_mm16<8>, grid, dim3(512), lds, st, rec, nitems, per_block, o, a);
+        hipLaunchKernelGGL(k_mm16<8>, grid, dim3(512), lds, st, rec, nitems, o, a);
     } else {
         if ((rc = set_lds(ctx, k_mm16<16>, lds))) return rc;
-        hipLaunchKernelGGL(k_mm16<16>, grid, dim3(512), lds, st, rec, nitems, per_block, o, a);
+        hipLaunchKernelGGL(k_mm16<16>, grid, dim3(512), lds, st, rec, nitems, o, a);
     }
     LAUNCH_CHECK(ctx, "k_mm16");
     return ETF_OK;
@@ -1284,13 +1286,18 @@ static int search_impl(etf_ctx *ctx, const float *queries, int64_t Q, int k, int
             o.term = term;
             o.term_map = reinterpret_cast<const uint32_t *>(ctx->dev_base + (flat ? L.sample_pos : L.sample_enc));
         }
-        // the matrix filter's margins and the blocks that it has taken lie where the product searches keep their shifts
+        // the matrix filter's margins, rooms and words per block lie where the product searches keep their shifts
         const bool mm = mm_wanted(ctx, P, nq);
         uint32_t *margins = mm ? reinterpret_cast<uint32_t *>(w + P.o_bm) : nullptr;
         LooseArgs la;
         memset(&la, 0, sizeof la);
         if (mm) {
+            la.margin = margins;
+            la.margin_table = (uint32_t)(ix.M + 2);
             la.room = reinterpret_cast<float *>(margins + nql);
+            o.done = margins + 2 * nql;
+            o.blocks = (int)((nql + MM_Q - 1) / MM_Q);
+            la.loose = o.done + o.blocks;
             la.queries = queries + q0 * ctx->d;
             la.mean = reinterpret_cast<const float *>(ctx->dev_base + L.cb_mean);
             la.d = ctx->d;
@@ -1298,9 +1305,11 @@ static int search_impl(etf_ctx *ctx, const float *queries, int64_t Q, int k, int
             // is left for the spread of the sample and of its duplicates, as in make_plan)
             const double fit = (double)P.C / 1.5 * (double)P.S / ((double)P.items * std::min(8.0, (double)ix.N / (double)ix.Nd));
             la.groups = (int)((double)P.ngroups * -std::expm1(-fit / (double)P.ngroups));
-            la.most = ctx->cb_norm_most;
+            // E is (2.05 - 0.115 ds) 4.4e-4 ||q|| C, C^2 the sum of the chunks' largest ||c||^2, within a factor of 0.8 to 1.4 for
+            // nearly all queries of clustered and unclustered vectors alike (the fewer dimensions a chunk has, the more of its
+            // largest error is in a single one)
+            la.typical = 4.4e-4f * (2.05f - 0.115f * (float)ctx->ds) * std::sqrt(ctx->cb_norm_most);
         }
-        o.done = mm ? margins + 2 * nql : nullptr;
         ReduceArgs r;
         const uint32_t *ecodes = reinterpret_cast<const uint32_t *>(ctx->dev_base + L.ecodes);
         if (!flat && !P.lds_path) {
@@ -1329,7 +1338,7 @@ static int search_impl(etf_ctx *ctx, const float *queries, int64_t Q, int k, int
                 if (rc) return rc;
             }
             if (mm) {
-                rc = launch_mm16(ctx, queries + q0 * ctx->d, ecodes, ix.Nd, nql, o, margins, const_cast<uint32_t *>(o.done), counter + 1);
+                rc = launch_mm16(ctx, queries + q0 * ctx->d, ecodes, ix.Nd, nql, o, la, counter + 1);
                 if (rc) return rc;
             }
             if (flat)
@@ -1361,7 +1370,7 @@ static int search_impl(etf_ctx *ctx, const float *queries, int64_t Q, int k, int
         // bound; twice that between two candidates
         sa.fx_margin = P.fx ? (uint32_t)(2 * (ix.M + 8 * (ix.M + 1)) + 16) : 0u;
         // 16-bit tables: truncation makes a sum too small by at most M units, everything else is far below one unit
-        if (P.fx16) sa.fx_margin = (uint32_t)(ix.M + 2);
+        if (P.fx16) sa.fx_margin = (uint32_t)(ix.M + 2);  // (la.margin_table too)
         sa.margins = margins;
         sa.fx_first_pass = P.fx16 ? 2 : 0;
         sa.lutT = lutT;

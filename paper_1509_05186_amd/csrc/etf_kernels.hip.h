@@ -1500,7 +1500,9 @@ struct OutArgs {
     int64_t ngroups;
     int64_t gstride;    // ngroups rounded up to a multiple of 64
     int gsize;
-    const uint32_t *done;  // k_lds16: per 128 queries, not zero where k_mm16 has filtered them; or nullptr
+    uint32_t *done;     // per block of 128 queries: not zero where k_mm16 has filtered it (k_lds16 takes the others), then as many
+                        // words where k_tau says whose error bound is too large; cleared by the sample pass of k_lds; or nullptr
+    int blocks;         // their number
     int wps;            // k_lds: waves that share a stretch of the sample (a power of two, at most 16)
     // OUT_FILTER
     const float *tau;   // [tiles*64]
@@ -1804,6 +1806,8 @@ __global__ __launch_bounds__(1024) void k_lds(const uint32_t *__restrict__ rec, 
     const int w = uniform(threadIdx.x >> 6), nw = blockDim.x >> 6;
     static_assert(!FX || MODE == OUT_FILTER, "the fixed-point form is a candidate filter");
     static_assert(!TERM || (MODE == OUT_FILTER && !FX), "TERM selects the filter pass with a leaf payload; the other modes test o.term");
+    if (MODE == OUT_SAMPLE && o.done && blockIdx.x + blockIdx.y + blockIdx.z == 0)
+        for (int i = threadIdx.x; i < 2 * o.blocks; i += blockDim.x) o.done[i] = 0u;
     // a sub-tile past the last query: nothing to write
     if ((MODE == OUT_ALLPAIRS || MODE == OUT_SAMPLE) && (int64_t)tile * QT + sub * Qs >= o.nq) return;
     if (FILTER) wcount[w][lane] = 0u;
@@ -2137,6 +2141,84 @@ __global__ __launch_bounds__(1024) void k_lds(const uint32_t *__restrict__ rec, 
 }
 
 // ------------------------------------------------------------------------------------------------
+// Who works on what where a filter pass is divided between k_mm16 and k_lds16 on the device: workgroup `wg` of `wgs` finds
+// its share of the items of its unit among the units that are left (block b has weight(b) of them).  The host sizes the launch
+// for all units; a few that are left get more shares each, so that they still fill the compute units.  The shares are chosen by
+// the rule of lds_blocks_for on the host (`given` > 0: that many), a candidate per lane.  (A launch cut for all of 79 blocks
+// gave a single one 16 long workgroups: a whole round of the pass, 4 ms of 20.)  Fewer units than `worth` are left alone.  Every
+// wave finds the same; the answer is uniform.
+// ------------------------------------------------------------------------------------------------
+constexpr int MM_Q = 128;  // queries per block of the divided pass
+struct Share {
+    int block, nth;     // the unit: the nth of its block
+    int share, shares;
+};
+template <class F>
+__device__ __forceinline__ bool find_share(uint32_t wg, uint32_t wgs, int blocks, int64_t nitems, int given, uint32_t worth, F weight,
+                                           Share &s)
+{
+    const int lane = threadIdx.x & 63;
+    uint32_t total = 0;
+    for (int b0 = 0; b0 < blocks; b0 += 64) {
+        uint32_t v = b0 + lane < blocks ? (uint32_t)weight(b0 + lane) : 0u;
+#pragma unroll
+        for (int dlt = 32; dlt >= 1; dlt >>= 1) v += (uint32_t)__shfl_xor((int)v, dlt);
+        total += v;
+    }
+    total = (uint32_t)uniform((int)total);
+    if (total < worth) return false;
+    uint32_t shares = (uint32_t)given;
+    if (given == 0) {
+        const uint32_t least = (uint32_t)(nitems >> 25) + 1u, most = max(least, (uint32_t)((nitems + 4095) / 4096));
+        float cost = __uint_as_float(0x7F800000u);
+        shares = least;  // (the launch has room for it)
+#pragma unroll
+        for (uint32_t i = 0; i < 4; ++i) {
+            const uint32_t n = least + i * 64u + (uint32_t)lane;
+            if (n > least && (n > most || n > wgs / total || total * (n - 1u) >= 16u * 256u)) continue;
+            const float c = (float)((total * n + 255u) / 256u) * (5000.f + (float)nitems / (float)n);
+            if (c < cost) {
+                cost = c;
+                shares = n;
+            }
+        }
+#pragma unroll
+        for (int dlt = 32; dlt >= 1; dlt >>= 1) {
+            const float oc = __shfl_xor(cost, dlt);
+            const uint32_t on = (uint32_t)__shfl_xor((int)shares, dlt);
+            if (oc < cost || (oc == cost && on < shares)) {
+                cost = oc;
+                shares = on;
+            }
+        }
+        shares = (uint32_t)uniform((int)shares);
+    }
+    const uint32_t unit = wg / shares;
+    if (unit >= total) return false;
+    uint32_t before = 0;
+    for (int b0 = 0;; b0 += 64) {
+        const uint32_t own = b0 + lane < blocks ? (uint32_t)weight(b0 + lane) : 0u;
+        uint32_t upto = own;
+#pragma unroll
+        for (int dlt = 1; dlt < 64; dlt <<= 1) {
+            const uint32_t v = (uint32_t)__shfl_up((int)upto, dlt);
+            if (lane >= dlt) upto += v;
+        }
+        const uint64_t past = __ballot(before + upto > unit);
+        if (past != 0ull) {
+            const int l = __ffsll((unsigned long long)past) - 1;
+            s.block = b0 + l;
+            s.nth = uniform((int)(unit - before) - __shfl((int)(upto - own), l));
+            s.share = (int)(wg - unit * shares);
+            s.shares = (int)shares;
+            return true;
+        }
+        before += (uint32_t)__shfl((int)upto, 63);
+        if (b0 + 64 >= blocks) return false;  // (not reached: the last unit is below the total)
+    }
+}
+
+// ------------------------------------------------------------------------------------------------
 // The filter pass of the LDS-resident search on 16-bit tables (option lds_filter = 2).
 //     The pass that looks at every encoding only has to decide which ones can be among the k nearest; it is bound by
 //     the LDS reads of table entries.  Here an entry is two bytes: scaled so that the query's bound becomes
@@ -2150,7 +2232,9 @@ __global__ __launch_bounds__(1024) void k_lds(const uint32_t *__restrict__ rec, 
 //     is ordered and returned (see SelectArgs::fx_margin).
 //     Geometry, item walk, distance context and line layout are those of k_lds<G> (rows of 64 or 32 bytes, lines
 //     of 256 bytes, chunk order rotated per lane group); a sub-tile has 128 / G queries.
-//     grid (blocks, G / 2, tiles), block 1024, dynamic LDS lds_table_bytes(G) + lds16_aux_bytes(); G in {4, 8}.
+//     grid (blocks, G / 2, tiles), or, behind k_mm16, (workgroups) for the sub-tiles of the blocks that it has not done
+//     (find_share; `per_block` is the number of shares there, 0: by the rule); block 1024, dynamic LDS lds_table_bytes(G) +
+//     lds16_aux_bytes(); G in {4, 8}.
 // ------------------------------------------------------------------------------------------------
 typedef unsigned short u16x8 __attribute__((ext_vector_type(8)));
 typedef __attribute__((address_space(3))) const u16x8 lds_u16x8_t;
@@ -2175,8 +2259,18 @@ __global__ __launch_bounds__(1024) void k_lds16(const uint32_t *__restrict__ rec
     uint32_t(*ringm)[RING] = reinterpret_cast<uint32_t(*)[RING]>(aux + 16 * RING * 16);
     uint32_t(*wcount)[64] = reinterpret_cast<uint32_t(*)[64]>(aux + 16 * RING * 20);
     uint32_t(*wpos)[64] = reinterpret_cast<uint32_t(*)[64]>(aux + 16 * RING * 20 + 16 * 64 * 4);
-    const int tile = blockIdx.z, sub = blockIdx.y;
-    if (o.done && o.done[tile >> 1] != 0u) return;
+    int tile = blockIdx.z, sub = blockIdx.y, share = blockIdx.x;
+    if (o.done) {
+        // a sub-tile of Qs queries: the nth of its block's that hold a query
+        Share s;
+        if (!find_share(blockIdx.x, gridDim.x, o.blocks, nitems, per_block, 1u,
+                        [&](int b) { return o.done[b] != 0u ? 0 : (int)((min<int64_t>(MM_Q, o.nq - (int64_t)b * MM_Q) + Qs - 1) / Qs); }, s))
+            return;
+        tile = s.block * (MM_Q / QT) + s.nth / (QT / Qs);
+        sub = s.nth % (QT / Qs);
+        share = s.share;
+        per_block = (int)((nitems + s.shares - 1) / s.shares);
+    }
     const int lane = threadIdx.x & 63;
     const int w = uniform(threadIdx.x >> 6), nw = blockDim.x >> 6;
     wcount[w][lane] = 0u;
@@ -2251,7 +2345,7 @@ __global__ __launch_bounds__(1024) void k_lds16(const uint32_t *__restrict__ rec
         }
         return *reinterpret_cast<lds_u32v4_t *>(__builtin_amdgcn_perm(src, pb[g][t], sh[g == 0 ? 0 : 1][t]));
     };
-    const int64_t blo = (int64_t)blockIdx.x * per_block;
+    const int64_t blo = (int64_t)share * per_block;
     const int64_t bhi = min(nitems, blo + per_block);
     // the largest sum that may pass, plus one, per query of this lane
     u16x8 tp1;
@@ -2400,18 +2494,22 @@ __global__ __launch_bounds__(1024) void k_lds16(const uint32_t *__restrict__ rec
 //     value; k_select takes everything within margin = 2 E of the k-th smallest and recomputes those from the tables.
 //     Where E is not small against the bound (tight clusters far from the mean), or the sample has so many encodings just above
 //     the bound that those up to tau + E would not fit the candidate list (`room`, from k_tau), a block of 128 queries with
-//     such a query is left to k_lds16 (`mode`), which is launched behind and otherwise ends at once.
+//     such a query is left to k_lds16, which is launched behind and otherwise ends at once: where k_tau sees it (`loose`) no
+//     workgroup takes the block, where it is found here all of its workgroups end.  The two share a batch from half of its blocks
+//     on; below that the second start costs more than the faster rate gives.  Ten million encodings of 16 chunks, 10 000
+//     queries (79 blocks) of which 1, 19 and 39 blocks are left: 15.4, 17.5 and 19.3 ms, k_lds16 alone 21.8 (M = 8, 4000
+//     queries, half: 2.74 and 2.82).
 //     What bounds it: the matrix cores under the card's power limit.  Ten million encodings of 16 chunks (128 dimensions),
 //     10 000 queries: 13.1 ms = 1.29 PFLOP/s, against 1.55 of the bare instruction on random operands and 1.16 to 1.21 of a large
 //     library product here; k_lds16 19.7 ms.
 //     Candidates: a lane that finds one among its 16 values parks all 16 in the wave's ring; a full ring is taken apart by
 //     all lanes (as in k_lds16).
 //     MC: chunks, each of at most 8 dimensions (a lane's operand is one chunk's codeword).
-//     grid (blocks, ceil(nql / 128)), block 512, dynamic LDS mm_lds_bytes(MC).
+//     grid (workgroups) for the blocks that k_tau has left (find_share), block 512, dynamic LDS mm_lds_bytes(MC).
 // ------------------------------------------------------------------------------------------------
 typedef float floatx4_t __attribute__((ext_vector_type(4)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-constexpr int MM_Q = 128, MM_RING = 128, MM_WAVES = 8;
+constexpr int MM_RING = 128, MM_WAVES = 8;
 __host__ __device__ constexpr size_t mm_lds_bytes(int MC)
 {
     return (size_t)MC * 5120 + (size_t)MM_WAVES * MM_RING * 68 + (size_t)MM_WAVES * MM_Q * 8 + MM_Q * 16 + 2 * 64 + 64;
@@ -2423,14 +2521,15 @@ struct MmArgs {
     int d, ds, dsp, K;
     const float *cbc, *cbnorm, *cbmean;  // centred codewords [M][K][dsp], their squared norms, the means [M][ds]
     ChunkOrder ord;
-    const float *room;     // [nql] from k_tau: the largest error bound with which the candidates still fit, negative: none
-    uint32_t *margin;      // [nql] for k_select
-    uint32_t *mode;        // [ceil(nql / 128)] 1: this kernel filtered the block, 0: left to k_lds16
+    const float *room;     // [nql] from k_tau: the largest error bound with which the candidates still fit
+    const uint32_t *loose; // [blocks] from k_tau: not zero where a query's error bound will exceed that
+    uint32_t *margin;      // [nql] for k_select: those of the blocks filtered here are written
+    int shares;            // workgroups per block (0: by the rule of find_share)
     uint32_t *taken;       // count of the blocks that it filtered (etf_last_matrix_blocks)
 };
 
 template <int MC>
-__global__ __launch_bounds__(512, 2) void k_mm16(const uint32_t *__restrict__ rec, int64_t nitems, int per_block, OutArgs o, MmArgs a)
+__global__ __launch_bounds__(512, 2) void k_mm16(const uint32_t *__restrict__ rec, int64_t nitems, OutArgs o, MmArgs a)
 {
     constexpr int M4 = MC / 4, KS = MC / 2, NB = MM_Q / 32, RING = MM_RING, NW = MM_WAVES;
     extern __shared__ __align__(16) char mm_raw[];
@@ -2452,20 +2551,12 @@ __global__ __launch_bounds__(512, 2) void k_mm16(const uint32_t *__restrict__ re
     uint32_t *fmaxs = cmax + 16, *shared = cmax + 32;                  // shared: max |q|, blocks too loose
     const int lane = threadIdx.x & 63, w = uniform(threadIdx.x >> 6);
     const int col = lane & 31, half = lane >> 5;
-    const int qb = blockIdx.y;
     const int K = a.K, ds = a.ds;
     const float inf = __uint_as_float(0x7F800000u);
-
-    auto decline = [&]() {
-        if (blockIdx.x == 0) {
-            if (threadIdx.x < MM_Q && (int64_t)qb * MM_Q + threadIdx.x < a.nql) a.margin[(int64_t)qb * MM_Q + threadIdx.x] = (uint32_t)(MC + 2);
-            if (threadIdx.x == 0) a.mode[qb] = 0u;
-        }
-    };
-    if (__syncthreads_or(threadIdx.x < MM_Q && (int64_t)qb * MM_Q + threadIdx.x < a.nql && a.room[(int64_t)qb * MM_Q + threadIdx.x] < 0.f)) {
-        decline();
-        return;
-    }
+    Share sh;
+    if (!find_share(blockIdx.x, gridDim.x, o.blocks, nitems, a.shares, (uint32_t)(o.blocks + 1) / 2u, [&](int b) { return a.loose[b] != 0u ? 0 : 1; }, sh)) return;
+    const int qb = sh.block;
+    const int per_block = (int)((nitems + sh.shares - 1) / sh.shares + 31) / 32 * 32;
     // ---- the largest norms
     if (threadIdx.x < 48) cmax[threadIdx.x] = 0u;
     __syncthreads();
@@ -2626,14 +2717,11 @@ __global__ __launch_bounds__(512, 2) void k_mm16(const uint32_t *__restrict__ re
         qc[t] = make_float4(thr, c0, c1, __uint_as_float(margin));
     }
     __syncthreads();
-    if (shared[1] != 0u) {
-        decline();
-        return;
-    }
-    if (blockIdx.x == 0) {
+    if (shared[1] != 0u) return;
+    if (sh.share == 0) {
         if (threadIdx.x < MM_Q && (int64_t)qb * MM_Q + threadIdx.x < a.nql) a.margin[(int64_t)qb * MM_Q + threadIdx.x] = __float_as_uint(qc[threadIdx.x].w);
         if (threadIdx.x == 0) {
-            a.mode[qb] = 1u;
+            o.done[qb] = 1u;
             atomicAdd(a.taken, 1u);
         }
     }
@@ -2647,7 +2735,7 @@ __global__ __launch_bounds__(512, 2) void k_mm16(const uint32_t *__restrict__ re
     }
     __syncthreads();  // the staging area becomes the rings and counters
     for (int i = lane; i < MM_Q; i += 64) wcount[w][i] = 0u;
-    const int64_t blo = (int64_t)blockIdx.x * per_block, bhi = min(nitems, blo + per_block);
+    const int64_t blo = (int64_t)sh.share * per_block, bhi = min(nitems, blo + per_block);
     if (blo >= bhi) return;
     const int live_items = (int)(bhi - blo);
     int held = 0;
@@ -2914,17 +3002,20 @@ __global__ __launch_bounds__(256) void k_reduce(ReduceArgs r, int64_t nitems, co
 //      (LooseArgs) how large the error bound E of k_mm16 may be: everything up to tau + E becomes a candidate there, and
 //      where a query's neighbourhood has many dimensions the count grows fast.  At most `groups` of the sample's
 //      minima may lie up to there (the number at which the list's capacity is expected to be two thirds full), found by a
-//      second bisection of the same registers.  A query whose E, about 4.4e-4 ||q|| C or more, will exceed that or a
-//      thirty-second of tau gets -1.  Only the choice of the filter hangs on it.
+//      second bisection of the same registers.  A query whose E (estimated, with a fifth to spare) will exceed that or a
+//      twenty-fourth of tau marks its block.  Only the choice of the filter hangs on it.
 //      grid (ceil(queries / 4)), block 256; S <= 64 NV.
 // ------------------------------------------------------------------------------------------------
 struct LooseArgs {
     float *room;           // [nql] or nullptr: not asked for
+    uint32_t *loose;       // [nql / 128] set to 1 for the blocks of queries without that room
+    uint32_t *margin;      // [nql] the table filter's margin, for the blocks that are left to it
+    uint32_t margin_table;
     const float *queries;  // [nq][d]
     const float *mean;     // [d]
     int d;
     int groups;            // sample groups whose minima may be at or below tau + E
-    float most;            // sum over the chunks of the largest squared norm of a centred codeword
+    float typical;         // E / ||q|| as it is found for most queries
 };
 
 template <int NV>
@@ -2998,8 +3089,12 @@ __global__ __launch_bounds__(256) void k_tau(const float *__restrict__ gmin, int
             }
 #pragma unroll
         for (int dlt = 32; dlt >= 1; dlt >>= 1) nn += __shfl_xor(nn, dlt);
-        const float least = 4.4e-4f * sqrtf(nn * la.most);
-        if (lane == 0) la.room[ql] = ql < nq && !(least <= room && 32.f * least <= __uint_as_float(bound)) ? -1.f : room;
+        const float e = la.typical * sqrtf(nn);
+        if (lane == 0) {
+            la.room[ql] = room;
+            la.margin[ql] = la.margin_table;
+            if (ql < nq && !(1.2f * e <= room && 28.f * e <= __uint_as_float(bound))) la.loose[ql / MM_Q] = 1u;  // (all write the same)
+        }
     }
     if (lane == 0) {
         tau[ql] = __uint_as_float(bound);
