@@ -999,8 +999,9 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void k_encode_bf(const float *__re
     }
     __syncthreads();
     // ---- codewords as operands
-    for (int idx = threadIdx.x; idx < gl * 256; idx += NT) {
-        const int ml = idx >> 8, k = idx & 255;
+    const int rows = (K + 32 * TS - 1) / (32 * TS) * (32 * TS);  // of the tiles that are walked
+    for (int idx = threadIdx.x; idx < gl * rows; idx += NT) {
+        const int ml = idx / rows, k = idx - ml * rows;
         const float *c = cb + ((int64_t)(m0 + ml) * K + min(k, K - 1)) * ds;
         bf16x8 *dst = ops + (size_t)(ml * 8 + (k >> 5)) * NB * 128 + (k & 31);
         float cc = 0.f;
@@ -1189,7 +1190,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void k_encode_bf(const float *__re
         for (int r = 0; r < 16; ++r) rmax[r] = -3.4e38f;
 #pragma unroll
         for (int tp = 0; tp < 8 / TS; ++tp) {
-            if (tp == 2 && K <= 128) break;
+            if (tp > 0 && K <= 32 * TS * tp) break;
             floatx16 acc[TS];
 #pragma unroll
             for (int q = 0; q < TS; ++q) {
