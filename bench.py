@@ -152,7 +152,8 @@ def make_inputs(cfg, etf, torch, scale_n=None, scale_q=None):
     encode = {"vectors": N, "kernel_ms": ms, "launches": cnt, "vectors_per_s": N / (ms / 1e3) if ms > 0 else None,
               "kernel": "float32 rule for every codeword (vector unit)" if plain else "distances on the matrix cores, near-ties by the float32 rule",
               "TFLOPs": flops / (ms / 1e3) / 1e12 if ms > 0 else None,
-              "ops_counted": "3 N d K unfused vector operations" if plain else "2 N d K of the float32 contraction",
+              "ops_counted": "3 N d K unfused vector operations" if plain else "2 N d K of the contraction x.c (up to 128 dimensions per group: "
+                             "three bf16 products for each, values as sums of two bf16 numbers)",
               "note": "device encoder kernel time only; generation on the host and the copies are not included"}
     log("generate + encode %d vectors: %.1f s (device encoder kernels %.1f ms, %.1f TFLOP/s)"
         % (N, time.time() - t0, ms, encode["TFLOPs"] or 0.0))
@@ -306,12 +307,17 @@ class Workload:
         ms_step = dt / steps * 1e3
         value = self.N * self.Q * steps / dt
         fallbacks = ctx.last_fallback_count()
+        # blocks of 128 queries of the last call that k_mm16 filtered, and all of them
+        last_q = (self.Q - 1) % Qc + 1
+        mm_blocks, blocks = ctx.last_matrix_blocks(), (last_q + 127) // 128
         log("%s T=%d top-%d, %s: %.2f ms/step, %.3e distances/s, %d queries of the last call via the exact kernel"
             % (cfg.name, T, self.k, TRAVERSAL_NAMES[traversal], ms_step, value, fallbacks))
         S = ctx.index_layout().n_sample_enc
         lds_path = any(n in prof and prof[n][1] > 0 for n in ("lds", "lds16"))
         ctx_path = traversal != 1 and T <= 4
         alg = algorithmic_bytes(stats, "forest_lds" if lds_path else "forest_ctx" if ctx_path else "forest", S, self.tiles)
+        if mm_blocks:
+            alg.pop("lds16", None)   # its table entries are read for the blocks that k_mm16 left, if any
         kernels = {}
         for name, (ms, cnt) in prof.items():
             if cnt:
@@ -325,12 +331,15 @@ class Workload:
             lps = kd["launches_per_step"]
             achieved = kd["alg_GBps"] or 0.0
             traffic, traffic_note = (None, "scaled run") if not self.valid else measured_traffic(cfg.name, dom, TRAVERSAL_NAMES[traversal])
-            if dom == "lds16" and cfg.M in (8, 16) and cfg.d <= 8 * cfg.M and \
-                    (cfg.query_batch or self.Q) * stats["n_distinct"] >= (1 << 29) * (2 if cfg.M == 8 else 1):
-                # chunks of at most 8 dimensions: the filter runs on the matrix cores (k_mm16), a contraction over the dimensions
+            if dom == "lds16" and mm_blocks:
+                # chunks of at most 8 dimensions: the filter runs on the matrix cores (k_mm16), a contraction over the dimensions;
+                # the class's second launch (k_lds16) takes the blocks that it leaves
                 tflops = 2.0 * self.Q * stats["n_distinct"] * cfg.d / (kd["ms_per_step"] / 1e3) / 1e12
-                roofline = {"bound": "alu", "resource": "16-bit matrix cores", "kernel": "k_mm16", "achieved": tflops, "peak": 2500.0,
-                            "unit": "TFLOP/s", "frac": tflops / 2500.0, "traffic": None, "traffic_note": "not counted for this kernel"}
+                whole = mm_blocks == blocks
+                roofline = {"bound": "alu", "resource": "16-bit matrix cores", "kernel": "k_mm16" if whole else "k_mm16 and k_lds16",
+                            "blocks": [mm_blocks, blocks], "achieved": tflops if whole else None, "peak": 2500.0,
+                            "unit": "TFLOP/s", "frac": tflops / 2500.0 if whole else None, "traffic": None,
+                            "traffic_note": "not counted for this kernel"}
             elif dom in ("lds", "lds16"):
                 # bound by the LDS pipe and the vector adds behind it: algorithmic bytes are the table entries this kernel
                 # reads from LDS per query, 4 bytes each in k_lds, 2 bytes each in k_lds16
@@ -357,7 +366,7 @@ class Workload:
             else:
                 roofline = {"bound": "hbm", "kernel": dom, "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                             "frac": achieved / HBM_PEAK_GBS, "traffic": traffic, "traffic_note": traffic_note}
-            roofline.update({"alg_bytes_per_launch": alg.get(dom, 0) / lps if lps else None,
+            roofline.update({"alg_bytes_per_launch": alg[dom] / lps if lps and dom in alg else None,
                              "avg_launch_ms": kd["ms_per_step"] / lps if lps else None, "launches_per_step": lps})
             if dom not in ("lds", "lds16"):
                 # the traversal as a whole (levels + leaves + reduction): the bandwidth figure of the table-based paths
@@ -495,15 +504,16 @@ def ivf_leg(etf, torch, args, steps, warmup):
            "ms_per_step": ms, "queries_per_s": cfg.Q / (ms / 1e3), "steps": steps, "kernels": kernels,
            "fallback_queries": c.last_fallback_count(), "index": st, "assign_gpu_kernel_ms": assign_ms,
            "coarse_quantiser": "8192 vectors drawn from the mixture, not trained"}
-    # rooflines of the two large kernel classes.  Coarse: the query-centroid products are a dense float32 contraction
-    # on the matrix cores (2 Q K' d operations); the class also holds the probe selection, which re-evaluates the cells
-    # near the w-th by the sequential float32 rule.  Scan: 4-byte table entries gathered from LDS, M per entry.
+    # rooflines of the two large kernel classes.  Coarse: the query-centroid products are a dense contraction on the bf16
+    # matrix cores, three products for each of the 2 Q K' d operations; the class also writes the Q K' results and holds the
+    # probe selection, which reads them three times and re-evaluates the cells near the w-th by the sequential float32 rule.
+    # Scan: 4-byte table entries gathered from LDS, M per entry.
     if "ivf_coarse" in kernels:
-        ach = 2.0 * cfg.Q * cells_n * cfg.d / (kernels["ivf_coarse"]["ms_per_step"] / 1e3) / 1e12
-        meas = CEILINGS.get("mfma_f32_32x32x2_TFLOPs")
-        leg["roofline_coarse"] = {"bound": "mfma", "kernel": "ivf_coarse (k_ivf_coarse_tc and k_ivf_probe_mfma together)",
-                                  "dtype": "f32", "achieved": ach, "peak": 157.3, "unit": "TFLOP/s", "frac": ach / 157.3, "traffic": None,
-                                  "frac_of_measured_peak": ach / meas if meas else None}
+        gbs = 4.0 * 4.0 * cfg.Q * cells_n / (kernels["ivf_coarse"]["ms_per_step"] / 1e3) / 1e9
+        leg["roofline_coarse"] = {"bound": "hbm", "kernel": "ivf_coarse (k_ivf_coarse_tc and k_ivf_probe_mfma together)",
+                                  "what": "the distance matrix written once and read three times, 16 Q K' bytes", "achieved": gbs,
+                                  "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": gbs / HBM_PEAK_GBS, "traffic": None,
+                                  "bf16_TFLOPs": 6.0 * cfg.Q * cells_n * cfg.d / (kernels["ivf_coarse"]["ms_per_step"] / 1e3) / 1e12}
     if not args.no_cpu:
         from oracle import ivfadc
         from parity import assert_topk_matches
@@ -615,6 +625,39 @@ def encode_leg(etf, torch, cfg_name):
     return info
 
 
+def short(v, digits=6):
+    """The same value with its floats to so many significant digits."""
+    if isinstance(v, float):
+        return float("%.*g" % (digits, v))
+    if isinstance(v, dict):
+        return {k: short(x, digits) for k, x in v.items()}
+    return [short(x, digits) for x in v] if isinstance(v, (list, tuple)) else v
+
+
+def emit(line, details):
+    """The result line on stdout.  Of the legs beside the headline it has the times, rates and roofline fractions; the whole of
+    them (kernel times, index statistics, notes) goes to the file `details` if one is given: with them the line grows past
+    15 KB, more than what reads it keeps."""
+    line = short(line)
+    if details:
+        with open(details, "w") as f:
+            json.dump(line, f, indent=1)
+    kept = {"ms_per_step", "value", "queries_per_s", "output_GBps", "workload", "fallback_queries", "fallbacks", "error"}
+    roof = {"bound", "kernel", "achieved", "peak", "unit", "frac", "blocks"}
+
+    def leg(x):
+        if not isinstance(x, dict):
+            return x
+        out = {k: v for k, v in x.items() if k in kept}
+        out.update({k: {n: r for n, r in v.items() if n in roof} for k, v in x.items() if k.startswith("roofline") and isinstance(v, dict)})
+        # legs that are a table of numbers stay whole
+        return out or {k: v for k, v in x.items() if not isinstance(v, (dict, list))}
+
+    line = dict(line, others={k: leg(v) for k, v in line["others"].items()})
+    line["index"] = {k: v for k, v in line["index"].items() if k != "trees"}
+    print(json.dumps(line), flush=True)
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -634,6 +677,7 @@ def main():
                     help="2 every table slice in LDS (default), 0 distance context in registers + result tables, 1 level-synchronous")
     ap.add_argument("--opt", action="append", default=[], metavar="NAME=VALUE", help="library option for every context (tuning)")
     ap.add_argument("--no-copy", action="store_true", help="skip the device copy and the memory ceilings")
+    ap.add_argument("--details", default="", metavar="FILE", help="also write every leg whole, as JSON")
     ap.add_argument("--encode-only", action="store_true", help="run the device encoder on the configuration's database and stop (counter runs)")
     args = ap.parse_args()
     EXTRA_OPTS[:] = list(args.opt)
@@ -943,7 +987,7 @@ def main():
                   "trees": stats["trees"], "sample": int(S)},
         "paper_context": PAPER_CONTEXT,
     }
-    print(json.dumps(line), flush=True)
+    emit(line, args.details)
 
 
 if __name__ == "__main__":
