@@ -329,7 +329,7 @@ int etf_index_export(const etf_ctx *ctx, void *host_buf, int64_t bytes);
  * "Efficient Encoding Tree Construction").  Same result definition as
  * etf_pq_encode, decided in float32: every squared distance is the sum of its
  * (x - c)^2 terms in dimension order, one rounding per operation, lowest index on
- * ties.  x [n][d] device, codes_out [n][M] device; ws is device scratch of at least
+ * ties, 0 where no distance is below the largest float.  x [n][d] device, codes_out [n][M] device; ws is device scratch of at least
  * etf_encode_workspace_bytes() bytes (256-byte aligned) that receives the codebooks;
  * the copy is enqueued on the context's stream from the context's host copy.
  * Option "encode_kernel" = 1 needs d/M <= 128 (ETF_EINVAL otherwise).  n = 0 is allowed. */

@@ -1120,7 +1120,8 @@ extern "C" int64_t etf_encode_workspace_bytes(const etf_ctx *ctx)
 {
     if (!ctx) return ETF_EINVAL;
     if (ctx->codebooks.empty()) return fail(ctx, ETF_ESTATE, "no codebooks: call etf_pq_train or etf_pq_set_codebooks first");
-    // the codebooks, then per group 256 halved squared norms and the largest norm (k_encode_norms)
+    // the codebooks, then per group 256 halved squared norms and the largest norm (k_encode_norms; only groups of more than
+    // 128 dimensions use them)
     return (int64_t)((ctx->codebooks.size() * sizeof(float) + 255) & ~(size_t)255) + (int64_t)(((size_t)ctx->M * 257 * sizeof(float) + 255) & ~(size_t)255);
 }
 

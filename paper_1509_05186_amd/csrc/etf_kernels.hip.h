@@ -930,10 +930,10 @@ __global__ __launch_bounds__(256, 2) void k_encode_mfma(const float *__restrict_
 //     kernel once the products were cheap.)
 //     A workgroup keeps the operands of as many groups as fit its LDS (16 KB per 16 dimensions, in instruction order)
 //     and walks the vectors, 32 per wave and step, whole rows at a time where all groups fit.
-//     What bounds it: vector and matrix issue together (about 300 vector instructions and 32 matrix instructions for 32
+//     What bounds it: vector and matrix issue together (about 350 vector instructions and 32 matrix instructions for 32
 //     vectors of a group of 16 dimensions; a matrix instruction takes the issue slot of about two others), the matrix
 //     cores for wide groups.  Kernel time against the float32 matrix instruction with three values tracked per codeword:
-//     a million vectors, 8 groups of 16, 0.81 -> 0.26 ms; 250 001 vectors, 8 groups of 120, 1.63 -> 0.36 ms.
+//     a million vectors, 8 groups of 16, 0.81 -> 0.27 ms; 250 001 vectors, 8 groups of 120, 1.63 -> 0.36 ms.
 //     grid (vector chunks, ceil(M / gs)), block NW * 64, dynamic LDS encode_bf_lds().
 // ------------------------------------------------------------------------------------------------
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -1293,17 +1293,6 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void k_encode_bf(const float *__re
     settle();
 }
 
-// ------------------------------------------------------------------------------------------------
-// The matrix-core assignment for wide groups (more than 64 dimensions per group, aligned rows): both operands go
-//     through LDS 32 dimensions at a time, fetched with coalesced 16-byte loads (eight threads per row) into registers
-//     while the previous stage is multiplied, as in k_ivf_coarse_tc; k_encode_mfma's per-lane loads of 16 bytes from
-//     64 different rows keep the matrix cores waiting for the cache's tag look-ups.  A workgroup owns 128 vectors
-//     and the group's 256 codewords: wave (wk, wv) multiplies codewords 128 wk .. by vectors 64 wv .. (A = codewords,
-//     4 x 2 accumulator blocks that start at -||c||^2 / 2), keeps largest, second largest and index per vector as
-//     k_encode_tc does, the two waves of a vector set merge through LDS, and near-ties go through the float32 rule.
-//     The codes are k_encode's, bit for bit.
-//     cc2: from k_encode_norms.  grid (ceil(n / 128), M), block 256; ds and d multiples of 4, K <= 256.
-// ------------------------------------------------------------------------------------------------
 // -0.5 ||c||^2 of every codeword (-3e38 beyond K) as cc2[M][256], and the largest ||c||^2 of every group as
 // cc2[M * 256 + m]: what k_encode_wide starts its accumulators from.  grid (M), block 256.
 __global__ __launch_bounds__(256) void k_encode_norms(const float *__restrict__ cb, int ds, int K, int M, float *__restrict__ cc2)
@@ -1323,6 +1312,18 @@ __global__ __launch_bounds__(256) void k_encode_norms(const float *__restrict__ 
     if (t == 0) cc2[M * 256 + m] = fmaxf(fmaxf(s_mx[0], s_mx[1]), fmaxf(s_mx[2], s_mx[3]));
 }
 
+// ------------------------------------------------------------------------------------------------
+// The matrix-core assignment for wide groups (more than 128 dimensions per group, aligned rows): both operands go
+//     through LDS 32 dimensions at a time, fetched with coalesced 16-byte loads (eight threads per row) into registers
+//     while the previous stage is multiplied, as in k_ivf_coarse_tc; k_encode_mfma's per-lane loads of 16 bytes from
+//     64 different rows keep the matrix cores waiting for the cache's tag look-ups.  A workgroup owns 128 vectors
+//     and the group's 256 codewords: wave (wk, wv) multiplies codewords 128 wk .. by vectors 64 wv .. (A = codewords,
+//     4 x 2 accumulator blocks that start at -||c||^2 / 2), keeps the largest value, its index and the second largest per
+//     vector (four instructions a value), the two waves of a vector set merge through LDS, and near-ties go through the
+//     float32 rule.
+//     The codes are k_encode's, bit for bit.
+//     cc2: from k_encode_norms.  grid (ceil(n / 128), M), block 256; ds and d multiples of 4, K <= 256.
+// ------------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(256, 2) void k_encode_wide(const float *__restrict__ x, int64_t n, int d, int ds, int K, int M,
                                                         const float *__restrict__ cb, const float *__restrict__ cc2, uint8_t *__restrict__ codes)
 {
@@ -2497,11 +2498,11 @@ __global__ __launch_bounds__(1024) void k_lds16(const uint32_t *__restrict__ rec
 //     the bound that those up to tau + E would not fit the candidate list (`room`, from k_tau), a block of 128 queries with
 //     such a query is left to k_lds16, which is launched behind and otherwise ends at once: where k_tau sees it (`loose`) no
 //     workgroup takes the block, where it is found here all of its workgroups end.  The two share a batch from half of its blocks
-//     on; below that the second start costs more than the faster rate gives.  Ten million encodings of 16 chunks, 10 000
+//     on; below that the second start costs more than the faster rate gives.  Ten million vectors of 16 chunks, 10 000
 //     queries (79 blocks) of which 1, 19 and 39 blocks are left: 15.4, 17.5 and 19.3 ms, k_lds16 alone 21.8 (M = 8, 4000
 //     queries, half: 2.74 and 2.82).
-//     What bounds it: the matrix cores under the card's power limit.  Ten million encodings of 16 chunks (128 dimensions),
-//     10 000 queries: 13.1 ms = 1.29 PFLOP/s, against 1.55 of the bare instruction on random operands and 1.16 to 1.21 of a large
+//     What bounds it: the matrix cores under the card's power limit.  Ten million vectors of 16 chunks (128 dimensions), 6.6
+//     million distinct encodings, 10 000 queries: 13.1 ms = 1.29 PFLOP/s, against 1.55 of the bare instruction on random operands and 1.16 to 1.21 of a large
 //     library product here; k_lds16 19.7 ms.
 //     Candidates: a lane that finds one among its 16 values parks all 16 in the wave's ring; a full ring is taken apart by
 //     all lanes (as in k_lds16).
