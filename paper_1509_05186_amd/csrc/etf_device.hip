@@ -761,7 +761,7 @@ int launch_lds(etf_ctx *ctx, const Plan &P, char *ws, const uint32_t *rec, int64
 }
 
 // the filter pass on 16-bit tables (see k_lds16)
-int launch_lds16(etf_ctx *ctx, const Plan &P, char *ws, const uint32_t *rec, int64_t nitems, int64_t tiles, const OutArgs &o)
+int launch_lds16(etf_ctx *ctx, const Plan &P, char *ws, const uint32_t *rec, int64_t nitems, int64_t tiles, OutArgs o)
 {
     if (nitems == 0) return ETF_OK;
     const int M = ctx->M, K = ctx->K;
@@ -770,7 +770,9 @@ int launch_lds16(etf_ctx *ctx, const Plan &P, char *ws, const uint32_t *rec, int
     int64_t bx = lds_blocks_for(tiles * (G / 2), nitems, (nitems >> 25) + 1);
     if (ctx->opt.lds_blocks > 0) bx = std::max<int64_t>(ctx->opt.lds_blocks, (nitems >> 25) + 1);
     // behind k_mm16 the workgroups divide the sub-tiles that it has left among themselves
-    const int per_block = o.done ? (int)(ctx->opt.lds_blocks > 0 ? bx : 0) : (int)((nitems + bx - 1) / bx);
+    o.shares = (int)bx;
+    o.fixed = ctx->opt.lds_blocks > 0;
+    const int per_block = (int)((nitems + bx - 1) / bx);
     const dim3 grid = o.done ? dim3((unsigned)(bx * (G / 2) * tiles)) : dim3((unsigned)bx, (unsigned)(G / 2), (unsigned)tiles);
     hipStream_t st = (hipStream_t)ctx->stream;
     const float *lutT = reinterpret_cast<const float *>(ws + P.o_lutT);
@@ -809,8 +811,7 @@ bool mm_wanted(const etf_ctx *ctx, const Plan &P, int64_t nq)
     return padded * 2 <= (nq + Qs - 1) / Qs * Qs * 3 && (double)padded * (double)ctx->idx.Nd >= (double)ctx->opt.matrix_filter * (ctx->M == 8 ? 2.0 : 1.0);
 }
 
-int launch_mm16(etf_ctx *ctx, const float *queries, const uint32_t *rec, int64_t nitems, int64_t nql, const OutArgs &o, const LooseArgs &la,
-                uint32_t *taken)
+int launch_mm16(etf_ctx *ctx, const float *queries, const uint32_t *rec, int64_t nitems, int64_t nql, OutArgs o, const LooseArgs &la, uint32_t *taken)
 {
     const int M = ctx->M;
     MmArgs a;
@@ -831,10 +832,9 @@ int launch_mm16(etf_ctx *ctx, const float *queries, const uint32_t *rec, int64_t
     a.loose = la.loose;
     a.taken = taken;
     int64_t bx = lds_blocks_for(o.blocks, nitems, (nitems >> 25) + 1);
-    if (ctx->opt.lds_blocks > 0) {
-        bx = std::max<int64_t>(ctx->opt.lds_blocks, (nitems >> 25) + 1);
-        a.shares = (int)bx;
-    }
+    if (ctx->opt.lds_blocks > 0) bx = std::max<int64_t>(ctx->opt.lds_blocks, (nitems >> 25) + 1);
+    o.shares = (int)bx;
+    o.fixed = ctx->opt.lds_blocks > 0;
     const dim3 grid((unsigned)(bx * o.blocks));
     hipStream_t st = (hipStream_t)ctx->stream;
     ProfScope prof(ctx, ETF_K_LDS16);

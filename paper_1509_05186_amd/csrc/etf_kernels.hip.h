@@ -1503,8 +1503,11 @@ struct OutArgs {
     int64_t gstride;    // ngroups rounded up to a multiple of 64
     int gsize;
     uint32_t *done;     // per block of 128 queries: not zero where k_mm16 has filtered it (k_lds16 takes the others), then as many
-                        // words where k_tau says whose error bound is too large; cleared by the sample pass of k_lds; or nullptr
-    int blocks;         // their number
+                        // words where k_tau says whose error bound is too large, then the number of the former; cleared by the
+                        // sample pass of k_lds; or nullptr
+    int blocks;         // the number of blocks
+    int shares;         // workgroups per unit of the launch as the host cut it
+    bool fixed;         // ... that many always (option lds_blocks)
     int wps;            // k_lds: waves that share a stretch of the sample (a power of two, at most 16)
     // OUT_FILTER
     const float *tau;   // [tiles*64]
@@ -1809,7 +1812,7 @@ __global__ __launch_bounds__(1024) void k_lds(const uint32_t *__restrict__ rec, 
     static_assert(!FX || MODE == OUT_FILTER, "the fixed-point form is a candidate filter");
     static_assert(!TERM || (MODE == OUT_FILTER && !FX), "TERM selects the filter pass with a leaf payload; the other modes test o.term");
     if (MODE == OUT_SAMPLE && o.done && blockIdx.x + blockIdx.y + blockIdx.z == 0)
-        for (int i = threadIdx.x; i < 2 * o.blocks; i += blockDim.x) o.done[i] = 0u;
+        for (int i = threadIdx.x; i < 2 * o.blocks + 1; i += blockDim.x) o.done[i] = 0u;
     // a sub-tile past the last query: nothing to write
     if ((MODE == OUT_ALLPAIRS || MODE == OUT_SAMPLE) && (int64_t)tile * QT + sub * Qs >= o.nq) return;
     if (FILTER) wcount[w][lane] = 0u;
@@ -2147,8 +2150,8 @@ __global__ __launch_bounds__(1024) void k_lds(const uint32_t *__restrict__ rec, 
 // its share of the items of its unit among the units that are left (block b has weight(b) of them).  The host sizes the launch
 // for all units; a few that are left get more shares each, so that they still fill the compute units.  The shares are chosen by
 // the rule of lds_blocks_for on the host (`given` > 0: that many), a candidate per lane.  (A launch cut for all of 79 blocks
-// gave a single one 16 long workgroups: a whole round of the pass, 4 ms of 20.)  Fewer units than `worth` are left alone.  Every
-// wave finds the same; the answer is uniform.
+// gave a single one 16 long workgroups: a whole round of the pass, 4 ms of 20.)  Every wave finds the same; the answer is uniform.
+// (Where all units are left, or none, the kernels know it without.)
 // ------------------------------------------------------------------------------------------------
 constexpr int MM_Q = 128;  // queries per block of the divided pass
 struct Share {
@@ -2156,8 +2159,7 @@ struct Share {
     int share, shares;
 };
 template <class F>
-__device__ __forceinline__ bool find_share(uint32_t wg, uint32_t wgs, int blocks, int64_t nitems, int given, uint32_t worth, F weight,
-                                           Share &s)
+__device__ __forceinline__ bool find_share(uint32_t wg, uint32_t wgs, int blocks, int64_t nitems, int given, F weight, Share &s)
 {
     const int lane = threadIdx.x & 63;
     uint32_t total = 0;
@@ -2168,7 +2170,7 @@ __device__ __forceinline__ bool find_share(uint32_t wg, uint32_t wgs, int blocks
         total += v;
     }
     total = (uint32_t)uniform((int)total);
-    if (total < worth) return false;
+    if (total == 0u) return false;
     uint32_t shares = (uint32_t)given;
     if (given == 0) {
         const uint32_t least = (uint32_t)(nitems >> 25) + 1u, most = max(least, (uint32_t)((nitems + 4095) / 4096));
@@ -2235,8 +2237,7 @@ __device__ __forceinline__ bool find_share(uint32_t wg, uint32_t wgs, int blocks
 //     Geometry, item walk, distance context and line layout are those of k_lds<G> (rows of 64 or 32 bytes, lines
 //     of 256 bytes, chunk order rotated per lane group); a sub-tile has 128 / G queries.
 //     grid (blocks, G / 2, tiles), or, behind k_mm16, (workgroups) for the sub-tiles of the blocks that it has not done
-//     (find_share; `per_block` is the number of shares there, 0: by the rule); block 1024, dynamic LDS lds_table_bytes(G) +
-//     lds16_aux_bytes(); G in {4, 8}.
+//     (find_share); block 1024, dynamic LDS lds_table_bytes(G) + lds16_aux_bytes(); G in {4, 8}.
 // ------------------------------------------------------------------------------------------------
 typedef unsigned short u16x8 __attribute__((ext_vector_type(8)));
 typedef __attribute__((address_space(3))) const u16x8 lds_u16x8_t;
@@ -2263,12 +2264,15 @@ __global__ __launch_bounds__(1024) void k_lds16(const uint32_t *__restrict__ rec
     uint32_t(*wpos)[64] = reinterpret_cast<uint32_t(*)[64]>(aux + 16 * RING * 20 + 16 * 64 * 4);
     int tile = blockIdx.z, sub = blockIdx.y, share = blockIdx.x;
     if (o.done) {
+        const uint32_t taken = o.done[2 * o.blocks];
+        if (taken == (uint32_t)o.blocks) return;
         // a sub-tile of Qs queries: the nth of its block's that hold a query
-        Share s;
-        if (!find_share(blockIdx.x, gridDim.x, o.blocks, nitems, per_block, 1u,
+        Share s = {0, (int)blockIdx.x / o.shares, (int)blockIdx.x % o.shares, o.shares};
+        if (taken != 0u &&
+            !find_share(blockIdx.x, gridDim.x, o.blocks, nitems, o.fixed ? o.shares : 0,
                         [&](int b) { return o.done[b] != 0u ? 0 : (int)((min<int64_t>(MM_Q, o.nq - (int64_t)b * MM_Q) + Qs - 1) / Qs); }, s))
             return;
-        tile = s.block * (MM_Q / QT) + s.nth / (QT / Qs);
+        tile = s.block * (MM_Q / QT) + s.nth / (QT / Qs);  // (all of them: numbered through)
         sub = s.nth % (QT / Qs);
         share = s.share;
         per_block = (int)((nitems + s.shares - 1) / s.shares);
@@ -2491,7 +2495,8 @@ __global__ __launch_bounds__(1024) void k_lds16(const uint32_t *__restrict__ rec
 //     Everything else is float32 rounding: in units of 2^-24
 //     (||q||^2 + C^2), C^2 the sum of the largest ||c||^2, the contraction (one unit in the last place per product)
 //     4 dpad + 16, ||q||^2 d, the table entries that the float32 distance is summed from 4 ds + 10, the sums of M terms
-//     3 M, the centring 4: below 6 dpad + 4 ds + 4 M + 64.  E bounds the difference between the value here and the float32
+//     3 M, the centring 4, e and f in 16 bits where their products cancel 8 (2^-11 of sum |e c^| + |q^ f|, each at most 2^-11
+//     of sum |q c|): below 6 dpad + 4 ds + 4 M + 64.  E bounds the difference between the value here and the float32
 //     distance of the tables, and everything with a value of at most tau + E passes.  Its candidates carry a 16-bit fixed-point
 //     value; k_select takes everything within margin = 2 E of the k-th smallest and recomputes those from the tables.
 //     Where E is not small against the bound (tight clusters far from the mean), or the sample has so many encodings just above
@@ -2526,7 +2531,6 @@ struct MmArgs {
     const float *room;     // [nql] from k_tau: the largest error bound with which the candidates still fit
     const uint32_t *loose; // [blocks] from k_tau: not zero where a query's error bound will exceed that
     uint32_t *margin;      // [nql] for k_select: those of the blocks filtered here are written
-    int shares;            // workgroups per block (0: by the rule of find_share)
     uint32_t *taken;       // count of the blocks that it filtered (etf_last_matrix_blocks)
 };
 
@@ -2555,8 +2559,13 @@ __global__ __launch_bounds__(512, 2) void k_mm16(const uint32_t *__restrict__ re
     const int col = lane & 31, half = lane >> 5;
     const int K = a.K, ds = a.ds;
     const float inf = __uint_as_float(0x7F800000u);
-    Share sh;
-    if (!find_share(blockIdx.x, gridDim.x, o.blocks, nitems, a.shares, (uint32_t)(o.blocks + 1) / 2u, [&](int b) { return a.loose[b] != 0u ? 0 : 1; }, sh)) return;
+    int left = 0;
+    for (int b0 = 0; b0 < o.blocks; b0 += 64) left += __popcll(__ballot(b0 + lane < o.blocks && a.loose[b0 + lane] != 0u));
+    if (2 * left > o.blocks) return;
+    Share sh = {(int)blockIdx.x / o.shares, 0, (int)blockIdx.x % o.shares, o.shares};
+    if (left != 0 &&
+        !find_share(blockIdx.x, gridDim.x, o.blocks, nitems, o.fixed ? o.shares : 0, [&](int b) { return a.loose[b] != 0u ? 0 : 1; }, sh))
+        return;
     const int qb = sh.block;
     const int per_block = (int)((nitems + sh.shares - 1) / sh.shares + 31) / 32 * 32;
     // ---- the largest norms
@@ -2702,7 +2711,8 @@ __global__ __launch_bounds__(512, 2) void k_mm16(const uint32_t *__restrict__ re
         }
 #pragma unroll
         for (int i = 0; i < NW; ++i) L += part[8 + i][t];
-        // (1.01: the rounding of e and f themselves; MC / 32: what to16 dropped of them, two units of 2^-14 per dimension)
+        // (1.01: the rounding of e and f themselves, and 8 units of G where their products cancel; MC / 32: what to16 dropped of
+        // them, two units of 2^-14 per dimension)
         const float G = (float)(6 * 8 * MC + 4 * ds + 4 * MC + 64) * 5.9604645e-8f;
         const float E = 1.01f * (2.f * L * 4.8828125e-4f + (float)MC * 0.03125f) / sigma + 2.02f * sqrtf(ee * F) + G * (nq + C);
         const float tau = ql < a.nql ? o.tau[ql] : -1.f;
@@ -2724,6 +2734,7 @@ __global__ __launch_bounds__(512, 2) void k_mm16(const uint32_t *__restrict__ re
         if (threadIdx.x < MM_Q && (int64_t)qb * MM_Q + threadIdx.x < a.nql) a.margin[(int64_t)qb * MM_Q + threadIdx.x] = __float_as_uint(qc[threadIdx.x].w);
         if (threadIdx.x == 0) {
             o.done[qb] = 1u;
+            atomicAdd(&o.done[2 * o.blocks], 1u);
             atomicAdd(a.taken, 1u);
         }
     }
@@ -3030,7 +3041,7 @@ __global__ __launch_bounds__(256) void k_tau(const float *__restrict__ gmin, int
     if (counter && blockIdx.x == 0 && threadIdx.x < 64) counter[lane] = 0u;
     if (ql >= nql) return;
     uint32_t bound = __float_as_uint(-1.f);  // a column past the last query: nothing passes
-    float room = 0.f;
+    float room = 0.f, nn = 0.f, e = 0.f;
     if (ql < nq) {
         const float *row = gmin + ql * gstride;
         uint32_t x[NV];
@@ -3067,7 +3078,17 @@ __global__ __launch_bounds__(256) void k_tau(const float *__restrict__ gmin, int
         }
         bound = S >= k ? hi : 0x7F800000u;
         if (la.room) {
-            if (la.groups >= S) {
+            nn = 0.f;
+            for (int j = lane; j < la.d; j += 64) {
+                const float v = la.queries[ql * la.d + j] - la.mean[j];
+                nn = fmaf(v, v, nn);
+            }
+#pragma unroll
+            for (int dlt = 32; dlt >= 1; dlt >>= 1) nn += __shfl_xor(nn, dlt);
+            e = la.typical * sqrtf(nn);
+            if (!(28.f * e <= __uint_as_float(bound))) {
+                room = -1.f;  // whatever the sample says
+            } else if (la.groups >= S) {
                 room = __uint_as_float(0x7F800000u);
             } else if (count(bound) <= la.groups) {
                 // at most la.groups minima are at or below lo, more at or below hi (to 2^-10 of the value)
@@ -3083,19 +3104,10 @@ __global__ __launch_bounds__(256) void k_tau(const float *__restrict__ gmin, int
         }
     }
     if (la.room) {
-        float nn = 0.f;
-        if (ql < nq)
-            for (int j = lane; j < la.d; j += 64) {
-                const float v = la.queries[ql * la.d + j] - la.mean[j];
-                nn = fmaf(v, v, nn);
-            }
-#pragma unroll
-        for (int dlt = 32; dlt >= 1; dlt >>= 1) nn += __shfl_xor(nn, dlt);
-        const float e = la.typical * sqrtf(nn);
         if (lane == 0) {
             la.room[ql] = room;
             la.margin[ql] = la.margin_table;
-            if (ql < nq && !(1.2f * e <= room && 28.f * e <= __uint_as_float(bound))) la.loose[ql / MM_Q] = 1u;  // (all write the same)
+            if (ql < nq && !(1.2f * e <= room)) la.loose[ql / MM_Q] = 1u;  // (all write the same)
         }
     }
     if (lane == 0) {
