@@ -84,6 +84,66 @@ def test_blocks_left_to_the_table_filter(M, T):
         q[list(at)] = tight
         own = 6 - len({i // 128 for i in at})
         check(c, q, 10, FOREST, taken=own if 2 * own >= 6 else 0)  # fewer than half are not worth a kernel of their own
+    q = p.q.copy()
+    q[[130, 650]] = tight
+    for blocks in (1, 5, 40):           # workgroups per unit by the option in place of the rule
+        c.set_option("lds_blocks", blocks)
+        check(c, q, 10, FOREST, taken=4)
+
+
+def test_replays_divide_the_batch_anew():
+    say("matrix filter: a captured search on other queries, other blocks left to the table kernel every time")
+    p, tight = with_a_tight_cluster(16, 8, 30000, 700, 53)
+    c = p.ctx(matrix_filter=0, T=4, sample_min=1 << 14, cand_cap=8192)
+    k, qd = 10, torch.from_numpy(p.q).cuda()
+    ws = c.alloc_workspace(700, k, FOREST)
+    ids = torch.zeros((700, k), dtype=torch.int32, device="cuda")
+    dist = torch.zeros((700, k), dtype=torch.float32, device="cuda")
+    c.search(qd, k, FOREST, ids, dist, ws)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        c.set_stream(torch.cuda.current_stream().cuda_stream)
+        c.search(qd, k, FOREST, ids, dist, ws)
+    c.set_stream(torch.cuda.current_stream().cuda_stream)
+    for at, taken in (([5, 300], 4), ([], 6), (range(0, 700, 64), 0), ([699], 5), ([0, 130, 260, 390], 0), ([], 6)):
+        q = torch.from_numpy(p.q).cuda()
+        q[list(at)] = torch.from_numpy(tight).cuda()
+        qd.copy_(q)
+        g.replay()
+        torch.cuda.synchronize()
+        assert c.last_matrix_blocks() == taken and c.last_fallback_count() == 0
+        c.set_option("matrix_filter", -1)
+        want_i, want_d = c.search(q, k, FOREST)
+        torch.cuda.synchronize()
+        c.set_option("matrix_filter", 0)
+        assert torch.equal(ids, want_i) and torch.equal(dist, want_d)
+        c.search(q, k, FOREST, want_i, want_d, ws)          # eager work on the same workspace, counts in place again
+        torch.cuda.synchronize()
+        assert c.last_matrix_blocks() == taken
+
+
+def test_batches_of_a_small_workspace():
+    """The blocks, their words and their counts belong to a batch of tiles: several batches, the last one of a single tile."""
+    say("matrix filter: one search in several batches")
+    p, tight = with_a_tight_cluster(8, 8, 30000, 1100, 54)
+    q = p.q.copy()
+    q[[130, 400, 900]] = tight
+    c = p.ctx(matrix_filter=0, T=2, sample_min=1 << 14, cand_cap=8192)
+    qd = torch.from_numpy(q).cuda()
+    want_i, want_d = c.search(qd, 10, FOREST)
+    torch.cuda.synchronize()
+    for tiles in (3, 4, 7):
+        c.set_option("ws_cap_bytes", int(c.alloc_workspace(64, 10, FOREST).numel() * (tiles + 0.5)))
+        ids, dist = c.search(qd, 10, FOREST)
+        torch.cuda.synchronize()
+        assert c.last_fallback_count() == 0
+        say("  batches of", tiles, "tiles:", c.last_matrix_blocks(), "blocks on the matrix cores")
+        assert torch.equal(ids, want_i) and torch.equal(dist, want_d)
+    ids.zero_()
+    c.search_static(qd, 10, FOREST, ids, dist)
+    torch.cuda.synchronize()
+    assert torch.equal(ids, want_i) and torch.equal(dist, want_d)
 
 
 def test_outliers():
