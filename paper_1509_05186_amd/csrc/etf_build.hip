@@ -31,6 +31,16 @@ constexpr int BT = 256;  // threads per workgroup of every kernel here
 inline int64_t al256(int64_t x) { return (x + 255) & ~(int64_t)255; }
 inline unsigned blocks(int64_t n) { return (unsigned)((n + BT - 1) / BT); }
 
+__device__ inline uint64_t mix64(uint64_t z)
+{
+    z += 0x9E3779B97F4A7C15ull;
+    z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
+    z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
+    return z ^ (z >> 31);
+}
+
+#include "etf_build_kernels.hip.h"
+
 // scal[0] = distinct encodings, scal[1] = largest number of vectors sharing one encoding, scal[2] = input faults
 // (bit 0: a code byte >= K, bit 1: a negative id)
 __global__ void __launch_bounds__(BT) k_build_init(const uint8_t *codes, const int32_t *ids, int64_t N, int M, int K,
@@ -227,14 +237,6 @@ __global__ void __launch_bounds__(BT) k_build_rec0(const uint8_t *ecodes, int M,
     for (int j = 0; j < rstride; ++j) rec0[e * rstride + j] = (j >= pad && j < pad + D0) ? ecodes[e * M + j - pad] : (uint8_t)0;
 }
 
-__device__ inline uint64_t mix64(uint64_t z)
-{
-    z += 0x9E3779B97F4A7C15ull;
-    z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
-    z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
-    return z ^ (z >> 31);
-}
-
 // A sample of S of n rows without repeats: [0, n) is cut into S strata of (almost) equal length and one row is
 // drawn from each.  Slot i of the sample holds stratum (i * A + B) mod S, A coprime to S: neighbouring slots (and
 // with them the sample groups the kernels cut the sample into) hold rows from all over the range.
@@ -401,13 +403,12 @@ int sort_pass(etf_ctx *ctx, const BuildWs &W, char *ws, const uint8_t *rows, int
     return ETF_OK;
 }
 
-int build_impl(etf_ctx *ctx, const uint8_t *codes, int64_t N, const int32_t *ids, int T, const std::vector<int32_t> &cb,
-               char *img, int64_t image_bytes, char *ws, const BuildWs &W)
+// the index's shape in the context; the chunk order of the build, true where it is the order of the input
+bool shape_index(etf_ctx *ctx, int64_t N, int T, const std::vector<int32_t> &cb, BuildOrder &ord)
 {
-    const int M = ctx->M, K = ctx->K;
-    hipStream_t st = (hipStream_t)ctx->stream;
+    const int M = ctx->M;
     HostIndex &ix = ctx->idx;
-    ix.M = M; ix.K = K; ix.T = T; ix.N = N;
+    ix.M = M; ix.K = ctx->K; ix.T = T; ix.N = N;
     ix.chunk_begin = cb;
     ix.device_built = true;
     ix.rstride0 = std::max(4, depth_class(cb[1] - cb[0]));
@@ -426,6 +427,272 @@ int build_impl(etf_ctx *ctx, const uint8_t *codes, int64_t N, const int32_t *ids
             tr.bucket[l].stride = (tr.bucket[l].width + 3) & ~3;
         }
     }
+    ix.order.resize(M);
+    bool identity = true;
+    for (int j = 0; j < ETF_MAX_M; ++j) {
+        const int src = (j < M && !ctx->next_order.empty()) ? ctx->next_order[j] : j;
+        if (j < M) ix.order[j] = src;
+        ord.src[j] = (uint8_t)src;
+        identity = identity && src == j;
+    }
+    return identity;
+}
+
+int put_quantiser(etf_ctx *ctx, char *img)
+{
+    hipStream_t st = (hipStream_t)ctx->stream;
+    const DevLayout &L = ctx->lay;
+    auto put = [&](int64_t off, const std::vector<float> &v) {
+        return v.empty() ? hipSuccess : hipMemcpyAsync(img + off, v.data(), v.size() * 4, hipMemcpyHostToDevice, st);
+    };
+    HIP_TRY(ctx, put(L.codebooks, ctx->codebooks));
+    HIP_TRY(ctx, put(L.cb_centered, ctx->cb_centered));
+    HIP_TRY(ctx, put(L.cb_norm, ctx->cb_norm));
+    HIP_TRY(ctx, put(L.cb_mean, ctx->cb_mean));
+    return ETF_OK;
+}
+
+// ---- the chain of etf_build_kernels.hip.h ------------------------------------------------------------------------
+
+// Where its arrays lie in the workspace.  ok: the chain is built for this many vectors.
+struct ChainPlan {
+    bool ok = false;
+    int KW = 0, KT = 0, wshift = 0, nt = 0;
+    uint32_t cap = 0, buckets = 0, samples = 0;
+    int lvl_tiles = 0;
+    int64_t S0 = 0;                                          // most draws of the threshold sample
+    int64_t slab, slab_t, smp, smp_t, zero, zero_words, nh, nh0, first, last, nh_t, nh0_t, first_t, last_t, faults, enc_of_rank, leaf,
+        dk, draw, kept, tile_cnt, total = 0;
+    int64_t rank, count, rank_t, count_t;                    // words from `zero` on
+    int64_t slab_stride, smp_stride, rank_stride, bucket_stride, key_stride;  // words between two trees
+};
+
+inline int key_words(int D) { return D <= 4 ? 1 : D <= 8 ? 2 : 4; }
+
+ChainPlan plan_chain(const etf_ctx *ctx, int64_t N, int T, const std::vector<int32_t> &cb, bool ids)
+{
+    ChainPlan P;
+    int Dmax = 0;
+    for (int t = 0; t < T; ++t) Dmax = std::max(Dmax, cb[t + 1] - cb[t]);
+    P.KW = key_words(ctx->M);
+    P.KT = key_words(Dmax);
+    // Up to 2 M vectors a bucket of 4096 (of 3 to 6 words each) lets three workgroups share a CU; beyond, the samples'
+    // ranks (quadratic in their number) are the larger part, and elements of at most 4 words go in buckets of 8192.
+    // The limits: the splitters and counts of one level of buckets in LDS (5120 of 7 words: 143 KB), and the ranks.
+    const bool wide = P.KW < 4 && N > ((int64_t)1 << 21);
+    if (N > (P.KW < 4 ? (int64_t)1 << 23 : (int64_t)5 << 20)) return P;
+    P.nt = wide ? 1024 : 512;
+    P.cap = (uint32_t)P.nt * 8;
+    P.wshift = wide ? 8 : 7;
+    P.buckets = n_buckets((uint32_t)N, P.cap, P.wshift);
+    P.samples = n_samples((uint32_t)N, P.cap, P.wshift);
+    P.lvl_tiles = (int)((N + LVL_TILE - 1) / LVL_TILE);
+    P.S0 = std::min(N, sample_size(ctx->opt, N));
+    const int W = P.KW + (ids ? 2 : 1), WT = P.KT + 1;
+    const int64_t B = P.buckets, S = std::max<int64_t>(P.samples, 1);
+    int64_t off = 0;
+    auto take = [&](int64_t words) {
+        const int64_t o = off;
+        off = al256(off + words * 4);
+        return o;
+    };
+    P.slab_stride = B * P.cap * WT;
+    P.smp_stride = S * WT;
+    P.rank_stride = S;
+    P.bucket_stride = B;
+    P.key_stride = B * P.KT;
+    // the slabs of the trees lie over the vectors', which nothing reads any more by then
+    P.slab = P.slab_t = take(std::max(B * P.cap * W, P.slab_stride * (T - 1)));
+    P.smp = take(S * W);
+    P.smp_t = take(P.smp_stride * (T - 1));
+    P.rank = sizeof(BuildScal) / 4;
+    P.count = P.rank + S;
+    P.rank_t = P.count + B;
+    P.count_t = P.rank_t + S * (T - 1);
+    P.zero_words = P.count_t + B * (T - 1);
+    P.zero = take(P.zero_words);
+    P.nh = take(B);
+    P.nh0 = take(B);
+    P.first = take(B * P.KW);
+    P.last = take(B * P.KW);
+    P.nh_t = take(B * (T - 1));
+    P.nh0_t = take(B * (T - 1));
+    P.first_t = take(P.key_stride * (T - 1));
+    P.last_t = take(P.key_stride * (T - 1));
+    P.faults = take((N + PREP_NT - 1) / PREP_NT);
+    P.enc_of_rank = take(N);
+    P.leaf = take(N * T);
+    P.dk = take(N * T * P.KT);
+    P.draw = take(P.S0);
+    P.kept = take((P.S0 + DRAW_TILE - 1) / DRAW_TILE);
+    P.tile_cnt = take((int64_t)T * P.lvl_tiles * CATS);
+    P.total = off;
+    P.ok = true;
+    return P;
+}
+
+int lds_limit(etf_ctx *ctx, const void *kernel, size_t bytes)
+{
+    if (bytes <= 65536) return ETF_OK;
+    HIP_TRY(ctx, hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes));
+    return ETF_OK;
+}
+
+template <int KW, int TW, int KT, int NT> int launch_chain(etf_ctx *ctx, const ChainPlan &P, const ChainArgs &a)
+{
+    hipStream_t st = (hipStream_t)ctx->stream;
+    constexpr size_t sort_lds = (size_t)(KW + TW) * (NT * 8 + NT / 4) * 4, sort_lds_t = (size_t)(KT + 1) * (NT * 8 + NT / 4) * 4;
+    const size_t cls_lds = (size_t)(KW + TW + 1) * P.buckets * 4, cls_lds_t = (size_t)(KT + 2) * P.buckets * 4;
+    auto cls = k_chain_classify<KW, TW>;
+    auto srt = k_chain_sort<KW, TW, NT>;
+    auto cls_t = k_chain_classify_trees<KW, KT>;
+    auto srt_t = k_chain_sort_trees<KW, KT, NT>;
+    int rc;
+    if ((rc = lds_limit(ctx, (const void *)cls, cls_lds)) || (rc = lds_limit(ctx, (const void *)srt, sort_lds)) ||
+        (rc = lds_limit(ctx, (const void *)cls_t, cls_lds_t)) || (rc = lds_limit(ctx, (const void *)srt_t, sort_lds_t)))
+        return rc;
+    const unsigned T = (unsigned)a.T, N = a.N, B = P.buckets;
+    auto per = [](int64_t n, int64_t each) { return (unsigned)((n + each - 1) / each); };
+    const unsigned rank_blocks = per(P.samples, 64) * RANK_PARTS, lvl = (unsigned)P.lvl_tiles;
+    // a workgroup of the draws also takes a slice of the id ranges, one of the samples a slice of the flat scan's
+    const unsigned draw_blocks = std::max(per(P.S0, DRAW_TILE), std::min(256u, per(N, 2048)));
+    const unsigned place_blocks = std::max(per(P.S0, DRAW_TILE), per(a.n_sample_pos, NT));
+    hipLaunchKernelGGL((k_chain_prep<KW, TW>), dim3(per(N, PREP_NT)), dim3(PREP_NT), 0, st, a);
+    HIP_TRY(ctx, hipGetLastError());
+    if (rank_blocks) hipLaunchKernelGGL((k_chain_rank<KW, TW>), dim3(rank_blocks), dim3(PREP_NT), 0, st, a);
+    HIP_TRY(ctx, hipGetLastError());
+    hipLaunchKernelGGL(cls, dim3(per(N, CLS_TILE)), dim3(CLS_NT), cls_lds, st, a, P.buckets);
+    HIP_TRY(ctx, hipGetLastError());
+    hipLaunchKernelGGL(srt, dim3(B), dim3(NT), sort_lds, st, a);
+    HIP_TRY(ctx, hipGetLastError());
+    hipLaunchKernelGGL((k_chain_encodings<KW, TW, KT, NT>), dim3(B), dim3(NT), 0, st, a);
+    HIP_TRY(ctx, hipGetLastError());
+    hipLaunchKernelGGL((k_chain_mid<KT>), dim3(std::max({rank_blocks, draw_blocks, lvl}), T + 1), dim3(PREP_NT), 0, st, a, draw_blocks);
+    HIP_TRY(ctx, hipGetLastError());
+    hipLaunchKernelGGL(cls_t, dim3(T > 1 ? per(N, CLS_TILE) : 1u, T), dim3(CLS_NT), T > 1 ? cls_lds_t : 0, st, a, P.buckets);
+    HIP_TRY(ctx, hipGetLastError());
+    hipLaunchKernelGGL(srt_t, dim3(T > 1 ? std::max(B, place_blocks) : place_blocks, T), dim3(NT), T > 1 ? sort_lds_t : 0, st, a, place_blocks);
+    HIP_TRY(ctx, hipGetLastError());
+    if (T > 1) {
+        hipLaunchKernelGGL((k_chain_leaves<KT, NT>), dim3(B, T - 1), dim3(NT), 0, st, a);
+        HIP_TRY(ctx, hipGetLastError());
+        hipLaunchKernelGGL((k_chain_levels<KT>), dim3(lvl, T - 1), dim3(PREP_NT), 0, st, a);
+        HIP_TRY(ctx, hipGetLastError());
+    }
+    hipLaunchKernelGGL((k_chain_write<KW, KT>), dim3(lvl, T + 1), dim3(PREP_NT), 0, st, a);
+    HIP_TRY(ctx, hipGetLastError());
+    return ETF_OK;
+}
+
+template <int KW, int TW> int launch_chain_kt(etf_ctx *ctx, const ChainPlan &P, const ChainArgs &a)
+{
+    if constexpr (KW == 4) {
+        if (P.KT == 1) return launch_chain<4, TW, 1, 512>(ctx, P, a);
+        if (P.KT == 2) return launch_chain<4, TW, 2, 512>(ctx, P, a);
+        return launch_chain<4, TW, 4, 512>(ctx, P, a);
+    } else if constexpr (KW == 2) {
+        if (P.KT == 1) return P.nt == 512 ? launch_chain<2, TW, 1, 512>(ctx, P, a) : launch_chain<2, TW, 1, 1024>(ctx, P, a);
+        return P.nt == 512 ? launch_chain<2, TW, 2, 512>(ctx, P, a) : launch_chain<2, TW, 2, 1024>(ctx, P, a);
+    } else {
+        return P.nt == 512 ? launch_chain<1, TW, 1, 512>(ctx, P, a) : launch_chain<1, TW, 1, 1024>(ctx, P, a);
+    }
+}
+
+// The build by the chain; `again`: a bucket ran over, nothing of the image is of use and the general path has to build.
+int build_chain(etf_ctx *ctx, const uint8_t *codes, int64_t N, const int32_t *ids, int T, const std::vector<int32_t> &cb, char *img,
+                char *ws, const ChainPlan &P, bool &again)
+{
+    const int M = ctx->M;
+    hipStream_t st = (hipStream_t)ctx->stream;
+    HostIndex &ix = ctx->idx;
+    BuildOrder ord;
+    const bool identity = shape_index(ctx, N, T, cb, ord);
+    const DevLayout &L = ctx->lay;
+    compute_layout(ctx);   // the arrays up to ebegin have their places
+    auto at = [&](int64_t o) { return (uint32_t *)(ws + o); };
+    ChainArgs a;
+    a.codes = codes;
+    a.ids = ids;
+    a.N = (uint32_t)N;
+    a.M = M; a.K = ctx->K; a.T = T;
+    a.permuted = !identity;
+    a.in_words = M == 4 * P.KW && (uintptr_t)codes % 4 == 0;
+    for (int j = 0; j < ETF_MAX_M; ++j) a.src[j] = ord.src[j];
+    for (int t = 0; t <= T; ++t) a.cb[t] = (uint8_t)cb[t];
+    a.wshift = P.wshift;
+    a.cap = P.cap;
+    a.sample_min = ctx->opt.sample_min;
+    a.sample_scale = ctx->opt.sample_scale;
+    a.seed = 0x1509051860ull ^ (uint64_t)N;
+    a.img = img;
+    a.o_codes = L.codes; a.o_ids_in = L.ids_in; a.o_ids_sorted = L.ids_sorted; a.o_ebegin = L.ebegin;
+    a.n_sample_pos = P.S0;
+    a.A_pos = spread_multiplier(P.S0);
+    a.B_pos = (uint64_t)(P.S0 / 3);
+    a.rstride0 = ix.rstride0;
+    a.scal = (BuildScal *)(ws + P.zero);
+    a.zero = at(P.zero);
+    a.zero_words = (uint32_t)P.zero_words;
+    a.faults = at(P.faults);
+    a.s0 = {at(P.slab), at(P.smp), a.zero + P.rank, a.zero + P.count, at(P.nh), at(P.nh0), at(P.first), at(P.last)};
+    a.st = {at(P.slab_t), at(P.smp_t), a.zero + P.rank_t, a.zero + P.count_t, at(P.nh_t), at(P.nh0_t), at(P.first_t), at(P.last_t)};
+    a.slab_stride = P.slab_stride; a.smp_stride = P.smp_stride; a.rank_stride = P.rank_stride;
+    a.bucket_stride = P.bucket_stride; a.key_stride = P.key_stride;
+    a.enc_of_rank = at(P.enc_of_rank);
+    a.leaf = at(P.leaf);
+    a.dk = at(P.dk);
+    a.draw = at(P.draw);
+    a.kept = at(P.kept);
+    a.tile_cnt = at(P.tile_cnt);
+    a.lvl_tiles = P.lvl_tiles;
+    a.NK = N;
+    int rc;
+    if (ids) rc = P.KW == 1 ? launch_chain_kt<1, 2>(ctx, P, a) : P.KW == 2 ? launch_chain_kt<2, 2>(ctx, P, a) : launch_chain_kt<4, 2>(ctx, P, a);
+    else rc = P.KW == 1 ? launch_chain_kt<1, 1>(ctx, P, a) : P.KW == 2 ? launch_chain_kt<2, 1>(ctx, P, a) : launch_chain_kt<4, 1>(ctx, P, a);
+    if (rc) return rc;
+    if ((rc = put_quantiser(ctx, img))) return rc;   // the host's copies of the tables while the kernels run
+    static_assert(sizeof(ctx->build_scal) == sizeof(BuildScal), "landing place of the counts");
+    HIP_TRY(ctx, hipMemcpyAsync(ctx->build_scal, a.scal, sizeof(BuildScal), hipMemcpyDeviceToHost, st));
+    HIP_TRY(ctx, hipStreamSynchronize(st));
+    BuildScal h;
+    std::memcpy(&h, ctx->build_scal, sizeof(h));
+    again = h.overflow != 0;
+    if (again) return ETF_OK;
+    if (h.faults & 1u) return fail(ctx, ETF_EINVAL, "a code byte is >= K=%d", ctx->K);
+    if (h.faults & 2u) return fail(ctx, ETF_EINVAL, "ids must be non-negative");
+    if (h.Nd < 1 || h.Nd > N) return fail(ctx, ETF_EHIP, "device build returned %lld distinct encodings for %lld vectors", (long long)h.Nd, (long long)N);
+    if (h.S_enc < 1 || h.S_enc > P.S0) return fail(ctx, ETF_EHIP, "device build: %lld of at most %lld sample draws kept", (long long)h.S_enc, (long long)P.S0);
+    ix.Nd = h.Nd;
+    ix.n_sample_enc = h.S_enc;
+    ix.n_sample_pos = P.S0;
+    for (int t = 0; t < T; ++t) {
+        HostTree &tr = ix.tree[t];
+        tr.U = h.U[t];
+        int64_t leaves = 0;
+        for (int l = 0; l < tr.D; ++l) {
+            tr.nI[l] = h.nI[tr.c0 + l];
+            tr.nL[l] = h.nL[tr.c0 + l];
+            leaves += tr.nL[l];
+        }
+        if (tr.U < 1 || tr.U > ix.Nd || leaves != tr.U)
+            return fail(ctx, ETF_EHIP, "device build: tree %d has %lld leaves in its levels, %lld sub-encodings", t, (long long)leaves, (long long)tr.U);
+    }
+    compute_layout(ctx);
+    ix.max_dup = h.max_dup;
+    if (ix.max_dup < 1) return fail(ctx, ETF_EHIP, "device build: no id range");
+    ix.built = true;
+    ctx->dev_base = img;
+    return ETF_OK;
+}
+
+int build_impl(etf_ctx *ctx, const uint8_t *codes, int64_t N, const int32_t *ids, int T, const std::vector<int32_t> &cb,
+               char *img, int64_t image_bytes, char *ws, const BuildWs &W)
+{
+    const int M = ctx->M, K = ctx->K;
+    hipStream_t st = (hipStream_t)ctx->stream;
+    HostIndex &ix = ctx->idx;
+    BuildOrder ord;
+    const bool identity = shape_index(ctx, N, T, cb, ord);
     // The layout grows with the counts: arrays whose sizes are known keep their offsets when later counts arrive.
     const DevLayout &L = ctx->lay;
     auto fits = [&](int64_t upto, const char *what) -> int {
@@ -441,25 +708,9 @@ int build_impl(etf_ctx *ctx, const uint8_t *codes, int64_t N, const int32_t *ids
     uint8_t *d_codes = (uint8_t *)(img + L.codes);
     int32_t *d_ids_in = (int32_t *)(img + L.ids_in);
 
-    // quantiser tables and the input codes
-    auto put = [&](int64_t off, const std::vector<float> &v) {
-        return v.empty() ? hipSuccess : hipMemcpyAsync(img + off, v.data(), v.size() * 4, hipMemcpyHostToDevice, st);
-    };
-    HIP_TRY(ctx, put(L.codebooks, ctx->codebooks));
-    HIP_TRY(ctx, put(L.cb_centered, ctx->cb_centered));
-    HIP_TRY(ctx, put(L.cb_norm, ctx->cb_norm));
-    HIP_TRY(ctx, put(L.cb_mean, ctx->cb_mean));
+    if ((rc = put_quantiser(ctx, img))) return rc;
     HIP_TRY(ctx, hipMemsetAsync(scal, 0, 16, st));
     const unsigned nb = blocks(N);
-    ix.order.resize(M);
-    BuildOrder ord;
-    bool identity = true;
-    for (int j = 0; j < ETF_MAX_M; ++j) {
-        const int src = (j < M && !ctx->next_order.empty()) ? ctx->next_order[j] : j;
-        if (j < M) ix.order[j] = src;
-        ord.src[j] = (uint8_t)src;
-        identity = identity && src == j;
-    }
     if (identity) {
         if (d_codes != codes) HIP_TRY(ctx, hipMemcpyAsync(d_codes, codes, (size_t)N * M, hipMemcpyDeviceToDevice, st));
     } else {
@@ -633,7 +884,7 @@ extern "C" int etf_index_build_device_bytes(const etf_ctx *ctx, int64_t N, int T
     rc = plan_ws(ctx, N, W);
     if (rc) return rc;
     *image_bytes = image_bytes_bound(ctx, N, T, cb.data());
-    *workspace_bytes = W.total;
+    *workspace_bytes = std::max(W.total, plan_chain(ctx, N, T, cb, true).total);
     return ETF_OK;
 }
 
@@ -655,6 +906,19 @@ extern "C" int etf_index_build_device(etf_ctx *ctx, const uint8_t *codes, int64_
     rc = plan_ws(ctx, N, W);
     if (rc) return rc;
     if (workspace_bytes < W.total) return fail(ctx, ETF_ENOMEM, "workspace too small: %lld < %lld", (long long)workspace_bytes, (long long)W.total);
+    // The chain places its arrays on the device, so the image has to hold the largest index of these sizes; a smaller
+    // image or workspace, or an input whose buckets ran over, is built with every array's place checked on the host.
+    const ChainPlan P = plan_chain(ctx, N, T, cb, ids != nullptr);
+    if (P.ok && workspace_bytes >= P.total && image_bytes >= image_bytes_bound(ctx, N, T, cb.data())) {
+        bool again = false;
+        drop_index(ctx);
+        rc = build_chain(ctx, codes, N, ids, T, cb, (char *)image, (char *)workspace, P, again);
+        if (rc) {
+            (void)hipStreamSynchronize((hipStream_t)ctx->stream);
+            drop_index(ctx);
+        }
+        if (rc || !again) return rc;
+    }
     drop_index(ctx);
     rc = build_impl(ctx, codes, N, ids, T, cb, (char *)image, image_bytes, (char *)workspace, W);
     if (rc) {

@@ -1,0 +1,116 @@
+"""The device build that keeps its counts on the device, against the general path (which an image buffer of exactly the
+size of the index asks for) byte for byte, samples included, and against numpy's sort: at the edges of its buckets,
+chunks and tiles, for every width of key, with ties everywhere, and on an input that overruns a bucket."""
+import numpy as np
+import pytest
+
+from test_gpu_build import arr, check_image
+from test_gpu_parity import say
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+import paper_1509_05186_amd as etf  # noqa: E402
+
+
+def build(c, codes, ids, T, chunk_begin, image_bytes):
+    image = torch.zeros(image_bytes + 256, dtype=torch.uint8, device="cuda")
+    off = (-image.data_ptr()) % 256
+    image = image[off:off + image_bytes]
+    c.index_build_device(codes, ids=ids, T=T, chunk_begin=chunk_begin, image=image)
+    torch.cuda.synchronize()
+    return image
+
+
+def compare(codes, ids=None, T=1, chunk_begin=None, K=256, order=None, sample_min=256):
+    N, M = codes.shape
+    c = etf.Context(device=0, stream=torch.cuda.current_stream().cuda_stream)
+    c.set_option("sample_min", sample_min)
+    c.pq_set_codebooks(np.zeros((M, K, 1), dtype=np.float32))
+    c.index_set_chunk_order(order)
+    d_codes, d_ids = torch.from_numpy(codes).cuda(), None if ids is None else torch.from_numpy(ids).cuda()
+    image = build(c, d_codes, d_ids, T, chunk_begin, c.index_build_device_bytes(N, T, chunk_begin)[0])
+    need, stats = c.index_device_bytes(), c.index_stats()
+    want_codes = codes if order is None else codes[:, order]
+    check_image(c, image, np.ascontiguousarray(want_codes), ids)
+    general = build(c, d_codes, d_ids, T, chunk_begin, need)     # below the bound: every array's place checked on the host
+    assert c.index_device_bytes() == need and c.index_stats() == stats
+    assert torch.equal(image[:need], general)
+    assert not image[need:].any()                                # nothing behind the index is written
+
+
+def clustered(rng, N, M, K):
+    codes = rng.integers(0, K, size=(N, M)).astype(np.uint8)
+    codes[:, : (M + 1) // 2] //= max(1, K // 6)
+    again = rng.integers(0, N, N // 4)
+    codes[again] = codes[rng.integers(0, N, N // 4)]
+    return codes
+
+
+@pytest.mark.parametrize("N", [1, 2, 8, 9, 63, 64, 65, 1023, 1025, 4095, 4096, 4097, 5119, 8191, 8193, 70001])
+def test_sizes(N):
+    say("build chain, sizes: N", N)
+    rng = np.random.default_rng(N)
+    compare(clustered(rng, N, 8, 256), T=2)
+    compare(clustered(rng, N, 8, 256), rng.permutation(3 * N).astype(np.int32)[:N], T=1)
+
+
+@pytest.mark.parametrize("M,T,chunk_begin", [
+    (1, 1, None), (2, 2, None), (3, 1, None), (4, 1, None), (4, 2, None), (4, 4, None),       # keys of one word
+    (5, 1, None), (7, 2, [0, 1, 7]), (8, 1, None), (8, 4, None), (8, 8, None), (8, 3, [0, 5, 6, 8]),   # two words
+    (9, 1, None), (11, 2, [0, 9, 11]), (12, 3, None), (16, 1, None), (16, 2, None), (16, 4, None), (16, 16, None), (16, 2, [0, 1, 16]),
+])
+@pytest.mark.parametrize("with_ids", [False, True])
+def test_shapes(M, T, chunk_begin, with_ids):
+    say("build chain, shapes: M", M, "T", T, chunk_begin, "ids", with_ids)
+    rng = np.random.default_rng(100 * M + T)
+    N, K = 20011, 200
+    codes = clustered(rng, N, M, K)
+    ids = np.sort(rng.integers(0, 50, N).astype(np.int32) * 1000)[::-1].copy() if with_ids else None   # equal ids: positions decide
+    compare(codes, ids, T, chunk_begin, K=K, order=list(rng.permutation(M)) if M in (7, 12) else None)
+
+
+@pytest.mark.parametrize("kind", ["equal", "sorted", "descending", "two", "last_byte"])
+def test_orders_and_ties(kind):
+    say("build chain, input", kind)
+    rng = np.random.default_rng(3)
+    N, M = 50003, 8
+    codes = rng.integers(0, 256, size=(N, M)).astype(np.uint8)
+    if kind == "equal":
+        codes[:] = 7                                             # one encoding in every bucket
+    elif kind == "two":
+        codes[:] = 255
+        codes[N // 3] = 0
+    elif kind == "last_byte":
+        codes[:, :-1] = 255                                      # keys that differ in the last byte only, the largest among them
+    else:
+        codes = codes[np.lexsort(codes.T[::-1])]
+        if kind == "descending":
+            codes = codes[::-1].copy()
+    compare(codes, T=2)
+    compare(codes, T=1)
+
+
+def mix64(z):
+    m = (1 << 64) - 1
+    z = (z + 0x9E3779B97F4A7C15) & m
+    z = ((z ^ (z >> 30)) * 0xBF58476D1CE4E5B9) & m
+    z = ((z ^ (z >> 27)) * 0x94D049BB133111EB) & m
+    return z ^ (z >> 31)
+
+
+def test_bucket_overrun():
+    say("build chain: samples that say nothing about the rest, so that one bucket takes nearly all")
+    rng = np.random.default_rng(9)
+    N, M = 40000, 8
+    codes = rng.integers(1, 256, size=(N, M)).astype(np.uint8)
+    s = np.arange(N >> 7)
+    codes[s * 128 + np.array([mix64(0x2545F4914F6CDD1D ^ int(i)) & 127 for i in s])] = 0
+    compare(codes, T=2)
+
+
+def test_wide_buckets():
+    say("build chain: more than two million vectors")
+    rng = np.random.default_rng(12)
+    N = (1 << 21) + 4099
+    compare(clustered(rng, N, 8, 256), T=2, sample_min=32768)
