@@ -452,19 +452,48 @@ int put_quantiser(etf_ctx *ctx, char *img)
     return ETF_OK;
 }
 
+// The quantiser's tables in pinned memory, laid out as at the start of an image, behind room for a build's counts: the
+// chain reads them from there and its last one writes the counts, without a copy in between (four
+// pageable copies and one of the counts took 75 us of a build).  Laid out again when the tables have changed; no build
+// is in flight then, every one waits for its kernels.
+int stage_tables(etf_ctx *ctx)
+{
+    const DevLayout &L = ctx->lay;
+    const int64_t head = al256(sizeof(BuildScal)), bytes = head + L.codes;   // the tables end where the codes start
+    if (ctx->build_stage_gen == ctx->tables_gen) return ETF_OK;
+    if (ctx->build_stage_bytes < bytes) {
+        if (ctx->build_stage) (void)hipHostFree(ctx->build_stage);
+        ctx->build_stage = nullptr;
+        ctx->build_stage_bytes = 0;
+        HIP_TRY(ctx, hipHostMalloc(&ctx->build_stage, (size_t)bytes, 0));
+        ctx->build_stage_bytes = bytes;
+    }
+    char *to = (char *)ctx->build_stage + head;
+    std::memset(to, 0, (size_t)L.codes);
+    auto put = [&](int64_t off, const std::vector<float> &v) {
+        if (!v.empty()) std::memcpy(to + off, v.data(), v.size() * 4);
+    };
+    put(L.codebooks, ctx->codebooks);
+    put(L.cb_centered, ctx->cb_centered);
+    put(L.cb_norm, ctx->cb_norm);
+    put(L.cb_mean, ctx->cb_mean);
+    ctx->build_stage_gen = ctx->tables_gen;
+    return ETF_OK;
+}
+
 // ---- the chain of etf_build_kernels.hip.h ------------------------------------------------------------------------
 
 // Where its arrays lie in the workspace.  ok: the chain is built for this many vectors.
 struct ChainPlan {
     bool ok = false;
     int KW = 0, KT = 0, wshift = 0, nt = 0;
-    uint32_t cap = 0, buckets = 0, samples = 0;
+    uint32_t cap = 0, buckets = 0, samples = 0, bstride = 0;
     int lvl_tiles = 0;
     int64_t S0 = 0;                                          // most draws of the threshold sample
-    int64_t slab, slab_t, smp, smp_t, zero, zero_words, nh, nh0, first, last, nh_t, nh0_t, first_t, last_t, faults, enc_of_rank, leaf,
+    int64_t grouped, sorted, bounds, bounds_t, smp, smp_t, zero, zero_words, count, count_t, nh, nh0, first, last, nh_t, nh0_t, first_t, last_t, faults, enc_of_rank, leaf,
         dk, draw, kept, tile_cnt, total = 0;
-    int64_t rank, count, rank_t, count_t;                    // words from `zero` on
-    int64_t slab_stride, smp_stride, rank_stride, bucket_stride, key_stride;  // words between two trees
+    int64_t rank, rank_t;                                    // words from `zero` on
+    int64_t elem_stride, bounds_stride, smp_stride, rank_stride, bucket_stride, key_stride;  // words between two trees
 };
 
 inline int key_words(int D) { return D <= 4 ? 1 : D <= 8 ? 2 : 4; }
@@ -476,9 +505,9 @@ ChainPlan plan_chain(const etf_ctx *ctx, int64_t N, int T, const std::vector<int
     for (int t = 0; t < T; ++t) Dmax = std::max(Dmax, cb[t + 1] - cb[t]);
     P.KW = key_words(ctx->M);
     P.KT = key_words(Dmax);
-    // Up to 2 M vectors a bucket of 4096 (of 3 to 6 words each) lets three workgroups share a CU; beyond, the samples'
-    // ranks (quadratic in their number) are the larger part, and elements of at most 4 words go in buckets of 8192.
-    // The limits: the splitters and counts of one level of buckets in LDS (5120 of 7 words: 143 KB), and the ranks.
+    // Beyond 2 M vectors the samples' ranks (quadratic in their number) are the larger part, and elements of at most 4
+    // words go in buckets of twice the size.  The limits: the splitters and counts of one level of buckets in LDS (5120
+    // of 7 words: 143 KB), and the ranks.
     const bool wide = P.KW < 4 && N > ((int64_t)1 << 21);
     if (N > (P.KW < 4 ? (int64_t)1 << 23 : (int64_t)5 << 20)) return P;
     P.nt = wide ? 1024 : 512;
@@ -496,21 +525,27 @@ ChainPlan plan_chain(const etf_ctx *ctx, int64_t N, int T, const std::vector<int
         off = al256(off + words * 4);
         return o;
     };
-    P.slab_stride = B * P.cap * WT;
+    const int64_t tiles = (N + CLS_TILE - 1) / CLS_TILE, bstride = (B + 2) & ~(int64_t)1;
+    P.bstride = (uint32_t)bstride;
+    P.elem_stride = N * WT;
+    P.bounds_stride = tiles * bstride;
     P.smp_stride = S * WT;
     P.rank_stride = S;
     P.bucket_stride = B;
     P.key_stride = B * P.KT;
-    // the slabs of the trees lie over the vectors', which nothing reads any more by then
-    P.slab = P.slab_t = take(std::max(B * P.cap * W, P.slab_stride * (T - 1)));
+    // the trees' elements lie over the vectors', which nothing reads any more by then
+    P.grouped = take(std::max(N * W, P.elem_stride * (T - 1)));
+    P.sorted = take(std::max(N * W, P.elem_stride * (T - 1)));
+    P.bounds = take(P.bounds_stride / 2);
+    P.bounds_t = take(P.bounds_stride / 2 * (T - 1));
     P.smp = take(S * W);
     P.smp_t = take(P.smp_stride * (T - 1));
     P.rank = sizeof(BuildScal) / 4;
-    P.count = P.rank + S;
-    P.rank_t = P.count + B;
-    P.count_t = P.rank_t + S * (T - 1);
-    P.zero_words = P.count_t + B * (T - 1);
+    P.rank_t = P.rank + S;
+    P.zero_words = P.rank_t + S * (T - 1);
     P.zero = take(P.zero_words);
+    P.count = take(B);
+    P.count_t = take(B * (T - 1));
     P.nh = take(B);
     P.nh0 = take(B);
     P.first = take(B * P.KW);
@@ -533,7 +568,7 @@ ChainPlan plan_chain(const etf_ctx *ctx, int64_t N, int T, const std::vector<int
 
 int lds_limit(etf_ctx *ctx, const void *kernel, size_t bytes)
 {
-    if (bytes <= 65536) return ETF_OK;
+    if (bytes <= 49152) return ETF_OK;
     HIP_TRY(ctx, hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes));
     return ETF_OK;
 }
@@ -541,12 +576,15 @@ int lds_limit(etf_ctx *ctx, const void *kernel, size_t bytes)
 template <int KW, int TW, int KT, int NT> int launch_chain(etf_ctx *ctx, const ChainPlan &P, const ChainArgs &a)
 {
     hipStream_t st = (hipStream_t)ctx->stream;
-    constexpr size_t sort_lds = (size_t)(KW + TW) * (NT * 8 + NT / 4) * 4, sort_lds_t = (size_t)(KT + 1) * (NT * 8 + NT / 4) * 4;
+    // a sort's threads: 512 where three workgroups' elements fit a CU's LDS, else 1024
+    constexpr uint32_t CAP = NT * 8;
+    constexpr int SNT = KW == 4 || NT == 1024 ? 1024 : 512;
+    constexpr size_t sort_lds = (size_t)(KW + TW) * CAP * 4, sort_lds_t = (size_t)(KT + 1) * CAP * 4;
     const size_t cls_lds = (size_t)(KW + TW + 1) * P.buckets * 4, cls_lds_t = (size_t)(KT + 2) * P.buckets * 4;
     auto cls = k_chain_classify<KW, TW>;
-    auto srt = k_chain_sort<KW, TW, NT>;
+    auto srt = k_chain_sort<KW, TW, SNT, CAP>;
     auto cls_t = k_chain_classify_trees<KW, KT>;
-    auto srt_t = k_chain_sort_trees<KW, KT, NT>;
+    auto srt_t = k_chain_sort_trees<KW, KT, SNT, CAP>;
     int rc;
     if ((rc = lds_limit(ctx, (const void *)cls, cls_lds)) || (rc = lds_limit(ctx, (const void *)srt, sort_lds)) ||
         (rc = lds_limit(ctx, (const void *)cls_t, cls_lds_t)) || (rc = lds_limit(ctx, (const void *)srt_t, sort_lds_t)))
@@ -556,30 +594,30 @@ template <int KW, int TW, int KT, int NT> int launch_chain(etf_ctx *ctx, const C
     const unsigned rank_blocks = per(P.samples, 64) * RANK_PARTS, lvl = (unsigned)P.lvl_tiles;
     // a workgroup of the draws also takes a slice of the id ranges, one of the samples a slice of the flat scan's
     const unsigned draw_blocks = std::max(per(P.S0, DRAW_TILE), std::min(256u, per(N, 2048)));
-    const unsigned place_blocks = std::max(per(P.S0, DRAW_TILE), per(a.n_sample_pos, NT));
+    const unsigned place_blocks = std::max(per(P.S0, DRAW_TILE), per(a.n_sample_pos, SNT));
     hipLaunchKernelGGL((k_chain_prep<KW, TW>), dim3(per(N, PREP_NT)), dim3(PREP_NT), 0, st, a);
     HIP_TRY(ctx, hipGetLastError());
     if (rank_blocks) hipLaunchKernelGGL((k_chain_rank<KW, TW>), dim3(rank_blocks), dim3(PREP_NT), 0, st, a);
     HIP_TRY(ctx, hipGetLastError());
     hipLaunchKernelGGL(cls, dim3(per(N, CLS_TILE)), dim3(CLS_NT), cls_lds, st, a, P.buckets);
     HIP_TRY(ctx, hipGetLastError());
-    hipLaunchKernelGGL(srt, dim3(B), dim3(NT), sort_lds, st, a);
+    hipLaunchKernelGGL(srt, dim3((B + 7) / 8 * 8), dim3(SNT), sort_lds, st, a);
     HIP_TRY(ctx, hipGetLastError());
     hipLaunchKernelGGL((k_chain_encodings<KW, TW, KT, NT>), dim3(B), dim3(NT), 0, st, a);
     HIP_TRY(ctx, hipGetLastError());
-    hipLaunchKernelGGL((k_chain_mid<KT>), dim3(std::max({rank_blocks, draw_blocks, lvl}), T + 1), dim3(PREP_NT), 0, st, a, draw_blocks);
+    hipLaunchKernelGGL((k_chain_mid<KT>), dim3(T > 1 ? std::max(rank_blocks, draw_blocks) : draw_blocks, T + 1), dim3(PREP_NT), 0, st, a, draw_blocks);
     HIP_TRY(ctx, hipGetLastError());
     hipLaunchKernelGGL(cls_t, dim3(T > 1 ? per(N, CLS_TILE) : 1u, T), dim3(CLS_NT), T > 1 ? cls_lds_t : 0, st, a, P.buckets);
     HIP_TRY(ctx, hipGetLastError());
-    hipLaunchKernelGGL(srt_t, dim3(T > 1 ? std::max(B, place_blocks) : place_blocks, T), dim3(NT), T > 1 ? sort_lds_t : 0, st, a, place_blocks);
+    hipLaunchKernelGGL(srt_t, dim3(T > 1 ? std::max((B + 7) / 8 * 8, place_blocks) : place_blocks, T), dim3(SNT), T > 1 ? sort_lds_t : 0, st, a, place_blocks);
     HIP_TRY(ctx, hipGetLastError());
     if (T > 1) {
         hipLaunchKernelGGL((k_chain_leaves<KT, NT>), dim3(B, T - 1), dim3(NT), 0, st, a);
         HIP_TRY(ctx, hipGetLastError());
-        hipLaunchKernelGGL((k_chain_levels<KT>), dim3(lvl, T - 1), dim3(PREP_NT), 0, st, a);
-        HIP_TRY(ctx, hipGetLastError());
     }
-    hipLaunchKernelGGL((k_chain_write<KW, KT>), dim3(lvl, T + 1), dim3(PREP_NT), 0, st, a);
+    hipLaunchKernelGGL((k_chain_levels<KT>), dim3(lvl, T), dim3(LVL_NT), 0, st, a);
+    HIP_TRY(ctx, hipGetLastError());
+    hipLaunchKernelGGL((k_chain_write<KW, KT>), dim3(lvl, T + 1), dim3(LVL_NT), 0, st, a);
     HIP_TRY(ctx, hipGetLastError());
     return ETF_OK;
 }
@@ -630,13 +668,23 @@ int build_chain(etf_ctx *ctx, const uint8_t *codes, int64_t N, const int32_t *id
     a.A_pos = spread_multiplier(P.S0);
     a.B_pos = (uint64_t)(P.S0 / 3);
     a.rstride0 = ix.rstride0;
+    int rc;
+    if (stage_tables(ctx) != ETF_OK) {   // no pinned memory: the general path does without
+        (void)hipGetLastError();
+        again = true;
+        return ETF_OK;
+    }
+    a.scal_host = (BuildScal *)ctx->build_stage;
+    a.tables = (const uint32_t *)((const char *)ctx->build_stage + al256(sizeof(BuildScal)));
+    a.table_words = (uint32_t)(L.codes / 4);
     a.scal = (BuildScal *)(ws + P.zero);
     a.zero = at(P.zero);
     a.zero_words = (uint32_t)P.zero_words;
     a.faults = at(P.faults);
-    a.s0 = {at(P.slab), at(P.smp), a.zero + P.rank, a.zero + P.count, at(P.nh), at(P.nh0), at(P.first), at(P.last)};
-    a.st = {at(P.slab_t), at(P.smp_t), a.zero + P.rank_t, a.zero + P.count_t, at(P.nh_t), at(P.nh0_t), at(P.first_t), at(P.last_t)};
-    a.slab_stride = P.slab_stride; a.smp_stride = P.smp_stride; a.rank_stride = P.rank_stride;
+    a.s0 = {at(P.grouped), at(P.sorted), (uint16_t *)at(P.bounds), at(P.smp), a.zero + P.rank, at(P.count), at(P.nh), at(P.nh0), at(P.first), at(P.last)};
+    a.st = {at(P.grouped), at(P.sorted), (uint16_t *)at(P.bounds_t), at(P.smp_t), a.zero + P.rank_t, at(P.count_t), at(P.nh_t), at(P.nh0_t), at(P.first_t), at(P.last_t)};
+    a.bstride = P.bstride;
+    a.elem_stride = P.elem_stride; a.bounds_stride = P.bounds_stride; a.smp_stride = P.smp_stride; a.rank_stride = P.rank_stride;
     a.bucket_stride = P.bucket_stride; a.key_stride = P.key_stride;
     a.enc_of_rank = at(P.enc_of_rank);
     a.leaf = at(P.leaf);
@@ -646,16 +694,12 @@ int build_chain(etf_ctx *ctx, const uint8_t *codes, int64_t N, const int32_t *id
     a.tile_cnt = at(P.tile_cnt);
     a.lvl_tiles = P.lvl_tiles;
     a.NK = N;
-    int rc;
     if (ids) rc = P.KW == 1 ? launch_chain_kt<1, 2>(ctx, P, a) : P.KW == 2 ? launch_chain_kt<2, 2>(ctx, P, a) : launch_chain_kt<4, 2>(ctx, P, a);
     else rc = P.KW == 1 ? launch_chain_kt<1, 1>(ctx, P, a) : P.KW == 2 ? launch_chain_kt<2, 1>(ctx, P, a) : launch_chain_kt<4, 1>(ctx, P, a);
     if (rc) return rc;
-    if ((rc = put_quantiser(ctx, img))) return rc;   // the host's copies of the tables while the kernels run
-    static_assert(sizeof(ctx->build_scal) == sizeof(BuildScal), "landing place of the counts");
-    HIP_TRY(ctx, hipMemcpyAsync(ctx->build_scal, a.scal, sizeof(BuildScal), hipMemcpyDeviceToHost, st));
     HIP_TRY(ctx, hipStreamSynchronize(st));
     BuildScal h;
-    std::memcpy(&h, ctx->build_scal, sizeof(h));
+    std::memcpy(&h, a.scal_host, sizeof(h));
     again = h.overflow != 0;
     if (again) return ETF_OK;
     if (h.faults & 1u) return fail(ctx, ETF_EINVAL, "a code byte is >= K=%d", ctx->K);

@@ -6,18 +6,18 @@
 // highest byte, the tail the position (below the id where ids are given), so that no two elements are equal and
 // repeated encodings spread over buckets like any others.  One element of each stratum of 128 positions is a sample; a
 // sample's rank is counted against all others (k_prep_rank), every eighth in rank is a splitter, an element finds its
-// bucket by bisection among the splitters and a place in the bucket's slab by an atomic of its workgroup
-// (classify), and a workgroup sorts a bucket in LDS (bucket_sort).  A bucket expects 1024 elements and holds 4096: more
-// than that needs fewer than eight of the 32 samples expected there, about 3e-7 per bucket.  Where it happens all the
-// same (the places of the samples are a fixed function, an input can be made for it) the flag `overflow` stops the chain
-// and the host builds by the general path.
+// bucket by bisection among the splitters, a workgroup writes its 4096 elements grouped by bucket with the groups'
+// bounds (classify), and a workgroup per bucket gathers its groups and sorts them in LDS (bucket_sort): no atomics on
+// memory and no slack between buckets.  A bucket expects 1024 elements and LDS holds 4096: more than that needs fewer
+// than eight of the 32 samples expected there, about 3e-7 per bucket.  Where it happens all the same (the places of the samples are a fixed function, an input can be made for it)
+// the flag `overflow` stops the chain and the host builds by the general path.
 //
 // Why not a radix sort: eight passes over 8-byte keys (or the twenty launches of a merge sort at these sizes) are bound
 // by their launches and their passes over memory; this is four launches and three passes.
 //
 // A million vectors of 8 chunks in two trees: 1180 us with device-wide library sorts and scans and eleven counts that
-// came back to the host between 90 launches, 365 by the chain (10 000: 627 -> 209, five million: 3255 -> 1322; a
-// million of 16 chunks in four trees: 2764 -> 623).
+// came back to the host between 90 launches, 266 by the chain (10 000: 627 -> 136, five million: 3255 -> 1292; a
+// million of 16 chunks in four trees: 2764 -> 578).
 
 // ---- keys and elements ------------------------------------------------------------------------------------------
 
@@ -133,11 +133,12 @@ template <int KW> __device__ __forceinline__ void row_of_key(uint8_t *rows, int6
 
 // ---- arguments --------------------------------------------------------------------------------------------------
 
-constexpr int PREP_NT = 256;   // threads of the kernels that go over rows, samples, draws and tree levels
-constexpr int CLS_NT = 512;    // ... that deal elements into buckets
-constexpr int CLS_TILE = 2048; // elements a workgroup deals
+constexpr int PREP_NT = 256;   // threads of the kernels that go over rows, samples and draws
+constexpr int CLS_NT = 1024;   // ... that deal elements into buckets
+constexpr int CLS_TILE = 4096; // elements a workgroup deals
 constexpr int RANK_PARTS = 8;  // workgroups that share the comparisons of 64 samples
-constexpr int DRAW_TILE = 1024;
+constexpr int DRAW_TILE = 256;
+constexpr int LVL_NT = 1024;   // threads of the level kernels
 constexpr int LVL_TILE = 4096; // sub-encodings of a workgroup of the level kernels
 constexpr int LVL_CH = LVL_TILE / 64;
 constexpr int CATS = 2 * ETF_MAX_M;  // counters of a tile: internal nodes per level, leaves per level
@@ -148,10 +149,13 @@ struct BuildScal {
     uint32_t U[ETF_MAX_M], nI[ETF_MAX_M], nL[ETF_MAX_M];
 };
 
-// Arrays of one sort: slab[bucket][cap] elements, samples, their ranks; per bucket the elements in it, how many
-// of them differ from their predecessor in the bucket (all chunks / tree 0's chunks), and the first and last key.
+// Arrays of one sort: the elements grouped by bucket within each tile, bounds[tile][bucket] of the groups, the elements
+// in order, samples, their ranks; per bucket the elements in it, how many of them differ from their predecessor in the
+// bucket (all chunks / tree 0's chunks), and the first and last key.
 struct SortBufs {
-    uint32_t *slab, *smp, *rank, *count, *nh, *nh0, *first, *last;
+    uint32_t *grouped, *sorted;
+    uint16_t *bounds;
+    uint32_t *smp, *rank, *count, *nh, *nh0, *first, *last;
 };
 
 struct ChainArgs {
@@ -164,6 +168,7 @@ struct ChainArgs {
     uint8_t cb[ETF_MAX_M + 1];
     int wshift;                       // log2 of the positions per sample
     uint32_t cap;                     // elements a bucket holds
+    uint32_t bstride;                 // bounds of a tile
     int64_t sample_min, sample_scale; // the options behind sample_size
     uint64_t seed;
     // the image: arrays whose places do not depend on counts
@@ -172,13 +177,16 @@ struct ChainArgs {
     int64_t n_sample_pos;
     uint64_t A_pos, B_pos;
     int rstride0;
+    const uint32_t *tables;           // the quantiser's tables as they stand at the image's start, in host memory
+    uint32_t table_words;
+    BuildScal *scal_host;             // where the counts go in the end, in host memory
     // workspace
     BuildScal *scal;
-    uint32_t *zero;                   // cleared by the first kernel: scal, the samples' ranks, the buckets' counts
+    uint32_t *zero;                   // cleared by the first kernel: scal, the samples' ranks
     uint32_t zero_words;
     uint32_t *faults;                 // [workgroups of the first kernel]
     SortBufs s0, st;                  // the vectors; tree 1 (tree t: t - 1 strides further)
-    int64_t slab_stride, smp_stride, rank_stride, bucket_stride, key_stride;
+    int64_t elem_stride, bounds_stride, smp_stride, rank_stride, bucket_stride, key_stride;
     uint32_t *enc_of_rank;            // [N] distinct encoding of the i-th vector in sorted order
     uint32_t *leaf;                   // [T][N] leaf of every distinct encoding
     uint32_t *dk;                     // [T][N] KT words: the distinct sub-encodings of every tree
@@ -192,7 +200,9 @@ __device__ __forceinline__ SortBufs tree_bufs(const ChainArgs &a, int t)
 {
     SortBufs s = a.st;
     const int64_t i = t - 1;
-    s.slab += i * a.slab_stride;
+    s.grouped += i * a.elem_stride;
+    s.sorted += i * a.elem_stride;
+    s.bounds += i * a.bounds_stride;
     s.smp += i * a.smp_stride;
     s.rank += i * a.rank_stride;
     s.count += i * a.bucket_stride;
@@ -203,8 +213,9 @@ __device__ __forceinline__ SortBufs tree_bufs(const ChainArgs &a, int t)
     return s;
 }
 
-__host__ __device__ inline uint32_t n_buckets(uint32_t n, uint32_t cap, int wshift) { return n <= cap ? 1u : n >> (wshift + 3); }
-__host__ __device__ inline uint32_t n_samples(uint32_t n, uint32_t cap, int wshift) { return n <= cap ? 0u : n >> wshift; }
+// (a bucket expects a quarter of what it can hold)
+__host__ __device__ inline uint32_t n_buckets(uint32_t n, uint32_t cap, int wshift) { return n <= cap / 4 ? 1u : n >> (wshift + 3); }
+__host__ __device__ inline uint32_t n_samples(uint32_t n, uint32_t cap, int wshift) { return n <= cap / 4 ? 0u : n >> wshift; }
 
 // position i of n is a sample (its number is i >> wshift)
 __device__ __forceinline__ bool is_sample(uint32_t i, uint32_t n, uint32_t cap, int wshift)
@@ -366,30 +377,42 @@ __global__ void __launch_bounds__(PREP_NT) k_chain_rank(ChainArgs a)
 
 // ---- elements into buckets ---------------------------------------------------------------------------------------
 // LDS: the splitters as W arrays of `stride` words, then a count per bucket.  Bound by latency: the bisection's ten to
-// twelve dependent reads, then one atomic per bucket and workgroup; four elements per thread in flight.
+// twelve dependent reads, four elements per thread in flight.  (Slabs that the workgroups filled through an atomic per
+// bucket and workgroup: 40 us for a million elements, most of it the atomics.)
 // elem(i): the i-th of n elements.
 template <int KW, int TW, typename F>
-__device__ void classify(const SortBufs &s, uint32_t n, uint32_t cap, int wshift, uint32_t stride, BuildScal *scal, uint32_t *lds, F elem)
+__device__ void classify(const SortBufs &s, uint32_t n, uint32_t cap, int wshift, uint32_t stride, uint32_t bstride, uint32_t *lds, F elem)
 {
     constexpr int W = KW + TW, PER = CLS_TILE / CLS_NT;
+    __shared__ uint32_t wave_sum[CLS_NT / 64];
     const uint32_t B = n_buckets(n, cap, wshift), S = n_samples(n, cap, wshift);
+    const uint32_t t = threadIdx.x, lane = t & 63, wave = t >> 6;
     uint32_t *cnt = lds + W * stride;
-    for (uint32_t b = threadIdx.x; b < B; b += CLS_NT) cnt[b] = 0;
-    for (uint32_t i = threadIdx.x; i < S; i += CLS_NT) {
-        const uint32_t r = s.rank[i];
-        if ((r & 7u) == 0 && r > 0 && (r >> 3) < B)
-#pragma unroll
-            for (int w = 0; w < W; ++w) lds[w * stride + (r >> 3) - 1] = s.smp[(int64_t)i * W + w];
-    }
-    __syncthreads();
     Elem<KW, TW> e[PER];
     uint32_t b[PER], slot[PER];
-    const uint32_t i0 = blockIdx.x * CLS_TILE + threadIdx.x;
+    const uint32_t i0 = blockIdx.x * CLS_TILE + t;
 #pragma unroll
     for (int q = 0; q < PER; ++q) {
         e[q] = elem(min(i0 + q * CLS_NT, n - 1));
         b[q] = 0;
     }
+    for (uint32_t x = t; x < B; x += CLS_NT) cnt[x] = 0;
+    for (uint32_t i = t; i < S; i += 4 * CLS_NT) {   // (four samples requested at once, wanted or not)
+        uint32_t r[4], w[4][W];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const uint32_t j = min(i + q * CLS_NT, S - 1);
+            r[q] = s.rank[j];
+#pragma unroll
+            for (int x = 0; x < W; ++x) w[q][x] = s.smp[(int64_t)j * W + x];
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            if ((r[q] & 7u) == 0 && r[q] > 0 && (r[q] >> 3) < B)
+#pragma unroll
+                for (int x = 0; x < W; ++x) lds[x * stride + (r[q] >> 3) - 1] = w[q][x];
+    }
+    __syncthreads();
     uint32_t step = 1;
     while (step * 2 <= B - 1) step *= 2;
     if (B > 1)
@@ -406,20 +429,32 @@ __device__ void classify(const SortBufs &s, uint32_t n, uint32_t cap, int wshift
 #pragma unroll
     for (int q = 0; q < PER; ++q) slot[q] = i0 + q * CLS_NT < n ? atomicAdd(&cnt[b[q]], 1u) : 0u;
     __syncthreads();
-    for (uint32_t x = threadIdx.x; x < B; x += CLS_NT) {
-        const uint32_t c = cnt[x];
-        if (c) {
-            const uint32_t base = atomicAdd(&s.count[x], c);
-            if (base + c > cap) scal->overflow = 1;
-            cnt[x] = base;
-        }
+    // counts to bounds: a thread sums `per` buckets, then waves and workgroup
+    const uint32_t per = (B + CLS_NT - 1) / CLS_NT, b0 = min(t * per, B), b1 = min(b0 + per, B);
+    uint32_t own = 0;
+    for (uint32_t x = b0; x < b1; ++x) own += cnt[x];
+    uint32_t incl = own;
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t y = __shfl_up(incl, o);
+        if ((int)lane >= o) incl += y;
     }
+    if (lane == 63) wave_sum[wave] = incl;
+    __syncthreads();
+    uint32_t at = incl - own;
+    for (uint32_t w = 0; w < wave; ++w) at += wave_sum[w];
+    uint16_t *bounds = s.bounds + (int64_t)blockIdx.x * bstride;
+    for (uint32_t x = b0; x < b1; ++x) {
+        const uint32_t c = cnt[x];
+        cnt[x] = at;
+        bounds[x] = (uint16_t)at;
+        at += c;
+    }
+    if (t == CLS_NT - 1) bounds[B] = (uint16_t)at;
     __syncthreads();
 #pragma unroll
-    for (int q = 0; q < PER; ++q) {
-        const uint32_t at = cnt[b[q]] + slot[q];
-        if (i0 + q * CLS_NT < n && at < cap) elem_store<KW, TW>(s.slab + ((int64_t)b[q] * cap + at) * W, e[q]);
-    }
+    for (int q = 0; q < PER; ++q)
+        if (i0 + q * CLS_NT < n)
+            elem_store<KW, TW>(s.grouped + ((int64_t)blockIdx.x * CLS_TILE + cnt[b[q]] + slot[q]) * W, e[q]);
 }
 
 template <int KW, int TW>
@@ -428,7 +463,7 @@ __global__ void __launch_bounds__(CLS_NT) k_chain_classify(ChainArgs a, uint32_t
     extern __shared__ uint32_t blds[];
     const uint8_t *rows = (const uint8_t *)(a.img + a.o_codes);
     const int32_t *ids = (const int32_t *)(a.img + a.o_ids_in);
-    classify<KW, TW>(a.s0, a.N, a.cap, a.wshift, stride, a.scal, blds, [&](uint32_t i) {
+    classify<KW, TW>(a.s0, a.N, a.cap, a.wshift, stride, a.bstride, blds, [&](uint32_t i) {
         Elem<KW, TW> e;
         e.key = key_of_row<KW>(rows, i, a.M, a.M == 4 * KW);
         e.tail = i;
@@ -438,19 +473,19 @@ __global__ void __launch_bounds__(CLS_NT) k_chain_classify(ChainArgs a, uint32_t
 }
 
 // ---- a bucket sorted in LDS --------------------------------------------------------------------------------------
-// A thread sorts eight elements in registers; then runs of equal length are merged pairwise, a thread finding the
-// start of its eight outputs by bisection along their diagonal and merging them one after the other: rounds of about
-// 2000 clocks, bound by the latency of dependent LDS reads, so several workgroups share a CU.  Words lie in W separate
-// arrays with one word of padding in 32 (eight consecutive elements per lane then meet at most two to a bank).
-// The sorted bucket goes back over its slab.
-__device__ __forceinline__ uint32_t padded(uint32_t i) { return i + (i >> 5); }
-
+// The workgroup gathers its group of every tile and sorts by sampling once more: every eighth element is a splitter,
+// elements are dealt into the parts between them, about eight to a part, and an element's rank in its part is counted
+// against all others there.  58 us for a million elements of 12 bytes, bound by latency (two dependent reads of memory,
+// some thirty of LDS, ten barriers: 50 000 clocks for a workgroup with two others on its CU) and comparisons: a third of
+// the issue slots.  (Merging sorted runs pairwise, eight rounds of twenty dependent reads each, took 51 us for a million elements;
+// with LDS for 2048 elements and the larger buckets in two halves 91, the halves of a single bucket one after the other.)
+// Words lie in W separate arrays.
 template <int KW, int TW> __device__ __forceinline__ Elem<KW, TW> lds_elem(const uint32_t *lds, uint32_t stride, uint32_t i)
 {
     constexpr int W = KW + TW;
     uint32_t w[W];
 #pragma unroll
-    for (int x = 0; x < W; ++x) w[x] = lds[x * stride + padded(i)];
+    for (int x = 0; x < W; ++x) w[x] = lds[x * stride + i];
     return elem_load<KW, TW>(w);
 }
 
@@ -460,95 +495,190 @@ template <int KW, int TW> __device__ __forceinline__ void lds_put(uint32_t *lds,
     uint32_t w[W];
     elem_store<KW, TW>(w, e);
 #pragma unroll
-    for (int x = 0; x < W; ++x) lds[x * stride + padded(i)] = w[x];
+    for (int x = 0; x < W; ++x) lds[x * stride + i] = w[x];
 }
 
-template <int KW, int TW> __device__ __forceinline__ void order2(Elem<KW, TW> &a, Elem<KW, TW> &b)
-{
-    const bool s = less(b, a);
-    const Elem<KW, TW> x = a;
-    a.key = s ? b.key : a.key;
-    a.tail = s ? b.tail : a.tail;
-    b.key = s ? x.key : b.key;
-    b.tail = s ? x.tail : b.tail;
-}
+// Workgroups go to the eight XCDs in turn: an XCD takes a stretch of the buckets, since neighbouring buckets' groups share
+// the lines of a tile (65 against 61 us for a million elements).
+__device__ __forceinline__ uint32_t bucket_of_block(uint32_t block, uint32_t B) { return (block & 7u) * ((B + 7) / 8) + (block >> 3); }
 
-template <int KW, int TW, int NT>
-__device__ void bucket_sort(const SortBufs &s, uint32_t bucket, int D0, uint32_t *lds)
+constexpr int MAX_SPLIT = 192;  // (with 256 the LDS of three workgroups of 4096 elements of three words is a little more than a CU has)
+
+template <int KW, int TW, int NT, uint32_t CAP>
+__device__ void bucket_sort(const SortBufs &s, uint32_t n, uint32_t bstride, uint32_t bucket, int D0, BuildScal *scal, uint32_t *lds)
 {
-    constexpr int W = KW + TW;
-    constexpr uint32_t CAP = NT * 8, STRIDE = CAP + CAP / 32;
-    __shared__ uint32_t heads[2];
+    constexpr int W = KW + TW, PER = CAP / NT;
+    __shared__ uint32_t heads[2], off_sum, wave_sum[NT / 64], rank[MAX_SPLIT], part_begin[MAX_SPLIT + 2];
+    __shared__ uint32_t split[W * MAX_SPLIT];
     using E = Elem<KW, TW>;
-    const uint32_t t = threadIdx.x, cnt = min(s.count[bucket], CAP);
-    uint32_t *slab = s.slab + (int64_t)bucket * CAP * W;
+    const uint32_t t = threadIdx.x, lane = t & 63, wave = t >> 6, tiles = (n + CLS_TILE - 1) / CLS_TILE;
     if (t < 2) heads[t] = 0;
-    E e[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        if (t * 8 + j < cnt) {
-            e[j] = elem_load<KW, TW>(slab + (int64_t)(t * 8 + j) * W);
-        } else {  // behind every element: positions are below 2^31
-            e[j].key = ~(Key<KW>)0;
-            e[j].tail = ~(decltype(e[j].tail))0;
-        }
+    if (t == 2) off_sum = 0;
+    for (uint32_t i = t; i < MAX_SPLIT + 2; i += NT) {
+        part_begin[i] = 0;
+        if (i < MAX_SPLIT) rank[i] = 0;
     }
-    // eight elements: Batcher's odd-even merge sort
-    constexpr int NETA[19] = {0, 2, 4, 6, 0, 1, 4, 5, 1, 5, 0, 1, 2, 3, 2, 3, 1, 3, 5};
-    constexpr int NETB[19] = {1, 3, 5, 7, 2, 3, 6, 7, 2, 6, 4, 5, 6, 7, 4, 5, 2, 4, 6};
-#pragma unroll
-    for (int x = 0; x < 19; ++x) order2(e[NETA[x]], e[NETB[x]]);
-    uint32_t run = 8;
-    for (; run < cnt; run *= 2) {  // every thread of the workgroup goes round the same number of times
-        const uint32_t live = (cnt + 2 * run - 1) / (2 * run) * (2 * run);  // the pairs of runs that hold elements
-        const bool on = t * 8 < live;
-        if (on)
-#pragma unroll
-            for (int j = 0; j < 8; ++j) lds_put(lds, STRIDE, t * 8 + j, e[j]);
-        __syncthreads();
-        if (on) {
-            const uint32_t a0 = t * 8 / (2 * run) * (2 * run), b0 = a0 + run, diag = t * 8 - a0;
-            uint32_t lo = diag > run ? diag - run : 0, hi = min(diag, run);
-            while (lo < hi) {
-                const uint32_t mid = (lo + hi) >> 1;
-                if (less(lds_elem<KW, TW>(lds, STRIDE, a0 + mid), lds_elem<KW, TW>(lds, STRIDE, b0 + diag - 1 - mid))) lo = mid + 1; else hi = mid;
-            }
-            uint32_t ia = lo, ib = diag - lo;
-            E x = lds_elem<KW, TW>(lds, STRIDE, a0 + min(ia, run - 1)), y = lds_elem<KW, TW>(lds, STRIDE, b0 + min(ib, run - 1));
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const bool from_a = ib >= run || (ia < run && less(x, y));
-                e[j].key = from_a ? x.key : y.key;
-                e[j].tail = from_a ? x.tail : y.tail;
-                if (from_a) ++ia; else ++ib;
-                const uint32_t at = from_a ? a0 + min(ia, run - 1) : b0 + min(ib, run - 1);
-                const E z = lds_elem<KW, TW>(lds, STRIDE, at);
-                if (from_a) x = z; else y = z;
-            }
-        }
-        __syncthreads();
-    }
-    if (t * 8 < cnt)
-#pragma unroll
-        for (int j = 0; j < 8; ++j) lds_put(lds, STRIDE, t * 8 + j, e[j]);
     __syncthreads();
+    // Where every tile's group starts in the bucket (the elements' LDS is still free); what the tiles hold before the
+    // bucket, summed, is its place in the whole order.
+    uint32_t *group_at = lds;
+    uint16_t *group_from = (uint16_t *)(lds + tiles);
+    uint32_t cnt = 0, before = 0;
+    for (uint32_t t0 = 0; t0 < tiles; t0 += NT) {
+        const uint32_t tile = t0 + t;
+        uint32_t lo = 0, hi = 0;
+        if (tile < tiles) {
+            lo = s.bounds[(int64_t)tile * bstride + bucket];
+            hi = s.bounds[(int64_t)tile * bstride + bucket + 1];
+        }
+        before += lo;
+        uint32_t incl = hi - lo;
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint32_t y = __shfl_up(incl, o);
+            if ((int)lane >= o) incl += y;
+        }
+        if (lane == 63) wave_sum[wave] = incl;
+        __syncthreads();
+        uint32_t at = cnt + incl - (hi - lo);
+        for (uint32_t w = 0; w < NT / 64; ++w) {
+            if (w < wave) at += wave_sum[w];
+            cnt += wave_sum[w];
+        }
+        __syncthreads();
+        if (tile < tiles) {
+            group_at[tile] = at;
+            group_from[tile] = (uint16_t)lo;
+        }
+    }
+    for (int o = 32; o > 0; o >>= 1) before += __shfl_xor(before, o);
+    if (lane == 0 && before) atomicAdd(&off_sum, before);
+    if (t == 0) s.count[bucket] = cnt;
+    __syncthreads();
+    if (cnt > CAP) {
+        if (t == 0) scal->overflow = 1;
+        return;
+    }
+    if (cnt == 0) {
+        if (t == 0) s.nh[bucket] = s.nh0[bucket] = 0;
+        return;
+    }
+    // an element's tile by bisection: the last one that starts at or before it
+    E e[PER];
+    {
+        uint32_t tl[PER], step = 1;
+        while (step * 2 <= tiles - 1) step *= 2;
+#pragma unroll
+        for (int q = 0; q < PER; ++q) tl[q] = 0;
+        for (; step > 0; step >>= 1)
+#pragma unroll
+            for (int q = 0; q < PER; ++q)
+                if (q * NT < cnt) {
+                    const uint32_t at = tl[q] + step;
+                    if (at < tiles && group_at[at] <= min(q * NT + t, cnt - 1)) tl[q] = at;
+                }
+#pragma unroll
+        for (int q = 0; q < PER; ++q)
+            if (q * NT < cnt) {
+                const uint32_t at = tl[q] * CLS_TILE + group_from[tl[q]] + min(q * NT + t, cnt - 1) - group_at[tl[q]];
+                e[q] = elem_load<KW, TW>(s.grouped + (int64_t)at * W);
+            }
+    }
+    __syncthreads();
+    // splitters: elements 0, stride, 2 stride, ... in order of their rank
+    const uint32_t ns = min(max(cnt / 8, 1u), (uint32_t)MAX_SPLIT), stride = cnt / ns, groups = (ns + 63) / 64, slices = NT / 64 / groups;
+#pragma unroll
+    for (int q = 0; q < PER; ++q)
+        if (q * NT + t < cnt) {
+            const uint32_t j = (q * NT + t) / stride;
+            if (j < ns && j * stride == q * NT + t) lds_put(lds, MAX_SPLIT, j, e[q]);
+        }
+    __syncthreads();
+    {
+        const uint32_t i = (wave % groups) * 64 + lane, slice = wave / groups;
+        if (slice < slices) {
+            const E me = lds_elem<KW, TW>(lds, MAX_SPLIT, min(i, ns - 1));
+            uint32_t r = 0;
+#pragma unroll 8
+            for (uint32_t j = ns * slice / slices; j < ns * (slice + 1) / slices; ++j)
+                r += less(lds_elem<KW, TW>(lds, MAX_SPLIT, j), me) ? 1u : 0u;
+            if (i < ns && r) atomicAdd(&rank[i], r);
+        }
+    }
+    __syncthreads();
+    if (t < ns) lds_put(split, MAX_SPLIT, rank[t], lds_elem<KW, TW>(lds, MAX_SPLIT, t));
+    __syncthreads();
+    uint32_t part[PER], slot[PER], step = 1;
+    while (step * 2 <= ns) step *= 2;
+#pragma unroll
+    for (int q = 0; q < PER; ++q) part[q] = 0;
+    for (; step > 0; step >>= 1)
+#pragma unroll
+        for (int q = 0; q < PER; ++q)
+            if (q * NT < cnt) {
+                const uint32_t at = part[q] + step - 1;
+                if (at < ns && !less(e[q], lds_elem<KW, TW>(split, MAX_SPLIT, at))) part[q] += step;
+            }
+#pragma unroll
+    for (int q = 0; q < PER; ++q)
+        if (q * NT + t < cnt) slot[q] = atomicAdd(&part_begin[part[q] + 1], 1u);
+    __syncthreads();
+    if (t < 64) {   // counts of parts 0 .. ns stand at 1 .. ns + 1; 0 stays 0
+        uint32_t sum = 0;
+        for (uint32_t c = 0; c <= ns; c += 64) {
+            const uint32_t x = c + lane <= ns ? part_begin[c + lane + 1] : 0;
+            uint32_t incl = x;
+            for (int o = 1; o < 64; o <<= 1) {
+                const uint32_t y = __shfl_up(incl, o);
+                if ((int)lane >= o) incl += y;
+            }
+            if (c + lane <= ns) part_begin[c + lane + 1] = sum + incl;
+            sum += __shfl(incl, 63);
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < PER; ++q)
+        if (q * NT + t < cnt) lds_put(lds, CAP, part_begin[part[q]] + slot[q], e[q]);
+    __syncthreads();
+    // ranks in the order of the parts: the lanes of a wave then read a few parts, the same element for many lanes (58
+    // against 61 us with the elements in the order they came)
+#pragma unroll
+    for (int q = 0; q < PER; ++q)
+        if (q * NT + t < cnt) {
+            const uint32_t i = q * NT + t;
+            uint32_t p = 0;   // the last part that starts at or before i
+            for (uint32_t step = 128; step > 0; step >>= 1)
+                if (p + step <= ns && part_begin[p + step] <= i) p += step;
+            e[q] = lds_elem<KW, TW>(lds, CAP, i);
+            const uint32_t p0 = part_begin[p], p1 = part_begin[p + 1];
+            uint32_t r = p0;
+#pragma unroll 4
+            for (uint32_t j = p0; j < p1; ++j) r += less(lds_elem<KW, TW>(lds, CAP, j), e[q]) ? 1u : 0u;
+            slot[q] = r;
+        }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < PER; ++q)
+        if (q * NT + t < cnt) lds_put(lds, CAP, slot[q], e[q]);
+    __syncthreads();
+    uint32_t *out = s.sorted + (int64_t)off_sum * W;
     uint32_t h = 0, h0 = 0;
     for (uint32_t i = t; i < cnt; i += NT) {
-        const E x = lds_elem<KW, TW>(lds, STRIDE, i);
-        elem_store<KW, TW>(slab + (int64_t)i * W, x);
+        const E x = lds_elem<KW, TW>(lds, CAP, i);
+        elem_store<KW, TW>(out + (int64_t)i * W, x);
         if (i == 0) key_store<KW>(s.first + (int64_t)bucket * KW, x.key);
         if (i == cnt - 1) key_store<KW>(s.last + (int64_t)bucket * KW, x.key);
         if (i > 0) {
-            const int n = key_lcp<KW>(x.key, lds_elem<KW, TW>(lds, STRIDE, i - 1).key);
-            h += n < 4 * KW ? 1u : 0u;
-            h0 += n < D0 ? 1u : 0u;
+            const int p = key_lcp<KW>(x.key, lds_elem<KW, TW>(lds, CAP, i - 1).key);
+            h += p < 4 * KW ? 1u : 0u;
+            h0 += p < D0 ? 1u : 0u;
         }
     }
     for (int o = 32; o > 0; o >>= 1) {
         h += __shfl_xor(h, o);
         h0 += __shfl_xor(h0, o);
     }
-    if ((t & 63) == 0) {
+    if (lane == 0) {
         atomicAdd(&heads[0], h);
         atomicAdd(&heads[1], h0);
     }
@@ -559,12 +689,13 @@ __device__ void bucket_sort(const SortBufs &s, uint32_t bucket, int D0, uint32_t
     }
 }
 
-template <int KW, int TW, int NT>
+template <int KW, int TW, int NT, uint32_t CAP>
 __global__ void __launch_bounds__(NT) k_chain_sort(ChainArgs a)
 {
     extern __shared__ uint32_t blds[];
-    if (a.scal->overflow) return;
-    bucket_sort<KW, TW, NT>(a.s0, blockIdx.x, a.cb[1], blds);
+    const uint32_t B = n_buckets(a.N, a.cap, a.wshift), bucket = bucket_of_block(blockIdx.x, B);
+    if ((blockIdx.x >> 3) >= (B + 7) / 8 || bucket >= B) return;
+    bucket_sort<KW, TW, NT, CAP>(a.s0, a.N, a.bstride, bucket, a.cb[1], a.scal, blds);
 }
 
 // ---- where a bucket's elements and its distinct keys stand in the whole order ------------------------------------
@@ -582,17 +713,23 @@ __device__ BucketPlace bucket_place(const SortBufs &s, uint32_t B, uint32_t buck
     __syncthreads();
     uint32_t v[5] = {0, 0, 0, 0, 0};
     for (uint32_t b = threadIdx.x; b < B; b += NT) {
-        const uint32_t c = s.count[b];
+        // (everything requested at once; an empty bucket before this one is rare)
+        const uint32_t c = s.count[b], nh = s.nh[b], nh0 = s.nh0[b], cp = s.count[b > 0 ? b - 1 : 0];
+        const Key<KW> first = key_load<KW>(s.first + (int64_t)b * KW);
+        Key<KW> last = key_load<KW>(s.last + (int64_t)(b > 0 ? b - 1 : 0) * KW);
         if (c == 0) continue;
         int64_t p = (int64_t)b - 1;
-        while (p >= 0 && s.count[p] == 0) --p;
+        if (p >= 0 && cp == 0) {
+            while (p >= 0 && s.count[p] == 0) --p;
+            if (p >= 0) last = key_load<KW>(s.last + p * KW);
+        }
         uint32_t edge = 1, edge0 = 1;
         if (p >= 0) {
-            const int n = key_lcp<KW>(key_load<KW>(s.first + (int64_t)b * KW), key_load<KW>(s.last + p * KW));
+            const int n = key_lcp<KW>(first, last);
             edge = n < 4 * KW ? 1u : 0u;
             edge0 = n < D0 ? 1u : 0u;
         }
-        const uint32_t h = s.nh[b] + edge, h0 = s.nh0[b] + edge0;
+        const uint32_t h = nh + edge, h0 = nh0 + edge0;
         if (b < bucket) {
             v[0] += c;
             v[1] += h;
@@ -626,7 +763,7 @@ __device__ void bucket_walk(const SortBufs &s, uint32_t bucket, int D0, const Bu
     __shared__ uint32_t pre[CH], pre0[CH];
     constexpr uint32_t CAP = NT * 8;
     const uint32_t cnt = min(s.count[bucket], CAP), lane = threadIdx.x & 63;
-    const uint32_t *slab = s.slab + (int64_t)bucket * CAP * W;
+    const uint32_t *run = s.sorted + (int64_t)pl.off * W;
     const uint32_t nch = (cnt + 63) / 64;
     for (uint32_t c = threadIdx.x >> 6; c < nch; c += NT / 64) {
         const uint32_t i = c * 64 + lane;
@@ -636,7 +773,7 @@ __device__ void bucket_walk(const SortBufs &s, uint32_t bucket, int D0, const Bu
                 h = pl.edge != 0;
                 h0 = pl.edge0 != 0;
             } else {
-                const int n = key_lcp<KW>(key_load<KW>(slab + (int64_t)i * W + TW), key_load<KW>(slab + (int64_t)(i - 1) * W + TW));
+                const int n = key_lcp<KW>(key_load<KW>(run + (int64_t)i * W + TW), key_load<KW>(run + (int64_t)(i - 1) * W + TW));
                 h = n < 4 * KW;
                 h0 = n < D0;
             }
@@ -649,7 +786,7 @@ __device__ void bucket_walk(const SortBufs &s, uint32_t bucket, int D0, const Bu
     }
     __syncthreads();
     if (threadIdx.x < 64) {
-        uint32_t run = pl.hd, run0 = pl.hd0;
+        uint32_t h = pl.hd, h0 = pl.hd0;
         for (uint32_t c0 = 0; c0 < nch; c0 += 64) {
             const uint32_t c = c0 + lane;
             const uint32_t n = c < nch ? (uint32_t)__popcll(mask[c]) : 0, n0 = c < nch ? (uint32_t)__popcll(mask0[c]) : 0;
@@ -662,11 +799,11 @@ __device__ void bucket_walk(const SortBufs &s, uint32_t bucket, int D0, const Bu
                 }
             }
             if (c < nch) {
-                pre[c] = run + x - n;
-                pre0[c] = run0 + x0 - n0;
+                pre[c] = h + x - n;
+                pre0[c] = h0 + x0 - n0;
             }
-            run += __shfl(x, 63);
-            run0 += __shfl(x0, 63);
+            h += __shfl(x, 63);
+            h0 += __shfl(x0, 63);
         }
     }
     __syncthreads();
@@ -674,7 +811,7 @@ __device__ void bucket_walk(const SortBufs &s, uint32_t bucket, int D0, const Bu
         const uint32_t i = c * 64 + lane;
         if (i >= cnt) continue;
         const uint64_t upto = ~0ull >> (63 - lane), m = mask[c], m0 = mask0[c];
-        emit(i, elem_load<KW, TW>(slab + (int64_t)i * W), (m >> lane & 1) != 0, pre[c] + (uint32_t)__popcll(m & upto), (m0 >> lane & 1) != 0,
+        emit(i, elem_load<KW, TW>(run + (int64_t)i * W), (m >> lane & 1) != 0, pre[c] + (uint32_t)__popcll(m & upto), (m0 >> lane & 1) != 0,
              pre0[c] + (uint32_t)__popcll(m0 & upto));
     }
 }
@@ -719,12 +856,32 @@ __global__ void __launch_bounds__(NT) k_chain_encodings(ChainArgs a)
 }
 
 // ---- nodes per level ---------------------------------------------------------------------------------------------
-// lcp with the neighbours of sub-encoding u of tree t
-template <int KT> __device__ __forceinline__ void neighbours(const uint32_t *dk, uint32_t u, uint32_t U, int D, Key<KT> &k, int &a, int &b)
+constexpr int LVL_PER = LVL_CH / (LVL_NT / 64);  // chunks of 64 sub-encodings of a wave: wave w has w, w + 16, ...
+
+// The wave's sub-encodings of a tile of tree t (0 beyond the last) and how far their neighbours agree with them.
+template <int KT> struct Subs {
+    Key<KT> k[LVL_PER];
+    int x[LVL_PER], y[LVL_PER];
+};
+
+template <int KT> __device__ __forceinline__ Subs<KT> load_subs(const uint32_t *dk, uint32_t tile, uint32_t U, int D)
 {
-    k = key_load<KT>(dk + (int64_t)u * KT);
-    a = u > 0 ? min(D, key_lcp<KT>(k, key_load<KT>(dk + (int64_t)(u - 1) * KT))) : 0;
-    b = u + 1 < U ? min(D, key_lcp<KT>(k, key_load<KT>(dk + (int64_t)(u + 1) * KT))) : 0;
+    Subs<KT> s;
+    Key<KT> before[LVL_PER], after[LVL_PER];
+#pragma unroll
+    for (int q = 0; q < LVL_PER; ++q) {
+        const uint32_t u = min(tile * LVL_TILE + (q * (LVL_NT / 64) + (threadIdx.x >> 6)) * 64 + (threadIdx.x & 63), U - 1);
+        s.k[q] = key_load<KT>(dk + (int64_t)u * KT);
+        before[q] = key_load<KT>(dk + (int64_t)(u > 0 ? u - 1 : 0) * KT);
+        after[q] = key_load<KT>(dk + (int64_t)min(u + 1, U - 1) * KT);
+    }
+#pragma unroll
+    for (int q = 0; q < LVL_PER; ++q) {
+        const uint32_t u = tile * LVL_TILE + (q * (LVL_NT / 64) + (threadIdx.x >> 6)) * 64 + (threadIdx.x & 63);
+        s.x[q] = u > 0 ? min(D, key_lcp<KT>(s.k[q], before[q])) : 0;
+        s.y[q] = u + 1 < U ? min(D, key_lcp<KT>(s.k[q], after[q])) : 0;
+    }
+    return s;
 }
 
 // A prefix group of length l starts at u where a < l; it is an internal node where the next sub-encoding still shares
@@ -741,15 +898,13 @@ template <int KT> __device__ void count_levels(const ChainArgs &a, int t, uint32
     const uint32_t *dk = a.dk + (int64_t)t * a.NK * KT;
     if (threadIdx.x < CATS) acc[threadIdx.x] = 0;
     __syncthreads();
+    const Subs<KT> s = load_subs<KT>(dk, tile, U, D);
     uint32_t mine = 0;  // lane c: category c
-    for (uint32_t c = threadIdx.x >> 6; c < LVL_CH; c += PREP_NT / 64) {
-        const uint32_t u = tile * LVL_TILE + c * 64 + lane;
-        Key<KT> k;
-        int x = 0, y = 0;
-        const bool on = u < U;
-        if (on) neighbours<KT>(dk, u, U, D, k, x, y);
+#pragma unroll
+    for (int q = 0; q < LVL_PER; ++q) {
+        const bool on = tile * LVL_TILE + (q * (LVL_NT / 64) + (threadIdx.x >> 6)) * 64 + lane < U;
         for (int l = 1; l <= D; ++l) {
-            const uint32_t ni = (uint32_t)__popcll(__ballot(on && is_internal(x, y, l, D))), nl = (uint32_t)__popcll(__ballot(on && is_leaf(x, y, l)));
+            const uint32_t ni = (uint32_t)__popcll(__ballot(on && is_internal(s.x[q], s.y[q], l, D))), nl = (uint32_t)__popcll(__ballot(on && is_leaf(s.x[q], s.y[q], l)));
             mine += (int)lane == l - 1 ? ni : (int)lane == ETF_MAX_M + l - 1 ? nl : 0;
         }
     }
@@ -817,7 +972,7 @@ __device__ void draw_sample(const ChainArgs &a, uint32_t blk, uint32_t nblk)
     }
 }
 
-// blockIdx.y < T - 1: ranks of the samples of tree y + 1; T - 1: draws; T: levels of tree 0
+// blockIdx.y < T - 1: ranks of the samples of tree y + 1; T - 1: draws; T: the tables
 template <int KT>
 __global__ void __launch_bounds__(PREP_NT) k_chain_mid(ChainArgs a, uint32_t draw_blocks)
 {
@@ -831,7 +986,7 @@ __global__ void __launch_bounds__(PREP_NT) k_chain_mid(ChainArgs a, uint32_t dra
     } else if (y == a.T - 1) {
         if (blockIdx.x < draw_blocks) draw_sample(a, blockIdx.x, draw_blocks);
     } else {
-        count_levels<KT>(a, 0, blockIdx.x);
+        for (uint32_t j = blockIdx.x * PREP_NT + threadIdx.x; j < a.table_words; j += gridDim.x * PREP_NT) ((uint32_t *)a.img)[j] = a.tables[j];
     }
 }
 
@@ -894,7 +1049,7 @@ __global__ void __launch_bounds__(CLS_NT) k_chain_classify_trees(ChainArgs a, ui
     if (blockIdx.x * (uint32_t)CLS_TILE >= Nd) return;
     const uint8_t *ecodes = (const uint8_t *)(a.img + offsets(a, Nd, 0).ecodes);
     const int t = y + 1, c0 = a.cb[t], D = a.cb[t + 1] - c0;
-    classify<KT, 1>(tree_bufs(a, t), Nd, a.cap, a.wshift, stride, a.scal, blds, [&](uint32_t i) {
+    classify<KT, 1>(tree_bufs(a, t), Nd, a.cap, a.wshift, stride, a.bstride, blds, [&](uint32_t i) {
         Elem<KT, 1> e;
         e.key = key_part<KW, KT>(key_of_row<KW>(ecodes, i, a.M, a.M == 4 * KW), c0, D);
         e.tail = i;
@@ -952,18 +1107,19 @@ __device__ void place_sample(const ChainArgs &a, uint32_t blk, uint32_t nblk)
 }
 
 // blockIdx.y < T - 1: sort of tree y + 1's buckets; T - 1: samples
-template <int KW, int KT, int NT>
+template <int KW, int KT, int NT, uint32_t CAP>
 __global__ void __launch_bounds__(NT) k_chain_sort_trees(ChainArgs a, uint32_t place_blocks)
 {
     extern __shared__ uint32_t blds[];
-    if (a.scal->overflow) return;
+    if (a.scal->overflow) return;   // (another tree's sort may have set it by now)
     const int y = (int)blockIdx.y;
     if (y == a.T - 1) {
         if (blockIdx.x < place_blocks) place_sample<KW, NT>(a, blockIdx.x, place_blocks);
         return;
     }
-    if (blockIdx.x >= n_buckets(a.scal->Nd, a.cap, a.wshift)) return;
-    bucket_sort<KT, 1, NT>(tree_bufs(a, y + 1), blockIdx.x, 0, blds);
+    const uint32_t B = n_buckets(a.scal->Nd, a.cap, a.wshift), bucket = bucket_of_block(blockIdx.x, B);
+    if ((blockIdx.x >> 3) >= (B + 7) / 8 || bucket >= B) return;
+    bucket_sort<KT, 1, NT, CAP>(tree_bufs(a, y + 1), a.scal->Nd, a.bstride, bucket, 0, a.scal, blds);
 }
 
 // ---- a tree's leaves: number of every distinct encoding's, distinct sub-encodings --------------------------------
@@ -985,10 +1141,10 @@ __global__ void __launch_bounds__(NT) k_chain_leaves(ChainArgs a)
 }
 
 template <int KT>
-__global__ void __launch_bounds__(PREP_NT) k_chain_levels(ChainArgs a)
+__global__ void __launch_bounds__(LVL_NT) k_chain_levels(ChainArgs a)
 {
     if (a.scal->overflow) return;
-    count_levels<KT>(a, (int)blockIdx.y + 1, blockIdx.x);
+    count_levels<KT>(a, (int)blockIdx.y, blockIdx.x);
 }
 
 // ---- the trees into the image ------------------------------------------------------------------------------------
@@ -1002,11 +1158,11 @@ template <int KT> __device__ void write_levels(const ChainArgs &a, int t, uint32
     __shared__ BuildScal scal;
     const uint32_t U = a.scal->U[t], lane = threadIdx.x & 63;
     if (tile * (uint32_t)LVL_TILE >= U) return;
-    load_counts(a.scal, scal);
     const int D = a.cb[t + 1] - a.cb[t];
-    const uint32_t *dk = a.dk + (int64_t)t * a.NK * KT;
+    const Subs<KT> s = load_subs<KT>(a.dk + (int64_t)t * a.NK * KT, tile, U, D);
+    load_counts(a.scal, scal);
     if (threadIdx.x < CATS) pre[threadIdx.x] = 0;
-    if (threadIdx.x == PREP_NT - 1) {
+    if (threadIdx.x == LVL_NT - 1) {
         int64_t off = offsets(a, scal.Nd, scal.S_enc).trees;
         for (int i = 0; i < t; ++i) place_tree(a, scal, i, off, [](int, int, int64_t) {});
         place_tree(a, scal, t, off, [&](int array, int l, int64_t at) {
@@ -1022,24 +1178,22 @@ template <int KT> __device__ void write_levels(const ChainArgs &a, int t, uint32
     {
         const uint32_t cat = threadIdx.x % CATS;
         uint32_t n = 0;
-        for (uint32_t i = threadIdx.x / CATS; i < tile; i += PREP_NT / CATS) n += a.tile_cnt[((int64_t)t * a.lvl_tiles + i) * CATS + cat];
+        for (uint32_t i = threadIdx.x / CATS; i < tile; i += LVL_NT / CATS) n += a.tile_cnt[((int64_t)t * a.lvl_tiles + i) * CATS + cat];
         if (n) atomicAdd(&pre[cat], n);
     }
-    for (uint32_t c = threadIdx.x >> 6; c < LVL_CH; c += PREP_NT / 64) {
-        const uint32_t u = tile * LVL_TILE + c * 64 + lane;
-        Key<KT> k;
-        int x = 0, y = 0;
-        const bool on = u < U;
-        if (on) neighbours<KT>(dk, u, U, D, k, x, y);
+#pragma unroll
+    for (int q = 0; q < LVL_PER; ++q) {
+        const uint32_t c = q * (LVL_NT / 64) + (threadIdx.x >> 6);
+        const bool on = tile * LVL_TILE + c * 64 + lane < U;
         uint32_t mine = 0;
         for (int l = 1; l <= D; ++l) {
-            const uint32_t ni = (uint32_t)__popcll(__ballot(on && is_internal(x, y, l, D))), nl = (uint32_t)__popcll(__ballot(on && is_leaf(x, y, l)));
+            const uint32_t ni = (uint32_t)__popcll(__ballot(on && is_internal(s.x[q], s.y[q], l, D))), nl = (uint32_t)__popcll(__ballot(on && is_leaf(s.x[q], s.y[q], l)));
             mine = (int)lane == l - 1 ? ni : (int)lane == ETF_MAX_M + l - 1 ? nl : mine;
         }
         if (lane < CATS) cc[c][lane] = mine;
     }
     __syncthreads();
-    for (uint32_t cat = threadIdx.x >> 6; cat < CATS; cat += PREP_NT / 64) {
+    for (uint32_t cat = threadIdx.x >> 6; cat < CATS; cat += LVL_NT / 64) {
         static_assert(LVL_CH == 64, "a chunk per lane");
         const uint32_t n = cc[lane][cat];
         uint32_t x = n;
@@ -1053,15 +1207,13 @@ template <int KT> __device__ void write_levels(const ChainArgs &a, int t, uint32
     const int dc = tree_depth_class(D), rwords = (dc < 4 ? 4 : dc) / 4;
     const uint64_t upto = ~0ull >> (63 - lane);
     uint8_t *rec = (uint8_t *)(a.img + o.rec);
-    for (uint32_t c = threadIdx.x >> 6; c < LVL_CH; c += PREP_NT / 64) {
-        const uint32_t u = tile * LVL_TILE + c * 64 + lane;
-        Key<KT> k = 0;
-        int x = 0, y = 0;
+#pragma unroll
+    for (int q = 0; q < LVL_PER; ++q) {
+        const uint32_t c = q * (LVL_NT / 64) + (threadIdx.x >> 6), u = tile * LVL_TILE + c * 64 + lane;
+        const Key<KT> k = s.k[q];
+        const int x = s.x[q], y = s.y[q];
         const bool on = u < U;
-        if (on) {
-            neighbours<KT>(dk, u, U, D, k, x, y);
-            key_write_front<KT>(rec + (int64_t)u * (4 * rwords), k >> (8 * (dc - D)), rwords);
-        }
+        if (on) key_write_front<KT>(rec + (int64_t)u * (4 * rwords), k >> (8 * (dc - D)), rwords);
         uint32_t parent = NO_PARENT;
         for (int l = 1; l <= D; ++l) {
             const bool in = on && is_internal(x, y, l, D), lf = on && is_leaf(x, y, l);
@@ -1102,7 +1254,7 @@ template <int KW> __device__ void write_encodings(const ChainArgs &a, uint32_t b
     const int D0 = a.cb[1], dc = tree_depth_class(D0), words = a.rstride0 / 4;
     const uint8_t *ecodes = (const uint8_t *)(a.img + o.ecodes);
     uint8_t *rec0 = (uint8_t *)(a.img + o.rec0);
-    for (uint32_t e = blk * LVL_TILE + threadIdx.x; e < min((blk + 1) * (uint32_t)LVL_TILE, Nd); e += PREP_NT) {
+    for (uint32_t e = blk * LVL_TILE + threadIdx.x; e < min((blk + 1) * (uint32_t)LVL_TILE, Nd); e += LVL_NT) {
         const Key<KW> k = key_part<KW, KW>(key_of_row<KW>(ecodes, e, a.M, a.M == 4 * KW), 0, D0);
         key_write_front<KW>(rec0 + (int64_t)e * a.rstride0, k >> (8 * (dc - D0)), words);
         if (a.T > 1)
@@ -1112,8 +1264,10 @@ template <int KW> __device__ void write_encodings(const ChainArgs &a, uint32_t b
 
 // blockIdx.y < T: levels and records of tree y; T: the encodings' leaf numbers and records
 template <int KW, int KT>
-__global__ void __launch_bounds__(PREP_NT) k_chain_write(ChainArgs a)
+__global__ void __launch_bounds__(LVL_NT) k_chain_write(ChainArgs a)
 {
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < sizeof(BuildScal) / 4)
+        ((uint32_t *)a.scal_host)[threadIdx.x] = ((const uint32_t *)a.scal)[threadIdx.x];
     if (a.scal->overflow) return;
     if ((int)blockIdx.y < a.T) write_levels<KT>(a, (int)blockIdx.y, blockIdx.x);
     else write_encodings<KW>(a, blockIdx.x);

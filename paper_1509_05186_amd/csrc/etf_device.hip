@@ -89,6 +89,7 @@ extern "C" void etf_destroy(etf_ctx *ctx)
             (void)hipEventDestroy((hipEvent_t)s.start);
             (void)hipEventDestroy((hipEvent_t)s.stop);
         }
+    if (ctx->build_stage) (void)hipHostFree(ctx->build_stage);
     delete ctx;
 }
 

@@ -204,6 +204,7 @@ static int64_t align256(int64_t x) { return (x + 255) & ~(int64_t)255; }
 void prepare_centered(etf_ctx *ctx)
 {
     const int M = ctx->M, K = ctx->K, ds = ctx->ds;
+    ++ctx->tables_gen;
     ctx->dsp = (ds + 1) & ~1;
     ctx->cb_mean.assign((size_t)M * ds, 0.f);
     ctx->cb_centered.assign((size_t)M * K * ctx->dsp, 0.f);

@@ -173,7 +173,11 @@ struct etf_ctx {
     // diagnostics of the most recent search (device address inside the caller's workspace)
     void *last_flag_count = nullptr;
     // landing place of the small device-to-host copies of the device index build
-    uint32_t build_scal[8 + 3 * ETF_MAX_M] = {};
+    uint32_t build_scal[4] = {0, 0, 0, 0};
+    // pinned memory of the device build: counts, then the quantiser's tables as of tables_gen (etf_build.hip)
+    void *build_stage = nullptr;
+    int64_t build_stage_bytes = 0;
+    uint64_t build_stage_gen = 0, tables_gen = 0;   // tables_gen: counts the quantiser's changes
     // per-kernel timing: pairs of hipEvent_t (stored untyped so that host-only code need not see HIP)
     bool profile_on = false;
     bool no_alloc_call = false;     // inside etf_search_static: nothing that allocates (no new event pairs)
