@@ -665,7 +665,7 @@ __device__ __forceinline__ float ivf_distance_words(const float *tab, const uint
 // lists.
 // CM, CK: M and K as constants (the common shape, loops unrolled and table offsets immediate), or 0: taken from a.
 template <int CM, int CK, class F>
-__device__ __forceinline__ void ivf_walk_shape(const IvfScanArgs &a, const float *tab, const uint32_t *s_off, const uint32_t *s_lo,
+__device__ __forceinline__ void ivf_walk(const IvfScanArgs &a, const float *tab, const uint32_t *s_off, const uint32_t *s_lo,
                                                const float *s_base, int nlists, F f)
 {
     const int M = CM ? CM : a.M, K = CK ? CK : a.K;
@@ -686,16 +686,6 @@ __device__ __forceinline__ void ivf_walk_shape(const IvfScanArgs &a, const float
             if (two) f(e1, d1);
         }
     }
-}
-
-template <class F>
-__device__ __forceinline__ void ivf_walk(const IvfScanArgs &a, const float *tab, const uint32_t *s_off, const uint32_t *s_lo,
-                                         const float *s_base, int nlists, F f)
-{
-    if (a.M == 8 && a.K == 256)
-        ivf_walk_shape<8, 256>(a, tab, s_off, s_lo, s_base, nlists, f);
-    else
-        ivf_walk_shape<0, 0>(a, tab, s_off, s_lo, s_base, nlists, f);
 }
 
 // The w probed lists of a query as one sequence of entries: s_off[p] = entries before list p.  Thread i of a flat
@@ -719,7 +709,7 @@ struct IvfLists {
 
 __device__ __forceinline__ void ivf_setup_lists(const IvfScanArgs &a, int64_t q, uint32_t *s_off, uint32_t *s_lo, float *s_base)
 {
-    // list lengths, then their running sum (w is small: one thread adds them up)
+    // list lengths, then their running sum (one wave, 64 lists at a time)
     for (int p = threadIdx.x; p < a.w; p += blockDim.x) {
         const int cell = a.probes[q * a.w + p];
         s_lo[p] = a.lbegin[cell];
@@ -727,22 +717,43 @@ __device__ __forceinline__ void ivf_setup_lists(const IvfScanArgs &a, int64_t q,
         s_base[p] = a.base[q * a.w + p];
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
+    if (threadIdx.x < 64) {
+        const int lane = threadIdx.x;
         uint32_t run = 0;
-        s_off[0] = 0;
-        for (int p = 0; p < a.w; ++p) {
-            run += s_off[p + 1];
-            s_off[p + 1] = run;
+        for (int p0 = 0; p0 < a.w; p0 += 64) {
+            const int p = p0 + lane;
+            uint32_t v = p < a.w ? s_off[p + 1] : 0u;
+#pragma unroll
+            for (int dlt = 1; dlt < 64; dlt <<= 1) {
+                const uint32_t up = (uint32_t)__shfl_up((int)v, dlt);
+                if (lane >= dlt) v += up;
+            }
+            v += run;
+            if (p < a.w) s_off[p + 1] = v;
+            run = (uint32_t)__shfl((int)v, 63);
         }
+        if (lane == 0) s_off[0] = 0;
     }
     __syncthreads();
 }
 
 // bytes of dynamic LDS of the two kernels below: tables, list bookkeeping, (scan only) the histogram
-constexpr int IVF_HIST_BITS = 12;  // sign-free float bits >> 19: exponent and four mantissa bits (bins 6 % wide)
+// The histogram's bins: exponent and four mantissa bits of the distance (6 % wide), from 2^-64 to 2^64; what lies below
+// counts in the first, above in the last.  (All 256 exponents take 16 KiB, which left room for six workgroups on a CU;
+// with 8 KiB it is eight, all the waves it holds.)
+constexpr int IVF_BINS = 2048, IVF_BIN_SHIFT = 19, IVF_BIN_FIRST = (127 - 64) << 4;
+__device__ __forceinline__ int ivf_bin(float d)
+{
+    return min(max((int)(__float_as_uint(d) >> IVF_BIN_SHIFT) - IVF_BIN_FIRST, 0), IVF_BINS - 1);
+}
+// the largest float (as bits) of a bin; everything passes the last one's
+__device__ __forceinline__ uint32_t ivf_bin_edge(int b)
+{
+    return b == IVF_BINS - 1 ? 0x7F800000u : ((uint32_t)(IVF_BIN_FIRST + b + 1) << IVF_BIN_SHIFT) - 1u;
+}
 __host__ __device__ inline size_t ivf_lds_bytes(int M, int K, int w, bool hist)
 {
-    return (size_t)M * K * 4 + (size_t)(3 * w + 4) * 4 + (hist ? ((size_t)4 << IVF_HIST_BITS) : 0);
+    return (size_t)M * K * 4 + (size_t)(3 * w + 4) * 4 + (hist ? (size_t)4 * IVF_BINS : 0);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -751,9 +762,14 @@ __host__ __device__ inline size_t ivf_lds_bytes(int M, int K, int w, bool hist)
 //     cells' lists, as many as together hold bound_entries entries, and finds the bin in which the running count
 //     reaches k: its upper edge bounds the k-th distance.  Pass 2 evaluates the entries of all lists and appends
 //     those at or below the bound to the query's candidate list, which k_select orders and expands.
+//     Bound by the latency of the entries' loads and of the table gathers, so by the waves in flight: eight workgroups per
+// CU (18 KiB of LDS at M = 8, K = 256 and w = 64, at most 64 vector and 96 scalar registers; M and K as template constants
+// keep the general walker's predicates out of the scalar registers).  With six workgroups, and running sums by one
+// thread, 10 000 queries took 677 us here and 1106 in all, 559 and 962 with eight.
 //     grid (queries), block 256, dynamic LDS ivf_lds_bytes(..., true).
 // ------------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_ivf_scan(IvfScanArgs a)
+template <int CM, int CK>
+__global__ __launch_bounds__(256, 8) void k_ivf_scan(IvfScanArgs a)
 {
     extern __shared__ float ivf_lds[];
     float *tab = ivf_lds;
@@ -761,9 +777,9 @@ __global__ __launch_bounds__(256) void k_ivf_scan(IvfScanArgs a)
     uint32_t *s_lo = s_off + a.w + 2;
     float *s_base = reinterpret_cast<float *>(s_lo + a.w + 1);
     uint32_t *hist = reinterpret_cast<uint32_t *>(s_base + a.w + 1);
-    __shared__ uint32_t s_part[256];
+    __shared__ uint32_t s_part[4];
     __shared__ uint32_t s_tau, s_cnt;
-    constexpr int NB = 1 << IVF_HIST_BITS, SH = 31 - IVF_HIST_BITS;
+    constexpr int NB = IVF_BINS;
     const int64_t q = blockIdx.x;
     for (int i = threadIdx.x; i < a.M * a.K; i += 256) tab[i] = a.lut[q * a.M * a.K + i];
     for (int i = threadIdx.x; i < NB; i += 256) hist[i] = 0;
@@ -784,20 +800,27 @@ __global__ __launch_bounds__(256) void k_ivf_scan(IvfScanArgs a)
         nbound = lo;
     }
     for (;;) {
-        ivf_walk(a, tab, s_off, s_lo, s_base, nbound, [&](uint32_t e, float d) {
-            atomicAdd(&hist[__float_as_uint(d) >> SH], min(a.ebegin[e + 1] - a.ebegin[e], (uint32_t)a.k));
+        ivf_walk<CM, CK>(a, tab, s_off, s_lo, s_base, nbound, [&](uint32_t e, float d) {
+            atomicAdd(&hist[ivf_bin(d)], min(a.ebegin[e + 1] - a.ebegin[e], (uint32_t)a.k));
         });
         __syncthreads();
         // the bin in which the running count of vectors reaches k (thread t owns bins [t * NB/256, (t+1) * NB/256))
         {
             constexpr int PER = NB / 256;
+            const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
             uint32_t part = 0;
             for (int b = 0; b < PER; ++b) part += hist[threadIdx.x * PER + b];
-            s_part[threadIdx.x] = part;
+            uint32_t inc = part;
+#pragma unroll
+            for (int dlt = 1; dlt < 64; dlt <<= 1) {
+                const uint32_t up = (uint32_t)__shfl_up((int)inc, dlt);
+                if (lane >= dlt) inc += up;
+            }
+            if (lane == 63) s_part[wave] = inc;
             if (threadIdx.x == 0) s_tau = 0x7F800000u;  // fewer than k vectors in the lists: everything passes
             __syncthreads();
-            uint32_t below = 0;
-            for (int t2 = 0; t2 < (int)threadIdx.x; ++t2) below += s_part[t2];
+            uint32_t below = inc - part;
+            for (int t2 = 0; t2 < wave; ++t2) below += s_part[t2];
             if (below < (uint32_t)a.k && below + part >= (uint32_t)a.k) {
                 int b = 0;
                 for (; b < PER - 1; ++b) {
@@ -805,12 +828,12 @@ __global__ __launch_bounds__(256) void k_ivf_scan(IvfScanArgs a)
                     if (below + h >= (uint32_t)a.k) break;
                     below += h;
                 }
-                s_tau = (((uint32_t)(threadIdx.x * PER + b) + 1u) << SH) - 1u;  // upper edge of that bin
+                s_tau = ivf_bin_edge((int)threadIdx.x * PER + b);
             }
             __syncthreads();
         }
         const uint32_t tau = s_tau;
-        ivf_walk(a, tab, s_off, s_lo, s_base, a.w, [&](uint32_t e, float d) {
+        ivf_walk<CM, CK>(a, tab, s_off, s_lo, s_base, a.w, [&](uint32_t e, float d) {
             const uint32_t bits = __float_as_uint(d);
             if (bits <= tau) {
                 const uint32_t pos = atomicAdd(&s_cnt, 1u);
@@ -1296,14 +1319,16 @@ extern "C" int etf_ivf_search(etf_ctx *ctx, const float *queries, int64_t Q, int
     if (ws_bytes < P.total) return fail(ctx, ETF_ENOMEM, "workspace too small: %lld < %lld", (long long)ws_bytes, (long long)P.total);
     const int M = ctx->M, K = ctx->K, d = ctx->d;
     const size_t lds_scan = ivf_lds_bytes(M, K, w, true), lds_exact = ivf_lds_bytes(M, K, w, false);
-    if (lds_scan > 150 * 1024) return fail(ctx, ETF_EINVAL, "w=%d with M=%d K=%d needs %zu bytes of LDS", w, M, K, lds_scan);
+    // (w is accepted up to where the scan's lists and tables leave room for a histogram of all 256 exponents)
+    if (lds_scan > 142 * 1024) return fail(ctx, ETF_EINVAL, "w=%d with M=%d K=%d needs %zu bytes of LDS", w, M, K, lds_scan);
     HIP_TRY(ctx, hipSetDevice(ctx->device));
     hipStream_t st = (hipStream_t)ctx->stream;
     char *wsp = (char *)ws;
     const char *img = iv.dev_base;
     uint32_t *counter = reinterpret_cast<uint32_t *>(wsp + P.o_counter);
     ctx->last_flag_count = counter;
-    rc = set_lds(ctx, k_ivf_scan, lds_scan);
+    const auto scan = M == 8 && K == 256 ? k_ivf_scan<8, 256> : k_ivf_scan<0, 0>;
+    rc = set_lds(ctx, scan, lds_scan);
     if (rc) return rc;
     rc = set_lds(ctx, k_ivf_exact, lds_exact);
     if (rc) return rc;
@@ -1383,7 +1408,7 @@ extern "C" int etf_ivf_search(etf_ctx *ctx, const float *queries, int64_t Q, int
         a.out_dist = out_dist + q0 * k;
         if (!ctx->opt.force_fallback) {
             ProfScope prof(ctx, ETF_K_IVF_SCAN);
-            hipLaunchKernelGGL(k_ivf_scan, dim3((unsigned)nq), dim3(256), lds_scan, st, a);
+            hipLaunchKernelGGL(scan, dim3((unsigned)nq), dim3(256), lds_scan, st, a);
             LAUNCH_CHECK(ctx, "k_ivf_scan");
         }
         SelectArgs sa;

@@ -219,6 +219,22 @@ def test_ivf_heavy_duplicates_and_query_batches():
     p.check(ids.cpu().numpy(), dist.cpu().numpy(), k, w, what="ivf dups")
 
 
+@pytest.mark.parametrize("e", [-40, -33, 31, 40])
+@pytest.mark.parametrize("M,K", [(8, 256), (4, 64)])
+def test_ivf_distances_at_the_ends_of_the_histogram(e, M, K):
+    """Everything scaled by a power of two: the same neighbours, and distances that are the same numbers times its square
+    (no rounding changes), with distances below, across and above the range 2^-64 .. 2^64 that the scan's bins tell apart."""
+    say("IVFADC: data scaled by 2 **", e, "M", M, "K", K)
+    p = IvfProblem(d=32, M=M, K=K, cells=70, N=6000, Q=70, seed=35)
+    k, w = 30, 66    # more than one wave's lists
+    want_i, want_d = p.ctx().ivf_search(torch.from_numpy(p.q).cuda(), k, w)
+    f = np.float32(2.0 ** e)
+    p.q, p.cb, p.cent = p.q * f, p.cb * f, p.cent * f
+    got_i, got_d = p.ctx().ivf_search(torch.from_numpy(p.q).cuda(), k, w)
+    torch.cuda.synchronize()
+    assert torch.equal(got_i, want_i) and torch.equal(got_d.double() * 2.0 ** (-2 * e), want_d.double())
+
+
 def test_ivf_error_paths(prob):
     c = etf.Context(device=0, stream=torch.cuda.current_stream().cuda_stream)
     c.pq_set_codebooks(prob.cb)
