@@ -479,6 +479,11 @@ __device__ __forceinline__ void ivf_for_row(const float *__restrict__ row, int K
     }
 }
 
+// HELD: a row of at most IVF_HELD cells (Kc a multiple of 4, 16-byte aligned rows) is read once, into registers, and the
+// three passes (range, histogram, collection) run on those; else each pass reads it again.  8192 cells are 32 registers a
+// thread, fewer than the rule's loads take later, so holding them costs no wave.  10 000 rows of 8192: 149 -> 123 us.
+constexpr int IVF_HELD = 8192;
+template <bool HELD>
 __global__ __launch_bounds__(256) void k_ivf_probe_mfma(const float *__restrict__ x, int d, const float *__restrict__ cent, float cmax, int units, float slack,
                                                         float *__restrict__ approx, int Kc, int w, int cap,
                                                         int32_t *__restrict__ probes, float *__restrict__ base)
@@ -493,6 +498,28 @@ __global__ __launch_bounds__(256) void k_ivf_probe_mfma(const float *__restrict_
     float *qs = reinterpret_cast<float *>(s_cell + cap);
     const int64_t q = blockIdx.x;
     float *row = approx + q * Kc;
+    typedef float vf4 __attribute__((ext_vector_type(4)));
+    constexpr int NH = HELD ? IVF_HELD / 1024 : 1;
+    vf4 held[NH];
+    const int n4 = Kc >> 2;
+    if constexpr (HELD) {
+#pragma unroll
+        for (int u = 0; u < NH; ++u) held[u] = reinterpret_cast<const vf4 *>(row)[min(u * 256 + (int)threadIdx.x, n4 - 1)];
+    }
+    auto for_row = [&](auto f) {
+        if constexpr (HELD) {
+#pragma unroll
+            for (int u = 0; u < NH; ++u) {
+                const int i = u * 256 + (int)threadIdx.x;
+                if (i < n4) {
+#pragma unroll
+                    for (int x = 0; x < 4; ++x) f(4 * i + x, held[u][x]);
+                }
+            }
+        } else {
+            ivf_for_row(row, Kc, f);
+        }
+    };
     float part = 0.f;
     for (int j = threadIdx.x; j < d; j += 256) {
         const float v = x[q * d + j];
@@ -512,7 +539,7 @@ __global__ __launch_bounds__(256) void k_ivf_probe_mfma(const float *__restrict_
     // w-th itself, but its first digits are the same for nearly all cells: every count lands on one LDS word.)
     constexpr int NB = 1024;
     float lo = 3.402823466e+38f, hi = -3.402823466e+38f;
-    ivf_for_row(row, Kc, [&](int, float v) {
+    for_row([&](int, float v) {
         lo = fminf(lo, v);
         hi = fmaxf(hi, v);
     });
@@ -535,7 +562,7 @@ __global__ __launch_bounds__(256) void k_ivf_probe_mfma(const float *__restrict_
     const bool usable = span >= 0.f && span < 3.0e38f && S * S > 1.0e-30f;
     const float scale = span > 0.f ? (float)NB / span : 0.f;
     auto bin_of = [&](float v) { return min(NB - 1, (int)((v - lo) * scale)); };
-    if (usable) ivf_for_row(row, Kc, [&](int, float v) { atomicAdd(&hist[bin_of(v)], 1u); });
+    if (usable) for_row([&](int, float v) { atomicAdd(&hist[bin_of(v)], 1u); });
     __syncthreads();
     {
         // thread t owns bins 4t .. 4t+3; the running count before them by a scan over the threads
@@ -567,7 +594,7 @@ __global__ __launch_bounds__(256) void k_ivf_probe_mfma(const float *__restrict_
     }
     const float thr = usable ? lo + (float)(sel_sh[4] + 1u) * (span / (float)NB) + E2 : -3.402823466e+38f;
     if (usable)
-        ivf_for_row(row, Kc, [&](int c, float v) {
+        for_row([&](int c, float v) {
             if (v <= thr) {
                 const uint32_t pos = atomicAdd(&s_n, 1u);
                 if (pos < (uint32_t)cap) s_cell[pos] = c;
@@ -597,6 +624,11 @@ __global__ __launch_bounds__(256) void k_ivf_probe_mfma(const float *__restrict_
         probes[q * w + i] = (int32_t)(pk[i] & 0xFFFFu);
         base[q * w + i] = __uint_as_float((uint32_t)(pk[i] >> 16));
     }
+}
+
+inline auto ivf_probe_kernel(const float *approx, int Kc)
+{
+    return Kc <= IVF_HELD && (Kc & 3) == 0 && (reinterpret_cast<uintptr_t>(approx) & 15) == 0 ? k_ivf_probe_mfma<true> : k_ivf_probe_mfma<false>;
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1273,13 +1305,14 @@ extern "C" int etf_ivf_assign_device(etf_ctx *ctx, const float *x, int64_t n, in
             const int cap = 1024;
             const size_t lds_probe = ivf_probe_lds_bytes(1, cap, d);
             if (lds_probe > 150 * 1024) return fail(ctx, ETF_EINVAL, "d=%d needs %zu bytes of LDS for the cell selection", d, lds_probe);
-            rc = set_lds(ctx, k_ivf_probe_mfma, lds_probe);
+            const auto probe = ivf_probe_kernel(matrix, iv.Kc);
+            rc = set_lds(ctx, probe, lds_probe);
             if (rc) return rc;
             for (int64_t v0 = 0; v0 < n; v0 += nb) {
                 const int64_t nv = std::min<int64_t>(nb, n - v0);
                 const int units = ivf_launch_coarse(ctx, x + v0 * d, nv, cent, cnorm, matrix);
                 LAUNCH_CHECK(ctx, "k_ivf_coarse_mfma");
-                hipLaunchKernelGGL(k_ivf_probe_mfma, dim3((unsigned)nv), dim3(256), lds_probe, st, x + v0 * d, d, cent, iv.cmax, units,
+                hipLaunchKernelGGL(probe, dim3((unsigned)nv), dim3(256), lds_probe, st, x + v0 * d, d, cent, iv.cmax, units,
                                    (float)ctx->opt.ivf_probe_slack, matrix, iv.Kc, 1, cap, cells_out + v0, nearest);
                 LAUNCH_CHECK(ctx, "k_ivf_probe_mfma");
             }
@@ -1334,7 +1367,8 @@ extern "C" int etf_ivf_search(etf_ctx *ctx, const float *queries, int64_t Q, int
     if (rc) return rc;
     const size_t lds_probe = ivf_probe_lds_bytes(w, P.cap, d);
     if (lds_probe > 150 * 1024) return fail(ctx, ETF_EINVAL, "w=%d with d=%d needs %zu bytes of LDS for the probe selection", w, d, lds_probe);
-    rc = set_lds(ctx, k_ivf_probe_mfma, lds_probe);
+    const auto probe = ivf_probe_kernel(reinterpret_cast<const float *>(wsp + P.o_coarse), iv.Kc);
+    rc = set_lds(ctx, probe, lds_probe);
     if (rc) return rc;
     const float *cent = reinterpret_cast<const float *>(img + iv.o_centroids);
     const float *cbd = reinterpret_cast<const float *>(img + iv.o_codebooks);
@@ -1356,7 +1390,7 @@ extern "C" int etf_ivf_search(etf_ctx *ctx, const float *queries, int64_t Q, int
                 const float *cnorm = reinterpret_cast<const float *>(img + iv.o_cnorm);
                 const int units = ivf_launch_coarse(ctx, qb, nq, cent, cnorm, coarse);
                 LAUNCH_CHECK(ctx, "k_ivf_coarse_mfma");
-                hipLaunchKernelGGL(k_ivf_probe_mfma, dim3((unsigned)nq), dim3(256), lds_probe, st, qb, d, cent, iv.cmax, units, (float)ctx->opt.ivf_probe_slack, coarse, iv.Kc, w, P.cap, probes,
+                hipLaunchKernelGGL(probe, dim3((unsigned)nq), dim3(256), lds_probe, st, qb, d, cent, iv.cmax, units, (float)ctx->opt.ivf_probe_slack, coarse, iv.Kc, w, P.cap, probes,
                                    pbase);
                 LAUNCH_CHECK(ctx, "k_ivf_probe_mfma");
             } else {

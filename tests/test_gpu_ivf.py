@@ -235,6 +235,33 @@ def test_ivf_distances_at_the_ends_of_the_histogram(e, M, K):
     assert torch.equal(got_i, want_i) and torch.equal(got_d.double() * 2.0 ** (-2 * e), want_d.double())
 
 
+@pytest.mark.parametrize("cells", [4, 1020, 1028, 8188, 8192, 8196])
+def test_ivf_probe_selection_at_the_ends_of_held_rows(cells):
+    """Rows of distances that are held in registers (at most 8192 cells, a multiple of four) and the first one that is not,
+    against the rule applied to every cell, bit for bit; also with every row redone by the rule."""
+    say("IVFADC: probes of", cells, "cells")
+    rng = np.random.default_rng(cells)
+    d, M, K, N, Q, k = 16, 2, 16, 20000, 67, 20
+    cent = rng.standard_normal((cells, d)).astype(np.float32)
+    cb = (0.1 * rng.standard_normal((M, K, d // M))).astype(np.float32)
+    x = torch.from_numpy(rng.standard_normal((N, d)).astype(np.float32)).cuda()
+    q = torch.from_numpy(rng.standard_normal((Q, d)).astype(np.float32)).cuda()
+    got = []
+    for opts in ({"ivf_coarse_kernel": 1}, {}, {"ivf_probe_slack": 10 ** 9}):
+        c = etf.Context(device=0, stream=torch.cuda.current_stream().cuda_stream)
+        for name, v in opts.items():
+            c.set_option(name, v)
+        c.pq_set_codebooks(cb)
+        c.ivf_set_coarse(cent)
+        cell, codes = c.ivf_assign_device(x)
+        c.ivf_build(cell.cpu().numpy(), codes.cpu().numpy())
+        c.ivf_upload()
+        got.append((cell, codes) + tuple(c.ivf_search(q, k, min(cells, 65))))
+    torch.cuda.synchronize()
+    for other in got[1:]:
+        assert all(torch.equal(a, b) for a, b in zip(got[0], other))
+
+
 def test_ivf_error_paths(prob):
     c = etf.Context(device=0, stream=torch.cuda.current_stream().cuda_stream)
     c.pq_set_codebooks(prob.cb)
