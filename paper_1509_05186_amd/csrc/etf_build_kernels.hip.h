@@ -5,7 +5,7 @@
 // The sorts are sample sorts.  Every element is (key, tail): the key is the chunks as one integer, first chunk in the
 // highest byte, the tail the position (below the id where ids are given), so that no two elements are equal and
 // repeated encodings spread over buckets like any others.  One element of each stratum of 128 positions is a sample; a
-// sample's rank is counted against all others (k_prep_rank), every eighth in rank is a splitter, an element finds its
+// sample's rank is counted against all others (k_chain_rank), every eighth in rank is a splitter, an element finds its
 // bucket by bisection among the splitters, a workgroup writes its 4096 elements grouped by bucket with the groups'
 // bounds (classify), and a workgroup per bucket gathers its groups and sorts them in LDS (bucket_sort): no atomics on
 // memory and no slack between buckets.  A bucket expects 1024 elements and LDS holds 4096: more than that needs fewer
