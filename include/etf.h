@@ -368,6 +368,15 @@ int etf_index_build_device(etf_ctx *ctx, const uint8_t *codes, int64_t N, const 
                            const int32_t *chunk_begin, void *image, int64_t image_bytes, void *workspace,
                            int64_t workspace_bytes);
 
+/* Which way the context's index came to the device (diagnostic): by a chain of kernels launched without waiting for one
+ * another, by the general path (a round trip to the host for every count), or by the general path after the chain had
+ * found one of its buckets too full.  ETF_BUILD_NONE without an index built by etf_index_build_device. */
+#define ETF_BUILD_NONE 0
+#define ETF_BUILD_CHAIN 1
+#define ETF_BUILD_GENERAL 2
+#define ETF_BUILD_GENERAL_AFTER_CHAIN 3
+int etf_last_build_path(const etf_ctx *ctx, int32_t *out);
+
 /* Workspace (device bytes) that etf_adc / etf_search need for Q queries in the
  * given mode (k is ignored by etf_adc: pass 0).  Negative = error code. */
 int64_t etf_workspace_bytes(const etf_ctx *ctx, int64_t Q, int k, int mode);

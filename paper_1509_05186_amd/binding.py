@@ -22,13 +22,14 @@ EXPORTS = [
     "etf_index_build", "etf_index_set_leaf_term", "etf_index_set_leaf_bytes", "etf_index_set_chunk_order", "etf_suggest_chunk_order", "etf_suggest_partition", "etf_index_stats", "etf_index_device_bytes", "etf_index_upload",
     "etf_index_layout", "etf_index_export",
     "etf_encode_workspace_bytes", "etf_pq_encode_device",
-    "etf_index_build_device_bytes", "etf_index_build_device",
+    "etf_index_build_device_bytes", "etf_index_build_device", "etf_last_build_path",
     "etf_workspace_bytes", "etf_lut_build", "etf_adc", "etf_search", "etf_last_fallback_count", "etf_last_matrix_blocks",
     "etf_static_scratch_bytes", "etf_search_static",
     "etf_profile_enable", "etf_profile_read", "etf_probe_bandwidth",
     "etf_ivf_set_coarse", "etf_ivf_assign_workspace_bytes", "etf_ivf_assign_device", "etf_ivf_build", "etf_ivf_stats",
     "etf_ivf_device_bytes", "etf_ivf_upload", "etf_ivf_workspace_bytes", "etf_ivf_search",
 ]
+ETF_BUILD_NONE, ETF_BUILD_CHAIN, ETF_BUILD_GENERAL, ETF_BUILD_GENERAL_AFTER_CHAIN = 0, 1, 2, 3
 ETF_PROBE_READ, ETF_PROBE_WRITE, ETF_PROBE_COPY, ETF_PROBE_ROWS, ETF_PROBE_LDS, ETF_PROBE_LDS_SCATTER = 0, 1, 2, 3, 4, 5
 ETF_PROBE_VALU_F32, ETF_PROBE_VALU_ADD3, ETF_PROBE_VALU_PK16, ETF_PROBE_MFMA_F32 = 6, 7, 8, 9
 KERNEL_CLASSES = ["lut", "level", "leaf", "flat", "reduce", "tau", "select", "exact", "sample", "lds", "encode",
@@ -156,6 +157,7 @@ def load_library():
         "etf_index_build_device_bytes": (I, [P, L, I, P, ctypes.POINTER(L), ctypes.POINTER(L)]),
         "etf_index_build_device": (I, [P, P, L, P, I, P, P, L, P, L]),
         "etf_workspace_bytes": (L, [P, L, I, I]),
+        "etf_last_build_path": (I, [P, ctypes.POINTER(I)]),
         "etf_lut_build": (I, [P, P, L, P]),
         "etf_adc": (I, [P, P, L, I, P, P, L]),
         "etf_search": (I, [P, P, L, I, I, P, P, P, L]),
@@ -462,6 +464,12 @@ class Context:
         self._keep["index"] = image
         self._N = N
         return image
+
+    def last_build_path(self) -> int:
+        """ETF_BUILD_*: the way the index came to the device."""
+        v = ctypes.c_int32(0)
+        self._ck(self._lib.etf_last_build_path(self._h, ctypes.byref(v)))
+        return int(v.value)
 
     def lut_build(self, queries, lut=None):
         import torch

@@ -725,6 +725,7 @@ int build_chain(etf_ctx *ctx, const uint8_t *codes, int64_t N, const int32_t *id
     ix.max_dup = h.max_dup;
     if (ix.max_dup < 1) return fail(ctx, ETF_EHIP, "device build: no id range");
     ix.built = true;
+    ix.build_path = ETF_BUILD_CHAIN;
     ctx->dev_base = img;
     return ETF_OK;
 }
@@ -908,6 +909,7 @@ int build_impl(etf_ctx *ctx, const uint8_t *codes, int64_t N, const int32_t *ids
     ix.max_dup = h_scal[1];
     if (ix.max_dup < 1) return fail(ctx, ETF_EHIP, "device build: no id range");
     ix.built = true;
+    ix.build_path = ETF_BUILD_GENERAL;
     ctx->dev_base = img;
     return ETF_OK;
 }
@@ -953,10 +955,10 @@ extern "C" int etf_index_build_device(etf_ctx *ctx, const uint8_t *codes, int64_
     // The chain places its arrays on the device, so the image has to hold the largest index of these sizes; a smaller
     // image or workspace, or an input whose buckets ran over, is built with every array's place checked on the host.
     const ChainPlan P = plan_chain(ctx, N, T, cb, ids != nullptr);
+    bool again = false;
     if (P.ok && workspace_bytes >= P.total && image_bytes >= image_bytes_bound(ctx, N, T, cb.data())) {
-        bool again = false;
         drop_index(ctx);
-        rc = build_chain(ctx, codes, N, ids, T, cb, (char *)image, (char *)workspace, P, again);
+        rc = build_chain(ctx, codes, N, ids, T, cb, (char *)image, (char *)workspace, P, again);   // again: a bucket ran over
         if (rc) {
             (void)hipStreamSynchronize((hipStream_t)ctx->stream);
             drop_index(ctx);
@@ -969,5 +971,14 @@ extern "C" int etf_index_build_device(etf_ctx *ctx, const uint8_t *codes, int64_
         (void)hipStreamSynchronize((hipStream_t)ctx->stream);  // nothing of a failed build may still be running in the buffers
         drop_index(ctx);
     }
+    if (!rc && again) ctx->idx.build_path = ETF_BUILD_GENERAL_AFTER_CHAIN;
     return rc;
+}
+
+extern "C" int etf_last_build_path(const etf_ctx *ctx, int32_t *out)
+{
+    if (!ctx) return ETF_EINVAL;
+    if (!out) return fail(ctx, ETF_EINVAL, "output pointer is null");
+    *out = ctx->idx.build_path;
+    return ETF_OK;
 }

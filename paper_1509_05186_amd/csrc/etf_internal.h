@@ -54,6 +54,7 @@ struct HostIndex {
     bool built = false;
     // Built on the device: the host holds the shape and the counts only, the image is already resident.
     bool device_built = false;
+    int32_t build_path = ETF_BUILD_NONE;
     int64_t n_sample_enc = 0, n_sample_pos = 0;  // entries of the two threshold samples
     int M = 0, K = 0, T = 0;
     int64_t N = 0, Nd = 0, max_dup = 0;

@@ -22,18 +22,21 @@ def build(c, codes, ids, T, chunk_begin, image_bytes):
     return image
 
 
-def compare(codes, ids=None, T=1, chunk_begin=None, K=256, order=None, sample_min=256):
+def compare(codes, ids=None, T=1, chunk_begin=None, K=256, order=None, sample_min=256, path=etf.ETF_BUILD_CHAIN):
     N, M = codes.shape
     c = etf.Context(device=0, stream=torch.cuda.current_stream().cuda_stream)
     c.set_option("sample_min", sample_min)
     c.pq_set_codebooks(np.zeros((M, K, 1), dtype=np.float32))
     c.index_set_chunk_order(order)
     d_codes, d_ids = torch.from_numpy(codes).cuda(), None if ids is None else torch.from_numpy(ids).cuda()
-    image = build(c, d_codes, d_ids, T, chunk_begin, c.index_build_device_bytes(N, T, chunk_begin)[0])
+    bound = c.index_build_device_bytes(N, T, chunk_begin)[0]
+    image = build(c, d_codes, d_ids, T, chunk_begin, bound)
+    assert c.last_build_path() == path
     need, stats = c.index_device_bytes(), c.index_stats()
     want_codes = codes if order is None else codes[:, order]
     check_image(c, image, np.ascontiguousarray(want_codes), ids)
     general = build(c, d_codes, d_ids, T, chunk_begin, need)     # below the bound: every array's place checked on the host
+    assert c.last_build_path() == (etf.ETF_BUILD_GENERAL if need < bound else path)   # (the smallest indexes are as large as their bound)
     assert c.index_device_bytes() == need and c.index_stats() == stats
     assert torch.equal(image[:need], general)
     assert not image[need:].any()                                # nothing behind the index is written
@@ -106,7 +109,7 @@ def test_bucket_overrun():
     codes = rng.integers(1, 256, size=(N, M)).astype(np.uint8)
     s = np.arange(N >> 7)
     codes[s * 128 + np.array([mix64(0x2545F4914F6CDD1D ^ int(i)) & 127 for i in s])] = 0
-    compare(codes, T=2)
+    compare(codes, T=2, path=etf.ETF_BUILD_GENERAL_AFTER_CHAIN)
 
 
 def test_wide_buckets():
