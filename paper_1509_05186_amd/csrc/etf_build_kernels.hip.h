@@ -1111,7 +1111,9 @@ template <int KW, int KT, int NT, uint32_t CAP>
 __global__ void __launch_bounds__(NT) k_chain_sort_trees(ChainArgs a, uint32_t place_blocks)
 {
     extern __shared__ uint32_t blds[];
-    if (a.scal->overflow) return;   // (another tree's sort may have set it by now)
+    // Another workgroup of this launch may set the word at any time: one decision for all waves of a workgroup, or those
+    // that go on would read LDS that those that left had yet to write.
+    if (__syncthreads_or(a.scal->overflow != 0)) return;
     const int y = (int)blockIdx.y;
     if (y == a.T - 1) {
         if (blockIdx.x < place_blocks) place_sample<KW, NT>(a, blockIdx.x, place_blocks);

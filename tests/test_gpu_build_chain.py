@@ -112,6 +112,20 @@ def test_bucket_overrun():
     compare(codes, T=2, path=etf.ETF_BUILD_GENERAL_AFTER_CHAIN)
 
 
+@pytest.mark.parametrize("M,T", [(8, 2), (16, 4)])
+def test_bucket_overrun_in_a_tree(M, T):
+    say("build chain: the vectors' buckets hold, those of the last tree do not: M", M, "T", T)
+    rng = np.random.default_rng(10)
+    N, D = 40000, M // T
+    codes = rng.integers(1, 256, size=(N, M)).astype(np.uint8)
+    codes[:, :4] = np.arange(N, dtype=">u4").view(np.uint8).reshape(N, 4)   # all distinct: encoding e is row e
+    s = np.arange(N >> 7)
+    codes[s * 128 + np.array([mix64(0x2545F4914F6CDD1D ^ int(i)) & 127 for i in s]), M - D:] = 0
+    codes = codes[rng.permutation(N)]                              # the vectors' samples are rows like any others
+    compare(codes, T=1)
+    compare(codes, T=T, path=etf.ETF_BUILD_GENERAL_AFTER_CHAIN)
+
+
 def test_wide_buckets():
     say("build chain: more than two million vectors")
     rng = np.random.default_rng(12)
