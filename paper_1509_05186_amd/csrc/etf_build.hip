@@ -636,9 +636,11 @@ template <int KW, int TW> int launch_chain_kt(etf_ctx *ctx, const ChainPlan &P, 
     }
 }
 
-// The build by the chain; `again`: a bucket ran over, nothing of the image is of use and the general path has to build.
+// What the chain did: built the index; nothing; found a bucket too full, with the rows in index order and the ids in the image.
+enum class Chain { BUILT, NOT_RUN, OVERRAN };
+
 int build_chain(etf_ctx *ctx, const uint8_t *codes, int64_t N, const int32_t *ids, int T, const std::vector<int32_t> &cb, char *img,
-                char *ws, const ChainPlan &P, bool &again)
+                char *ws, const ChainPlan &P, Chain &end)
 {
     const int M = ctx->M;
     hipStream_t st = (hipStream_t)ctx->stream;
@@ -671,7 +673,7 @@ int build_chain(etf_ctx *ctx, const uint8_t *codes, int64_t N, const int32_t *id
     int rc;
     if (stage_tables(ctx) != ETF_OK) {   // no pinned memory: the general path does without
         (void)hipGetLastError();
-        again = true;
+        end = Chain::NOT_RUN;
         return ETF_OK;
     }
     a.scal_host = (BuildScal *)ctx->build_stage;
@@ -700,8 +702,8 @@ int build_chain(etf_ctx *ctx, const uint8_t *codes, int64_t N, const int32_t *id
     HIP_TRY(ctx, hipStreamSynchronize(st));
     BuildScal h;
     std::memcpy(&h, a.scal_host, sizeof(h));
-    again = h.overflow != 0;
-    if (again) return ETF_OK;
+    end = h.overflow ? Chain::OVERRAN : Chain::BUILT;
+    if (h.overflow) return ETF_OK;
     if (h.faults & 1u) return fail(ctx, ETF_EINVAL, "a code byte is >= K=%d", ctx->K);
     if (h.faults & 2u) return fail(ctx, ETF_EINVAL, "ids must be non-negative");
     if (h.Nd < 1 || h.Nd > N) return fail(ctx, ETF_EHIP, "device build returned %lld distinct encodings for %lld vectors", (long long)h.Nd, (long long)N);
@@ -730,7 +732,8 @@ int build_chain(etf_ctx *ctx, const uint8_t *codes, int64_t N, const int32_t *id
     return ETF_OK;
 }
 
-int build_impl(etf_ctx *ctx, const uint8_t *codes, int64_t N, const int32_t *ids, int T, const std::vector<int32_t> &cb,
+// rows_placed: the image's array of codes holds the rows in index order already, `codes` is not read
+int build_impl(etf_ctx *ctx, const uint8_t *codes, bool rows_placed, int64_t N, const int32_t *ids, int T, const std::vector<int32_t> &cb,
                char *img, int64_t image_bytes, char *ws, const BuildWs &W)
 {
     const int M = ctx->M, K = ctx->K;
@@ -756,7 +759,9 @@ int build_impl(etf_ctx *ctx, const uint8_t *codes, int64_t N, const int32_t *ids
     if ((rc = put_quantiser(ctx, img))) return rc;
     HIP_TRY(ctx, hipMemsetAsync(scal, 0, 16, st));
     const unsigned nb = blocks(N);
-    if (identity) {
+    if (rows_placed) {
+        // nothing to do
+    } else if (identity) {
         if (d_codes != codes) HIP_TRY(ctx, hipMemcpyAsync(d_codes, codes, (size_t)N * M, hipMemcpyDeviceToDevice, st));
     } else {
         hipLaunchKernelGGL(k_build_permute, dim3(nb), dim3(BT), 0, st, codes, d_codes, N, M, ord);
@@ -955,23 +960,26 @@ extern "C" int etf_index_build_device(etf_ctx *ctx, const uint8_t *codes, int64_
     // The chain places its arrays on the device, so the image has to hold the largest index of these sizes; a smaller
     // image or workspace, or an input whose buckets ran over, is built with every array's place checked on the host.
     const ChainPlan P = plan_chain(ctx, N, T, cb, ids != nullptr);
-    bool again = false;
+    Chain end = Chain::NOT_RUN;
     if (P.ok && workspace_bytes >= P.total && image_bytes >= image_bytes_bound(ctx, N, T, cb.data())) {
         drop_index(ctx);
-        rc = build_chain(ctx, codes, N, ids, T, cb, (char *)image, (char *)workspace, P, again);   // again: a bucket ran over
+        rc = build_chain(ctx, codes, N, ids, T, cb, (char *)image, (char *)workspace, P, end);
         if (rc) {
             (void)hipStreamSynchronize((hipStream_t)ctx->stream);
             drop_index(ctx);
         }
-        if (rc || !again) return rc;
+        if (rc || end == Chain::BUILT) return rc;
     }
+    // (the caller's rows and ids may lie in the image, where the chain has written over them)
+    const bool overran = end == Chain::OVERRAN;
+    if (overran && ids) ids = (const int32_t *)((const char *)image + ctx->lay.ids_in);
     drop_index(ctx);
-    rc = build_impl(ctx, codes, N, ids, T, cb, (char *)image, image_bytes, (char *)workspace, W);
+    rc = build_impl(ctx, codes, overran, N, ids, T, cb, (char *)image, image_bytes, (char *)workspace, W);
     if (rc) {
         (void)hipStreamSynchronize((hipStream_t)ctx->stream);  // nothing of a failed build may still be running in the buffers
         drop_index(ctx);
     }
-    if (!rc && again) ctx->idx.build_path = ETF_BUILD_GENERAL_AFTER_CHAIN;
+    if (!rc && overran) ctx->idx.build_path = ETF_BUILD_GENERAL_AFTER_CHAIN;
     return rc;
 }
 

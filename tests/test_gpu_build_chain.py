@@ -4,7 +4,7 @@ chunks and tiles, for every width of key, with ties everywhere, and on an input 
 import numpy as np
 import pytest
 
-from test_gpu_build import arr, check_image
+from test_gpu_build import arr, check_image, image_arrays
 from test_gpu_parity import say
 
 pytestmark = pytest.mark.gpu
@@ -102,14 +102,63 @@ def mix64(z):
     return z ^ (z >> 31)
 
 
-def test_bucket_overrun():
-    say("build chain: samples that say nothing about the rest, so that one bucket takes nearly all")
+def overrunning_codes():
+    """Samples that say nothing about the rest, so that one bucket takes nearly all."""
     rng = np.random.default_rng(9)
     N, M = 40000, 8
     codes = rng.integers(1, 256, size=(N, M)).astype(np.uint8)
     s = np.arange(N >> 7)
     codes[s * 128 + np.array([mix64(0x2545F4914F6CDD1D ^ int(i)) & 127 for i in s])] = 0
-    compare(codes, T=2, path=etf.ETF_BUILD_GENERAL_AFTER_CHAIN)
+    return codes
+
+
+def test_bucket_overrun():
+    say("build chain: a bucket of the vectors runs over")
+    compare(overrunning_codes(), T=2, path=etf.ETF_BUILD_GENERAL_AFTER_CHAIN)
+
+
+def build_in_place(codes, ids, T, order, at):
+    """The index of codes and ids that lie in the image itself, each at the given array's place."""
+    N, M = codes.shape
+    out = []
+    for inside in (False, True):
+        c = etf.Context(device=0, stream=torch.cuda.current_stream().cuda_stream)
+        c.pq_set_codebooks(np.zeros((M, 256, 1), dtype=np.float32))
+        c.index_set_chunk_order(order)
+        image = torch.zeros(c.index_build_device_bytes(N, T)[0] + 256, dtype=torch.uint8, device="cuda")
+        off = (-image.data_ptr()) % 256
+        image = image[off:image.numel() - 256 + off]
+        given = {"codes": torch.from_numpy(codes).cuda(), "ids": None if ids is None else torch.from_numpy(ids).cuda()}
+        if inside:
+            for name, array in at.items():
+                x = given[name]
+                place = image[getattr(lay, array):][:x.numel() * x.element_size()]
+                place.copy_(x.reshape(-1).view(torch.uint8))
+                given[name] = place.view(x.dtype).view(x.shape)
+        c.index_build_device(given["codes"], ids=given["ids"], T=T, image=image)
+        torch.cuda.synchronize()
+        lay = c.index_layout()
+        out.append((c, image))
+    return out
+
+
+def assert_same_arrays(out, M):
+    (a, ia), (b, ib) = out
+    assert a.index_stats() == b.index_stats()
+    for name, off, nbytes in image_arrays(a.index_layout(), a.index_stats(), M):
+        assert torch.equal(ia[off:off + nbytes], ib[off:off + nbytes]), name
+
+
+@pytest.mark.parametrize("T", [1, 2])
+@pytest.mark.parametrize("with_ids", [False, True])
+def test_bucket_overrun_of_codes_in_the_image(T, with_ids):
+    say("build chain: codes (and ids) at their place in the image, another chunk order, a bucket that runs over: T", T, "ids", with_ids)
+    codes = overrunning_codes()
+    ids = np.random.default_rng(11).permutation(3 * len(codes)).astype(np.int32)[:len(codes)] if with_ids else None
+    at = {"codes": "codes", "ids": "ids_in"} if with_ids else {"codes": "codes"}
+    out = build_in_place(codes, ids, T, [3, 1, 7, 0, 2, 6, 4, 5], at)
+    assert all(c.last_build_path() == etf.ETF_BUILD_GENERAL_AFTER_CHAIN for c, _ in out)
+    assert_same_arrays(out, codes.shape[1])
 
 
 @pytest.mark.parametrize("M,T", [(8, 2), (16, 4)])
