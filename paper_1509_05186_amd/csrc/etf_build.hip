@@ -636,6 +636,11 @@ template <int KW, int TW> int launch_chain_kt(etf_ctx *ctx, const ChainPlan &P, 
     }
 }
 
+bool apart(const void *a, int64_t bytes_a, const void *b, int64_t bytes_b)
+{
+    return (uintptr_t)a + bytes_a <= (uintptr_t)b || (uintptr_t)b + bytes_b <= (uintptr_t)a;
+}
+
 // What the chain did: built the index; nothing; found a bucket too full, with the rows in index order and the ids in the image.
 enum class Chain { BUILT, NOT_RUN, OVERRAN };
 
@@ -649,6 +654,15 @@ int build_chain(etf_ctx *ctx, const uint8_t *codes, int64_t N, const int32_t *id
     const bool identity = shape_index(ctx, N, T, cb, ord);
     const DevLayout &L = ctx->lay;
     compute_layout(ctx);   // the arrays up to ebegin have their places
+    // The chain's first kernel reads rows and ids while others of its threads write the image's and the workspace: inputs
+    // that lie there, unless each is at its own place, are the general path's, which copies one after the other.
+    auto clear = [&](const void *in, int64_t bytes, int64_t own) {
+        return (in == img + own || apart(in, bytes, img + L.codes, L.ids_sorted - L.codes)) && apart(in, bytes, ws, P.total);
+    };
+    if (!clear(codes, N * M, L.codes) || (ids && !clear(ids, N * 4, L.ids_in))) {
+        end = Chain::NOT_RUN;
+        return ETF_OK;
+    }
     auto at = [&](int64_t o) { return (uint32_t *)(ws + o); };
     ChainArgs a;
     a.codes = codes;

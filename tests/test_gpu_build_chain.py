@@ -161,6 +161,23 @@ def test_bucket_overrun_of_codes_in_the_image(T, with_ids):
     assert_same_arrays(out, codes.shape[1])
 
 
+@pytest.mark.parametrize("at,path", [
+    ({"codes": "codes"}, etf.ETF_BUILD_CHAIN),
+    ({"codes": "codes", "ids": "ids_in"}, etf.ETF_BUILD_CHAIN),
+    ({"codes": "ids_in"}, etf.ETF_BUILD_GENERAL),        # over an array that the first kernel writes
+    ({"codes": "ids_sorted"}, etf.ETF_BUILD_CHAIN),      # ... and one that only later ones do
+    ({"ids": "ids_sorted"}, etf.ETF_BUILD_CHAIN),
+])
+def test_inputs_in_the_image(at, path):
+    say("build chain: inputs that lie in the image:", at)
+    rng = np.random.default_rng(13)
+    N = 300007
+    codes = rng.integers(0, 256, size=(N, 8)).astype(np.uint8)
+    out = build_in_place(codes, rng.permutation(N).astype(np.int32) if "ids" in at else None, 2, None, at)
+    assert out[0][0].last_build_path() == etf.ETF_BUILD_CHAIN and out[1][0].last_build_path() == path
+    assert_same_arrays(out, 8)
+
+
 @pytest.mark.parametrize("M,T", [(8, 2), (16, 4)])
 def test_bucket_overrun_in_a_tree(M, T):
     say("build chain: the vectors' buckets hold, those of the last tree do not: M", M, "T", T)
