@@ -12,6 +12,7 @@
 #include <rocprim/device/device_scan.hpp>
 
 #include <algorithm>
+#include <cmath>
 #include <numeric>
 
 #include "etf_internal.h"
@@ -510,6 +511,8 @@ ChainPlan plan_chain(const etf_ctx *ctx, int64_t N, int T, const std::vector<int
     // of 7 words: 143 KB), and the ranks.
     const bool wide = P.KW < 4 && N > ((int64_t)1 << 21);
     if (N > (P.KW < 4 ? (int64_t)1 << 23 : (int64_t)5 << 20)) return P;
+    // (sample sizes beyond 64-bit integers: the host's and the device's conversions disagree about them)
+    if ((double)ctx->opt.sample_scale * std::sqrt((double)N) >= 0x1p62) return P;
     P.nt = wide ? 1024 : 512;
     P.cap = (uint32_t)P.nt * 8;
     P.wshift = wide ? 8 : 7;

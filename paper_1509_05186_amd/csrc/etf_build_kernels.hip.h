@@ -919,11 +919,12 @@ template <int KT> __device__ void count_levels(const ChainArgs &a, int t, uint32
 }
 
 // ---- draws of the threshold sample, the longest id range, the input's faults -------------------------------------
+// sample_size of the host; n_sample_pos is that of N >= Nd vectors, and what the arrays of draws have room for
 __device__ inline uint32_t sample_draws(const ChainArgs &a, uint32_t Nd)
 {
     const int64_t n = (int64_t)((double)a.sample_scale * sqrt((double)Nd));
     const int64_t s = n > a.sample_min ? n : a.sample_min;
-    return (uint32_t)(s < (int64_t)Nd ? s : (int64_t)Nd);
+    return (uint32_t)min(min(s, a.n_sample_pos), (int64_t)Nd);
 }
 
 // the encoding of the vector drawn from stratum s of S0

@@ -22,10 +22,11 @@ def build(c, codes, ids, T, chunk_begin, image_bytes):
     return image
 
 
-def compare(codes, ids=None, T=1, chunk_begin=None, K=256, order=None, sample_min=256, path=etf.ETF_BUILD_CHAIN):
+def compare(codes, ids=None, T=1, chunk_begin=None, K=256, order=None, sample_min=256, sample_scale=120, path=etf.ETF_BUILD_CHAIN):
     N, M = codes.shape
     c = etf.Context(device=0, stream=torch.cuda.current_stream().cuda_stream)
     c.set_option("sample_min", sample_min)
+    c.set_option("sample_scale", sample_scale)
     c.pq_set_codebooks(np.zeros((M, K, 1), dtype=np.float32))
     c.index_set_chunk_order(order)
     d_codes, d_ids = torch.from_numpy(codes).cuda(), None if ids is None else torch.from_numpy(ids).cuda()
@@ -190,6 +191,17 @@ def test_bucket_overrun_in_a_tree(M, T):
     codes = codes[rng.permutation(N)]                              # the vectors' samples are rows like any others
     compare(codes, T=1)
     compare(codes, T=T, path=etf.ETF_BUILD_GENERAL_AFTER_CHAIN)
+
+
+@pytest.mark.parametrize("sample_min,sample_scale,path", [
+    (1, 0, etf.ETF_BUILD_CHAIN),
+    (1 << 40, 120, etf.ETF_BUILD_CHAIN),                 # every vector, every encoding
+    (1, 1 << 40, etf.ETF_BUILD_CHAIN),
+    (256, 1 << 62, etf.ETF_BUILD_GENERAL),               # (times a root: no 64-bit integer)
+])
+def test_sample_sizes(sample_min, sample_scale, path):
+    say("build chain: sample_min", sample_min, "sample_scale", sample_scale)
+    compare(clustered(np.random.default_rng(14), 9001, 8, 256), T=2, sample_min=sample_min, sample_scale=sample_scale, path=path)
 
 
 def test_wide_buckets():
