@@ -491,15 +491,21 @@ struct ChainPlan {
     uint32_t cap = 0, buckets = 0, samples = 0, bstride = 0;
     int lvl_tiles = 0;
     int64_t S0 = 0;                                          // most draws of the threshold sample
-    int64_t grouped, sorted, bounds, bounds_t, smp, smp_t, zero, zero_words, count, count_t, nh, nh0, first, last, nh_t, nh0_t, first_t, last_t, faults, enc_of_rank, leaf,
-        dk, draw, kept, tile_cnt, total = 0;
+    int64_t grouped, sorted, bounds, smp, smp_t, zero, zero_words, count, count_t, nh, nh0, first, last, nh_t, nh0_t, first_t, last_t, faults, leaf, dk, draw,
+        kept, tile_cnt, total = 0;
+    int64_t leaf_t;                                          // words from `grouped` on: tree 1's leaves (its sub-encodings: at 0)
     int64_t rank, rank_t;                                    // words from `zero` on
     int64_t elem_stride, bounds_stride, smp_stride, rank_stride, bucket_stride, key_stride;  // words between two trees
 };
 
 inline int key_words(int D) { return D <= 4 ? 1 : D <= 8 ? 2 : 4; }
 
-ChainPlan plan_chain(const etf_ctx *ctx, int64_t N, int T, const std::vector<int32_t> &cb, bool ids)
+// The chain's workspace stays within the general path's (69 bytes a vector; the smallest builds aside), which an overrun
+// needs anyway: 34 bytes a vector for 8 chunks in two trees, 59 to 65 for 16 in four.  Every further tree takes 16 at
+// least (75 in five, 123 in eight, 258 in sixteen), and such builds are the general path's.
+constexpr int64_t CHAIN_WS_SMALL = 64 << 10;
+
+ChainPlan plan_chain(const etf_ctx *ctx, int64_t N, int T, const std::vector<int32_t> &cb, bool ids, const BuildWs &W_general)
 {
     ChainPlan P;
     int Dmax = 0;
@@ -536,11 +542,21 @@ ChainPlan plan_chain(const etf_ctx *ctx, int64_t N, int T, const std::vector<int
     P.rank_stride = S;
     P.bucket_stride = B;
     P.key_stride = B * P.KT;
-    // the trees' elements lie over the vectors', which nothing reads any more by then
-    P.grouped = take(std::max(N * W, P.elem_stride * (T - 1)));
-    P.sorted = take(std::max(N * W, P.elem_stride * (T - 1)));
-    P.bounds = take(P.bounds_stride / 2);
-    P.bounds_t = take(P.bounds_stride / 2 * (T - 1));
+    // The trees' elements and bounds lie over the vectors', which nothing reads any more by then.  So do, from the kernel of
+    // the encodings on (the vectors' groups are sorted, the trees' not yet there), the encodings of the vectors in order, up
+    // to the draws, and from the leaves' kernel on (the trees' groups are sorted) the trees' sub-encodings and leaves, which
+    // are as many words as their elements.  Tree 0's sub-encodings and leaves stay from the encodings' kernel to the end:
+    // behind the trees' elements and those encodings, where the vectors' leave room.
+    const int64_t grouped_words = std::max(N * W, P.elem_stride * (T - 1));
+    int64_t used = std::max(N, P.elem_stride * (T - 1));
+    P.grouped = take(grouped_words);
+    auto take_behind = [&](int64_t words) {
+        if (used + words > grouped_words) return take(words);
+        used += words;
+        return P.grouped + 4 * (used - words);
+    };
+    P.sorted = take(grouped_words);
+    P.bounds = take(P.bounds_stride / 2 * std::max(1, T - 1));
     P.smp = take(S * W);
     P.smp_t = take(P.smp_stride * (T - 1));
     P.rank = sizeof(BuildScal) / 4;
@@ -558,14 +574,14 @@ ChainPlan plan_chain(const etf_ctx *ctx, int64_t N, int T, const std::vector<int
     P.first_t = take(P.key_stride * (T - 1));
     P.last_t = take(P.key_stride * (T - 1));
     P.faults = take((N + PREP_NT - 1) / PREP_NT);
-    P.enc_of_rank = take(N);
-    P.leaf = take(N * T);
-    P.dk = take(N * T * P.KT);
+    P.dk = take_behind(N * P.KT);
+    P.leaf = take_behind(N);
+    P.leaf_t = N * P.KT;
     P.draw = take(P.S0);
     P.kept = take((P.S0 + DRAW_TILE - 1) / DRAW_TILE);
     P.tile_cnt = take((int64_t)T * P.lvl_tiles * CATS);
     P.total = off;
-    P.ok = true;
+    P.ok = P.total <= std::max(W_general.total, CHAIN_WS_SMALL);
     return P;
 }
 
@@ -701,18 +717,19 @@ int build_chain(etf_ctx *ctx, const uint8_t *codes, int64_t N, const int32_t *id
     a.zero_words = (uint32_t)P.zero_words;
     a.faults = at(P.faults);
     a.s0 = {at(P.grouped), at(P.sorted), (uint16_t *)at(P.bounds), at(P.smp), a.zero + P.rank, at(P.count), at(P.nh), at(P.nh0), at(P.first), at(P.last)};
-    a.st = {at(P.grouped), at(P.sorted), (uint16_t *)at(P.bounds_t), at(P.smp_t), a.zero + P.rank_t, at(P.count_t), at(P.nh_t), at(P.nh0_t), at(P.first_t), at(P.last_t)};
+    a.st = {at(P.grouped), at(P.sorted), (uint16_t *)at(P.bounds), at(P.smp_t), a.zero + P.rank_t, at(P.count_t), at(P.nh_t), at(P.nh0_t), at(P.first_t), at(P.last_t)};
     a.bstride = P.bstride;
     a.elem_stride = P.elem_stride; a.bounds_stride = P.bounds_stride; a.smp_stride = P.smp_stride; a.rank_stride = P.rank_stride;
     a.bucket_stride = P.bucket_stride; a.key_stride = P.key_stride;
-    a.enc_of_rank = at(P.enc_of_rank);
+    a.enc_of_rank = at(P.grouped);
     a.leaf = at(P.leaf);
     a.dk = at(P.dk);
+    a.dk_t = at(P.grouped);
+    a.leaf_t = a.dk_t + P.leaf_t;
     a.draw = at(P.draw);
     a.kept = at(P.kept);
     a.tile_cnt = at(P.tile_cnt);
     a.lvl_tiles = P.lvl_tiles;
-    a.NK = N;
     if (ids) rc = P.KW == 1 ? launch_chain_kt<1, 2>(ctx, P, a) : P.KW == 2 ? launch_chain_kt<2, 2>(ctx, P, a) : launch_chain_kt<4, 2>(ctx, P, a);
     else rc = P.KW == 1 ? launch_chain_kt<1, 1>(ctx, P, a) : P.KW == 2 ? launch_chain_kt<2, 1>(ctx, P, a) : launch_chain_kt<4, 1>(ctx, P, a);
     if (rc) return rc;
@@ -952,7 +969,8 @@ extern "C" int etf_index_build_device_bytes(const etf_ctx *ctx, int64_t N, int T
     rc = plan_ws(ctx, N, W);
     if (rc) return rc;
     *image_bytes = image_bytes_bound(ctx, N, T, cb.data());
-    *workspace_bytes = std::max(W.total, plan_chain(ctx, N, T, cb, true).total);
+    const ChainPlan P = plan_chain(ctx, N, T, cb, true, W);
+    *workspace_bytes = std::max(W.total, P.ok ? P.total : 0);
     return ETF_OK;
 }
 
@@ -976,7 +994,7 @@ extern "C" int etf_index_build_device(etf_ctx *ctx, const uint8_t *codes, int64_
     if (workspace_bytes < W.total) return fail(ctx, ETF_ENOMEM, "workspace too small: %lld < %lld", (long long)workspace_bytes, (long long)W.total);
     // The chain places its arrays on the device, so the image has to hold the largest index of these sizes; a smaller
     // image or workspace, or an input whose buckets ran over, is built with every array's place checked on the host.
-    const ChainPlan P = plan_chain(ctx, N, T, cb, ids != nullptr);
+    const ChainPlan P = plan_chain(ctx, N, T, cb, ids != nullptr, W);
     Chain end = Chain::NOT_RUN;
     if (P.ok && workspace_bytes >= P.total && image_bytes >= image_bytes_bound(ctx, N, T, cb.data())) {
         drop_index(ctx);

@@ -188,13 +188,15 @@ struct ChainArgs {
     SortBufs s0, st;                  // the vectors; tree 1 (tree t: t - 1 strides further)
     int64_t elem_stride, bounds_stride, smp_stride, rank_stride, bucket_stride, key_stride;
     uint32_t *enc_of_rank;            // [N] distinct encoding of the i-th vector in sorted order
-    uint32_t *leaf;                   // [T][N] leaf of every distinct encoding
-    uint32_t *dk;                     // [T][N] KT words: the distinct sub-encodings of every tree
+    uint32_t *leaf, *leaf_t;          // [N] leaf of every distinct encoding: tree 0; tree 1 (further ones: as elem_stride)
+    uint32_t *dk, *dk_t;              // [N] KT words: the distinct sub-encodings of tree 0; of tree 1 (likewise)
     uint32_t *draw, *kept;            // [S0] encodings drawn for the sample, [tiles] draws kept
     uint32_t *tile_cnt;               // [T][tiles][CATS]
     int lvl_tiles;
-    int64_t NK;                       // elements between the leaf / dk arrays of two trees
 };
+
+__device__ __forceinline__ uint32_t *tree_leaf(const ChainArgs &a, int t) { return t == 0 ? a.leaf : a.leaf_t + (t - 1) * a.elem_stride; }
+__device__ __forceinline__ uint32_t *tree_dk(const ChainArgs &a, int t) { return t == 0 ? a.dk : a.dk_t + (t - 1) * a.elem_stride; }
 
 __device__ __forceinline__ SortBufs tree_bufs(const ChainArgs &a, int t)
 {
@@ -895,7 +897,7 @@ template <int KT> __device__ void count_levels(const ChainArgs &a, int t, uint32
     const uint32_t U = a.scal->U[t], lane = threadIdx.x & 63;
     if (tile * (uint32_t)LVL_TILE >= U) return;
     const int c0 = a.cb[t], D = a.cb[t + 1] - c0;
-    const uint32_t *dk = a.dk + (int64_t)t * a.NK * KT;
+    const uint32_t *dk = tree_dk(a, t);
     if (threadIdx.x < CATS) acc[threadIdx.x] = 0;
     __syncthreads();
     const Subs<KT> s = load_subs<KT>(dk, tile, U, D);
@@ -1136,7 +1138,7 @@ __global__ void __launch_bounds__(NT) k_chain_leaves(ChainArgs a)
     const SortBufs s = tree_bufs(a, t);
     const BucketPlace pl = bucket_place<KT, NT>(s, B, blockIdx.x, 0);
     if (blockIdx.x == 0 && threadIdx.x == 0) a.scal->U[t] = pl.tot;
-    uint32_t *leaf = a.leaf + (int64_t)t * a.NK, *dk = a.dk + (int64_t)t * a.NK * KT;
+    uint32_t *leaf = tree_leaf(a, t), *dk = tree_dk(a, t);
     bucket_walk<KT, 1, NT>(s, blockIdx.x, 0, pl, [&](uint32_t, const Elem<KT, 1> &x, bool head, uint32_t rank, bool, uint32_t) {
         leaf[x.tail] = rank - 1;
         if (head) key_store<KT>(dk + (int64_t)(rank - 1) * KT, x.key);
@@ -1162,7 +1164,7 @@ template <int KT> __device__ void write_levels(const ChainArgs &a, int t, uint32
     const uint32_t U = a.scal->U[t], lane = threadIdx.x & 63;
     if (tile * (uint32_t)LVL_TILE >= U) return;
     const int D = a.cb[t + 1] - a.cb[t];
-    const Subs<KT> s = load_subs<KT>(a.dk + (int64_t)t * a.NK * KT, tile, U, D);
+    const Subs<KT> s = load_subs<KT>(tree_dk(a, t), tile, U, D);
     load_counts(a.scal, scal);
     if (threadIdx.x < CATS) pre[threadIdx.x] = 0;
     if (threadIdx.x == LVL_NT - 1) {
@@ -1261,7 +1263,7 @@ template <int KW> __device__ void write_encodings(const ChainArgs &a, uint32_t b
         const Key<KW> k = key_part<KW, KW>(key_of_row<KW>(ecodes, e, a.M, a.M == 4 * KW), 0, D0);
         key_write_front<KW>(rec0 + (int64_t)e * a.rstride0, k >> (8 * (dc - D0)), words);
         if (a.T > 1)
-            for (int t = 0; t < a.T; ++t) ((uint32_t *)(a.img + leaf_of[t]))[e] = a.leaf[(int64_t)t * a.NK + e];
+            for (int t = 0; t < a.T; ++t) ((uint32_t *)(a.img + leaf_of[t]))[e] = tree_leaf(a, t)[e];
     }
 }
 

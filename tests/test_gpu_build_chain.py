@@ -62,7 +62,7 @@ def test_sizes(N):
 @pytest.mark.parametrize("M,T,chunk_begin", [
     (1, 1, None), (2, 2, None), (3, 1, None), (4, 1, None), (4, 2, None), (4, 4, None),       # keys of one word
     (5, 1, None), (7, 2, [0, 1, 7]), (8, 1, None), (8, 4, None), (8, 8, None), (8, 3, [0, 5, 6, 8]),   # two words
-    (9, 1, None), (11, 2, [0, 9, 11]), (12, 3, None), (16, 1, None), (16, 2, None), (16, 4, None), (16, 16, None), (16, 2, [0, 1, 16]),
+    (9, 1, None), (11, 2, [0, 9, 11]), (12, 3, None), (16, 1, None), (16, 2, None), (16, 4, None), (16, 5, [0, 4, 8, 12, 14, 16]), (16, 16, None), (16, 2, [0, 1, 16]),
 ])
 @pytest.mark.parametrize("with_ids", [False, True])
 def test_shapes(M, T, chunk_begin, with_ids):
@@ -71,7 +71,21 @@ def test_shapes(M, T, chunk_begin, with_ids):
     N, K = 20011, 200
     codes = clustered(rng, N, M, K)
     ids = np.sort(rng.integers(0, 50, N).astype(np.int32) * 1000)[::-1].copy() if with_ids else None   # equal ids: positions decide
-    compare(codes, ids, T, chunk_begin, K=K, order=list(rng.permutation(M)) if M in (7, 12) else None)
+    path = etf.ETF_BUILD_CHAIN if T <= 4 else etf.ETF_BUILD_GENERAL     # (more trees: the chain would need more workspace)
+    compare(codes, ids, T, chunk_begin, K=K, order=list(rng.permutation(M)) if M in (7, 12) else None, path=path)
+
+
+@pytest.mark.parametrize("N", [1 << 16, 1000003, (1 << 21) + 1, 5 << 20, 1 << 23, (1 << 23) + 1])
+def test_workspace_is_that_of_the_general_path(N):
+    say("build chain: workspace for N", N)
+    c = etf.Context(device=0)
+    want = None
+    for M, T, chunk_begin in [(4, 1, None), (4, 4, None), (8, 2, None), (8, 3, [0, 5, 6, 8]), (8, 4, None), (8, 8, None), (16, 1, None),
+                              (16, 2, [0, 1, 16]), (16, 4, None), (16, 5, [0, 4, 8, 12, 14, 16]), (16, 16, None)]:
+        c.pq_set_codebooks(np.zeros((M, 256, 1), dtype=np.float32))
+        got = c.index_build_device_bytes(N, T, chunk_begin)[1]
+        want = want or got
+        assert got == want and got <= 70 * N, (M, T)      # (the general path's does not depend on the shape)
 
 
 @pytest.mark.parametrize("kind", ["equal", "sorted", "descending", "two", "last_byte"])
