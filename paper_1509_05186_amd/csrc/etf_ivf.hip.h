@@ -770,18 +770,20 @@ __device__ __forceinline__ void ivf_setup_lists(const IvfScanArgs &a, int64_t q,
 }
 
 // bytes of dynamic LDS of the two kernels below: tables, list bookkeeping, (scan only) the histogram
-// The histogram's bins: exponent and four mantissa bits of the distance (6 % wide), from 2^-64 to 2^64; what lies below
-// counts in the first, above in the last.  (All 256 exponents take 16 KiB, which left room for six workgroups on a CU;
-// with 8 KiB it is eight, all the waves it holds.)
-constexpr int IVF_BINS = 2048, IVF_BIN_SHIFT = 19, IVF_BIN_FIRST = (127 - 64) << 4;
-__device__ __forceinline__ int ivf_bin(float d)
+// The histogram's bins: exponent and four mantissa bits of the distance (6 % wide), half of the exponents, from `first`
+// on; what lies below counts in the first bin, above in the last.  (All 256 exponents take 16 KiB, which left room for six
+// workgroups on a CU; with 8 KiB it is eight, all the waves it holds.)  The scan starts with 2^-64 to 2^64 and counts again
+// with the lower or the upper half where an end bin holds the k-th distance among many.
+constexpr int IVF_BINS = 2048, IVF_BIN_SHIFT = 19;
+constexpr int IVF_FIRST_LOW = 0, IVF_FIRST_MIDDLE = (127 - 64) << 4, IVF_FIRST_HIGH = IVF_BINS;
+__device__ __forceinline__ int ivf_bin(float d, int first)
 {
-    return min(max((int)(__float_as_uint(d) >> IVF_BIN_SHIFT) - IVF_BIN_FIRST, 0), IVF_BINS - 1);
+    return min(max((int)(__float_as_uint(d) >> IVF_BIN_SHIFT) - first, 0), IVF_BINS - 1);
 }
 // the largest float (as bits) of a bin; everything passes the last one's
-__device__ __forceinline__ uint32_t ivf_bin_edge(int b)
+__device__ __forceinline__ uint32_t ivf_bin_edge(int b, int first)
 {
-    return b == IVF_BINS - 1 ? 0x7F800000u : ((uint32_t)(IVF_BIN_FIRST + b + 1) << IVF_BIN_SHIFT) - 1u;
+    return b == IVF_BINS - 1 ? 0x7F800000u : ((uint32_t)(first + b + 1) << IVF_BIN_SHIFT) - 1u;
 }
 __host__ __device__ inline size_t ivf_lds_bytes(int M, int K, int w, bool hist)
 {
@@ -810,8 +812,10 @@ __global__ __launch_bounds__(256, 8) void k_ivf_scan(IvfScanArgs a)
     float *s_base = reinterpret_cast<float *>(s_lo + a.w + 1);
     uint32_t *hist = reinterpret_cast<uint32_t *>(s_base + a.w + 1);
     __shared__ uint32_t s_part[4];
-    __shared__ uint32_t s_tau, s_cnt;
+    __shared__ uint32_t s_fill, s_cnt;
+    __shared__ int s_bin;
     constexpr int NB = IVF_BINS;
+    int first = IVF_FIRST_MIDDLE;
     const int64_t q = blockIdx.x;
     for (int i = threadIdx.x; i < a.M * a.K; i += 256) tab[i] = a.lut[q * a.M * a.K + i];
     for (int i = threadIdx.x; i < NB; i += 256) hist[i] = 0;
@@ -833,7 +837,7 @@ __global__ __launch_bounds__(256, 8) void k_ivf_scan(IvfScanArgs a)
     }
     for (;;) {
         ivf_walk<CM, CK>(a, tab, s_off, s_lo, s_base, nbound, [&](uint32_t e, float d) {
-            atomicAdd(&hist[ivf_bin(d)], min(a.ebegin[e + 1] - a.ebegin[e], (uint32_t)a.k));
+            atomicAdd(&hist[ivf_bin(d, first)], min(a.ebegin[e + 1] - a.ebegin[e], (uint32_t)a.k));
         });
         __syncthreads();
         // the bin in which the running count of vectors reaches k (thread t owns bins [t * NB/256, (t+1) * NB/256))
@@ -849,7 +853,7 @@ __global__ __launch_bounds__(256, 8) void k_ivf_scan(IvfScanArgs a)
                 if (lane >= dlt) inc += up;
             }
             if (lane == 63) s_part[wave] = inc;
-            if (threadIdx.x == 0) s_tau = 0x7F800000u;  // fewer than k vectors in the lists: everything passes
+            if (threadIdx.x == 0) s_bin = -1;  // fewer than k vectors in the lists: everything passes
             __syncthreads();
             uint32_t below = inc - part;
             for (int t2 = 0; t2 < wave; ++t2) below += s_part[t2];
@@ -860,11 +864,22 @@ __global__ __launch_bounds__(256, 8) void k_ivf_scan(IvfScanArgs a)
                     if (below + h >= (uint32_t)a.k) break;
                     below += h;
                 }
-                s_tau = ivf_bin_edge((int)threadIdx.x * PER + b);
+                s_bin = (int)threadIdx.x * PER + b;
+                s_fill = below + hist[threadIdx.x * PER + b];
             }
             __syncthreads();
         }
-        const uint32_t tau = s_tau;
+        const int bin = __builtin_amdgcn_readfirstlane(s_bin);
+        // An end bin with many more than k up to it tells nothing: the data's scale is outside the bins (all entries would
+        // pass, and the query go to the exact kernel: ten times the time).  A few distances of zero do not count again.
+        if (first == IVF_FIRST_MIDDLE && (bin == 0 || bin == NB - 1) && s_fill > min(4u * (uint32_t)a.k, a.C)) {
+            first = bin == 0 ? IVF_FIRST_LOW : IVF_FIRST_HIGH;
+            __syncthreads();
+            for (int i = threadIdx.x; i < NB; i += 256) hist[i] = 0;
+            __syncthreads();
+            continue;
+        }
+        const uint32_t tau = bin < 0 ? 0x7F800000u : ivf_bin_edge(bin, first);
         ivf_walk<CM, CK>(a, tab, s_off, s_lo, s_base, a.w, [&](uint32_t e, float d) {
             const uint32_t bits = __float_as_uint(d);
             if (bits <= tau) {
@@ -876,6 +891,7 @@ __global__ __launch_bounds__(256, 8) void k_ivf_scan(IvfScanArgs a)
         if (nbound == a.w || s_cnt <= a.C) break;
         __syncthreads();
         nbound = a.w;
+        first = IVF_FIRST_MIDDLE;
         for (int i = threadIdx.x; i < NB; i += 256) hist[i] = 0;
         if (threadIdx.x == 0) s_cnt = 0;
         __syncthreads();

@@ -235,6 +235,29 @@ def test_ivf_distances_at_the_ends_of_the_histogram(e, M, K):
     assert torch.equal(got_i, want_i) and torch.equal(got_d.double() * 2.0 ** (-2 * e), want_d.double())
 
 
+@pytest.mark.parametrize("e", [-52, -40, -34, 32, 40, 52])
+def test_ivf_scan_bounds_distances_of_any_scale(e):
+    """The scan's bound tells distances apart whatever their scale: no query more goes to the exact kernel, also where the
+    bound is taken from all lists at once, and results stay the same numbers times a power of two."""
+    say("IVFADC: queries through the exact kernel, data scaled by 2 **", e)
+    p = IvfProblem(d=32, M=8, K=256, cells=40, N=20000, Q=130, seed=36)
+    f = np.float32(2.0 ** e)
+    for k, w, factor in ((40, 30, 16), (1, 8, 16), (7, 40, 0)):
+        got = []
+        for s in (np.float32(1), f):
+            c = etf.Context(device=0, stream=torch.cuda.current_stream().cuda_stream)
+            c.set_option("ivf_bound_factor", factor)
+            c.pq_set_codebooks(p.cb * s)
+            c.ivf_set_coarse(p.cent * s)
+            c.ivf_build(p.cells, p.codes, None)
+            c.ivf_upload()
+            ids, dist = c.ivf_search(torch.from_numpy(p.q * s).cuda(), k, w)
+            torch.cuda.synchronize()
+            got.append((ids, dist.double() / float(s) ** 2, c.last_fallback_count()))
+        assert torch.equal(got[1][0], got[0][0]) and torch.equal(got[1][1], got[0][1])
+        assert got[0][2] == 0 and got[1][2] == 0
+
+
 @pytest.mark.parametrize("cells", [4, 1020, 1028, 8188, 8192, 8196])
 def test_ivf_probe_selection_at_the_ends_of_held_rows(cells):
     """Rows of distances that are held in registers (at most 8192 cells, a multiple of four) and the first one that is not,
