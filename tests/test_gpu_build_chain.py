@@ -22,12 +22,12 @@ def build(c, codes, ids, T, chunk_begin, image_bytes):
     return image
 
 
-def compare(codes, ids=None, T=1, chunk_begin=None, K=256, order=None, sample_min=256, sample_scale=120, path=etf.ETF_BUILD_CHAIN):
+def compare(codes, ids=None, T=1, chunk_begin=None, K=256, order=None, sample_min=256, sample_scale=120, path=etf.ETF_BUILD_CHAIN, numpy=True):
     N, M = codes.shape
     c = etf.Context(device=0, stream=torch.cuda.current_stream().cuda_stream)
     c.set_option("sample_min", sample_min)
     c.set_option("sample_scale", sample_scale)
-    c.pq_set_codebooks(np.zeros((M, K, 1), dtype=np.float32))
+    c.pq_set_codebooks(np.random.default_rng(M).standard_normal((M, K, 1)).astype(np.float32))   # in the image: also compared
     c.index_set_chunk_order(order)
     d_codes, d_ids = torch.from_numpy(codes).cuda(), None if ids is None else torch.from_numpy(ids).cuda()
     bound = c.index_build_device_bytes(N, T, chunk_begin)[0]
@@ -35,7 +35,8 @@ def compare(codes, ids=None, T=1, chunk_begin=None, K=256, order=None, sample_mi
     assert c.last_build_path() == path
     need, stats = c.index_device_bytes(), c.index_stats()
     want_codes = codes if order is None else codes[:, order]
-    check_image(c, image, np.ascontiguousarray(want_codes), ids)
+    if numpy:
+        check_image(c, image, np.ascontiguousarray(want_codes), ids)
     general = build(c, d_codes, d_ids, T, chunk_begin, need)     # below the bound: every array's place checked on the host
     assert c.last_build_path() == (etf.ETF_BUILD_GENERAL if need < bound else path)   # (the smallest indexes are as large as their bound)
     assert c.index_device_bytes() == need and c.index_stats() == stats
@@ -223,3 +224,40 @@ def test_wide_buckets():
     rng = np.random.default_rng(12)
     N = (1 << 21) + 4099
     compare(clustered(rng, N, 8, 256), T=2, sample_min=32768)
+
+
+@pytest.mark.parametrize("N,M,T,with_ids,path", [
+    ((1 << 21) + 4099, 4, 2, False, etf.ETF_BUILD_CHAIN),       # wide buckets of the other widths of key, and with ids
+    ((1 << 21) + 4099, 4, 4, True, etf.ETF_BUILD_CHAIN),
+    ((1 << 21) + 4099, 8, 2, True, etf.ETF_BUILD_CHAIN),
+    (1 << 23, 8, 4, True, etf.ETF_BUILD_CHAIN),                 # the largest of the chain's, and the first that are not
+    ((1 << 23) + 1, 8, 2, False, etf.ETF_BUILD_GENERAL),
+    (5 << 20, 16, 4, True, etf.ETF_BUILD_CHAIN),
+    (5 << 20, 16, 1, False, etf.ETF_BUILD_CHAIN),
+    ((5 << 20) + 1, 16, 2, True, etf.ETF_BUILD_GENERAL),
+])
+def test_large_builds(N, M, T, with_ids, path):
+    say("build chain, large: N", N, "M", M, "T", T, "ids", with_ids)
+    rng = np.random.default_rng(N % 1009 + M)
+    codes = clustered(rng, N, M, 256)
+    ids = rng.permutation(N).astype(np.int32) if with_ids else None
+    compare(codes, ids, T=T, sample_min=32768, path=path, numpy=False)
+
+
+def test_other_codebooks_on_the_same_context():
+    say("build chain: codebooks set again between builds of one context, also of another shape")
+    rng = np.random.default_rng(15)
+    c = etf.Context(device=0, stream=torch.cuda.current_stream().cuda_stream)
+    for M, ds in ((8, 2), (8, 2), (4, 9), (8, 33), (16, 1), (8, 2)):
+        cb = rng.standard_normal((M, 256, ds)).astype(np.float32)
+        codes = torch.from_numpy(rng.integers(0, 256, size=(3001, M)).astype(np.uint8)).cuda()
+        c.pq_set_codebooks(cb)
+        bound = c.index_build_device_bytes(3001, 2)[0]
+        image = build(c, codes, None, 2, None, bound)
+        assert c.last_build_path() == etf.ETF_BUILD_CHAIN
+        fresh = etf.Context(device=0, stream=torch.cuda.current_stream().cuda_stream)
+        fresh.pq_set_codebooks(cb)
+        general = build(fresh, codes, None, 2, None, c.index_device_bytes())
+        assert fresh.last_build_path() == etf.ETF_BUILD_GENERAL
+        assert torch.equal(image[:general.numel()], general)
+        assert np.array_equal(arr(image, c.index_layout().codebooks, cb.size, np.float32), cb.reshape(-1))
