@@ -339,9 +339,9 @@ int etf_pq_encode_device(etf_ctx *ctx, const float *x, int64_t n, uint8_t *codes
 /* Index build on the device (paper: "Efficient Encoding Tree Construction":
  * Algorithm 1 — the in-place lexicographic sort of the encoded dataset and the
  * tree from the common prefixes of consecutive sorted encodings — built in
- * parallel, as the closing remark of that section suggests: radix sort, then per
- * level one flag pass over the neighbours' common prefix lengths, a prefix sum that
- * numbers the nodes, and a scatter).  Same arguments and the same index as
+ * parallel, as the closing remark of that section suggests: a sort of the encodings,
+ * then per level the neighbours' common prefix lengths, running counts that number
+ * the nodes, and a scatter).  Same arguments and the same index as
  * etf_index_build, except:
  *   codes   [N][M] u8, DEVICE (for example the output of etf_pq_encode_device)
  *   ids     [N] non-negative, DEVICE, or NULL for ids = position
@@ -353,15 +353,19 @@ int etf_pq_encode_device(etf_ctx *ctx, const float *x, int64_t n, uint8_t *codes
  *           array at its largest: as many distinct encodings as vectors); the
  *           build uses etf_index_device_bytes() of it, known afterwards, and
  *           returns ETF_ENOMEM as soon as an array does not fit a smaller buffer
- *   workspace  device scratch, 256-byte aligned, at least *workspace_bytes; free
- *           to reuse when the call returns
+ *   workspace  device scratch, 256-byte aligned, at least *workspace_bytes (69 bytes a
+ *           vector, whatever the shape); free to reuse when the call returns
  * The image has the layout of etf_index_layout, array for array what
  * etf_index_build + etf_index_upload produce, except the two threshold samples
  * (one row from each of n_sample equal strata here; which rows are sampled
  * changes no result).  etf_index_export and etf_index_upload return ETF_ESTATE:
  * the host holds no copy.
- * Synchronises the stream several times (the counts that size the arrays come
- * back to the host).  On any error the context holds no index. */
+ * The counts that size the arrays come back to the host once, at the end, for up to
+ * 2^23 vectors (5 * 2^20 of more than 8 chunks) in up to four trees of like width (the
+ * arrays of that way have to fit the workspace), with an image of *image_bytes at
+ * least; else one by one.  The stream is synchronised each time.  The first build after
+ * the codebooks were set lays out a copy of them in pinned host memory, which the context
+ * keeps until it is destroyed.  On any error the context holds no index. */
 int etf_index_build_device_bytes(const etf_ctx *ctx, int64_t N, int T, const int32_t *chunk_begin,
                                  int64_t *image_bytes, int64_t *workspace_bytes);
 int etf_index_build_device(etf_ctx *ctx, const uint8_t *codes, int64_t N, const int32_t *ids, int T,

@@ -1,9 +1,11 @@
 // Index build on the device (Algorithm 1; the remark on building in parallel that closes "Efficient Encoding Tree
 // Construction"): the lexicographic sort of the encodings, the merge of repeated encodings into id ranges, every
 // tree's level arrays from the longest common prefixes of neighbouring sorted (sub-)encodings, and the threshold
-// samples.  The sorts and the prefix sums are rocPRIM's device-wide radix sort and scan; everything around them is
-// kernels of this file.  The image has the layout the host builder's has (the same layout function, fed with the
-// counts as they come back from the device), so the two are interchangeable byte for byte, samples aside.
+// samples.  Two ways: the chain of kernels of etf_build_kernels.hip.h, whose counts stay on the device until its end, and
+// the general path (larger builds, smaller images, what the chain hands back), whose sorts and prefix sums are rocPRIM's
+// device-wide radix sort and scan with kernels of this file around them and counts that come back one by one.  The image
+// has the layout the host builder's has (the same layout function, fed with the counts), so the two are interchangeable
+// byte for byte, samples aside.
 #include <cstring>
 
 #include <hip/hip_runtime.h>
@@ -512,9 +514,14 @@ ChainPlan plan_chain(const etf_ctx *ctx, int64_t N, int T, const std::vector<int
     for (int t = 0; t < T; ++t) Dmax = std::max(Dmax, cb[t + 1] - cb[t]);
     P.KW = key_words(ctx->M);
     P.KT = key_words(Dmax);
-    // Beyond 2 M vectors the samples' ranks (quadratic in their number) are the larger part, and elements of at most 4
-    // words go in buckets of twice the size.  The limits: the splitters and counts of one level of buckets in LDS (5120
-    // of 7 words: 143 KB), and the ranks.
+    // Beyond 2^21 vectors the samples' ranks (quadratic in their number) are the larger part, and elements of at most 4
+    // words go in buckets of twice the size.  us with the narrow / the wide buckets, 8 chunks in two trees: 309 / 326 for
+    // 1.0 M vectors, 513 / 521 for 2.0 M, 675 / 648 for 2.5 M, 1115 / 1002 for 4 M; 4 chunks in one: 291 / 323 for 2.0 M, 380 / 388
+    // for 2.5 M, 583 / 544 for 4 M.  (With ids the wide ones are ahead from 1.5 M on, by 5 %.)
+    // The chain ends where the splitters and counts of one level of buckets fill the LDS of the kernels that deal (5120
+    // buckets of 7 words: 143 KB; 4096 of 5: 82, twice that is more than there is).  It is ahead of the general path up to
+    // there: 2358 against 4827 us for 2^23 vectors of 8 chunks in two trees, 4557 against 7900 for 5 * 2^20 of 16 in four,
+    // and as far down as it goes (10 000: 138 against 681).
     const bool wide = P.KW < 4 && N > ((int64_t)1 << 21);
     if (N > (P.KW < 4 ? (int64_t)1 << 23 : (int64_t)5 << 20)) return P;
     // (sample sizes beyond 64-bit integers: the host's and the device's conversions disagree about them)

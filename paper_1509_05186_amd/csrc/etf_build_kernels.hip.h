@@ -16,8 +16,9 @@
 // by their launches and their passes over memory; this is four launches and three passes.
 //
 // A million vectors of 8 chunks in two trees: 1180 us with device-wide library sorts and scans and eleven counts that
-// came back to the host between 90 launches, 266 by the chain (10 000: 627 -> 136, five million: 3255 -> 1292; a
-// million of 16 chunks in four trees: 2764 -> 578).
+// came back to the host between 90 launches, 268 by the chain (10 000: 627 -> 136, five million: 3255 -> 1292; a
+// million of 16 chunks in four trees: 2764 -> 578).  The first build after the codebooks were set also lays out their
+// copy in pinned memory: 60 to 90 us more.
 
 // ---- keys and elements ------------------------------------------------------------------------------------------
 
@@ -99,7 +100,7 @@ template <int KW, int KT> __device__ __forceinline__ Key<KT> key_part(Key<KW> k,
 // chunk j of a key
 template <int KW> __device__ __forceinline__ uint8_t key_chunk(Key<KW> k, int j) { return (uint8_t)(k >> (8 * (4 * KW - 1 - j))); }
 
-// The bytes of a key in order, from the front of `words` words (zeros behind the key's own).
+// The first 4 `words` bytes of a key in order (`words` at most the key's).
 template <int KW> __device__ __forceinline__ void key_write_front(uint8_t *dst, Key<KW> k, int words)
 {
     uint32_t *d = (uint32_t *)dst;
@@ -477,10 +478,11 @@ __global__ void __launch_bounds__(CLS_NT) k_chain_classify(ChainArgs a, uint32_t
 // ---- a bucket sorted in LDS --------------------------------------------------------------------------------------
 // The workgroup gathers its group of every tile and sorts by sampling once more: every eighth element is a splitter,
 // elements are dealt into the parts between them, about eight to a part, and an element's rank in its part is counted
-// against all others there.  58 us for a million elements of 12 bytes, bound by latency (two dependent reads of memory,
+// against all others there.  58 us for a million elements of 12 bytes, the gather included, bound by latency (two dependent reads of memory,
 // some thirty of LDS, ten barriers: 50 000 clocks for a workgroup with two others on its CU) and comparisons: a third of
-// the issue slots.  (Merging sorted runs pairwise, eight rounds of twenty dependent reads each, took 51 us for a million elements;
-// with LDS for 2048 elements and the larger buckets in two halves 91, the halves of a single bucket one after the other.)
+// the issue slots.  (Merging sorted runs pairwise, eight rounds of twenty dependent reads each, took 51 us for a million
+// elements that lay side by side, in slabs whose filling took 40 us more than the tiles' groups do; with LDS for 2048
+// elements and the larger buckets in two halves 91, the halves of a single bucket one after the other.)
 // Words lie in W separate arrays.
 template <int KW, int TW> __device__ __forceinline__ Elem<KW, TW> lds_elem(const uint32_t *lds, uint32_t stride, uint32_t i)
 {

@@ -799,7 +799,10 @@ __host__ __device__ inline size_t ivf_lds_bytes(int M, int K, int w, bool hist)
 //     Bound by the latency of the entries' loads and of the table gathers, so by the waves in flight: eight workgroups per
 // CU (18 KiB of LDS at M = 8, K = 256 and w = 64, at most 64 vector and 96 scalar registers; M and K as template constants
 // keep the general walker's predicates out of the scalar registers).  With six workgroups, and running sums by one
-// thread, 10 000 queries took 677 us here and 1106 in all, 559 and 962 with eight.
+// thread, 10 000 queries took 677 us here and 1106 in all, 559 and 962 with eight.  The general instance spills scalar
+// registers to lanes of a vector register under the same limit and is still ahead of six workgroups: 10 000 queries,
+// 32 of 2048 cells, whole searches: M = 8, K = 100 1125 -> 974 us, K = 64 1110 -> 964; K = 256, M = 4 1455 -> 1254, M = 16
+// 1926 -> 1511; M = 5, K = 200 1980 -> 1736.
 //     grid (queries), block 256, dynamic LDS ivf_lds_bytes(..., true).
 // ------------------------------------------------------------------------------------------------
 template <int CM, int CK>
