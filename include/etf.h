@@ -106,6 +106,10 @@ const char *etf_last_error(const etf_ctx *ctx);
  *   "matrix_filter"   the 16-bit filter pass runs on the matrix cores where chunks have at most 8 dimensions, the batch
  *                     fills its blocks of 128 queries and has at least this many (query, distinct encoding) pairs
  *                     (default 2^29, twice that at M = 8; -1: never).  Same results
+ *   "prune_filter"    from this many (query, distinct encoding) pairs a search on 16-bit tables (squared distances, a workspace of
+ *                     etf_workspace_bytes) of at least 2048 queries and a clustered index puts its queries in the order of
+ *                     their nearest codewords and leaves out, for every group of them, the parts of the tree that hold
+ *                     nothing at or below a query's bound (default 2^31; 0: wherever it can; -1: never).  Same results
  *   "lds_blocks"      workgroups per sub-tile of queries in the LDS-resident kernels (0 = chosen by the
  *                     library from the number of sub-tiles and items; for experiments)
  *   "metric"          0 (default): squared Euclidean distance.  1: scalar product (the paper notes, after

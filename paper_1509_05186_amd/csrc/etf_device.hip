@@ -10,6 +10,7 @@
 #include "etf_internal.h"
 #include "etf_kernels.hip.h"
 #include "etf_ctx_kernels.hip.h"
+#include "etf_prune_kernels.hip.h"
 
 using namespace etf;
 
@@ -187,7 +188,11 @@ struct Plan {
     bool flat_lds = false;    // flat mode through the same kernels
     bool fx = false;          // the main pass of the LDS-resident search filters candidates in fixed point
     bool fx16 = false;        // ... on 16-bit tables (k_lds16)
+    bool prune = false;       // ... on queries in the order of their nearest codewords, and on the parts of the index that a group of them needs
+    int shift = 0, nblk = 0;  // the index in blocks of 2^shift x 64 encodings
+    int near_blocks = 0, near_wgs = 1;  // blocks a closer bound is taken from, by that many workgroups
     int64_t o_counter = 0, o_lutT = 0, o_gmin = 0, o_tau = 0, o_bm = 0, o_cnt = 0, o_flag = 0, o_cand = 0;
+    int64_t o_keys = 0, o_perm = 0, o_sorted = 0, o_span = 0, o_list = 0, o_kind = 0, o_count = 0, o_near = 0, o_units = 0, o_least = 0, o_state = 0;
     int64_t o_part[ETF_MAX_M][ETF_MAX_M];
     int64_t o_leafp[ETF_MAX_M];
     int64_t total = 0;
@@ -203,10 +208,12 @@ int pow2_at_least_host(int n)
 int tmax_class(int T);
 int pick_G(int width, int K);
 bool lds_eligible(int M, int K, int T, const int32_t *chunk_begin);
+void plan_prune(const etf_ctx *ctx, int64_t Q, bool ws_cap_given, Plan &P);
 
 int make_plan(const etf_ctx *ctx, int64_t Q, int k, int mode, bool search, Plan &P, int64_t ws_cap = 0)
 {
-    if (ws_cap <= 0) ws_cap = ctx->opt.ws_cap_bytes;
+    const bool ws_cap_given = ws_cap > 0;
+    if (!ws_cap_given) ws_cap = ctx->opt.ws_cap_bytes;
     const HostIndex &ix = ctx->idx;
     if (!ix.built) return fail(ctx, ETF_ESTATE, "no index: call etf_index_build first");
     if (Q <= 0) return fail(ctx, ETF_EINVAL, "Q must be positive");
@@ -269,6 +276,7 @@ int make_plan(const etf_ctx *ctx, int64_t Q, int k, int mode, bool search, Plan 
     // 16-bit tables: built for rows of 64 and 32 bytes (M = 8 and M = 16 at K = 256); other shapes keep the float32 sums
     P.fx16 = search && P.lds_path && P.use_tau && ctx->opt.lds_filter == 2 && !ctx->opt.force_fallback && !ix.has_term &&
              (M == 8 || M == 16) && std::max(2, pick_G(M, K)) == (M == 8 ? 4 : 8);
+    if (P.fx16) plan_prune(ctx, Q, ws_cap_given, P);
     P.ctx_path = !P.lds_path && tmax_class(ix.T) != 0 && mode != ETF_MODE_FLAT && ctx->opt.traversal != 1;
     for (int t = 1; t < ix.T; ++t)  // the register-context kernels address a tree's result table with 32-bit offsets
         if (ix.tree[t].U >= ((int64_t)1 << 24)) P.ctx_path = false;
@@ -280,9 +288,11 @@ int make_plan(const etf_ctx *ctx, int64_t Q, int k, int mode, bool search, Plan 
                 for (int l = 0; l + 1 < tr.D; ++l) per_tile += al256(tr.nI[l] * QT * 4);
             per_tile += al256(tr.U * QT * 4);
         }
+    const int64_t gmin_row = P.prune ? std::max<int64_t>(P.gstride, 1024 * P.near_wgs) : P.gstride;
     if (search) {
-        if (P.use_tau) per_tile += al256(P.gstride * QT * 4);
+        if (P.use_tau) per_tile += al256(gmin_row * QT * 4);
         per_tile += (int64_t)QT * (12 + (int64_t)P.C * 8);
+        if (P.prune) per_tile += (int64_t)QT * (ctx->d * 4 + 6 + 16) + (int64_t)(M / 4) * (3 * (int64_t)P.nblk + 36);
     }
     int64_t nt = ws_cap / std::max<int64_t>(per_tile + 4096, 1);
     P.NT = std::max<int64_t>(1, std::min<int64_t>(nt, P.tiles_total));
@@ -303,12 +313,26 @@ int make_plan(const etf_ctx *ctx, int64_t Q, int k, int mode, bool search, Plan 
             P.o_leafp[t] = take(P.NT * tr.U * QT * 4);
         }
     if (search) {
-        if (P.use_tau) P.o_gmin = take(P.NT * P.gstride * QT * 4);
+        if (P.use_tau) P.o_gmin = take(P.NT * gmin_row * QT * 4);
         P.o_tau = take(P.NT * QT * 4);
         P.o_bm = take(P.NT * M * QT * 4);
         P.o_cnt = take(P.NT * QT * 4);
         P.o_flag = take(P.NT * QT * 4);
         P.o_cand = take(P.NT * QT * (int64_t)P.C * 8);
+        if (P.prune) {
+            const int64_t subs = P.NT * (M / 4);  // sub-tiles of 32 queries at M = 8, 16 at M = 16
+            P.o_keys = take(P.NT * QT * 2);
+            P.o_perm = take(P.NT * QT * 4);
+            P.o_sorted = take(P.NT * QT * ctx->d * 4);
+            P.o_span = take((int64_t)P.nblk * 8);
+            P.o_list = take(subs * P.nblk * 2);
+            P.o_kind = take(subs * P.nblk);
+            P.o_count = take(subs * 4);
+            P.o_near = take(subs * 16);
+            P.o_units = take((subs + 1024) * 16);  // a whole number for every sub-tile, 1024 or fewer beside
+            P.o_least = take(P.NT * QT * 16);
+            P.o_state = take((2 + (P.NT * QT + MM_Q - 1) / MM_Q) * 4);
+        }
     }
     P.total = off;
     return ETF_OK;
@@ -690,6 +714,58 @@ bool lds_eligible(int M, int K, int T, const int32_t *chunk_begin)
     return M % lds_chunks_per_line(G) == 0;  // whole lines of 4 (8 at eight queries per sub-tile) chunks
 }
 
+// Whether a batch's queries are put in order and the index is pruned for them (etf_prune_kernels.hip.h).  What that costs grows with the
+// queries (0.25 ms for 10 000: order, two prunings, the second bound), what it saves with the pairs of query and encoding and with how
+// clustered the encodings are.  Of that the tree's second level tells: a clustered database has few of the two-chunk prefixes
+// that independent chunks would have (64 to 4096 overlapping clusters: 0.05 to 0.25; one Gaussian 0.4 to 1, where nothing can be
+// left out), up to half of them where a large one has filled in the clusters' edges, and then many vectors share an encoding.
+// On 1033 random problems (N up to 4 million, 2048 to 10 000 queries, k up to 500, 6 to 120 dimensions a chunk)
+// this rule took 390: between 3.9 times and 0.96 times as fast, half of them at least 1.8 times; without its lines for k and the pairs
+// the worst took 1.4 times as long (k of 400 in 270 000 encodings).
+void plan_prune(const etf_ctx *ctx, int64_t Q, bool ws_cap_given, Plan &P)
+{
+    const HostIndex &ix = ctx->idx;
+    const Options &opt = ctx->opt;
+    // a workspace of a given size (etf_search_static) has no room for the lists; the experiments' options mean the plain walk
+    if (opt.prune_filter < 0 || ws_cap_given || opt.lds_blocks > 0 || opt.lds16_context == 0 || opt.metric != 0) return;
+    if (ix.Nd >= ((int64_t)1 << 26) || ix.Nd < 64) return;  // (candidate records and byte offsets of records; whole blocks)
+    if (opt.prune_filter > 0) {
+        if (Q < 2048 || ix.Nd < ((int64_t)1 << 18) || ix.Nd < 3000 * (int64_t)P.k || (double)Q * (double)ix.Nd < (double)opt.prune_filter) return;
+        const HostTree &t0 = ix.tree[0];
+        if (t0.D < 2) return;
+        const double prefixes = (double)(t0.nI[1] + t0.nL[1] + t0.nL[0]), pairs = (double)ix.K * ix.K;
+        if (prefixes > ((double)ix.Nd <= 0.75 * (double)ix.N ? 0.5 : 0.25) * pairs * -std::expm1(-(double)ix.Nd / pairs)) return;
+    }
+    P.prune = true;
+    while ((ix.Nd + ((int64_t)64 << P.shift) - 1) / ((int64_t)64 << P.shift) > PRUNE_BLOCKS) ++P.shift;
+    P.nblk = (int)((ix.Nd + ((int64_t)64 << P.shift) - 1) / ((int64_t)64 << P.shift));
+    const int64_t Qs = ix.M == 8 ? 32 : 16, subs = (std::min<int64_t>(Q, 1 << 16) + Qs - 1) / Qs;
+    // The bound's sample only has to find the neighbourhood: a 64th of the index will do, at least a quarter of the sample (its
+    // order is scattered: a part of it is a sample too).  The bound itself comes from the nearest blocks.
+    const int64_t near = std::max<int64_t>(16384, P.S * 3 / 8), groups = std::max<int64_t>(P.ngroups, 1);
+    const int64_t first = std::min(P.S, std::max(ix.Nd / 128, P.S / 8));
+    const int64_t gsize = std::max<int64_t>(1, (first + groups - 1) / groups), ngroups = (first + gsize - 1) / gsize;
+    if (ngroups >= std::min<int64_t>(P.ngroups, 2 * P.k)) {
+        P.S = first;
+        P.gsize = (int)gsize;
+        P.ngroups = ngroups;
+        P.gstride = (ngroups + 63) & ~(int64_t)63;
+    }
+    // a query to whose neighbours that does not lead keeps the sample's bound: room for twice the candidates it lets through
+    const double expect = 1.3 * (double)P.k * (double)ix.Nd / (double)P.S * std::min(8.0, (double)ix.N / (double)ix.Nd);
+    while (ctx->opt.cand_cap == 0 && P.C < 2.0 * expect + 2048.0 && P.C < (1u << 17)) P.C <<= 1;
+    P.near_blocks = (int)std::max<int64_t>(1, near >> (6 + P.shift));
+    // 1024 minima a workgroup, and enough of them for k to lie in different ones
+    int64_t best = -1;
+    for (int wgs = P.k <= 400 ? 1 : P.k <= 800 ? 2 : 4; wgs <= 4; wgs *= 2) {
+        const int64_t cost = ((subs * wgs + 255) / 256) * (5000 + near / wgs) + subs * wgs * 100;  // (and k_tau's time)
+        if (best < 0 || cost < best) {
+            best = cost;
+            P.near_wgs = wgs;
+        }
+    }
+}
+
 template <int MODE, bool CTX, bool FX = false, bool TERM = false>
 int launch_lds(etf_ctx *ctx, const Plan &P, char *ws, const uint32_t *rec, int64_t nitems, const uint32_t *map, int T,
                int64_t tiles, OutArgs o, int cls)
@@ -782,18 +858,116 @@ int launch_lds16(etf_ctx *ctx, const Plan &P, char *ws, const uint32_t *rec, int
     const bool cx = ctx->opt.lds16_context != 0;
     if (M == 8 && cx) {
         if ((rc = set_lds(ctx, k_lds16<4, 2, true>, lds))) return rc;
-        hipLaunchKernelGGL((k_lds16<4, 2, true>), grid, dim3(1024), lds, st, rec, nitems, lutT, K, per_block, o);
+        hipLaunchKernelGGL((k_lds16<4, 2, true>), grid, dim3(1024), lds, st, rec, nitems, lutT, K, per_block, o, ListArgs{});
     } else if (M == 8) {
         if ((rc = set_lds(ctx, k_lds16<4, 2, false>, lds))) return rc;
-        hipLaunchKernelGGL((k_lds16<4, 2, false>), grid, dim3(1024), lds, st, rec, nitems, lutT, K, per_block, o);
+        hipLaunchKernelGGL((k_lds16<4, 2, false>), grid, dim3(1024), lds, st, rec, nitems, lutT, K, per_block, o, ListArgs{});
     } else if (M == 16 && cx) {
         if ((rc = set_lds(ctx, k_lds16<8, 4, true>, lds))) return rc;
-        hipLaunchKernelGGL((k_lds16<8, 4, true>), grid, dim3(1024), lds, st, rec, nitems, lutT, K, per_block, o);
+        hipLaunchKernelGGL((k_lds16<8, 4, true>), grid, dim3(1024), lds, st, rec, nitems, lutT, K, per_block, o, ListArgs{});
     } else if (M == 16) {
         if ((rc = set_lds(ctx, k_lds16<8, 4, false>, lds))) return rc;
-        hipLaunchKernelGGL((k_lds16<8, 4, false>), grid, dim3(1024), lds, st, rec, nitems, lutT, K, per_block, o);
+        hipLaunchKernelGGL((k_lds16<8, 4, false>), grid, dim3(1024), lds, st, rec, nitems, lutT, K, per_block, o, ListArgs{});
     } else {
         return fail(ctx, ETF_EINVAL, "no 16-bit filter kernel for M=%d", M);
+    }
+    LAUNCH_CHECK(ctx, "k_lds16");
+    return ETF_OK;
+}
+
+// the queries of a batch in the order of their nearest codewords, and the prefixes at the ends of the index's blocks
+int launch_order(etf_ctx *ctx, const Plan &P, char *ws, const float *queries, int64_t nq, int64_t tiles)
+{
+    const DevLayout &L = ctx->lay;
+    hipStream_t st = (hipStream_t)ctx->stream;
+    uint8_t *keys = reinterpret_cast<uint8_t *>(ws + P.o_keys);
+    uint32_t *perm = reinterpret_cast<uint32_t *>(ws + P.o_perm);
+    ChunkOrder ord;
+    for (int j = 0; j < ETF_MAX_M; ++j) ord.src[j] = (uint8_t)((size_t)j < ctx->idx.order.size() ? ctx->idx.order[j] : j);
+    ProfScope prof(ctx, ETF_K_LUT);
+    hipLaunchKernelGGL(k_order_keys, dim3((unsigned)tiles, 2), dim3(1024), 0, st, queries, nq, tiles * QT, ctx->d, ctx->ds, ctx->K,
+                       reinterpret_cast<const float *>(ctx->dev_base + L.codebooks), ord, keys);
+    LAUNCH_CHECK(ctx, "k_order_keys");
+    hipLaunchKernelGGL(k_order_sort, dim3(1), dim3(1024), 0, st, keys, nq, tiles * QT, perm, reinterpret_cast<uint32_t *>(ws + P.o_state),
+                       (int)(2 + (nq + MM_Q - 1) / MM_Q));
+    LAUNCH_CHECK(ctx, "k_order_sort");
+    hipLaunchKernelGGL(k_order_gather, dim3((unsigned)((nq + 3) / 4 + (P.nblk + 255) / 256)), dim3(256), 0, st, queries, nq, ctx->d, perm,
+                       reinterpret_cast<float *>(ws + P.o_sorted), reinterpret_cast<const uint8_t *>(ctx->dev_base + L.ecodes), ctx->idx.Nd,
+                       ctx->M, P.shift, P.nblk, reinterpret_cast<uint2 *>(ws + P.o_span));
+    LAUNCH_CHECK(ctx, "k_order_gather");
+    return ETF_OK;
+}
+
+// what every sub-tile needs of the index (mm: k_mm16 runs behind, and leaves it the blocks of queries that need little)
+int launch_prune(etf_ctx *ctx, const Plan &P, char *ws, const OutArgs &o, int64_t nql, uint32_t *loose, bool again)
+{
+    PruneArgs a;
+    memset(&a, 0, sizeof a);
+    a.lutT = reinterpret_cast<const float *>(ws + P.o_lutT);
+    a.tau = o.tau;
+    a.least = reinterpret_cast<float *>(ws + P.o_least);
+    a.nql = nql;
+    a.again = again;
+    a.span = reinterpret_cast<const uint2 *>(ws + P.o_span);
+    a.nblk = P.nblk;
+    a.M = ctx->M;
+    a.K = ctx->K;
+    a.nq = o.nq;
+    a.near_blocks = P.near_blocks;
+    a.kind = reinterpret_cast<uint8_t *>(ws + P.o_kind);
+    a.list = reinterpret_cast<uint16_t *>(ws + P.o_list);
+    a.count = reinterpret_cast<uint32_t *>(ws + P.o_count);
+    a.near = reinterpret_cast<uint4 *>(ws + P.o_near);
+    a.state = reinterpret_cast<uint32_t *>(ws + P.o_state) + 2;
+    a.loose = loose;
+    a.mm_share = ctx->M == 8 ? 0.7f : 0.55f;
+    hipStream_t st = (hipStream_t)ctx->stream;
+    ProfScope prof(ctx, ETF_K_TAU);
+    const int Qs = ctx->M == 8 ? 32 : 16;
+    const dim3 grid((unsigned)((o.nq + Qs - 1) / Qs));
+    if (Qs == 32) hipLaunchKernelGGL(k_prune<32>, grid, dim3(1024), 0, st, a);
+    else hipLaunchKernelGGL(k_prune<16>, grid, dim3(1024), 0, st, a);
+    LAUNCH_CHECK(ctx, "k_prune");
+    return ETF_OK;
+}
+
+// the closer bound's minima (WALK_NEAR), or the filter pass over the parts of the index that k_prune has kept (WALK_KEPT)
+template <int WALK>
+int launch_lds16_list(etf_ctx *ctx, const Plan &P, char *ws, const uint32_t *rec, int64_t nitems, OutArgs o)
+{
+    const int M = ctx->M, K = ctx->K;
+    const int G = M == 8 ? 4 : 8;
+    const size_t lds = lds_table_bytes(G, M, K) + lds16_aux_bytes();
+    ListArgs la;
+    memset(&la, 0, sizeof la);
+    la.list = reinterpret_cast<const uint16_t *>(ws + P.o_list);
+    la.near = reinterpret_cast<const uint4 *>(ws + P.o_near);
+    la.units = reinterpret_cast<const uint4 *>(ws + P.o_units);
+    la.state = reinterpret_cast<uint32_t *>(ws + P.o_state);
+    la.nblk = P.nblk;
+    la.shift = P.shift;
+    const int subs = (int)((o.nq + 128 / G - 1) / (128 / G));
+    la.ebegin = reinterpret_cast<const uint32_t *>(ctx->dev_base + ctx->lay.ebegin);
+    la.gmin = o.gmin;
+    la.gstride = 1024 * P.near_wgs;
+    // the filter: a workgroup per CU takes unit after unit
+    const dim3 grid = WALK == WALK_NEAR ? dim3((unsigned)P.near_wgs, (unsigned)subs) : dim3(256);
+    const float *lutT = reinterpret_cast<const float *>(ws + P.o_lutT);
+    hipStream_t st = (hipStream_t)ctx->stream;
+    ProfScope prof(ctx, WALK == WALK_NEAR ? ETF_K_SAMPLE : ETF_K_LDS16);
+    if (WALK == WALK_KEPT) {
+        hipLaunchKernelGGL(k_units, dim3(1), dim3(1024), 0, st, reinterpret_cast<const uint32_t *>(ws + P.o_count), subs, 64 << P.shift, o.done,
+                           MM_Q / (128 / G), la.state, reinterpret_cast<uint4 *>(ws + P.o_units));
+        LAUNCH_CHECK(ctx, "k_units");
+    }
+    constexpr bool cx = WALK == WALK_KEPT;  // (without the context at M = 16: option lds16_context)
+    int rc;
+    if (M == 8) {
+        if ((rc = set_lds(ctx, k_lds16<4, 2, cx, WALK>, lds))) return rc;
+        hipLaunchKernelGGL((k_lds16<4, 2, cx, WALK>), grid, dim3(1024), lds, st, rec, nitems, lutT, K, 0, o, la);
+    } else {
+        if ((rc = set_lds(ctx, k_lds16<8, 4, false, WALK>, lds))) return rc;
+        hipLaunchKernelGGL((k_lds16<8, 4, false, WALK>), grid, dim3(1024), lds, st, rec, nitems, lutT, K, 0, o, la);
     }
     LAUNCH_CHECK(ctx, "k_lds16");
     return ETF_OK;
@@ -853,18 +1027,22 @@ int launch_mm16(etf_ctx *ctx, const float *queries, const uint32_t *rec, int64_t
 }
 
 // the bound of every query from its sample groups' minima (and the per-query state of the passes behind it)
-int launch_tau(etf_ctx *ctx, const Plan &P, const OutArgs &o, int64_t nql, uint32_t *flag, uint32_t *counter, const LooseArgs &la)
+// (tighter: the minima of the nearest blocks, beside the bound that is there)
+int launch_tau(etf_ctx *ctx, const Plan &P, const OutArgs &o, int64_t nql, uint32_t *flag, uint32_t *counter, const LooseArgs &la, bool tighter = false)
 {
     ProfScope prof(ctx, ETF_K_TAU);
     const dim3 grid((unsigned)((nql + 3) / 4)), block(256);
     hipStream_t st = (hipStream_t)ctx->stream;
     float *tau = const_cast<float *>(o.tau);
-    const int S = (int)P.ngroups;
-#define TAU_CASE(NV) hipLaunchKernelGGL(k_tau<NV>, grid, block, 0, st, o.gmin, S, o.gstride, P.k, o.nq, nql, tau, o.cnt, flag, counter, la)
-    if (S <= 256) TAU_CASE(4);
-    else if (S <= 1024) TAU_CASE(16);
-    else if (S <= 2048) TAU_CASE(32);
-    else TAU_CASE(64);
+    const int S = tighter ? 1024 * P.near_wgs : (int)P.ngroups;
+    const int64_t gstride = tighter ? S : o.gstride;
+#define TAU_CASE(NV) \
+    if (tighter) hipLaunchKernelGGL((k_tau<NV, true>), grid, block, 0, st, o.gmin, S, gstride, P.k, o.nq, nql, tau, o.cnt, flag, counter, la); \
+    else hipLaunchKernelGGL((k_tau<NV, false>), grid, block, 0, st, o.gmin, S, gstride, P.k, o.nq, nql, tau, o.cnt, flag, counter, la)
+    if (S <= 256) { TAU_CASE(4); }
+    else if (S <= 1024) { TAU_CASE(16); }
+    else if (S <= 2048) { TAU_CASE(32); }
+    else { TAU_CASE(64); }
 #undef TAU_CASE
     LAUNCH_CHECK(ctx, "k_tau");
     return ETF_OK;
@@ -1259,7 +1437,15 @@ static int search_impl(etf_ctx *ctx, const float *queries, int64_t Q, int k, int
         uint32_t *cnt = reinterpret_cast<uint32_t *>(w + P.o_cnt);
         uint32_t *flag = reinterpret_cast<uint32_t *>(w + P.o_flag);
         uint64_t *cand = reinterpret_cast<uint64_t *>(w + P.o_cand);
-        rc = launch_lut(ctx, queries, Q, q0, tiles, lutT, nullptr);
+        const float *bq = queries + q0 * ctx->d;  // the batch's queries, in the order of its tables
+        if (P.prune) {
+            rc = launch_order(ctx, P, w, bq, nq, tiles);
+            if (rc) return rc;
+            bq = reinterpret_cast<const float *>(w + P.o_sorted);
+            rc = launch_lut(ctx, bq, nq, 0, tiles, lutT, nullptr);
+        } else {
+            rc = launch_lut(ctx, queries, Q, q0, tiles, lutT, nullptr);
+        }
         if (rc) return rc;
         float *bm = nullptr;
         if (ctx->opt.metric == 1) {  // the selection orders non-negative values, smallest first
@@ -1300,7 +1486,7 @@ static int search_impl(etf_ctx *ctx, const float *queries, int64_t Q, int k, int
             o.done = margins + 2 * nql;
             o.blocks = (int)((nql + MM_Q - 1) / MM_Q);
             la.loose = o.done + o.blocks;
-            la.queries = queries + q0 * ctx->d;
+            la.queries = bq;
             la.mean = reinterpret_cast<const float *>(ctx->dev_base + L.cb_mean);
             la.d = ctx->d;
             // an expected two thirds of the candidate list, in encodings of the sample and in groups that hold one of them (a third
@@ -1339,14 +1525,25 @@ static int search_impl(etf_ctx *ctx, const float *queries, int64_t Q, int k, int
                 rc = launch_tau(ctx, P, o, nql, flag, clear, la);
                 if (rc) return rc;
             }
+            if (P.prune) {
+                rc = launch_prune(ctx, P, w, o, nql, nullptr, false);
+                if (rc) return rc;
+                rc = launch_lds16_list<WALK_NEAR>(ctx, P, w, ecodes, ix.Nd, o);
+                if (rc) return rc;
+                rc = launch_tau(ctx, P, o, nql, flag, nullptr, LooseArgs{}, true);
+                if (rc) return rc;
+                rc = launch_prune(ctx, P, w, o, nql, la.loose, true);
+                if (rc) return rc;
+            }
             if (mm) {
-                rc = launch_mm16(ctx, queries + q0 * ctx->d, ecodes, ix.Nd, nql, o, la, counter + 1);
+                rc = launch_mm16(ctx, bq, ecodes, ix.Nd, nql, o, la, counter + 1);
                 if (rc) return rc;
             }
             if (flat)
                 rc = launch_flat<OUT_FILTER>(ctx, P, w, ix.N, nullptr, tiles, o);
             else if (P.lds_path)
-                rc = P.fx16 ? launch_lds16(ctx, P, w, ecodes, ix.Nd, tiles, o)
+                rc = P.prune ? launch_lds16_list<WALK_KEPT>(ctx, P, w, ecodes, ix.Nd, o)
+                    : P.fx16 ? launch_lds16(ctx, P, w, ecodes, ix.Nd, tiles, o)
                     : P.fx ? launch_lds<OUT_FILTER, true, true>(ctx, P, w, ecodes, ix.Nd, nullptr, ix.T, tiles, o, ETF_K_LDS)
                     : ix.has_term ? launch_lds<OUT_FILTER, true, false, true>(ctx, P, w, ecodes, ix.Nd, nullptr, ix.T, tiles, o, ETF_K_LDS)
                                   : launch_lds<OUT_FILTER, true>(ctx, P, w, ecodes, ix.Nd, nullptr, ix.T, tiles, o, ETF_K_LDS);
@@ -1365,6 +1562,7 @@ static int search_impl(etf_ctx *ctx, const float *queries, int64_t Q, int k, int
         sa.k = k;
         sa.out_ids = out_ids + q0 * k;
         sa.out_dist = out_dist + q0 * k;
+        sa.perm = P.prune ? reinterpret_cast<const uint32_t *>(w + P.o_perm) : nullptr;
         sa.flag = flag;
         sa.bm = bm;
         // fixed-point candidates: rounding moves a sum by at most M units (truncated entries) plus 2^-24 relative per
@@ -1417,6 +1615,7 @@ static int search_impl(etf_ctx *ctx, const float *queries, int64_t Q, int k, int
         ea.k = k;
         ea.out_ids = sa.out_ids;
         ea.out_dist = sa.out_dist;
+        ea.perm = sa.perm;
         ea.bm = bm;
         {
             ProfScope prof(ctx, ETF_K_EXACT);

@@ -418,6 +418,9 @@ extern "C" int etf_set_option(etf_ctx *ctx, const char *name, int64_t value)
     } else if (n == "matrix_filter") {
         if (value < -1) return fail(ctx, ETF_EINVAL, "matrix_filter is a number of pairs, or -1");
         ctx->opt.matrix_filter = value;
+    } else if (n == "prune_filter") {
+        if (value < -1) return fail(ctx, ETF_EINVAL, "prune_filter is a number of pairs, or -1");
+        ctx->opt.prune_filter = value;
     } else if (n == "lds_blocks") {
         if (value < 0 || value > 65535) return fail(ctx, ETF_EINVAL, "lds_blocks out of range");
         ctx->opt.lds_blocks = value;

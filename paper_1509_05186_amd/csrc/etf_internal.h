@@ -125,6 +125,7 @@ struct Options {
     int64_t cand_cap = 0;
     int64_t traversal = 2;  // 0: distance context in registers, 1: level-synchronous kernels, 2: searches with all tables in LDS
     int64_t matrix_filter = (int64_t)1 << 29;  // (query, encoding) pairs from which k_mm16 filters (-1: never)
+    int64_t prune_filter = (int64_t)1 << 31;  // (query, encoding) pairs from which queries are ordered and the index pruned (0: always, -1: never)
     int lds16_context = 1;  // k_lds16 keeps a distance context of two levels (1) or looks every chunk up (0)
     int64_t lds_blocks = 0; // workgroups per sub-tile of queries in the LDS-resident search kernel (0: chosen by the library)
     int64_t metric = 0;     // 0: squared Euclidean distance (smallest first), 1: scalar product (largest first)

@@ -1779,7 +1779,7 @@ __host__ __device__ inline size_t lds_aux_bytes(bool filter) { return filter ? (
 constexpr size_t LDS_SAMPLE_BYTES = 16 * 64 * 16;  // sample mode with shared stretches: a partial minimum per lane
 // k_lds16: a ring entry is a lane's eight results (16 bytes) and a word that says whose they are
 constexpr int LDS16_RING = 76;
-__host__ __device__ inline size_t lds16_aux_bytes() { return (size_t)16 * LDS16_RING * 20 + 2 * 16 * 64 * 4; }
+__host__ __device__ inline size_t lds16_aux_bytes() { return (size_t)16 * LDS16_RING * 20 + 2 * 16 * 64 * 4 + 16; }
 
 typedef __attribute__((address_space(3))) const vecq lds_vecq_t;
 
@@ -2236,17 +2236,34 @@ __device__ __forceinline__ bool find_share(uint32_t wg, uint32_t wgs, int blocks
 //     is ordered and returned (see SelectArgs::fx_margin).
 //     Geometry, item walk, distance context and line layout are those of k_lds<G> (rows of 64 or 32 bytes, lines
 //     of 256 bytes, chunk order rotated per lane group); a sub-tile has 128 / G queries.
+//     WALK_KEPT: the blocks of 64 encodings that a sub-tile's list names, unit after unit of the work that k_units has cut.  The next
+//     block's records are requested a block ahead (as many pairs a second as the walk of everything; without that, and with the
+//     units cut here instead of in a launch, which cost 79 scalar registers too many, 0.6 of it).  WALK_NEAR: the least sums of the
+//     nearest blocks, for k_tau.
 //     grid (blocks, G / 2, tiles), or, behind k_mm16, (workgroups) for the sub-tiles of the blocks that it has not done
-//     (find_share); block 1024, dynamic LDS lds_table_bytes(G) + lds16_aux_bytes(); G in {4, 8}.
+//     (find_share), or (256) for WALK_KEPT, (workgroups per sub-tile, sub-tiles) for WALK_NEAR; block 1024, dynamic LDS
+//     lds_table_bytes(G) + lds16_aux_bytes(); G in {4, 8}.
 // ------------------------------------------------------------------------------------------------
 typedef unsigned short u16x8 __attribute__((ext_vector_type(8)));
 typedef __attribute__((address_space(3))) const u16x8 lds_u16x8_t;
 
 __host__ __device__ constexpr int fx16_cap_bits(int M) { return M <= 4 ? 14 : M <= 8 ? 13 : 12; }
 
-template <int G, int M4, bool CTX>
+enum { WALK_ALL = 0, WALK_KEPT = 1, WALK_NEAR = 2 };
+struct ListArgs {
+    const uint16_t *list;   // [sub-tiles][nblk] kept blocks of 2^shift x 64 encodings, nearest first (k_prune)
+    int nblk, shift;
+    const uint4 *units;     // WALK_KEPT: sub-tile, part of its list
+    uint32_t *state;        // WALK_KEPT: the number of units, the next one to take
+    const uint4 *near;      // WALK_NEAR: [sub-tiles] blocks of the list to take all of, the number of those to take some of, how many of them
+    const uint32_t *ebegin; // WALK_NEAR: id range of every encoding
+    float *gmin;            // WALK_NEAR: [tiles*64][gstride] a query's minima, one for each of 64 positions in a block and wave
+    int64_t gstride;
+};
+
+template <int G, int M4, bool CTX, int WALK = WALK_ALL>
 __global__ __launch_bounds__(1024) void k_lds16(const uint32_t *__restrict__ rec, int64_t nitems, const float *__restrict__ lutT,
-                                                int K, int per_block, OutArgs o)
+                                                int K, int per_block, OutArgs o, ListArgs la)
 {
     constexpr int M = 4 * M4, Qs = 2 * WAVE / G, V = 8, LPI = Qs / V, IPS = WAVE / LPI;
     constexpr int CPL = lds_chunks_per_line(G), NG = M / CPL, U = M4 >= 4 ? 2 : 4, RING = LDS16_RING;
@@ -2263,7 +2280,31 @@ __global__ __launch_bounds__(1024) void k_lds16(const uint32_t *__restrict__ rec
     uint32_t(*wcount)[64] = reinterpret_cast<uint32_t(*)[64]>(aux + 16 * RING * 20);
     uint32_t(*wpos)[64] = reinterpret_cast<uint32_t(*)[64]>(aux + 16 * RING * 20 + 16 * 64 * 4);
     int tile = blockIdx.z, sub = blockIdx.y, share = blockIdx.x;
-    if (o.done) {
+    const int lane = threadIdx.x & 63;
+    const int w = uniform(threadIdx.x >> 6), nw = blockDim.x >> 6;
+    constexpr bool LIST = WALK != WALK_ALL;
+    uint4 near = make_uint4(0u, 0u, 0u, 0u);
+    uint32_t from = 0u, to = 0u, cs = 0u;  // the part of the list of sub-tile cs
+    for (;;) {  // (once, or once per unit)
+    if (WALK == WALK_KEPT) {
+        uint32_t *ticket = reinterpret_cast<uint32_t *>(aux + 16 * RING * 20 + 2 * 16 * 64 * 4);
+        if (threadIdx.x == 0) *ticket = atomicAdd(&la.state[1], 1u);
+        __syncthreads();
+        const uint32_t u = (uint32_t)uniform((int)*ticket);
+        if (u >= la.state[0]) return;
+        const uint4 unit = la.units[u];
+        cs = (uint32_t)uniform((int)unit.x);
+        from = (uint32_t)uniform((int)unit.y);
+        to = (uint32_t)uniform((int)unit.z);
+        tile = (int)cs / (QT / Qs);
+        sub = (int)cs % (QT / Qs);
+    } else if (WALK == WALK_NEAR) {
+        cs = blockIdx.y;
+        tile = (int)cs / (QT / Qs);
+        sub = (int)cs % (QT / Qs);
+        near = la.near[cs];
+        to = near.x + near.z;
+    } else if (o.done) {
         const uint32_t taken = o.done[2 * o.blocks];
         if (taken == (uint32_t)o.blocks) return;
         // a sub-tile of Qs queries: the nth of its block's that hold a query
@@ -2277,8 +2318,6 @@ __global__ __launch_bounds__(1024) void k_lds16(const uint32_t *__restrict__ rec
         share = s.share;
         per_block = (int)((nitems + s.shares - 1) / s.shares);
     }
-    const int lane = threadIdx.x & 63;
-    const int w = uniform(threadIdx.x >> 6), nw = blockDim.x >> 6;
     wcount[w][lane] = 0u;
     // ---- stage the sub-tile's tables as 16-bit entries: piece p of row (m, k) holds queries 8p .. 8p+7
     {
@@ -2351,7 +2390,7 @@ __global__ __launch_bounds__(1024) void k_lds16(const uint32_t *__restrict__ rec
         }
         return *reinterpret_cast<lds_u32v4_t *>(__builtin_amdgcn_perm(src, pb[g][t], sh[g == 0 ? 0 : 1][t]));
     };
-    const int64_t blo = (int64_t)share * per_block;
+    const int64_t blo = LIST ? 0 : (int64_t)share * per_block;
     const int64_t bhi = min(nitems, blo + per_block);
     // the largest sum that may pass, plus one, per query of this lane
     u16x8 tp1;
@@ -2414,6 +2453,167 @@ __global__ __launch_bounds__(1024) void k_lds16(const uint32_t *__restrict__ rec
         }
         held += n;
     };
+    uint32_t prev0 = 0u;
+    u32v4 top = 0u;
+    // U steps of the wave: records dw, step u live in this lane if alive(u) (`whole`: in all lanes); item(u) is the item's number,
+    // `start` the walk's first step.  (The walk of a list has one copy of this: two of them spill at M = 16.)
+    auto evaluate = [&](const uint32_t (&dw)[U][M4], bool start, bool whole, auto check, auto alive, auto item) {
+        constexpr bool CHECK = decltype(check)::value;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const bool live = !CHECK || alive(u);
+            bool fast = false;
+            if (CTX) {
+                const bool differs = live && ((dw[u][0] ^ prev0) & 0xFFFFu) != 0u;
+                fast = __ballot(differs) == 0ull && !(start && u == 0);
+                prev0 = dw[u][0];
+            }
+            if (!CTX || !fast) top = look(dw[u], 0, 0) + look(dw[u], 0, 1);
+            u32v4 d = top;
+            {
+                // the remaining M - 2 entries, two at a time
+                u32v4 e[M - 2];
+#pragma unroll
+                for (int j = 2; j < M; ++j) e[j - 2] = look(dw[u], j / CPL, j % CPL);
+#pragma unroll
+                for (int j = 0; j < M - 2; j += 2) d = d + e[j] + e[j + 1];
+            }
+            // a sum at or below its bound: (bound + 1) - sum, saturating at zero, is not zero
+            u32v4 x = __builtin_bit_cast(u32v4, __builtin_elementwise_sub_sat(tp1, __builtin_bit_cast(u16x8, d)));
+            if (CHECK && !live) x = 0u;
+            if (LIST && !whole) {
+                asm volatile("" ::: "memory");  // (a branch, not four selects in every step)
+                if (!alive(u)) x = 0u;
+            }
+            const uint64_t bal = __ballot(((x.x | x.y) | (x.z | x.w)) != 0u);
+            if (bal != 0ull) emit(x, bal, item(u));
+        }
+    };
+    if constexpr (LIST) {
+        static_assert(U * IPS == 64, "a block of 64 is one round of the walk");
+        const uint16_t *list = la.list + (int64_t)cs * la.nblk;
+        const rsrc_t rr = make_rsrc(rec, (uint32_t)(nitems * (M4 * 4)));
+        const uint32_t voff = (uint32_t)lg * (M4 * 4);
+        // The block of 64 from item `at` on; at the index's end its last 64, of which those below `at` have had their turn.  The records
+        // of the next block are requested before this one's are looked up.
+        auto first_of = [&](uint32_t at) { return min(at, (uint32_t)nitems - 64u); };
+        auto load = [&](uint32_t (&dw)[U][M4], uint32_t at) {
+            const uint32_t base = first_of(at);
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int k2 = 0; k2 < M4; ++k2)
+                    dw[u][k2] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rr, (int)voff + 4 * k2, (int)((base + u * IPS) * (M4 * 4)), 0);
+        };
+        uint32_t dw[U][M4], nx[U][M4];
+        if constexpr (WALK == WALK_KEPT) {
+            // a wave takes a run of the part's blocks of 64 encodings; the numbers of the next 64 kept blocks lie in its lanes
+            const uint32_t n64 = (to - from) << la.shift;
+            const uint32_t i0 = n64 * (uint32_t)w / 16u, i1 = n64 * (uint32_t)(w + 1) / 16u;
+            uint32_t held_from = from + (i0 >> la.shift), held_blk = list[min(held_from + (uint32_t)lane, to - 1u)];
+            auto block_at = [&](uint32_t i) -> uint32_t {
+                const uint32_t e = from + (i >> la.shift);
+                if (e - held_from == 64u) {
+                    held_from = e;
+                    held_blk = list[min(e + (uint32_t)lane, to - 1u)];
+                }
+                const uint32_t blk = (uint32_t)__builtin_amdgcn_readlane((int)held_blk, (int)(e - held_from));
+                return ((blk << la.shift) + (i & ((1u << la.shift) - 1u))) << 6;
+            };
+            if (i0 < i1) {
+                uint32_t at = block_at(i0);
+                load(dw, at);
+                for (uint32_t i = i0; i < i1; ++i) {
+                    const uint32_t next = block_at(min(i + 1u, i1 - 1u));
+                    load(nx, next);
+                    const uint32_t base = first_of(at);
+                    auto item = [&](int u) { return base + (uint32_t)(u * IPS + lg); };
+                    evaluate(dw, i == i0, base == at, std::false_type{}, [&](int u) { return item(u) >= at; }, item);
+                    at = next;
+#pragma unroll
+                    for (int u = 0; u < U; ++u)
+#pragma unroll
+                        for (int k2 = 0; k2 < M4; ++k2) dw[u][k2] = nx[u][k2];
+                }
+            }
+            flush();
+            __syncthreads();
+            continue;
+        } else {
+            // The least sum of every position in a block, over the blocks of 64 that this wave takes: neighbours in the index go to
+            // different minima.  The low four bits of a sum make room for how many vectors have the encoding, as 15 - log2: the k-th
+            // nearest vector is what has to be bounded, and a small tight cluster may have fewer than k encodings.  A sum with an
+            // entry that was cut off is at least CAP: no bound.  Otherwise the encoding's distance is at most the sum, rounded up,
+            // and one unit for every entry's truncation, over the scale.
+            const rsrc_t re = make_rsrc(la.ebegin, (uint32_t)((nitems + 1) * 4));
+            uint32_t eb[U], nb[U];  // how many, of this block and of the next
+            auto load_many = [&](uint32_t (&many)[U], uint32_t at) {
+                const uint32_t base = first_of(at);
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    many[u] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(re, lg * 4 + 4, (int)((base + u * IPS) * 4), 0) -
+                              (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(re, lg * 4, (int)((base + u * IPS) * 4), 0);
+            };
+            const uint32_t waves = gridDim.x * 16u, g = blockIdx.x * 16u + (uint32_t)w, n64 = to << la.shift;
+            u16x8 lo[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) lo[u] = (unsigned short)0xFFFFu;
+            // this wave's j-th block of 64 is number g + j waves; the numbers of the next 64 lie in its lanes
+            const uint32_t mine = g < n64 ? (n64 - g + waves - 1u) / waves : 0u;
+            uint32_t held = 0u;
+            auto block_at = [&](uint32_t j) -> uint32_t {
+                if ((j & 63u) == 0u) {
+                    const uint32_t i = min(g + (j + (uint32_t)lane) * waves, n64 - 1u);
+                    uint32_t e = i >> la.shift;
+                    if (e >= near.x) e = near.x + (uint32_t)((uint64_t)(e - near.x) * near.y / near.z);
+                    held = (((uint32_t)list[e] << la.shift) + (i & ((1u << la.shift) - 1u))) << 6;
+                }
+                return (uint32_t)__builtin_amdgcn_readlane((int)held, (int)(j & 63u));
+            };
+            if (mine != 0u) {
+                uint32_t at = block_at(0u);
+                load(dw, at);
+                load_many(eb, at);
+                for (uint32_t j = 0; j < mine; ++j) {
+                    const uint32_t next = j + 1u < mine ? block_at(j + 1u) : at;
+                    load(nx, next);
+                    load_many(nb, next);
+                    const uint32_t base = first_of(at);
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        u32v4 e[M - 2], d = look(dw[u], 0, 0) + look(dw[u], 0, 1);
+#pragma unroll
+                        for (int c = 2; c < M; ++c) e[c - 2] = look(dw[u], c / CPL, c % CPL);
+#pragma unroll
+                        for (int c = 0; c < M - 2; c += 2) d = d + e[c] + e[c + 1];
+                        d = (d | 0x000F000Fu) - min(31u - (uint32_t)__builtin_clz(eb[u] | 1u), 15u) * 0x00010001u;
+                        if (base != at && base + (uint32_t)(u * IPS + lg) < at) d = 0xFFFFFFFFu;  // (another block's: an encoding counts once)
+                        lo[u] = __builtin_elementwise_min(lo[u], __builtin_bit_cast(u16x8, d));
+                    }
+                    at = next;
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        eb[u] = nb[u];
+#pragma unroll
+                        for (int k2 = 0; k2 < M4; ++k2) dw[u][k2] = nx[u][k2];
+                    }
+                }
+            }
+#pragma unroll
+            for (int v = 0; v < V; ++v) {
+                const float t = o.tau[(int64_t)tile * QT + col + v], scale = TOP / fmaxf(t, 8.0779e-28f);
+                float *row = la.gmin + ((int64_t)tile * QT + col + v) * la.gstride + g * 64u;
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const uint32_t raw = lo[u][v], top = raw | 15u;
+                    // (log2 of how many in the low four bits of the number too)
+                    const uint32_t bits = (__float_as_uint((float)(top + M + 1) / scale * (1.f + 1.9073486e-6f)) + 15u) & ~15u;
+                    row[u * IPS + lg] = __uint_as_float(top < CAP && bits < 0x7F800000u ? bits | (15u - (raw & 15u)) : 0x7F800000u);
+                }
+            }
+            return;
+        }
+    } else {
     constexpr int RF = IPS;
     if (blo >= bhi) return;
     const int nruns = nw * IPS / RF;
@@ -2430,8 +2630,6 @@ __global__ __launch_bounds__(1024) void k_lds16(const uint32_t *__restrict__ rec
     const rsrc_t rr = make_rsrc(rec + blo * M4, (uint32_t)((bhi - blo) * (M4 * 4)));
     const uint32_t first = (uint32_t)(rlo - blo) + (uint32_t)ph;
     const uint32_t voff = len > 0 ? first * (M4 * 4) : 0u;
-    uint32_t prev0 = 0u;
-    u32v4 top = 0u;
     auto steps = [&](int i, auto check) {
         constexpr bool CHECK = decltype(check)::value;
         uint32_t dw[U][M4];
@@ -2446,36 +2644,15 @@ __global__ __launch_bounds__(1024) void k_lds16(const uint32_t *__restrict__ rec
 #pragma unroll
             for (int k2 = 0; k2 < M4; ++k2) dw[u][k2] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rr, (int)vo + 4 * k2, so, 0);
         }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const bool live = !CHECK || i + u < len;
-            bool fast = false;
-            if (CTX) {
-                const bool differs = live && ((dw[u][0] ^ prev0) & 0xFFFFu) != 0u;
-                fast = __ballot(differs) == 0ull && i + u != 0;
-                prev0 = dw[u][0];
-            }
-            if (!CTX || !fast) top = look(dw[u], 0, 0) + look(dw[u], 0, 1);
-            u32v4 d = top;
-            {
-                // the remaining M - 2 entries, two at a time
-                u32v4 e[M - 2];
-#pragma unroll
-                for (int j = 2; j < M; ++j) e[j - 2] = look(dw[u], j / CPL, j % CPL);
-#pragma unroll
-                for (int j = 0; j < M - 2; j += 2) d = d + e[j] + e[j + 1];
-            }
-            // a sum at or below its bound: (bound + 1) - sum, saturating at zero, is not zero
-            u32v4 x = __builtin_bit_cast(u32v4, __builtin_elementwise_sub_sat(tp1, __builtin_bit_cast(u16x8, d)));
-            if (CHECK && !live) x = 0u;
-            const uint64_t bal = __ballot(((x.x | x.y) | (x.z | x.w)) != 0u);
-            if (bal != 0ull) emit(x, bal, first + (uint32_t)(i + u) * RF);
-        }
+        evaluate(dw, i == 0, !CHECK, check, [&](int u) { return i + u < len; }, [&](int u) { return first + (uint32_t)(i + u) * RF; });
     };
     int i = 0;
     for (; i + U <= minlen; i += U) steps(i, std::false_type{});
     for (; i < RL; i += U) steps(i, std::true_type{});
     flush();
+    return;
+    }
+    }
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -3011,6 +3188,8 @@ __global__ __launch_bounds__(256) void k_reduce(ReduceArgs r, int64_t nitems, co
 //      value: a step is NV compares whose lane masks are counted on the scalar unit, no LDS and no barrier.  (A radix
 //      select over LDS histograms of 64 queries per workgroup took 28 us however few queries there were and 32 us
 //      for ten thousand, mostly clearing and scanning 64 KB of counters three times; this takes 10 and 25 us.)
+//      MANY: the low four bits of a minimum are the logarithm of how many vectors have its encoding, and vectors are counted; the bound
+//      that is there stays where it is the closer one.
 //      The kernel also sets the query's candidate count and flag, so that no launch is needed for those, and says
 //      (LooseArgs) how large the error bound E of k_mm16 may be: everything up to tau + E becomes a candidate there, and
 //      where a query's neighbourhood has many dimensions the count grows fast.  At most `groups` of the sample's
@@ -3031,7 +3210,7 @@ struct LooseArgs {
     float typical;         // E / ||q|| as it is found for most queries
 };
 
-template <int NV>
+template <int NV, bool MANY>
 __global__ __launch_bounds__(256) void k_tau(const float *__restrict__ gmin, int S, int64_t gstride, int k, int64_t nq, int64_t nql,
                                              float *__restrict__ tau, uint32_t *__restrict__ cnt, uint32_t *__restrict__ flag,
                                              uint32_t *__restrict__ counter, LooseArgs la)
@@ -3066,6 +3245,13 @@ __global__ __launch_bounds__(256) void k_tau(const float *__restrict__ gmin, int
         const uint32_t largest = hi;
         auto count = [&](uint32_t upto) {
             int c = 0;
+            if (MANY) {
+#pragma unroll
+                for (int i = 0; i < NV; ++i) c += x[i] <= upto ? 1 << (x[i] & 15u) : 0;
+#pragma unroll
+                for (int dlt = 32; dlt >= 1; dlt >>= 1) c += __shfl_xor(c, dlt);
+                return uniform(c);
+            }
 #pragma unroll
             for (int i = 0; i < NV; ++i) c += __popcll(__ballot(x[i] <= upto));
             return c;
@@ -3077,6 +3263,8 @@ __global__ __launch_bounds__(256) void k_tau(const float *__restrict__ gmin, int
             else lo = mid + 1;
         }
         bound = S >= k ? hi : 0x7F800000u;
+        // (the bound that is there stands too; and hi was a bound only if there are k vectors at all)
+        if (MANY) bound = min(count(hi) >= k ? hi : 0x7F800000u, __float_as_uint(tau[ql]));
         if (la.room) {
             nn = 0.f;
             for (int j = lane; j < la.d; j += 64) {
@@ -3309,6 +3497,7 @@ struct SelectArgs {
     int k;
     int32_t *out_ids;        // [nq][k]
     float *out_dist;         // [nq][k]
+    const uint32_t *perm;    // [nq] the row of the results that query ql's go to, or nullptr: row ql
     uint32_t *flag;          // [nq]  set to 1 when the query needs the exact kernel
     const float *bm;         // [tiles][M][64] or nullptr: results are written as B(q) - value (scalar-product searches)
     // Candidates from a fixed-point filter (k_lds with FX, k_lds16): the upper word of a candidate is a fixed-point
@@ -3383,7 +3572,7 @@ __global__ __launch_bounds__(256) void k_select(SelectArgs a)
     __shared__ uint32_t hist[256];
     __shared__ uint32_t s_a, s_b, s_c, s_d;
     __shared__ uint32_t sel_sh[8];
-    const int64_t ql = blockIdx.x;
+    const int64_t ql = blockIdx.x, orow = a.perm ? (int64_t)a.perm[ql] : ql;
     if (a.flag[ql]) return;  // already routed to the exact kernel
     const uint32_t craw = a.cnt[ql];
     if (craw > a.C) {
@@ -3476,8 +3665,8 @@ __global__ __launch_bounds__(256) void k_select(SelectArgs a)
     const int nk = (int)s_c;
     if (nk == 0 && a.allow_short) {  // nothing in reach of this query
         for (int i = threadIdx.x; i < k; i += 256) {
-            a.out_ids[ql * k + i] = -1;
-            a.out_dist[ql * k + i] = __uint_as_float(0x7F800000u);
+            a.out_ids[orow * k + i] = -1;
+            a.out_dist[orow * k + i] = __uint_as_float(0x7F800000u);
         }
         return;
     }
@@ -3514,8 +3703,8 @@ __global__ __launch_bounds__(256) void k_select(SelectArgs a)
             sort_u64(xkeys, nx2s);
             for (int i = threadIdx.x; i < k; i += 256) {
                 const bool have = i < (int)total;
-                a.out_ids[ql * k + i] = have ? (int32_t)(uint32_t)xkeys[i] : -1;
-                a.out_dist[ql * k + i] = have ? __uint_as_float((uint32_t)(xkeys[i] >> 32)) : __uint_as_float(0x7F800000u);
+                a.out_ids[orow * k + i] = have ? (int32_t)(uint32_t)xkeys[i] : -1;
+                a.out_dist[orow * k + i] = have ? __uint_as_float((uint32_t)(xkeys[i] >> 32)) : __uint_as_float(0x7F800000u);
             }
             return;
         }
@@ -3564,9 +3753,9 @@ __global__ __launch_bounds__(256) void k_select(SelectArgs a)
     sort_u64(xkeys, nx2);
     const float boff = a.bm ? product_shift(a.bm, a.M, ql) : 0.f;
     for (int i = threadIdx.x; i < k; i += 256) {
-        a.out_ids[ql * k + i] = (int32_t)(uint32_t)xkeys[i];
+        a.out_ids[orow * k + i] = (int32_t)(uint32_t)xkeys[i];
         const float v = __uint_as_float((uint32_t)(xkeys[i] >> 32));
-        a.out_dist[ql * k + i] = a.bm ? boff - v : v;
+        a.out_dist[orow * k + i] = a.bm ? boff - v : v;
     }
 }
 
@@ -3593,6 +3782,7 @@ struct ExactArgs {
     int k;
     int32_t *out_ids;
     float *out_dist;
+    const uint32_t *perm;     // as in SelectArgs
     const float *bm;          // as in SelectArgs
 };
 
@@ -3612,7 +3802,7 @@ __global__ __launch_bounds__(256) void k_exact(ExactArgs a)
     __shared__ uint32_t hist[256];
     __shared__ uint64_t okeys[ETF_MAX_TOPK];
     __shared__ uint32_t s_digit, s_rank, s_n;
-    const int64_t ql = blockIdx.x;
+    const int64_t ql = blockIdx.x, orow = a.perm ? (int64_t)a.perm[ql] : ql;
     if (!a.flag[ql]) return;
     if (threadIdx.x == 0) atomicAdd(a.nflag, 1u);
     const int tile = (int)(ql / QT), col = (int)(ql % QT);
@@ -3681,9 +3871,9 @@ __global__ __launch_bounds__(256) void k_exact(ExactArgs a)
     bitonic_sort_u64(okeys, n2);
     const float boff = a.bm ? product_shift(a.bm, a.M, ql) : 0.f;
     for (int i = threadIdx.x; i < a.k; i += 256) {
-        a.out_ids[ql * a.k + i] = (int32_t)(uint32_t)okeys[i];
+        a.out_ids[orow * a.k + i] = (int32_t)(uint32_t)okeys[i];
         const float v = __uint_as_float((uint32_t)(okeys[i] >> 32));
-        a.out_dist[ql * a.k + i] = a.bm ? boff - v : v;
+        a.out_dist[orow * a.k + i] = a.bm ? boff - v : v;
     }
 }
 

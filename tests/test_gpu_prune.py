@@ -1,0 +1,102 @@
+"""Searches on queries put in order and on the parts of the index that a group of them needs (k_order_*, k_prune, k_units and
+the two walks of k_lds16 over lists).  They only leave out what cannot be among the k nearest: ids and float32 distances are those
+of the float32 filter over everything and of the exact whole-database selection, bit for bit, and no query may need the latter.
+Sizes lie around the blocks of 64 encodings, the sub-tiles of 32 and 16 queries and the blocks of 128."""
+import numpy as np
+import pytest
+
+from test_gpu_parity import FOREST, TREE, Problem, torch
+
+pytestmark = pytest.mark.gpu
+
+
+def check(c, q, k, mode, fallback=0):
+    qd = torch.from_numpy(q).cuda()
+    c.set_option("prune_filter", -1)
+    plain = c.workspace_bytes(len(q), k, mode)
+    c.set_option("prune_filter", 0)
+    assert c.workspace_bytes(len(q), k, mode) != plain  # it has lists
+    ids, dist = c.search(qd, k, mode)
+    torch.cuda.synchronize()
+    assert c.last_fallback_count() == fallback
+    c.set_option("lds_filter", 0)
+    ids0, dist0 = c.search(qd, k, mode)
+    c.set_option("force_fallback", 1)
+    wi, wd = c.search(qd, k, mode)
+    torch.cuda.synchronize()
+    c.set_option("force_fallback", 0)
+    c.set_option("lds_filter", 2)
+    assert torch.equal(dist, dist0) and torch.equal(ids, ids0)
+    assert torch.equal(dist, wd) and torch.equal(ids, wi)
+
+
+@pytest.mark.parametrize("M,ds,T,N,Q,k", [(8, 4, 2, 20000, 1, 10), (8, 4, 1, 20031, 33, 1), (8, 3, 2, 20032, 129, 100), (8, 16, 2, 30001, 400, 300),
+                                          (16, 2, 4, 20063, 17, 10), (16, 4, 1, 20064, 130, 50), (16, 1, 2, 30000, 257, 900)])
+def test_shapes_and_block_edges(M, ds, T, N, Q, k):
+    p = Problem(d=M * ds, M=M, K=256, N=N, Q=Q, ntrain=3000, seed=M + ds)
+    check(p.ctx(T=T, sample_min=1 << 13, cand_cap=16384 if k > 500 else 8192, matrix_filter=-1), p.q, k, TREE if T == 1 else FOREST)
+
+
+@pytest.mark.parametrize("M,K", [(8, 200), (16, 137)])
+def test_fewer_codewords_and_a_chunk_order(M, K):
+    p = Problem(d=4 * M, M=M, K=K, N=25000, Q=150, ntrain=3000, seed=7)
+    c = p.ctx(T=1, sample_min=1 << 13, cand_cap=8192, matrix_filter=-1)
+    c.index_set_chunk_order(list(range(M))[::-1])
+    c.index_build(p.codes, T=2)
+    c.index_upload()
+    check(c, p.q, 20, FOREST)
+
+
+def test_clusters_of_few_encodings():
+    """Vectors of tight clusters share encodings: fewer than k of them hold a query's k neighbours."""
+    p = Problem(d=32, M=8, K=256, N=24000, Q=300, ntrain=3000, seed=3)
+    rng = np.random.default_rng(1)
+    p.codes[:12000] = p.codes[rng.integers(12000, 12040, 12000)]  # 300 vectors an encoding
+    near = rng.integers(12000, 12040, 100)
+    p.q[:100] = p.xb[near] + rng.normal(0, 1e-3, (100, 32)).astype(np.float32)
+    check(p.ctx(T=2, sample_min=1 << 13, cand_cap=8192), p.q, 200, FOREST)
+
+
+def test_beside_the_matrix_filter():
+    p = Problem(d=128, M=16, K=256, N=30000, Q=400, ntrain=3000, seed=5)
+    check(p.ctx(T=4, sample_min=1 << 14, cand_cap=8192, matrix_filter=0), p.q, 20, FOREST)
+
+
+def test_batches_of_a_small_workspace():
+    p = Problem(d=32, M=8, K=256, N=20000, Q=300, ntrain=3000, seed=9)
+    c = p.ctx(T=2, sample_min=1 << 13, cand_cap=4096, prune_filter=0)
+    c.set_option("ws_cap_bytes", int(c.workspace_bytes(64, 10, FOREST) * 2.5))
+    check(c, p.q, 10, FOREST)
+
+
+def test_queries_that_are_not_finite():
+    p = Problem(d=32, M=8, K=256, N=20000, Q=200, ntrain=3000, seed=13)
+    c = p.ctx(T=2, sample_min=1 << 13, cand_cap=8192)
+    want = c.search(torch.from_numpy(p.q).cuda(), 10, FOREST)
+    bad = p.q.copy()
+    bad[5], bad[40, 3], bad[190] = np.nan, np.inf, 3e38
+    c.set_option("prune_filter", 0)
+    got = c.search(torch.from_numpy(bad).cuda(), 10, FOREST)
+    torch.cuda.synchronize()
+    keep = [i for i in range(200) if i not in (5, 40, 190)]
+    assert torch.equal(got[0][keep], want[0][keep]) and torch.equal(got[1][keep], want[1][keep])
+
+
+def test_replays_of_a_graph():
+    p = Problem(d=32, M=8, K=256, N=20000, Q=150, ntrain=3000, seed=17)
+    c = p.ctx(T=2, sample_min=1 << 13, cand_cap=8192, prune_filter=0)
+    q = torch.from_numpy(p.q).cuda()
+    ws = c.alloc_workspace(150, 10, FOREST)
+    ids, dist = torch.empty((150, 10), dtype=torch.int32, device="cuda"), torch.empty((150, 10), device="cuda")
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        c.set_stream(torch.cuda.current_stream().cuda_stream)  # the capturing stream
+        c.search(q, 10, FOREST, ids, dist, ws)
+    c.set_stream(torch.cuda.current_stream().cuda_stream)
+    for i in range(3):
+        q.copy_(torch.from_numpy(np.roll(p.q, 31 * i, axis=0)))
+        want = c.search(q, 10, FOREST, ws=ws)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(ids, want[0]) and torch.equal(dist, want[1])
