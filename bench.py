@@ -316,6 +316,13 @@ class Workload:
         lds_path = any(n in prof and prof[n][1] > 0 for n in ("lds", "lds16"))
         ctx_path = traversal != 1 and T <= 4
         alg = algorithmic_bytes(stats, "forest_lds" if lds_path else "forest_ctx" if ctx_path else "forest", S, self.tiles)
+        kept = ctx.last_kept_encodings() if "lds16" in alg else 0
+        if kept:
+            # the filter left out what a group of queries does not need: the entries of what it looked at, in this call (a
+            # walk of 8 chunks keeps a context of two), times the step's calls; the bound's second pass has no count
+            grp, read = (32, stats["M"] - 2) if stats["M"] == 8 else (16, stats["M"])
+            alg["lds16"] = 2 * kept * grp * read * ((self.Q + Qc - 1) // Qc)
+            alg.pop("sample", None)
         if mm_blocks:
             alg.pop("lds16", None)   # its table entries are read for the blocks that k_mm16 left, if any
         kernels = {}
@@ -355,10 +362,11 @@ class Workload:
                             "frac_of_measured_ceiling": achieved / ceil if ceil else None,
                             "measured_ceiling": {"GBps": ceil, "what": "ds_read_b128 of scattered 64-byte rows, this run's probe"} if ceil else None,
                             "traffic": traffic, "traffic_note": traffic_note,
+                            "kept_share": kept * (32 if stats["M"] == 8 else 16) / (stats["n_distinct"] * last_q) if kept else None,
                             "lookups_per_s": achieved * 1e9 / eb,
                             # the same time priced on the lookups the paper's single E-Tree needs for this database
                             # (L1 + L2 + postfix lengths): prefixes this kernel recomputes are not useful work
-                            "method_frac": frac * tree_lookups / kernel_lookups,
+                            "method_frac": None if kept else frac * tree_lookups / kernel_lookups,
                             "lookups_per_query": {"this_kernel": kernel_lookups, "e_tree": tree_lookups,
                                                   "e_forest_trees": forest_lookups, "flat_distinct": stats["n_distinct"] * stats["M"],
                                                   "flat": stats["N"] * stats["M"]},

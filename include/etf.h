@@ -107,7 +107,7 @@ const char *etf_last_error(const etf_ctx *ctx);
  *                     fills its blocks of 128 queries and has at least this many (query, distinct encoding) pairs
  *                     (default 2^29, twice that at M = 8; -1: never).  Same results
  *   "prune_filter"    from this many (query, distinct encoding) pairs a search on 16-bit tables (squared distances, a workspace of
- *                     etf_workspace_bytes) of at least 2048 queries and a clustered index puts its queries in the order of
+ *                     etf_workspace_bytes) of at least 1000 queries (below 2048 from twice as many pairs) and a clustered index puts its queries in the order of
  *                     their nearest codewords and leaves out, for every group of them, the parts of the tree that hold
  *                     nothing at or below a query's bound (default 2^31; 0: wherever it can; -1: never).  Same results
  *   "lds_blocks"      workgroups per sub-tile of queries in the LDS-resident kernels (0 = chosen by the
@@ -431,6 +431,10 @@ int etf_last_fallback_count(etf_ctx *ctx, int64_t *out);
 /* Number of blocks of 128 queries whose candidates the most recent search on this context filtered on the matrix
  * cores (option "matrix_filter"; diagnostic).  The count lies beside the one above and the same holds for it. */
 int etf_last_matrix_blocks(etf_ctx *ctx, int64_t *out);
+
+/* Encodings that the filter pass of the most recent search looked at, summed over its groups of 32 (M = 8) or 16 (M = 16) queries, where it left
+ * out what they do not need (option "prune_filter"; diagnostic); 0 where it looked at all.  The same holds for this count. */
+int etf_last_kept_encodings(etf_ctx *ctx, int64_t *out);
 
 /* ---- IVFADC on the merged, sorted encodings -------------------------------- */
 

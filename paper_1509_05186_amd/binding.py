@@ -23,7 +23,7 @@ EXPORTS = [
     "etf_index_layout", "etf_index_export",
     "etf_encode_workspace_bytes", "etf_pq_encode_device",
     "etf_index_build_device_bytes", "etf_index_build_device", "etf_last_build_path",
-    "etf_workspace_bytes", "etf_lut_build", "etf_adc", "etf_search", "etf_last_fallback_count", "etf_last_matrix_blocks",
+    "etf_workspace_bytes", "etf_lut_build", "etf_adc", "etf_search", "etf_last_fallback_count", "etf_last_matrix_blocks", "etf_last_kept_encodings",
     "etf_static_scratch_bytes", "etf_search_static",
     "etf_profile_enable", "etf_profile_read", "etf_probe_bandwidth",
     "etf_ivf_set_coarse", "etf_ivf_assign_workspace_bytes", "etf_ivf_assign_device", "etf_ivf_build", "etf_ivf_stats",
@@ -163,6 +163,7 @@ def load_library():
         "etf_search": (I, [P, P, L, I, I, P, P, P, L]),
         "etf_last_fallback_count": (I, [P, ctypes.POINTER(L)]),
         "etf_last_matrix_blocks": (I, [P, ctypes.POINTER(L)]),
+        "etf_last_kept_encodings": (I, [P, ctypes.POINTER(L)]),
         "etf_static_scratch_bytes": (L, []),
         "etf_search_static": (I, [P, P, L, I, I, P, P]),
         "etf_profile_enable": (I, [P, I]),
@@ -517,6 +518,12 @@ class Context:
     def last_matrix_blocks(self) -> int:
         v = ctypes.c_int64(0)
         self._ck(self._lib.etf_last_matrix_blocks(self._h, ctypes.byref(v)))
+        return int(v.value)
+
+    def last_kept_encodings(self) -> int:
+        """Encodings the last search's filter looked at, summed over its groups of 32 (M = 8) or 16 queries; 0: all of them."""
+        v = ctypes.c_int64()
+        self._ck(self._lib.etf_last_kept_encodings(self._h, ctypes.byref(v)))
         return int(v.value)
 
     # ---- IVFADC

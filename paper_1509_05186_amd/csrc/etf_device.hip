@@ -721,7 +721,9 @@ bool lds_eligible(int M, int K, int T, const int32_t *chunk_begin)
 // left out), up to half of them where a large one has filled in the clusters' edges, and then many vectors share an encoding.
 // On 1033 random problems (N up to 4 million, 2048 to 10 000 queries, k up to 500, 6 to 120 dimensions a chunk)
 // this rule took 390: between 3.9 times and 0.96 times as fast, half of them at least 1.8 times; without its lines for k and the pairs
-// the worst took 1.4 times as long (k of 400 in 270 000 encodings).
+// the worst took 1.4 times as long (k of 400 in 270 000 encodings).  Fewer queries have less in common: from 1000 on, with twice
+// the pairs, between 0.93 and 4.2 times as fast on 198 problems (N 3 to 20 million), half of them at least 1.4 times; 256 queries on 17
+// million encodings 0.97.
 void plan_prune(const etf_ctx *ctx, int64_t Q, bool ws_cap_given, Plan &P)
 {
     const HostIndex &ix = ctx->idx;
@@ -730,7 +732,7 @@ void plan_prune(const etf_ctx *ctx, int64_t Q, bool ws_cap_given, Plan &P)
     if (opt.prune_filter < 0 || ws_cap_given || opt.lds_blocks > 0 || opt.lds16_context == 0 || opt.metric != 0) return;
     if (ix.Nd >= ((int64_t)1 << 26) || ix.Nd < 64) return;  // (candidate records and byte offsets of records; whole blocks)
     if (opt.prune_filter > 0) {
-        if (Q < 2048 || ix.Nd < ((int64_t)1 << 18) || ix.Nd < 3000 * (int64_t)P.k || (double)Q * (double)ix.Nd < (double)opt.prune_filter) return;
+        if (Q < 1000 || ix.Nd < ((int64_t)1 << 18) || ix.Nd < 3000 * (int64_t)P.k || (double)Q * (double)ix.Nd < (double)opt.prune_filter * (Q < 2048 ? 2.0 : 1.0)) return;
         const HostTree &t0 = ix.tree[0];
         if (t0.D < 2) return;
         const double prefixes = (double)(t0.nI[1] + t0.nL[1] + t0.nL[0]), pairs = (double)ix.K * ix.K;
@@ -758,7 +760,7 @@ void plan_prune(const etf_ctx *ctx, int64_t Q, bool ws_cap_given, Plan &P)
     // 1024 minima a workgroup, and enough of them for k to lie in different ones
     int64_t best = -1;
     for (int wgs = P.k <= 400 ? 1 : P.k <= 800 ? 2 : 4; wgs <= 4; wgs *= 2) {
-        const int64_t cost = ((subs * wgs + 255) / 256) * (5000 + near / wgs) + subs * wgs * 100;  // (and k_tau's time)
+        const int64_t cost = ((subs * wgs + 255) / 256) * (5000 + near / wgs) + (subs * 100 + 6000) * wgs;  // (and k_tau's time)
         if (best < 0 || cost < best) {
             best = cost;
             P.near_wgs = wgs;
@@ -957,7 +959,8 @@ int launch_lds16_list(etf_ctx *ctx, const Plan &P, char *ws, const uint32_t *rec
     ProfScope prof(ctx, WALK == WALK_NEAR ? ETF_K_SAMPLE : ETF_K_LDS16);
     if (WALK == WALK_KEPT) {
         hipLaunchKernelGGL(k_units, dim3(1), dim3(1024), 0, st, reinterpret_cast<const uint32_t *>(ws + P.o_count), subs, 64 << P.shift, o.done,
-                           MM_Q / (128 / G), la.state, reinterpret_cast<uint4 *>(ws + P.o_units));
+                           MM_Q / (128 / G), la.state, reinterpret_cast<uint4 *>(ws + P.o_units),
+                           reinterpret_cast<uint32_t *>(ws + P.o_counter) + 2);
         LAUNCH_CHECK(ctx, "k_units");
     }
     constexpr bool cx = WALK == WALK_KEPT;  // (without the context at M = 16: option lds16_context)
@@ -1702,5 +1705,14 @@ static int last_count(etf_ctx *ctx, int word, int64_t *out)
 extern "C" int etf_last_fallback_count(etf_ctx *ctx, int64_t *out) { return last_count(ctx, 0, out); }
 
 extern "C" int etf_last_matrix_blocks(etf_ctx *ctx, int64_t *out) { return last_count(ctx, 1, out); }
+
+extern "C" int etf_last_kept_encodings(etf_ctx *ctx, int64_t *out)
+{
+    int64_t items = 0;
+    int rc = last_count(ctx, 3, &items);
+    if (rc == ETF_OK) rc = last_count(ctx, 2, out);
+    if (rc == ETF_OK) *out *= items;
+    return rc;
+}
 
 #include "etf_ivf.hip.h"

@@ -310,8 +310,8 @@ __global__ __launch_bounds__(1024) void k_prune(PruneArgs a)
         else f = x[0][0][a0] + x[1][0][a1] + least_of(2, a2, b2);
         return f <= 1.f ? min((uint32_t)(255.f * __builtin_amdgcn_sqrtf(f)), 254u) : 255u;
     };
-    // four blocks of a thread at a time: a wave has 64 neighbours of each
-    constexpr int AT = 4;
+    // eight blocks of a thread at a time: a wave has 64 neighbours of each
+    constexpr int AT = 8;
     uint16_t *list = a.list + (int64_t)s * a.nblk;
     if (a.again) {
         // all that are kept
@@ -425,9 +425,10 @@ __global__ __launch_bounds__(1024) void k_prune(PruneArgs a)
 // four.  grid 1, block 1024.
 // ------------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(1024) void k_units(const uint32_t *__restrict__ count, int subs, int block_items, const uint32_t *__restrict__ done,
-                                                int subs_per_done, uint32_t *__restrict__ state, uint4 *__restrict__ units)
+                                                int subs_per_done, uint32_t *__restrict__ state, uint4 *__restrict__ units,
+                                                uint32_t *__restrict__ kept)
 {
-    __shared__ uint32_t wsum[16];
+    __shared__ uint32_t wsum[16], first[1024], many[1024];
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
     auto weight = [&](int i) -> uint32_t { return i < subs && !(done && done[i / subs_per_done] != 0u) ? count[i] : 0u; };
     uint32_t sum = 0u;
@@ -459,13 +460,23 @@ __global__ __launch_bounds__(1024) void k_units(const uint32_t *__restrict__ cou
             at += j < w ? wsum[j] : 0u;
             all += wsum[j];
         }
-        for (uint32_t j = 0; j < own; ++j)
-            units[at + j] = make_uint4((uint32_t)i, (uint32_t)((uint64_t)n * j / own), (uint32_t)((uint64_t)n * (j + 1u) / own), 0u);
+        first[t] = at;
+        many[t] = own;
+        __syncthreads();
+        // a wave a sub-tile, a lane a unit (few sub-tiles of a large index have a hundred units each)
+        for (int k = w; k < 1024 && i0 + k < subs; k += 16) {
+            const uint32_t nk = weight(i0 + k), mk = many[k];
+            for (uint32_t j = (uint32_t)lane; j < mk; j += 64u)
+                units[first[k] + j] = make_uint4((uint32_t)(i0 + k), (uint32_t)((uint64_t)nk * j / mk), (uint32_t)((uint64_t)nk * (j + 1u) / mk), 0u);
+        }
+        __syncthreads();
         base += all;
     }
     if (t == 0) {
         state[0] = base;
         state[1] = 0u;
+        kept[0] += total;  // (over the batches of a call: etf_last_kept_encodings)
+        kept[1] = (uint32_t)block_items;
     }
 }
 

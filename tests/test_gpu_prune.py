@@ -19,8 +19,10 @@ def check(c, q, k, mode, fallback=0):
     ids, dist = c.search(qd, k, mode)
     torch.cuda.synchronize()
     assert c.last_fallback_count() == fallback
+    assert c.last_kept_encodings() > 0 or c.last_matrix_blocks() > 0
     c.set_option("lds_filter", 0)
     ids0, dist0 = c.search(qd, k, mode)
+    assert c.last_kept_encodings() == 0
     c.set_option("force_fallback", 1)
     wi, wd = c.search(qd, k, mode)
     torch.cuda.synchronize()
