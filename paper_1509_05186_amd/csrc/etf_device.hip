@@ -296,6 +296,8 @@ int make_plan(const etf_ctx *ctx, int64_t Q, int k, int mode, bool search, Plan 
     }
     int64_t nt = ws_cap / std::max<int64_t>(per_tile + 4096, 1);
     P.NT = std::max<int64_t>(1, std::min<int64_t>(nt, P.tiles_total));
+    // (k_units adds up a batch's kept blocks in 32 bits, and cuts as many units as o_units holds only if that sum is right)
+    if (P.prune) P.NT = std::min<int64_t>(P.NT, (int64_t)UINT32_MAX / ((int64_t)P.nblk * (M / 4)));
     // offsets
     int64_t off = 0;
     auto take = [&](int64_t bytes) {
