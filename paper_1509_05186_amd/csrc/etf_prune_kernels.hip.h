@@ -384,15 +384,14 @@ __global__ __launch_bounds__(1024) void k_prune(PruneArgs a)
         }
         const uint32_t n = (uint32_t)__shfl((int)upto, 63), near = min((uint32_t)a.near_blocks, n);
         uint32_t before = upto - own;
-        if (lane == 0) {
+        if (lane == 0 && near == n) {  // (all of them: no lane finds a class below)
             part[1] = n;
             part[3] = 255u;
             a.near[s] = make_uint4(n, 0u, 0u, 0u);
         }
-        __builtin_amdgcn_wave_barrier();
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            if (near < n && before <= near && before + v[i] > near) {  // (one lane, once)
+            if (near < n && before <= near && before + v[i] > near) {  // (one lane, once: of near < n exactly one class holds that number)
                 part[1] = before;
                 part[3] = (uint32_t)(4 * lane + i);
                 a.near[s] = make_uint4(before, v[i], near - before, 0u);
