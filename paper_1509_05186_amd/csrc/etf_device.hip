@@ -744,10 +744,16 @@ void plan_prune(const etf_ctx *ctx, int64_t Q, bool ws_cap_given, Plan &P)
     while ((ix.Nd + ((int64_t)64 << P.shift) - 1) / ((int64_t)64 << P.shift) > PRUNE_BLOCKS) ++P.shift;
     P.nblk = (int)((ix.Nd + ((int64_t)64 << P.shift) - 1) / ((int64_t)64 << P.shift));
     const int64_t Qs = ix.M == 8 ? 32 : 16, subs = (std::min<int64_t>(Q, 1 << 16) + Qs - 1) / Qs;
-    // The bound's sample only has to find the neighbourhood: a 64th of the index will do, at least a quarter of the sample (its
-    // order is scattered: a part of it is a sample too).  The bound itself comes from the nearest blocks.
+    // The bound's sample only has to find the neighbourhood: a 128th of the index will do, at least an eighth of the sample (its
+    // order is scattered: a part of it is a sample too).  The bound itself comes from the nearest blocks; but a query to whose
+    // neighbours those do not lead keeps the sample's, and the longest list that a query can have has room for twice the candidates
+    // that one lets through.  (Without that, 500 of 200 000 encodings whose first three chunks tell nothing, lists of 4096: every query
+    // overran its list and took the exact selection.)
     const int64_t near = std::max<int64_t>(16384, P.S * 3 / 8), groups = std::max<int64_t>(P.ngroups, 1);
-    const int64_t first = std::min(P.S, std::max(ix.Nd / 128, P.S / 8));
+    const double reach = 1.3 * (double)P.k * (double)ix.Nd * std::min(8.0, (double)ix.N / (double)ix.Nd);  // candidates, times S
+    const int64_t longest = opt.cand_cap > 0 ? opt.cand_cap : 1 << 17;
+    const double holds = longest > 2048 ? std::min((double)P.S, 2.0 * reach / (double)(longest - 2048)) : (double)P.S;
+    const int64_t first = std::min(P.S, std::max({ix.Nd / 128, P.S / 8, (int64_t)holds + 1}));
     const int64_t gsize = std::max<int64_t>(1, (first + groups - 1) / groups), ngroups = (first + gsize - 1) / gsize;
     if (ngroups >= std::min<int64_t>(P.ngroups, 2 * P.k)) {
         P.S = first;
@@ -755,9 +761,7 @@ void plan_prune(const etf_ctx *ctx, int64_t Q, bool ws_cap_given, Plan &P)
         P.ngroups = ngroups;
         P.gstride = (ngroups + 63) & ~(int64_t)63;
     }
-    // a query to whose neighbours that does not lead keeps the sample's bound: room for twice the candidates it lets through
-    const double expect = 1.3 * (double)P.k * (double)ix.Nd / (double)P.S * std::min(8.0, (double)ix.N / (double)ix.Nd);
-    while (ctx->opt.cand_cap == 0 && P.C < 2.0 * expect + 2048.0 && P.C < (1u << 17)) P.C <<= 1;
+    while (opt.cand_cap == 0 && P.C < 2.0 * reach / (double)P.S + 2048.0 && P.C < (1u << 17)) P.C <<= 1;
     P.near_blocks = (int)std::max<int64_t>(1, near >> (6 + P.shift));
     // 1024 minima a workgroup, and enough of them for k to lie in different ones
     int64_t best = -1;

@@ -5,7 +5,7 @@ Sizes lie around the blocks of 64 encodings, the sub-tiles of 32 and 16 queries 
 import numpy as np
 import pytest
 
-from test_gpu_parity import FOREST, TREE, Problem, torch
+from test_gpu_parity import FOREST, TREE, Problem, etf, torch
 
 pytestmark = pytest.mark.gpu
 
@@ -57,6 +57,22 @@ def test_clusters_of_few_encodings():
     near = rng.integers(12000, 12040, 100)
     p.q[:100] = p.xb[near] + rng.normal(0, 1e-3, (100, 32)).astype(np.float32)
     check(p.ctx(T=2, sample_min=1 << 13, cand_cap=8192), p.q, 200, FOREST)
+
+
+@pytest.mark.parametrize("M", [8, 16])
+def test_a_bound_that_the_nearest_blocks_do_not_better(M):
+    """The first three chunks tell nothing (their codewords are as good as one), the lists have room for what the whole sample's
+    bound lets through (1.3 k N / S = 2400) and no more: no query may overrun its list."""
+    rng = np.random.default_rng(3)
+    cb = rng.normal(0, 1, (M, 256, 4)).astype(np.float32)
+    cb[:3] *= 1e-3
+    c = etf.Context(device=0, stream=torch.cuda.current_stream().cuda_stream)
+    for name, v in (("cand_cap", 4096), ("matrix_filter", -1)):
+        c.set_option(name, v)
+    c.pq_set_codebooks(cb)
+    c.index_build(rng.integers(0, 256, (200000, M)).astype(np.uint8), T=2)
+    c.index_upload()
+    check(c, rng.normal(0, 1, (200, 4 * M)).astype(np.float32), 500, FOREST)
 
 
 def test_beside_the_matrix_filter():
