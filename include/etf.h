@@ -386,7 +386,12 @@ int etf_index_build_device(etf_ctx *ctx, const uint8_t *codes, int64_t N, const 
 int etf_last_build_path(const etf_ctx *ctx, int32_t *out);
 
 /* Workspace (device bytes) that etf_adc / etf_search need for Q queries in the
- * given mode (k is ignored by etf_adc: pass 0).  Negative = error code. */
+ * given mode (k is ignored by etf_adc: pass 0).  Negative = error code.
+ * A workspace that was sized for a larger Q or k holds the smaller call too, unless
+ * "ws_cap_bytes" cuts one of them into batches.  Where a search puts its queries in
+ * order (option "prune_filter") this is the size of that plan, up to four times the
+ * plain one's; in a smaller workspace that holds the plain plan (its size is the one
+ * under "prune_filter" -1) the search takes that, with the same results. */
 int64_t etf_workspace_bytes(const etf_ctx *ctx, int64_t Q, int k, int mode);
 
 /* Precomputed distance tables (paper: Eq. 1, first term, on each group's own

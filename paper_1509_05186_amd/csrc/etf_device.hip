@@ -208,12 +208,12 @@ int pow2_at_least_host(int n)
 int tmax_class(int T);
 int pick_G(int width, int K);
 bool lds_eligible(int M, int K, int T, const int32_t *chunk_begin);
-void plan_prune(const etf_ctx *ctx, int64_t Q, bool ws_cap_given, Plan &P);
+void plan_prune(const etf_ctx *ctx, int64_t Q, Plan &P);
 
-int make_plan(const etf_ctx *ctx, int64_t Q, int k, int mode, bool search, Plan &P, int64_t ws_cap = 0)
+// ordered: a search's plan on queries in order, if plan_prune takes them
+int make_plan(const etf_ctx *ctx, int64_t Q, int k, int mode, bool search, Plan &P, int64_t ws_cap = 0, bool ordered = false)
 {
-    const bool ws_cap_given = ws_cap > 0;
-    if (!ws_cap_given) ws_cap = ctx->opt.ws_cap_bytes;
+    if (ws_cap <= 0) ws_cap = ctx->opt.ws_cap_bytes;
     const HostIndex &ix = ctx->idx;
     if (!ix.built) return fail(ctx, ETF_ESTATE, "no index: call etf_index_build first");
     if (Q <= 0) return fail(ctx, ETF_EINVAL, "Q must be positive");
@@ -276,7 +276,7 @@ int make_plan(const etf_ctx *ctx, int64_t Q, int k, int mode, bool search, Plan 
     // 16-bit tables: built for rows of 64 and 32 bytes (M = 8 and M = 16 at K = 256); other shapes keep the float32 sums
     P.fx16 = search && P.lds_path && P.use_tau && ctx->opt.lds_filter == 2 && !ctx->opt.force_fallback && !ix.has_term &&
              (M == 8 || M == 16) && std::max(2, pick_G(M, K)) == (M == 8 ? 4 : 8);
-    if (P.fx16) plan_prune(ctx, Q, ws_cap_given, P);
+    if (P.fx16 && ordered) plan_prune(ctx, Q, P);
     P.ctx_path = !P.lds_path && tmax_class(ix.T) != 0 && mode != ETF_MODE_FLAT && ctx->opt.traversal != 1;
     for (int t = 1; t < ix.T; ++t)  // the register-context kernels address a tree's result table with 32-bit offsets
         if (ix.tree[t].U >= ((int64_t)1 << 24)) P.ctx_path = false;
@@ -288,7 +288,9 @@ int make_plan(const etf_ctx *ctx, int64_t Q, int k, int mode, bool search, Plan 
                 for (int l = 0; l + 1 < tr.D; ++l) per_tile += al256(tr.nI[l] * QT * 4);
             per_tile += al256(tr.U * QT * 4);
         }
-    const int64_t gmin_row = P.prune ? std::max<int64_t>(P.gstride, 1024 * P.near_wgs) : P.gstride;
+    // (at most 4096 groups, and 1024 minima of each of at most four workgroups: room for those however many a call's Q asks for, so that
+    // the workspace of a larger call holds the plan of a smaller one)
+    const int64_t gmin_row = P.prune ? 4096 : P.gstride;
     if (search) {
         if (P.use_tau) per_tile += al256(gmin_row * QT * 4);
         per_tile += (int64_t)QT * (12 + (int64_t)P.C * 8);
@@ -337,6 +339,24 @@ int make_plan(const etf_ctx *ctx, int64_t Q, int k, int mode, bool search, Plan 
         }
     }
     P.total = off;
+    return ETF_OK;
+}
+
+// The plan of a search: on queries in order where the rule takes them and the workspace (ws_bytes) holds that, else the plain one.  Which
+// workspaces are too small is for the plain plan to say: its size grows with Q and k, the other's does not (it is not taken for
+// a large k).  bytes: of a workspace that holds either, more than the plain one's also where the cap gives the ordered plan a smaller
+// batch: a caller can tell from the size which of them a workspace is for.
+int plan_search(const etf_ctx *ctx, int64_t Q, int k, int mode, int64_t ws_cap, int64_t ws_bytes, Plan &P, int64_t &bytes)
+{
+    int rc = make_plan(ctx, Q, k, mode, true, P, ws_cap);
+    if (rc) return rc;
+    bytes = P.total;
+    if (!P.fx16 || ws_cap > 0) return ETF_OK;  // (a scratch array of a given size has no room for the lists)
+    Plan O;
+    rc = make_plan(ctx, Q, k, mode, true, O, 0, true);
+    if (rc || !O.prune) return rc;
+    bytes = std::max(bytes + 256, O.total);
+    if (ws_bytes >= bytes) P = O;
     return ETF_OK;
 }
 
@@ -726,12 +746,12 @@ bool lds_eligible(int M, int K, int T, const int32_t *chunk_begin)
 // the worst took 1.4 times as long (k of 400 in 270 000 encodings).  Fewer queries have less in common: from 1000 on, with twice
 // the pairs, between 0.93 and 4.2 times as fast on 198 problems (N 3 to 20 million), half of them at least 1.4 times; 256 queries on 17
 // million encodings 0.97.
-void plan_prune(const etf_ctx *ctx, int64_t Q, bool ws_cap_given, Plan &P)
+void plan_prune(const etf_ctx *ctx, int64_t Q, Plan &P)
 {
     const HostIndex &ix = ctx->idx;
     const Options &opt = ctx->opt;
-    // a workspace of a given size (etf_search_static) has no room for the lists; the experiments' options mean the plain walk
-    if (opt.prune_filter < 0 || ws_cap_given || opt.lds_blocks > 0 || opt.lds16_context == 0 || opt.metric != 0) return;
+    // (the experiments' options mean the plain walk)
+    if (opt.prune_filter < 0 || opt.lds_blocks > 0 || opt.lds16_context == 0 || opt.metric != 0) return;
     if (ix.Nd >= ((int64_t)1 << 26) || ix.Nd < 64) return;  // (candidate records and byte offsets of records; whole blocks)
     if (opt.prune_filter > 0) {
         if (Q < 1000 || ix.Nd < ((int64_t)1 << 18) || ix.Nd < 3000 * (int64_t)P.k || (double)Q * (double)ix.Nd < (double)opt.prune_filter * (Q < 2048 ? 2.0 : 1.0)) return;
@@ -1176,9 +1196,10 @@ extern "C" int64_t etf_workspace_bytes(const etf_ctx *ctx, int64_t Q, int k, int
 {
     if (!ctx) return ETF_EINVAL;
     Plan P;
-    int rc = make_plan(ctx, Q, k, mode, k > 0, P);
+    int64_t bytes = 0;
+    int rc = k > 0 ? plan_search(ctx, Q, k, mode, 0, 0, P, bytes) : make_plan(ctx, Q, k, mode, false, P);
     if (rc) return rc;
-    return P.total;
+    return k > 0 ? bytes : P.total;
 }
 
 // =============================================================================================
@@ -1420,7 +1441,8 @@ static int search_impl(etf_ctx *ctx, const float *queries, int64_t Q, int k, int
     if (rc) return rc;
     if (!out_ids || !out_dist) return fail(ctx, ETF_EINVAL, "output pointer is null");
     Plan P;
-    rc = make_plan(ctx, Q, k, mode, true, P, ws_cap);
+    int64_t bytes = 0;
+    rc = plan_search(ctx, Q, k, mode, ws_cap, ws_bytes, P, bytes);
     if (rc) return rc;
     if (ws_bytes < P.total) {
         if (ws_cap > 0)

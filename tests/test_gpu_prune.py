@@ -5,6 +5,7 @@ Sizes lie around the blocks of 64 encodings, the sub-tiles of 32 and 16 queries 
 import numpy as np
 import pytest
 
+from test_host_order_plan import context
 from test_gpu_parity import FOREST, TREE, Problem, etf, torch
 
 pytestmark = pytest.mark.gpu
@@ -78,6 +79,24 @@ def test_a_bound_that_the_nearest_blocks_do_not_better(M):
 def test_beside_the_matrix_filter():
     p = Problem(d=128, M=16, K=256, N=30000, Q=400, ntrain=3000, seed=5)
     check(p.ctx(T=4, sample_min=1 << 14, cand_cap=8192, matrix_filter=0), p.q, 20, FOREST)
+
+
+def test_workspaces_of_larger_calls():
+    """One workspace for the largest call serves the smaller ones: on queries in order where it holds that plan, else as they come."""
+    c = context(300000, device=0, prune_filter=1)
+    c.set_stream(torch.cuda.current_stream().cuda_stream)
+    c.index_upload()
+    q = torch.randn((1100, 32), device="cuda", generator=torch.Generator("cuda").manual_seed(1))
+    for Q, k, n, m, ordered in ((1100, 101, 1100, 99, False), (1100, 300, 1000, 50, False), (1100, 300, 1000, 10, True), (1100, 100, 1001, 100, True), (1100, 100, 999, 100, False)):
+        ws = c.alloc_workspace(Q, k, FOREST)
+        ids, dist = c.search(q[:n], m, FOREST, ws=ws)
+        assert (c.last_kept_encodings() > 0) == ordered
+        own = c.search(q[:n], m, FOREST)
+        assert (c.last_kept_encodings() > 0) == (n >= 1000)
+        assert torch.equal(ids, own[0]) and torch.equal(dist, own[1])
+    ws = torch.empty(c.workspace_bytes(1100, 101, FOREST) - 256, dtype=torch.uint8, device="cuda")
+    with pytest.raises(etf.EtfError):
+        c.search(q, 101, FOREST, ws=ws[(-ws.data_ptr()) % 256:])
 
 
 def test_batches_of_a_small_workspace():

@@ -7,18 +7,17 @@ import paper_1509_05186_amd as etf
 FOREST = etf.ETF_MODE_FOREST
 
 
-def context(N, M=8, groups=40, seed=0, T=2, d=None, **opts):
+def context(N, M=8, groups=40, seed=0, T=2, device=None, **opts):
     """Codes around `groups` centres: a few neighbouring codewords in every chunk, and a number in the last three that makes them distinct."""
     rng = np.random.default_rng(seed)
-    d = d or 4 * M
     centre = rng.integers(0, 248, (groups, M))[rng.integers(0, groups, N)]
     codes = (centre + rng.integers(0, 8, (N, M))).astype(np.uint8)
     i = np.arange(N)
     codes[:, M - 3], codes[:, M - 2], codes[:, M - 1] = i >> 16, (i >> 8) & 255, i & 255
-    c = etf.Context(device=None)
+    c = etf.Context(device=device)
     for name, v in opts.items():
         c.set_option(name, v)
-    c.pq_set_codebooks(rng.normal(0, 1, (M, 256, d // M)).astype(np.float32))
+    c.pq_set_codebooks(rng.normal(0, 1, (M, 256, 4)).astype(np.float32))
     c.index_build(codes, T=T)
     return c
 
@@ -36,3 +35,29 @@ def test_a_batch_s_kept_blocks_fit_32_bits(M):
     most = (2**32 - 1) // ((N + 63) // 64) // (M // 4) * 64   # queries of a batch
     assert size(c, 0, most + most // 50, 10) == size(c, 0, most, 10)
     assert size(c, 0, most // 2, 10) < size(c, 0, most, 10)
+
+
+@pytest.fixture(scope="module")
+def clustered():
+    return context(300000)
+
+
+def test_the_workspace_of_a_larger_call_holds_a_smaller_one(clustered):
+    """A search takes the plain plan where the ordered one does not fit: that has to fit any workspace sized for a larger call.  With
+    the same k the ordered one fits too."""
+    c = clustered
+    for Q in (1000, 1100, 3200, 3232, 10000):
+        for k in (1, 30, 99, 100, 101, 300):
+            assert size(c, 1, Q, k) >= size(c, -1, Q, k)
+    assert size(c, 1, 10000, 99) > size(c, 1, 10000, 101) == size(c, -1, 10000, 101)  # (queries are put in order up to k = 100)
+    for k in (10, 50, 100):
+        sizes = [size(c, 1, Q, k) for Q in range(1000, 12000, 32)]
+        assert sizes == sorted(sizes)
+    try:
+        for cap in (4 << 20, 64 << 20, 256 << 20, 1 << 30):
+            c.set_option("ws_cap_bytes", cap)
+            for Q in (1000, 3232, 10000):
+                for k in (1, 50, 101):
+                    assert size(c, 0, Q, k) >= size(c, -1, Q, k)
+    finally:
+        c.set_option("ws_cap_bytes", 8 << 30)
