@@ -175,7 +175,8 @@ struct Plan {
     bool search = false;
     int k = 0;
     int64_t tiles_total = 0;  // ceil(Q / 64)
-    int64_t NT = 0;           // tiles per batch
+    int64_t NT = 0;           // tiles per batch that the workspace has room for
+    int64_t step = 0;         // tiles per batch of a search
     int64_t items = 0;        // candidates per query: N (flat) or distinct encodings
     int64_t S = 0;            // threshold sample size
     int gsize = 1;            // sample entries per group (only group minima are kept)
@@ -190,7 +191,8 @@ struct Plan {
     bool fx16 = false;        // ... on 16-bit tables (k_lds16)
     bool prune = false;       // ... on queries in the order of their nearest codewords, and on the parts of the index that a group of them needs
     int shift = 0, nblk = 0;  // the index in blocks of 2^shift x 64 encodings
-    int near_blocks = 0, near_wgs = 1;  // blocks a closer bound is taken from, by that many workgroups
+    int64_t near = 0;         // encodings a closer bound is taken from ...
+    int near_blocks = 0, near_wgs = 1;  // ... which is that many blocks, by that many workgroups
     int64_t o_counter = 0, o_lutT = 0, o_gmin = 0, o_tau = 0, o_bm = 0, o_cnt = 0, o_flag = 0, o_cand = 0;
     int64_t o_keys = 0, o_perm = 0, o_sorted = 0, o_span = 0, o_list = 0, o_kind = 0, o_count = 0, o_near = 0, o_units = 0, o_least = 0, o_state = 0;
     int64_t o_part[ETF_MAX_M][ETF_MAX_M];
@@ -208,9 +210,11 @@ int pow2_at_least_host(int n)
 int tmax_class(int T);
 int pick_G(int width, int K);
 bool lds_eligible(int M, int K, int T, const int32_t *chunk_begin);
-void plan_prune(const etf_ctx *ctx, int64_t Q, Plan &P);
+bool order_pays(const etf_ctx *ctx, int64_t Q, int k);
+void plan_prune(const etf_ctx *ctx, Plan &P);
+int near_workgroups(const etf_ctx *ctx, int64_t Q, const Plan &P);
 
-// ordered: a search's plan on queries in order, if plan_prune takes them
+// ordered: a search's plan on queries in order, if order_pays takes its batches
 int make_plan(const etf_ctx *ctx, int64_t Q, int k, int mode, bool search, Plan &P, int64_t ws_cap = 0, bool ordered = false)
 {
     if (ws_cap <= 0) ws_cap = ctx->opt.ws_cap_bytes;
@@ -276,7 +280,7 @@ int make_plan(const etf_ctx *ctx, int64_t Q, int k, int mode, bool search, Plan 
     // 16-bit tables: built for rows of 64 and 32 bytes (M = 8 and M = 16 at K = 256); other shapes keep the float32 sums
     P.fx16 = search && P.lds_path && P.use_tau && ctx->opt.lds_filter == 2 && !ctx->opt.force_fallback && !ix.has_term &&
              (M == 8 || M == 16) && std::max(2, pick_G(M, K)) == (M == 8 ? 4 : 8);
-    if (P.fx16 && ordered) plan_prune(ctx, Q, P);
+    if (P.fx16 && ordered && order_pays(ctx, Q, k)) plan_prune(ctx, P);
     P.ctx_path = !P.lds_path && tmax_class(ix.T) != 0 && mode != ETF_MODE_FLAT && ctx->opt.traversal != 1;
     for (int t = 1; t < ix.T; ++t)  // the register-context kernels address a tree's result table with 32-bit offsets
         if (ix.tree[t].U >= ((int64_t)1 << 24)) P.ctx_path = false;
@@ -298,8 +302,18 @@ int make_plan(const etf_ctx *ctx, int64_t Q, int k, int mode, bool search, Plan 
     }
     int64_t nt = ws_cap / std::max<int64_t>(per_tile + 4096, 1);
     P.NT = std::max<int64_t>(1, std::min<int64_t>(nt, P.tiles_total));
-    // (k_units adds up a batch's kept blocks in 32 bits, and cuts as many units as o_units holds only if that sum is right)
-    if (P.prune) P.NT = std::min<int64_t>(P.NT, (int64_t)UINT32_MAX / ((int64_t)P.nblk * (M / 4)));
+    P.step = P.NT;
+    if (P.prune) {
+        // (k_units adds up a batch's kept blocks in 32 bits, and cuts as many units as o_units holds only if that sum is right)
+        P.NT = std::min<int64_t>(P.NT, (int64_t)UINT32_MAX / ((int64_t)P.nblk * (M / 4)));
+        // It is the batch that is put in order, so the rule is asked about that; batches of one size leave no small last one.  (10 000
+        // queries on 700 000 encodings under a cap of 256 MB, batches of 960: 3.9 ms, plain 2.2; under 64 MB, batches of 192: 14.8, plain 3.0.)
+        const int64_t batches = (P.tiles_total + P.NT - 1) / P.NT;
+        P.step = (P.tiles_total + batches - 1) / batches;
+        const int64_t batch = std::min<int64_t>(Q, P.step * QT);
+        P.prune = order_pays(ctx, batch, k);
+        P.near_wgs = near_workgroups(ctx, batch, P);
+    }
     // offsets
     int64_t off = 0;
     auto take = [&](int64_t bytes) {
@@ -746,24 +760,29 @@ bool lds_eligible(int M, int K, int T, const int32_t *chunk_begin)
 // the worst took 1.4 times as long (k of 400 in 270 000 encodings).  Fewer queries have less in common: from 1000 on, with twice
 // the pairs, between 0.93 and 4.2 times as fast on 198 problems (N 3 to 20 million), half of them at least 1.4 times; 256 queries on 17
 // million encodings 0.97.
-void plan_prune(const etf_ctx *ctx, int64_t Q, Plan &P)
+bool order_pays(const etf_ctx *ctx, int64_t Q, int k)
 {
     const HostIndex &ix = ctx->idx;
     const Options &opt = ctx->opt;
     // (the experiments' options mean the plain walk)
-    if (opt.prune_filter < 0 || opt.lds_blocks > 0 || opt.lds16_context == 0 || opt.metric != 0) return;
-    if (ix.Nd >= ((int64_t)1 << 26) || ix.Nd < 64) return;  // (candidate records and byte offsets of records; whole blocks)
-    if (opt.prune_filter > 0) {
-        if (Q < 1000 || ix.Nd < ((int64_t)1 << 18) || ix.Nd < 3000 * (int64_t)P.k || (double)Q * (double)ix.Nd < (double)opt.prune_filter * (Q < 2048 ? 2.0 : 1.0)) return;
-        const HostTree &t0 = ix.tree[0];
-        if (t0.D < 2) return;
-        const double prefixes = (double)(t0.nI[1] + t0.nL[1] + t0.nL[0]), pairs = (double)ix.K * ix.K;
-        if (prefixes > ((double)ix.Nd <= 0.75 * (double)ix.N ? 0.5 : 0.25) * pairs * -std::expm1(-(double)ix.Nd / pairs)) return;
-    }
+    if (opt.prune_filter < 0 || opt.lds_blocks > 0 || opt.lds16_context == 0 || opt.metric != 0) return false;
+    if (ix.Nd >= ((int64_t)1 << 26) || ix.Nd < 64) return false;  // (candidate records and byte offsets of records; whole blocks)
+    if (opt.prune_filter == 0) return true;
+    if (Q < 1000 || ix.Nd < ((int64_t)1 << 18) || ix.Nd < 3000 * (int64_t)k || (double)Q * (double)ix.Nd < (double)opt.prune_filter * (Q < 2048 ? 2.0 : 1.0)) return false;
+    const HostTree &t0 = ix.tree[0];
+    if (t0.D < 2) return false;
+    const double prefixes = (double)(t0.nI[1] + t0.nL[1] + t0.nL[0]), pairs = (double)ix.K * ix.K;
+    return prefixes <= ((double)ix.Nd <= 0.75 * (double)ix.N ? 0.5 : 0.25) * pairs * -std::expm1(-(double)ix.Nd / pairs);
+}
+
+// the sample, the lists and the blocks of a search that order_pays takes
+void plan_prune(const etf_ctx *ctx, Plan &P)
+{
+    const HostIndex &ix = ctx->idx;
+    const Options &opt = ctx->opt;
     P.prune = true;
     while ((ix.Nd + ((int64_t)64 << P.shift) - 1) / ((int64_t)64 << P.shift) > PRUNE_BLOCKS) ++P.shift;
     P.nblk = (int)((ix.Nd + ((int64_t)64 << P.shift) - 1) / ((int64_t)64 << P.shift));
-    const int64_t Qs = ix.M == 8 ? 32 : 16, subs = (std::min<int64_t>(Q, 1 << 16) + Qs - 1) / Qs;
     // The bound's sample only has to find the neighbourhood: a 128th of the index will do, at least an eighth of the sample (its
     // order is scattered: a part of it is a sample too).  The bound itself comes from the nearest blocks; but a query to whose
     // neighbours those do not lead keeps the sample's, and the longest list that a query can have has room for twice the candidates
@@ -783,15 +802,23 @@ void plan_prune(const etf_ctx *ctx, int64_t Q, Plan &P)
     }
     while (opt.cand_cap == 0 && P.C < 2.0 * reach / (double)P.S + 2048.0 && P.C < (1u << 17)) P.C <<= 1;
     P.near_blocks = (int)std::max<int64_t>(1, near >> (6 + P.shift));
-    // 1024 minima a workgroup, and enough of them for k to lie in different ones
+    P.near = near;
+}
+
+// the workgroups that take a sub-tile's closer bound: 1024 minima each, and enough of them for k to lie in different ones
+int near_workgroups(const etf_ctx *ctx, int64_t Q, const Plan &P)
+{
+    const int64_t Qs = ctx->idx.M == 8 ? 32 : 16, subs = (std::min<int64_t>(Q, 1 << 16) + Qs - 1) / Qs;
     int64_t best = -1;
+    int n = 4;
     for (int wgs = P.k <= 400 ? 1 : P.k <= 800 ? 2 : 4; wgs <= 4; wgs *= 2) {
-        const int64_t cost = ((subs * wgs + 255) / 256) * (5000 + near / wgs) + (subs * 100 + 6000) * wgs;  // (and k_tau's time)
+        const int64_t cost = ((subs * wgs + 255) / 256) * (5000 + P.near / wgs) + (subs * 100 + 6000) * wgs;  // (and k_tau's time)
         if (best < 0 || cost < best) {
             best = cost;
-            P.near_wgs = wgs;
+            n = wgs;
         }
     }
+    return n;
 }
 
 template <int MODE, bool CTX, bool FX = false, bool TERM = false>
@@ -1458,8 +1485,8 @@ static int search_impl(etf_ctx *ctx, const float *queries, int64_t Q, int k, int
     const bool flat = mode == ETF_MODE_FLAT;
     uint32_t *counter = reinterpret_cast<uint32_t *>(w + P.o_counter);
     ctx->last_flag_count = counter;
-    for (int64_t t0 = 0; t0 < P.tiles_total; t0 += P.NT) {
-        const int64_t tiles = std::min<int64_t>(P.NT, P.tiles_total - t0);
+    for (int64_t t0 = 0; t0 < P.tiles_total; t0 += P.step) {
+        const int64_t tiles = std::min<int64_t>(P.step, P.tiles_total - t0);
         const int64_t q0 = t0 * QT;
         const int64_t nq = std::min<int64_t>(tiles * QT, Q - q0);
         const int64_t nql = tiles * QT;

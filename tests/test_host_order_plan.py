@@ -61,3 +61,22 @@ def test_the_workspace_of_a_larger_call_holds_a_smaller_one(clustered):
                     assert size(c, 0, Q, k) >= size(c, -1, Q, k)
     finally:
         c.set_option("ws_cap_bytes", 8 << 30)
+
+
+def test_the_rule_goes_by_the_batch(clustered):
+    """A cap that leaves batches of fewer than 1000 queries leaves the plain plan."""
+    c = clustered
+    try:
+        one = size(c, 1, 1024, 10)
+        for cap in (one * 2, one + one // 8):
+            c.set_option("ws_cap_bytes", cap)
+            assert size(c, 1, 10000, 10) > size(c, -1, 10000, 10)
+        for cap in (one - one // 8, one // 2, one // 8):
+            c.set_option("ws_cap_bytes", cap)
+            assert size(c, 1, 10000, 10) == size(c, -1, 10000, 10)
+        # the pairs are the batch's too
+        c.set_option("ws_cap_bytes", one * 5)
+        assert size(c, 2500 * 300000, 10000, 10) > size(c, -1, 10000, 10)
+        assert size(c, 9000 * 300000, 10000, 10) == size(c, -1, 10000, 10)
+    finally:
+        c.set_option("ws_cap_bytes", 8 << 30)
