@@ -954,12 +954,13 @@ int launch_order(etf_ctx *ctx, const Plan &P, char *ws, const float *queries, in
 }
 
 // what every sub-tile needs of the index (mm: k_mm16 runs behind, and leaves it the blocks of queries that need little)
-int launch_prune(etf_ctx *ctx, const Plan &P, char *ws, const OutArgs &o, int64_t nql, uint32_t *loose, bool again)
+int launch_prune(etf_ctx *ctx, const Plan &P, char *ws, const OutArgs &o, int64_t nql, uint32_t *flag, uint32_t *loose, bool again)
 {
     PruneArgs a;
     memset(&a, 0, sizeof a);
     a.lutT = reinterpret_cast<const float *>(ws + P.o_lutT);
-    a.tau = o.tau;
+    a.tau = const_cast<float *>(o.tau);
+    a.flag = flag;
     a.least = reinterpret_cast<float *>(ws + P.o_least);
     a.nql = nql;
     a.again = again;
@@ -1584,13 +1585,13 @@ static int search_impl(etf_ctx *ctx, const float *queries, int64_t Q, int k, int
                 if (rc) return rc;
             }
             if (P.prune) {
-                rc = launch_prune(ctx, P, w, o, nql, nullptr, false);
+                rc = launch_prune(ctx, P, w, o, nql, flag, la.loose, false);
                 if (rc) return rc;
                 rc = launch_lds16_list<WALK_NEAR>(ctx, P, w, ecodes, ix.Nd, o);
                 if (rc) return rc;
                 rc = launch_tau(ctx, P, o, nql, flag, nullptr, LooseArgs{}, true);
                 if (rc) return rc;
-                rc = launch_prune(ctx, P, w, o, nql, la.loose, true);
+                rc = launch_prune(ctx, P, w, o, nql, flag, la.loose, true);
                 if (rc) return rc;
             }
             if (mm) {

@@ -3263,8 +3263,12 @@ __global__ __launch_bounds__(256) void k_tau(const float *__restrict__ gmin, int
             else lo = mid + 1;
         }
         bound = S >= k ? hi : 0x7F800000u;
-        // (the bound that is there stands too; and hi was a bound only if there are k vectors at all)
-        if (MANY) bound = min(count(hi) >= k ? hi : 0x7F800000u, __float_as_uint(tau[ql]));
+        if (MANY) {
+            // (the bound that is there stands too, also the one below everything that k_prune gives a query whose tables are not
+            // finite; and hi was a bound only if there are k vectors at all)
+            const float t = tau[ql];
+            bound = t < 0.f ? __float_as_uint(-1.f) : min(count(hi) >= k ? hi : 0x7F800000u, __float_as_uint(t));
+        }
         if (la.room) {
             nn = 0.f;
             for (int j = lane; j < la.d; j += 64) {
@@ -3300,8 +3304,10 @@ __global__ __launch_bounds__(256) void k_tau(const float *__restrict__ gmin, int
     }
     if (lane == 0) {
         tau[ql] = __uint_as_float(bound);
-        cnt[ql] = 0u;
-        flag[ql] = 0u;
+        if (!MANY) {  // (no candidates yet, and k_prune's flags stand)
+            cnt[ql] = 0u;
+            flag[ql] = 0u;
+        }
     }
 }
 

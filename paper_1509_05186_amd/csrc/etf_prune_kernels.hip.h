@@ -170,7 +170,8 @@ __global__ __launch_bounds__(256) void k_order_gather(const float *__restrict__ 
 // ------------------------------------------------------------------------------------------------
 struct PruneArgs {
     const float *lutT;     // [tiles][M][K][64]
-    const float *tau;      // [tiles*64]
+    float *tau;            // [tiles*64]
+    uint32_t *flag;        // [tiles*64] set to 1 for the exact kernel
     float *least;          // [4][tiles*64] the sum of a query's least entries, those of the first three chunks
     int64_t nql;           // tiles*64
     const uint2 *span;     // [nblk]
@@ -246,7 +247,7 @@ __global__ __launch_bounds__(1024) void k_prune(PruneArgs a)
     }
     __syncthreads();
     if (t < Qs) {
-        const float tau = a.tau[col + t];
+        float tau = a.tau[col + t];
         float sum = 0.f;
         if (a.again) {
             sum = a.least[col + t];
@@ -258,8 +259,15 @@ __global__ __launch_bounds__(1024) void k_prune(PruneArgs a)
 #pragma unroll
             for (int m = 0; m < 3; ++m) a.least[(m + 1) * a.nql + col + t] = low[m][t] = __uint_as_float(least[m][t]);
         }
+        // A query without a finite entry in some chunk (a NaN or an infinity in it, or its squares are infinite) has no finite distance:
+        // the exact selection answers it, and a bound below everything keeps it from keeping all of the index for its sub-tile.
+        if (!a.again && tau >= 0.f && sum == inf) {
+            tau = a.tau[col + t] = -1.f;
+            a.flag[col + t] = 1u;
+            if (a.loose) a.loose[(col + t) / MM_Q] = 1u;  // (k_mm16 scales a block by its queries: not for it)
+        }
         if (tau == inf) endless = 1u;  // (fewer than k finite distances in the sample: everything is kept)
-        // a column past the last query has a negative bound, that of a query with a NaN is below nothing: inv < 0, nothing matters
+        // a column past the last query has a negative bound too: inv < 0, nothing matters
         float room = tau >= 0.f ? fmaxf(fmaf(tau, 1.52587890625e-5f, tau) - sum, 1e-30f) : -1.f;
         if (!a.again) {
             // Nearness goes by the geometric mean of the query's s and the least one: where a cluster has fewer encodings than the

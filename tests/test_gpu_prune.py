@@ -5,8 +5,8 @@ Sizes lie around the blocks of 64 encodings, the sub-tiles of 32 and 16 queries 
 import numpy as np
 import pytest
 
-from test_host_order_plan import context
-from test_gpu_parity import FOREST, TREE, Problem, etf, torch
+from test_host_order_plan import clusters, context, near
+from test_gpu_parity import FOREST, TREE, Problem, etf, say, torch
 
 pytestmark = pytest.mark.gpu
 
@@ -117,6 +117,35 @@ def test_queries_that_are_not_finite():
     torch.cuda.synchronize()
     keep = [i for i in range(200) if i not in (5, 40, 190)]
     assert torch.equal(got[0][keep], want[0][keep]) and torch.equal(got[1][keep], want[1][keep])
+
+
+@pytest.mark.parametrize("M,mm", [(8, -1), (16, -1), (16, 0)])
+def test_a_query_that_is_not_finite_costs_its_neighbours_nothing(M, mm):
+    """Such a query (a NaN or an infinity in one chunk, squares that are infinite) takes the exact selection, and its sub-tile keeps what
+    the others need."""
+    N, Q = 30000, 400
+    cb, codes = clusters(N, M)
+    q = near(cb, codes, Q)
+    c = context(N, M, device=0, prune_filter=0, matrix_filter=mm, sample_min=1 << 13, cand_cap=8192)
+    c.set_stream(torch.cuda.current_stream().cuda_stream)
+    c.index_upload()
+    bad = q.copy()
+    bad[7, 5], bad[99], bad[150, :4], bad[251, 8], bad[333] = np.nan, np.nan, np.inf, -np.inf, 3e38
+    wrong = [7, 99, 150, 251, 333]
+    fine = [i for i in range(Q) if i not in wrong]
+    want = c.search(torch.from_numpy(q).cuda(), 10, FOREST)
+    clean = c.last_kept_encodings()
+    got = c.search(torch.from_numpy(bad).cuda(), 10, FOREST)
+    kept = c.last_kept_encodings()
+    assert c.last_fallback_count() == len(wrong)
+    assert torch.equal(got[0][fine], want[0][fine]) and torch.equal(got[1][fine], want[1][fine])
+    c.set_option("prune_filter", -1)
+    plain = c.search(torch.from_numpy(bad).cuda(), 10, FOREST)
+    assert torch.equal(got[0], plain[0]) and torch.equal(got[1].nan_to_num(), plain[1].nan_to_num())
+    whole = 30016 * ((Q * M // 4 + 63) // 64)   # encodings that all sub-tiles look at when nothing is left out
+    say("kept", clean, kept, "of", whole)
+    assert 0 < clean < 0.3 * whole
+    assert kept < clean + 0.05 * whole          # (five sub-tiles that keep everything: a fifth or a tenth; the order moves a little)
 
 
 def test_replays_of_a_graph():

@@ -7,17 +7,33 @@ import paper_1509_05186_amd as etf
 FOREST = etf.ETF_MODE_FOREST
 
 
-def context(N, M=8, groups=40, seed=0, T=2, device=None, **opts):
-    """Codes around `groups` centres: a few neighbouring codewords in every chunk, and a number in the last three that makes them distinct."""
+def clusters(N, M=8, groups=40, seed=0):
+    """Codebooks of 32 tight groups of 8 codewords, and codes around `groups` centres: one of those groups in every chunk, and a number in
+    the last three, whose codewords are small, that makes the codes distinct.  M x 4 dimensions."""
     rng = np.random.default_rng(seed)
-    centre = rng.integers(0, 248, (groups, M))[rng.integers(0, groups, N)]
+    cb = (np.repeat(rng.normal(0, 3, (M, 32, 4)), 8, axis=1) + rng.normal(0, 0.1, (M, 256, 4))).astype(np.float32)
+    cb[M - 3:] *= 0.03
+    centre = 8 * rng.integers(0, 32, (groups, M))[rng.integers(0, groups, N)]
     codes = (centre + rng.integers(0, 8, (N, M))).astype(np.uint8)
     i = np.arange(N)
     codes[:, M - 3], codes[:, M - 2], codes[:, M - 1] = i >> 16, (i >> 8) & 255, i & 255
+    return cb, codes
+
+
+def near(cb, codes, n, seed=1):
+    """n queries beside vectors of the index."""
+    rng = np.random.default_rng(seed)
+    row = codes[rng.integers(0, len(codes), n)]
+    x = cb[np.arange(cb.shape[0])[None, :], row].reshape(n, -1)
+    return x + rng.normal(0, 0.05, x.shape).astype(np.float32)
+
+
+def context(N, M=8, groups=40, seed=0, T=2, device=None, **opts):
+    cb, codes = clusters(N, M, groups, seed)
     c = etf.Context(device=device)
     for name, v in opts.items():
         c.set_option(name, v)
-    c.pq_set_codebooks(rng.normal(0, 1, (M, 256, 4)).astype(np.float32))
+    c.pq_set_codebooks(cb)
     c.index_build(codes, T=T)
     return c
 
