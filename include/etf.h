@@ -437,8 +437,9 @@ int etf_last_fallback_count(etf_ctx *ctx, int64_t *out);
  * cores (option "matrix_filter"; diagnostic).  The count lies beside the one above and the same holds for it. */
 int etf_last_matrix_blocks(etf_ctx *ctx, int64_t *out);
 
-/* Encodings that the filter pass of the most recent search looked at, summed over its groups of 32 (M = 8) or 16 (M = 16) queries, where it left
- * out what they do not need (option "prune_filter"; diagnostic); 0 where it looked at all.  The same holds for this count. */
+/* Encodings that the filter pass of the most recent search looked at, in whole blocks and summed over its groups of 32 (M = 8) or 16
+ * (M = 16) queries, where the queries were put in order (option "prune_filter"; diagnostic); 0 where they were not, and where the
+ * matrix cores filtered every group (then etf_last_matrix_blocks is not 0).  The same holds for this count. */
 int etf_last_kept_encodings(etf_ctx *ctx, int64_t *out);
 
 /* ---- IVFADC on the merged, sorted encodings -------------------------------- */

@@ -521,7 +521,8 @@ class Context:
         return int(v.value)
 
     def last_kept_encodings(self) -> int:
-        """Encodings the last search's filter looked at, summed over its groups of 32 (M = 8) or 16 queries; 0: all of them."""
+        """Encodings the last search's filter looked at, summed over its groups of 32 (M = 8) or 16 queries; 0: its queries were not put
+        in order, or the matrix cores filtered all of them (last_matrix_blocks)."""
         v = ctypes.c_int64()
         self._ck(self._lib.etf_last_kept_encodings(self._h, ctypes.byref(v)))
         return int(v.value)

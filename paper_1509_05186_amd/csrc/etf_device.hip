@@ -1014,7 +1014,7 @@ int launch_lds16_list(etf_ctx *ctx, const Plan &P, char *ws, const uint32_t *rec
     if (WALK == WALK_KEPT) {
         hipLaunchKernelGGL(k_units, dim3(1), dim3(1024), 0, st, reinterpret_cast<const uint32_t *>(ws + P.o_count), subs, 64 << P.shift, o.done,
                            MM_Q / (128 / G), la.state, reinterpret_cast<uint4 *>(ws + P.o_units),
-                           reinterpret_cast<uint32_t *>(ws + P.o_counter) + 2);
+                           reinterpret_cast<uint64_t *>(ws + P.o_counter) + 1);
         LAUNCH_CHECK(ctx, "k_units");
     }
     constexpr bool cx = WALK == WALK_KEPT;  // (without the context at M = 16: option lds16_context)
@@ -1764,10 +1764,10 @@ extern "C" int etf_last_matrix_blocks(etf_ctx *ctx, int64_t *out) { return last_
 
 extern "C" int etf_last_kept_encodings(etf_ctx *ctx, int64_t *out)
 {
-    int64_t items = 0;
-    int rc = last_count(ctx, 3, &items);
+    int64_t upper = 0;  // (words 2 and 3: a 64-bit count)
+    int rc = last_count(ctx, 3, &upper);
     if (rc == ETF_OK) rc = last_count(ctx, 2, out);
-    if (rc == ETF_OK) *out *= items;
+    if (rc == ETF_OK) *out |= upper << 32;
     return rc;
 }
 

@@ -433,7 +433,7 @@ __global__ __launch_bounds__(1024) void k_prune(PruneArgs a)
 // ------------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(1024) void k_units(const uint32_t *__restrict__ count, int subs, int block_items, const uint32_t *__restrict__ done,
                                                 int subs_per_done, uint32_t *__restrict__ state, uint4 *__restrict__ units,
-                                                uint32_t *__restrict__ kept)
+                                                uint64_t *__restrict__ kept)
 {
     __shared__ uint32_t wsum[16], first[1024], many[1024];
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
@@ -482,8 +482,7 @@ __global__ __launch_bounds__(1024) void k_units(const uint32_t *__restrict__ cou
     if (t == 0) {
         state[0] = base;
         state[1] = 0u;
-        kept[0] += total;  // (over the batches of a call: etf_last_kept_encodings)
-        kept[1] = (uint32_t)block_items;
+        *kept += (uint64_t)total * (uint32_t)block_items;  // (over the batches of a call: etf_last_kept_encodings)
     }
 }
 

@@ -106,6 +106,24 @@ def test_batches_of_a_small_workspace():
     check(c, p.q, 10, FOREST)
 
 
+@pytest.mark.parametrize("M,group", [(8, 32), (16, 16)])
+def test_the_count_of_what_was_looked_at(M, group):
+    """Codes without structure and a large k: every group of queries keeps every block of 64, in one batch and in several."""
+    rng = np.random.default_rng(4)
+    N, Q = 20001, 333
+    c = etf.Context(device=0, stream=torch.cuda.current_stream().cuda_stream)
+    for name, v in (("cand_cap", 16384), ("matrix_filter", -1), ("sample_min", 1 << 13), ("prune_filter", 0)):
+        c.set_option(name, v)
+    c.pq_set_codebooks(rng.normal(0, 1, (M, 256, 4)).astype(np.float32))
+    c.index_build(rng.integers(0, 256, (N, M)).astype(np.uint8), T=2)
+    c.index_upload()
+    q = torch.from_numpy(rng.normal(0, 1, (Q, 4 * M)).astype(np.float32)).cuda()
+    for cap in (8 << 30, int(c.workspace_bytes(64, 900, FOREST) * 2.5)):
+        c.set_option("ws_cap_bytes", cap)
+        c.search(q, 900, FOREST)
+        assert c.last_kept_encodings() == -(-Q // group) * -(-N // 64) * 64
+
+
 def test_queries_that_are_not_finite():
     p = Problem(d=32, M=8, K=256, N=20000, Q=200, ntrain=3000, seed=13)
     c = p.ctx(T=2, sample_min=1 << 13, cand_cap=8192)
