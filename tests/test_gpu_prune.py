@@ -60,6 +60,45 @@ def test_clusters_of_few_encodings():
     check(p.ctx(T=2, sample_min=1 << 13, cand_cap=8192), p.q, 200, FOREST)
 
 
+def clustered(N, M, **opts):
+    c = etf.Context(device=0, stream=torch.cuda.current_stream().cuda_stream)
+    for name, v in opts.items():
+        c.set_option(name, v)
+    cb, codes = clusters(N, M)
+    c.pq_set_codebooks(cb)
+    c.index_build_device(torch.from_numpy(codes).cuda(), T=2)
+    assert c.index_stats()["n_distinct"] == N
+    return c, cb, codes
+
+
+@pytest.mark.parametrize("M", [8, 16])
+@pytest.mark.parametrize("N", [64 * 313, 64 * 313 + 1, 64 * 313 + 63])
+@pytest.mark.parametrize("Q", [256, 1100])   # at M = 8: two workgroups for the closer bound of a sub-tile, one
+def test_edges_of_the_distinct_encodings(M, N, Q):
+    c, cb, codes = clustered(N, M, sample_min=1 << 13, cand_cap=8192, matrix_filter=-1)
+    check(c, near(cb, codes, Q), 10, FOREST)
+
+
+@pytest.mark.parametrize("M,shift,over", [(8, 1, 1), (8, 1, 64), (8, 1, 128 * 7), (8, 2, 65), (8, 2, 193), (16, 1, 127), (16, 2, 256 * 3 + 64)])
+def test_blocks_of_several_runs_of_64(M, shift, over):
+    """Above 2^16 x 64 encodings a block of the lists is 2 or 4 runs of 64, the last of which may lie past the end of the index."""
+    N = (1 << (21 + shift)) + over
+    c, cb, codes = clustered(N, M, matrix_filter=-1, prune_filter=0)
+    last = near(cb, codes[-64:], 8, seed=2)   # (the highest numbers; and vectors of the last encodings in the tree's order)
+    end = codes[np.lexsort(codes[:, ::-1].T)[-200:]]
+    q = torch.from_numpy(np.concatenate([near(cb, codes, 130), last, near(cb, end, 64, seed=3)])).cuda()
+    got = c.search(q, 20, FOREST)
+    assert c.last_fallback_count() == 0
+    group = 32 if M == 8 else 16
+    kept, whole = c.last_kept_encodings(), -(-len(q) // group) * N
+    say("kept %.3f" % (kept / whole))
+    assert 0 < kept < 0.5 * whole and kept % (64 << shift) == 0
+    c.set_option("prune_filter", -1)
+    want = c.search(q, 20, FOREST)
+    assert c.last_kept_encodings() == 0
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+
+
 @pytest.mark.parametrize("M", [8, 16])
 def test_a_bound_that_the_nearest_blocks_do_not_better(M):
     """The first three chunks tell nothing (their codewords are as good as one), the lists have room for what the whole sample's
@@ -79,6 +118,28 @@ def test_a_bound_that_the_nearest_blocks_do_not_better(M):
 def test_beside_the_matrix_filter():
     p = Problem(d=128, M=16, K=256, N=30000, Q=400, ntrain=3000, seed=5)
     check(p.ctx(T=4, sample_min=1 << 14, cand_cap=8192, matrix_filter=0), p.q, 20, FOREST)
+
+
+def test_the_matrix_filter_and_the_lists_share_a_batch():
+    """Two blocks of 128 queries beside vectors of the index, which keep little, and two of queries far from everything, which keep it all.  The
+    latter lie at a group of codewords of the first chunk that no vector has, so that they come last."""
+    M, N = 16, 30000
+    cb, codes = clusters(N, M)
+    codes[:, 0] %= 248
+    rng = np.random.default_rng(6)
+    far = rng.normal(0, 3, (256, M, 4)).astype(np.float32)
+    far[:, 0] = cb[0, 248:].mean(axis=0)
+    q = np.concatenate([near(cb, codes, 256), far.reshape(256, -1)])[rng.permutation(512)]
+    c = etf.Context(device=0, stream=torch.cuda.current_stream().cuda_stream)
+    for name, v in (("sample_min", 1 << 13), ("cand_cap", 8192), ("matrix_filter", 0), ("prune_filter", 0)):
+        c.set_option(name, v)
+    c.pq_set_codebooks(cb)
+    c.index_build(codes, T=2)
+    c.index_upload()
+    c.search(torch.from_numpy(q).cuda(), 20, FOREST)
+    say("blocks on the matrix cores", c.last_matrix_blocks(), "kept", c.last_kept_encodings())
+    assert 0 < c.last_matrix_blocks() < 4 and c.last_kept_encodings() > 0
+    check(c, q, 20, FOREST)
 
 
 def test_workspaces_of_larger_calls():

@@ -96,3 +96,40 @@ def test_the_rule_goes_by_the_batch(clustered):
         assert size(c, 9000 * 300000, 10000, 10) == size(c, -1, 10000, 10)
     finally:
         c.set_option("ws_cap_bytes", 8 << 30)
+
+
+def ordered(c, prune, Q, k, mode=FOREST):
+    c.set_option("prune_filter", -1)
+    plain = c.workspace_bytes(Q, k, mode)
+    c.set_option("prune_filter", prune)
+    return c.workspace_bytes(Q, k, mode) != plain
+
+
+def test_which_searches_are_put_in_order(clustered):
+    """2^31 pairs, twice as many below 2048 queries, 1000 queries, 3000 encodings for each of k."""
+    c, Nd = clustered, 300000
+    assert ordered(c, 1 << 31, 7159, 10) and not ordered(c, 1 << 31, 7158, 10)
+    assert ordered(c, 1, 1000, 10) and not ordered(c, 1, 999, 10)
+    assert ordered(c, 2048 * Nd, 2048, 10) and not ordered(c, 2048 * Nd + 1, 2048, 10)
+    assert ordered(c, 1000 * Nd, 2000, 10) and not ordered(c, 1000 * Nd + 1, 2000, 10) and not ordered(c, 1000 * Nd, 1999, 10)
+    assert ordered(c, 1, 2048, 100) and not ordered(c, 1, 2048, 101)
+    assert not ordered(c, -1, 10000, 10) and ordered(c, 0, 1, 10)
+    assert not ordered(c, 0, 10000, 10, etf.ETF_MODE_FLAT)
+    for name, value, default in (("metric", 1, 0), ("lds16_context", 0, 1), ("lds_blocks", 3, 0), ("lds_filter", 0, 2), ("lds_filter", 1, 2)):
+        c.set_option(name, value)
+        assert not ordered(c, 0, 10000, 10)
+        c.set_option(name, default)
+
+
+@pytest.mark.parametrize("N,yes", [((1 << 18) - 1, False), (1 << 18, True)])
+def test_small_indexes_are_not(N, yes):
+    assert ordered(context(N), 1, 2048, 10) == yes
+    assert ordered(context(N), 0, 2048, 10)
+
+
+def test_indexes_without_clusters_are_not():
+    rng = np.random.default_rng(0)
+    c = etf.Context(device=None)
+    c.pq_set_codebooks(rng.normal(0, 1, (8, 256, 4)).astype(np.float32))
+    c.index_build(rng.integers(0, 256, (300000, 8)).astype(np.uint8), T=2)
+    assert not ordered(c, 1, 2048, 10) and ordered(c, 0, 2048, 10)
