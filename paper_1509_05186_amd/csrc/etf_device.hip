@@ -1006,8 +1006,9 @@ int launch_lds16_list(etf_ctx *ctx, const Plan &P, char *ws, const uint32_t *rec
     la.ebegin = reinterpret_cast<const uint32_t *>(ctx->dev_base + ctx->lay.ebegin);
     la.gmin = o.gmin;
     la.gstride = 1024 * P.near_wgs;
-    // the filter: a workgroup per CU takes unit after unit
-    const dim3 grid = WALK == WALK_NEAR ? dim3((unsigned)P.near_wgs, (unsigned)subs) : dim3(256);
+    // (a grid has at most 65 535 workgroups along y: a million queries of 16-byte codes are more sub-tiles.)  The filter: a workgroup per
+    // CU takes unit after unit
+    const dim3 grid = WALK == WALK_NEAR ? dim3((unsigned)subs, (unsigned)P.near_wgs) : dim3(256);
     const float *lutT = reinterpret_cast<const float *>(ws + P.o_lutT);
     hipStream_t st = (hipStream_t)ctx->stream;
     ProfScope prof(ctx, WALK == WALK_NEAR ? ETF_K_SAMPLE : ETF_K_LDS16);

@@ -2241,7 +2241,7 @@ __device__ __forceinline__ bool find_share(uint32_t wg, uint32_t wgs, int blocks
 //     units cut here instead of in a launch, which cost 79 scalar registers too many, 0.6 of it).  WALK_NEAR: the least sums of the
 //     nearest blocks, for k_tau.
 //     grid (blocks, G / 2, tiles), or, behind k_mm16, (workgroups) for the sub-tiles of the blocks that it has not done
-//     (find_share), or (256) for WALK_KEPT, (workgroups per sub-tile, sub-tiles) for WALK_NEAR; block 1024, dynamic LDS
+//     (find_share), or (256) for WALK_KEPT, (sub-tiles, workgroups per sub-tile) for WALK_NEAR; block 1024, dynamic LDS
 //     lds_table_bytes(G) + lds16_aux_bytes(); G in {4, 8}.
 // ------------------------------------------------------------------------------------------------
 typedef unsigned short u16x8 __attribute__((ext_vector_type(8)));
@@ -2299,7 +2299,7 @@ __global__ __launch_bounds__(1024) void k_lds16(const uint32_t *__restrict__ rec
         tile = (int)cs / (QT / Qs);
         sub = (int)cs % (QT / Qs);
     } else if (WALK == WALK_NEAR) {
-        cs = blockIdx.y;
+        cs = blockIdx.x;
         tile = (int)cs / (QT / Qs);
         sub = (int)cs % (QT / Qs);
         near = la.near[cs];
@@ -2554,7 +2554,7 @@ __global__ __launch_bounds__(1024) void k_lds16(const uint32_t *__restrict__ rec
                     many[u] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(re, lg * 4 + 4, (int)((base + u * IPS) * 4), 0) -
                               (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(re, lg * 4, (int)((base + u * IPS) * 4), 0);
             };
-            const uint32_t waves = gridDim.x * 16u, g = blockIdx.x * 16u + (uint32_t)w, n64 = to << la.shift;
+            const uint32_t waves = gridDim.y * 16u, g = blockIdx.y * 16u + (uint32_t)w, n64 = to << la.shift;
             u16x8 lo[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) lo[u] = (unsigned short)0xFFFFu;

@@ -167,6 +167,32 @@ def test_batches_of_a_small_workspace():
     check(c, p.q, 10, FOREST)
 
 
+def test_more_sub_tiles_than_a_grid_has_rows():
+    """A batch of a million queries, 65 537 groups of 16: more than the 65 535 workgroups that a launch may have along y."""
+    N, M, Q = 20000, 16, 65536 * 16 + 5
+    rng = np.random.default_rng(11)
+    cb, codes = clusters(N, M)
+    cb = np.ascontiguousarray(cb[:, :, :1])     # one dimension a chunk: small queries
+    c = etf.Context(device=0, stream=torch.cuda.current_stream().cuda_stream)
+    for name, v in (("cand_cap", 2048), ("sample_min", 1 << 13), ("matrix_filter", -1), ("prune_filter", 0), ("ws_cap_bytes", 1 << 36)):
+        c.set_option(name, v)
+    c.pq_set_codebooks(cb)
+    c.index_build(codes, T=2)
+    c.index_upload()
+    assert c.workspace_bytes(Q, 5, FOREST) < 1 << 36   # (one batch)
+    q = torch.from_numpy(near(cb, codes, 4096)).cuda()[torch.from_numpy(rng.integers(0, 4096, Q)).cuda()]
+    q += torch.randn(q.shape, device="cuda", generator=torch.Generator("cuda").manual_seed(2)) * 0.01
+    got = c.search(q, 5, FOREST)
+    kept = c.last_kept_encodings()
+    say("kept %.3f" % (kept / (65537 * N)), "exact selections", c.last_fallback_count())
+    assert kept > 0
+    c.set_option("prune_filter", -1)
+    c.set_option("ws_cap_bytes", 1 << 33)
+    want = c.search(q, 5, FOREST)
+    assert c.last_kept_encodings() == 0
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+
+
 @pytest.mark.parametrize("M,group", [(8, 32), (16, 16)])
 def test_the_count_of_what_was_looked_at(M, group):
     """Codes without structure and a large k: every group of queries keeps every block of 64, in one batch and in several."""
