@@ -194,7 +194,7 @@ struct Plan {
     int64_t near = 0;         // encodings a closer bound is taken from ...
     int near_blocks = 0, near_wgs = 1;  // ... which is that many blocks, by that many workgroups
     int64_t o_counter = 0, o_lutT = 0, o_gmin = 0, o_tau = 0, o_bm = 0, o_cnt = 0, o_flag = 0, o_cand = 0;
-    int64_t o_keys = 0, o_perm = 0, o_sorted = 0, o_span = 0, o_list = 0, o_kind = 0, o_count = 0, o_near = 0, o_units = 0, o_least = 0, o_state = 0;
+    int64_t o_keys = 0, o_perm = 0, o_sorted = 0, o_span = 0, o_list = 0, o_kind = 0, o_count = 0, o_near = 0, o_units = 0, o_least = 0, o_state = 0, o_again = 0;
     int64_t o_part[ETF_MAX_M][ETF_MAX_M];
     int64_t o_leafp[ETF_MAX_M];
     int64_t total = 0;
@@ -298,7 +298,7 @@ int make_plan(const etf_ctx *ctx, int64_t Q, int k, int mode, bool search, Plan 
     if (search) {
         if (P.use_tau) per_tile += al256(gmin_row * QT * 4);
         per_tile += (int64_t)QT * (12 + (int64_t)P.C * 8);
-        if (P.prune) per_tile += (int64_t)QT * (ctx->d * 4 + 6 + 16) + (int64_t)(M / 4) * (3 * (int64_t)P.nblk + 36);
+        if (P.prune) per_tile += (int64_t)QT * (ctx->d * 4 + 6 + 16 + 4) + (int64_t)(M / 4) * (3 * (int64_t)P.nblk + 36);
     }
     int64_t nt = ws_cap / std::max<int64_t>(per_tile + 4096, 1);
     P.NT = std::max<int64_t>(1, std::min<int64_t>(nt, P.tiles_total));
@@ -350,6 +350,7 @@ int make_plan(const etf_ctx *ctx, int64_t Q, int k, int mode, bool search, Plan 
             P.o_units = take((subs + 1024) * 16);  // a whole number for every sub-tile, 1024 or fewer beside
             P.o_least = take(P.NT * QT * 16);
             P.o_state = take((2 + (P.NT * QT + MM_Q - 1) / MM_Q) * 4);
+            P.o_again = take((1 + P.NT * QT) * 4);
         }
     }
     P.total = off;
@@ -944,7 +945,7 @@ int launch_order(etf_ctx *ctx, const Plan &P, char *ws, const float *queries, in
                        reinterpret_cast<const float *>(ctx->dev_base + L.codebooks), ord, keys);
     LAUNCH_CHECK(ctx, "k_order_keys");
     hipLaunchKernelGGL(k_order_sort, dim3(1), dim3(1024), 0, st, keys, nq, tiles * QT, perm, reinterpret_cast<uint32_t *>(ws + P.o_state),
-                       (int)(2 + (nq + MM_Q - 1) / MM_Q));
+                       (int)(2 + (nq + MM_Q - 1) / MM_Q), reinterpret_cast<uint32_t *>(ws + P.o_again));
     LAUNCH_CHECK(ctx, "k_order_sort");
     hipLaunchKernelGGL(k_order_gather, dim3((unsigned)((nq + 3) / 4 + (P.nblk + 255) / 256)), dim3(256), 0, st, queries, nq, ctx->d, perm,
                        reinterpret_cast<float *>(ws + P.o_sorted), reinterpret_cast<const uint8_t *>(ctx->dev_base + L.ecodes), ctx->idx.Nd,
@@ -1624,6 +1625,9 @@ static int search_impl(etf_ctx *ctx, const float *queries, int64_t Q, int k, int
         sa.out_dist = out_dist + q0 * k;
         sa.perm = P.prune ? reinterpret_cast<const uint32_t *>(w + P.o_perm) : nullptr;
         sa.flag = flag;
+        sa.again = P.prune ? reinterpret_cast<uint32_t *>(w + P.o_again) : nullptr;
+        sa.cnt_again = cnt;
+        sa.tau = tau;
         sa.bm = bm;
         // fixed-point candidates: rounding moves a sum by at most M units (truncated entries) plus 2^-24 relative per
         // entry and per float32 addition of the distance it stands for, 2^27 * (M + 1) * 2^-24 = 8 (M + 1) units at the
@@ -1677,6 +1681,25 @@ static int search_impl(etf_ctx *ctx, const float *queries, int64_t Q, int k, int
         ea.out_dist = sa.out_dist;
         ea.perm = sa.perm;
         ea.bm = bm;
+        if (P.prune) {  // (both end at once where no list overran)
+            RefillArgs ra;
+            ra.e = ea;
+            ra.queue = sa.again;
+            ra.tau = tau;
+            ra.cnt = cnt;
+            ra.cand = cand;
+            ra.C = P.C;
+            ra.stretch = 16384;
+            ProfScope prof(ctx, ETF_K_SELECT);
+            hipLaunchKernelGGL(k_refill, dim3(512), dim3(1024), 0, st, ra);
+            LAUNCH_CHECK(ctx, "k_refill");
+            sa.again = nullptr;  // (a list that overruns once more is the exact selection's)
+            sa.fx_margin = 0u;
+            sa.margins = nullptr;
+            sa.fx_first_pass = 0;
+            hipLaunchKernelGGL(k_select_refilled, dim3(256), dim3(256), select_lds_bytes(k), st, sa, ra.queue);
+            LAUNCH_CHECK(ctx, "k_select_refilled");
+        }
         {
             ProfScope prof(ctx, ETF_K_EXACT);
             hipLaunchKernelGGL(k_exact, dim3((unsigned)nq), dim3(256), 0, st, ea);

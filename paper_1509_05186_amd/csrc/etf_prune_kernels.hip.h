@@ -83,15 +83,16 @@ __global__ __launch_bounds__(1024) void k_order_keys(const float *__restrict__ q
 // Positions of the queries in the order of (codeword of chunk 0, codeword of chunk 1 mod 16): a counting sort by one workgroup
 // (4096 counts in LDS; queries of one codeword of chunk 1 stay together, and what a codeword of chunk 0 has, a few sub-tiles,
 // needs no finer division).  Inside a bin the order is whichever comes first; results do not depend on it.
-//     perm[position] = query.  Clears `words` of state.  grid 1, block 1024.
+//     perm[position] = query.  Clears `words` of state and the number of queries whose lists overran.  grid 1, block 1024.
 // ------------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(1024) void k_order_sort(const uint8_t *__restrict__ keys, int64_t nq, int64_t nql, uint32_t *__restrict__ perm,
-                                                     uint32_t *__restrict__ state, int words)
+                                                     uint32_t *__restrict__ state, int words, uint32_t *__restrict__ again)
 {
     __shared__ uint32_t bin[4096];
     __shared__ uint32_t wsum[16];
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
     for (int i = t; i < words; i += 1024) state[i] = 0u;
+    if (t == 0) again[0] = 0u;
     for (int i = t; i < 4096; i += 1024) bin[i] = 0u;
     __syncthreads();
     auto bin_of = [&](int64_t q) { return ((uint32_t)keys[q] << 4) | (keys[nql + q] & 15u); };

@@ -115,6 +115,41 @@ def test_a_bound_that_the_nearest_blocks_do_not_better(M):
     check(c, rng.normal(0, 1, (200, 4 * M)).astype(np.float32), 500, FOREST)
 
 
+@pytest.mark.parametrize("M,far,k,mm", [(8, 1, 10, -1), (8, 300, 100, -1), (16, 1, 20, -1), (16, 37, 1, 0), (16, 300, 300, -1)])
+def test_queries_whose_lists_overrun(M, far, k, mm):
+    """All distances from a query far away lie within the rounding of the 16-bit tables: every encoding is at or below its bound.  Its list
+    is made anew with the k-th distance of what the first one held; nothing is left to the exact selection, also in repeated calls."""
+    N, Q = 30000, 300
+    cb, codes = clusters(N, M)
+    q = near(cb, codes, Q)
+    q[np.random.default_rng(1).permutation(Q)[:far]] += 20000.0
+    c = context(N, M, device=0, matrix_filter=mm, sample_min=1 << 13, cand_cap=4096)
+    c.set_stream(torch.cuda.current_stream().cuda_stream)
+    c.index_upload()
+    check(c, q, k, FOREST)
+    qd = torch.from_numpy(q).cuda()
+    c.set_option("prune_filter", -1)
+    want = c.search(qd, k, FOREST)
+    assert c.last_fallback_count() >= far
+    c.set_option("prune_filter", 0)
+    c.set_option("ws_cap_bytes", int(c.workspace_bytes(64, k, FOREST) * 2.5))   # batches of two tiles
+    got = c.search(qd, k, FOREST)
+    assert c.last_fallback_count() == 0
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+
+
+def test_lists_that_overrun_twice():
+    """1000 neighbours in a list of 2048 out of 30 000: some 15 000 encodings are at or below the second bound."""
+    N, M = 30000, 8
+    cb, codes = clusters(N, M)
+    q = near(cb, codes, 70)
+    q[5] += 20000.0
+    c = context(N, M, device=0, matrix_filter=-1, sample_min=1 << 13, cand_cap=2048)
+    c.set_stream(torch.cuda.current_stream().cuda_stream)
+    c.index_upload()
+    check(c, q[:6], 1000, FOREST, fallback=1)
+
+
 def test_beside_the_matrix_filter():
     p = Problem(d=128, M=16, K=256, N=30000, Q=400, ntrain=3000, seed=5)
     check(p.ctx(T=4, sample_min=1 << 14, cand_cap=8192, matrix_filter=0), p.q, 20, FOREST)
