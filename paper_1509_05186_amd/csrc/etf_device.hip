@@ -752,15 +752,21 @@ bool lds_eligible(int M, int K, int T, const int32_t *chunk_begin)
 }
 
 // Whether a batch's queries are put in order and the index is pruned for them (etf_prune_kernels.hip.h).  What that costs grows with the
-// queries (0.25 ms for 10 000: order, two prunings, the second bound), what it saves with the pairs of query and encoding and with how
-// clustered the encodings are.  Of that the tree's second level tells: a clustered database has few of the two-chunk prefixes
+// queries (0.3 ms for 10 000: order, two prunings, the near walk and its bound), what it saves with the pairs of query and encoding and
+// with how clustered the encodings are.  Of that the tree's second level tells: a clustered database has few of the two-chunk prefixes
 // that independent chunks would have (64 to 4096 overlapping clusters: 0.05 to 0.25; one Gaussian 0.4 to 1, where nothing can be
 // left out), up to half of them where a large one has filled in the clusters' edges, and then many vectors share an encoding.
-// On 1033 random problems (N up to 4 million, 2048 to 10 000 queries, k up to 500, 6 to 120 dimensions a chunk)
-// this rule took 390: between 3.9 times and 0.96 times as fast, half of them at least 1.8 times; without its lines for k and the pairs
-// the worst took 1.4 times as long (k of 400 in 270 000 encodings).  Fewer queries have less in common: from 1000 on, with twice
-// the pairs, between 0.93 and 4.2 times as fast on 198 problems (N 3 to 20 million), half of them at least 1.4 times; 256 queries on 17
-// million encodings 0.97.
+// Measured as plain time over ordered time on random problems (N 0.06 to 12 million, 150 to 10 000 queries, k 2 to 1000, 6 to 32 dimensions
+// a chunk, M 8 and 16):
+//     taken, queries like the vectors     1198 problems: median 1.8, 5 % below 1.16, 13 below 1, the worst 0.88 (chunks of 6 or 8
+//                                         dimensions, where the plain walk has the matrix filter and few blocks are left out)
+//     below 1000 queries                  1872: median 0.53, 60 above 1, the best 1.8
+//     below 2^18 encodings                853: median 0.80, 122 above 1, 1.6
+//     below 3000 encodings for each of k  239: median 0.92, 99 above 1, 1.9
+//     below the pairs                     424: median 0.91, 151 above 1, 2.5
+//     too many prefixes                   421: median 0.95, 122 above 1, 3.6 (where most of the blocks are left out all the same)
+// Nothing is known here of the queries.  Those far from all vectors need all blocks and get a bound that lets through more candidates: of
+// the problems taken, with queries drawn evenly from the data's box, median 0.91, the worst 0.61; with a tenth of them so, 1.02 and 0.64.
 bool order_pays(const etf_ctx *ctx, int64_t Q, int k)
 {
     const HostIndex &ix = ctx->idx;

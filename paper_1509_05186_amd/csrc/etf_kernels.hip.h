@@ -2237,9 +2237,14 @@ __device__ __forceinline__ bool find_share(uint32_t wg, uint32_t wgs, int blocks
 //     Geometry, item walk, distance context and line layout are those of k_lds<G> (rows of 64 or 32 bytes, lines
 //     of 256 bytes, chunk order rotated per lane group); a sub-tile has 128 / G queries.
 //     WALK_KEPT: the blocks of 64 encodings that a sub-tile's list names, unit after unit of the work that k_units has cut.  The next
-//     block's records are requested a block ahead (as many pairs a second as the walk of everything; without that, and with the
-//     units cut here instead of in a launch, which cost 79 scalar registers too many, 0.6 of it).  WALK_NEAR: the least sums of the
-//     nearest blocks, for k_tau.
+//     block's records are requested a block ahead (without that, and with the units cut here instead of in a launch, which cost 79
+//     scalar registers too many, it ran at 0.6 of this rate).  At M = 8 it looks at 0.7 of the pairs a second that the walk of
+//     everything does (10 000 queries on 700 000 encodings: 0.40 ms for 0.21 of them, 1.31 for all): a step takes 44 clocks of the
+//     LDS pipe in place of 39 and 42 vector instructions in place of 34 (neighbours of a list are not neighbours in the tree: the
+//     context helps less; and every unit stages its tables), and the pipe is busy 0.55
+//     of the time in place of 0.66, the rest waits where units begin and end.  At M = 16, without the context, 0.67 of the pipe's
+//     time, 2.5 ms for 0.114 of 6.5 million encodings.
+//     WALK_NEAR: the least sums of the nearest blocks, for k_tau.  0.27 of the pipe's time at M = 8: 313 workgroups in two rounds of 256.
 //     grid (blocks, G / 2, tiles), or, behind k_mm16, (workgroups) for the sub-tiles of the blocks that it has not done
 //     (find_share), or (256) for WALK_KEPT, (sub-tiles, workgroups per sub-tile) for WALK_NEAR; block 1024, dynamic LDS
 //     lds_table_bytes(G) + lds16_aux_bytes(); G in {4, 8}.
@@ -2251,7 +2256,8 @@ __host__ __device__ constexpr int fx16_cap_bits(int M) { return M <= 4 ? 14 : M 
 
 enum { WALK_ALL = 0, WALK_KEPT = 1, WALK_NEAR = 2 };
 struct ListArgs {
-    const uint16_t *list;   // [sub-tiles][nblk] kept blocks of 2^shift x 64 encodings, nearest first (k_prune)
+    const uint16_t *list;   // [sub-tiles][nblk] kept blocks of 2^shift x 64 encodings (k_prune): all of them in any order, or, first, the nearest
+                            // classes and behind them the next one
     int nblk, shift;
     const uint4 *units;     // WALK_KEPT: sub-tile, part of its list
     uint32_t *state;        // WALK_KEPT: the number of units, the next one to take
@@ -3480,8 +3486,8 @@ __device__ __forceinline__ int pow2_at_least(int n)
 // S5b  final selection of one query from its candidate list (all encodings at or below the bound).
 //      Only the k closest candidate encodings can contribute; they are sorted, expanded into their
 //      vector ids (each encoding at most as many as are still needed), sorted by (distance, id), and
-//      the first k are written.  Anything that does not fit the fixed LDS buffers (candidate overflow,
-//      huge groups of exactly equal distances) is flagged for the exact whole-database kernel.
+//      the first k are written.  Anything that does not fit the fixed LDS buffers (huge groups of exactly equal
+//      distances) or its list (unless SelectArgs::again is there) is flagged for the exact whole-database kernel.
 //      grid (queries of the batch), block 256, dynamic LDS select_lds_bytes(k).
 // ------------------------------------------------------------------------------------------------
 // capacity of the kept list and of the expanded list: twice k rounded up to a power of two, at least 256

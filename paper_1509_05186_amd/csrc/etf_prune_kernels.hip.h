@@ -2,17 +2,18 @@
 //
 //     Queries that are near each other need the same few parts of a clustered database.  So the queries of a large batch are
 //     put in the order of their nearest codewords of the first two chunks before their tables are built (k_order_keys,
-//     k_order_sort, k_order_gather; of the kernels behind them only k_select and k_exact, which write a query's results,
-//     know of it).  Then, for every sub-tile of the 16-bit filter, k_prune finds the nodes of the tree's second level below
-//     which something can be at or below a query's bound: its table entry of chunk 0, plus that of chunk 1, plus the
-//     query's least entry of every other chunk, is at or below every sum under the node.  A block of consecutive encodings
-//     is kept if any prefix in its range is.  k_lds16<.., WALK_NEAR> takes a closer bound from the nearest of the kept blocks, and
-//     k_lds16<.., WALK_KEPT> walks the kept blocks only.
+//     k_order_sort, k_order_gather; of the kernels behind them only those that write a query's results know of it: k_select, k_refill's
+//     second selection and k_exact).  The index is taken in blocks of 64 encodings (or 2, 4, .. times that), which are ranges of the
+//     tree's leaves.  For every sub-tile of the 16-bit filter k_prune makes a table for each of the first three chunks: how much of what
+//     a query's bound leaves above its least sum an entry takes, least over the sub-tile's queries.  A block is kept if a prefix of
+//     three chunks in its range can stay within 1.  k_lds16<.., WALK_NEAR> takes a closer bound from the nearest of the kept blocks,
+//     k_prune goes over all blocks again with that, and k_lds16<.., WALK_KEPT> walks the blocks that are then kept.
 //     Nothing at or below a bound is lost: a float32 sum of at most 16 entries moves by less than 16 2^-24 of itself with the
 //     order of its additions, and the bound is widened by 2^-16 of itself.
-//     Measured (MI355X), 10^6 x 128 in 8 chunks, 64 overlapping clusters, 10 000 queries, k = 100: the filter pass 1.31 -> 0.38 ms (a fifth
-//     of the blocks kept, 220 candidates a query in place of 900), the bound's sample 0.34 -> 0.19, k_select 0.165 -> 0.12, against
-//     0.03 for the queries' order and two times 0.03 for k_prune: 1.86 -> 0.92 ms.  10^7 x 128 in 16 chunks, 1024 clusters: 15.1 -> 4.2.
+//     Measured (MI355X), 10^6 x 128 in 8 chunks, 64 overlapping clusters, 10 000 queries, k = 100: the filter pass 1.31 -> 0.40 ms (a fifth
+//     of the blocks kept, 220 candidates a query in place of 900), the bound's sample 0.33 -> 0.20 (the first 0.08, the near walk
+//     0.12), k_select 0.165 -> 0.13, against 0.03 for the queries' order, 0.05 and 0.03 for k_prune, 0.03 for the second k_tau and
+//     0.02 for k_units: 1.87 -> 0.94 ms.  10^7 x 128 in 16 chunks, 1024 clusters: 14.9 -> 4.1 to 4.4.
 #pragma once
 
 namespace etf {
@@ -38,7 +39,8 @@ __global__ __launch_bounds__(1024) void k_order_keys(const float *__restrict__ q
     float acc[16];
 #pragma unroll
     for (int c = 0; c < 16; ++c) acc[c] = 0.f;
-    // (at most eight pieces of four dimensions: of wide chunks every so many-th, which orders the queries as well)
+    // (pieces of four dimensions; of chunks of 64 dimensions and more every so many-th piece, eight to fifteen in all, which orders the
+    // queries as well)
     const int step = 4 * max(1, ds / 32);
     int j = 0;
     for (; j + 4 <= ds; j += step) {
@@ -167,7 +169,8 @@ __global__ __launch_bounds__(256) void k_order_gather(const float *__restrict__ 
 // `near_blocks` by that sum are what k_lds16<.., WALK_NEAR> takes a closer bound from: the sums in 255 classes, all of the
 // blocks of the classes that fit and of the next class every so many-th.
 //     again: with the closer bound, all kept blocks in any order; the least entries are there from the first call.
-//     Bound by the read of the sub-tile's tables, again by the chain of its steps.  grid (sub-tiles that hold a query), block 1024.
+//     Bound by the read of the sub-tile's tables (10 000 queries, 8 chunks of 700 000 encodings: 50 us; 16 chunks of 6.5 million: 172), again
+//     by the chain of its steps (30 and 101 us).  grid (sub-tiles that hold a query), block 1024.
 // ------------------------------------------------------------------------------------------------
 struct PruneArgs {
     const float *lutT;     // [tiles][M][K][64]
@@ -430,7 +433,7 @@ __global__ __launch_bounds__(1024) void k_prune(PruneArgs a)
 
 // ------------------------------------------------------------------------------------------------
 // The filter's work: the lists cut into about equal units, a whole number for every sub-tile, as many as give each compute unit one to
-// four.  grid 1, block 1024.
+// four.  Bound by the divisions of one workgroup, two for a unit (313 sub-tiles: 16 us, 625: 30 to 35).  grid 1, block 1024.
 // ------------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(1024) void k_units(const uint32_t *__restrict__ count, int subs, int block_items, const uint32_t *__restrict__ done,
                                                 int subs_per_done, uint32_t *__restrict__ state, uint4 *__restrict__ units,
