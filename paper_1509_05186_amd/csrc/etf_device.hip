@@ -760,11 +760,11 @@ bool lds_eligible(int M, int K, int T, const int32_t *chunk_begin)
 // a chunk, M 8 and 16):
 //     taken, queries like the vectors     1198 problems: median 1.8, 5 % below 1.16, 13 below 1, the worst 0.88 (chunks of 6 or 8
 //                                         dimensions, where the plain walk has the matrix filter and few blocks are left out)
-//     below 1000 queries                  1872: median 0.53, 60 above 1, the best 1.8
-//     below 2^18 encodings                853: median 0.80, 122 above 1, 1.6
-//     below 3000 encodings for each of k  239: median 0.92, 99 above 1, 1.9
-//     below the pairs                     424: median 0.91, 151 above 1, 2.5
-//     too many prefixes                   421: median 0.95, 122 above 1, 3.6 (where most of the blocks are left out all the same)
+//     below 1000 queries                  1872: median 0.53, 61 above 1, the best 1.8
+//     below 2^18 encodings                853: median 0.80, 128 above 1, 1.6
+//     below 3000 encodings for each of k  239: median 0.92, 100 above 1, 1.9
+//     below the pairs                     424: median 0.91, 154 above 1, 2.5
+//     too many prefixes                   421: median 0.95, 130 above 1, 3.6 (where most of the blocks are left out all the same)
 // Nothing is known here of the queries.  Those far from all vectors need all blocks and get a bound that lets through more candidates: of
 // the problems taken, with queries drawn evenly from the data's box, median 0.91, the worst 0.61; with a tenth of them so, 1.02 and 0.64.
 bool order_pays(const etf_ctx *ctx, int64_t Q, int k)

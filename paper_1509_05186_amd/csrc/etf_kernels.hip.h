@@ -2242,8 +2242,8 @@ __device__ __forceinline__ bool find_share(uint32_t wg, uint32_t wgs, int blocks
 //     everything does (10 000 queries on 700 000 encodings: 0.40 ms for 0.21 of them, 1.31 for all): a step takes 44 clocks of the
 //     LDS pipe in place of 39 and 42 vector instructions in place of 34 (neighbours of a list are not neighbours in the tree: the
 //     context helps less; and every unit stages its tables), and the pipe is busy 0.55
-//     of the time in place of 0.66, the rest waits where units begin and end.  At M = 16, without the context, 0.67 of the pipe's
-//     time, 2.5 ms for 0.114 of 6.5 million encodings.
+//     of the time in place of 0.66, with half as many waits again (units begin and end).  At M = 16, without the context, 0.67 of
+//     the pipe's time, 2.5 ms for 0.114 of 6.5 million encodings.
 //     WALK_NEAR: the least sums of the nearest blocks, for k_tau.  0.27 of the pipe's time at M = 8: 313 workgroups in two rounds of 256.
 //     grid (blocks, G / 2, tiles), or, behind k_mm16, (workgroups) for the sub-tiles of the blocks that it has not done
 //     (find_share), or (256) for WALK_KEPT, (sub-tiles, workgroups per sub-tile) for WALK_NEAR; block 1024, dynamic LDS
