@@ -3831,7 +3831,8 @@ __device__ __forceinline__ float exact_distance_row(const ExactArgs &a, const fl
 
 // ------------------------------------------------------------------------------------------------
 // Lists anew for the queries whose list overran (SelectArgs::again): every encoding whose float32 distance, associated as it is
-// returned, is at or below the k-th of the C encodings that the list held, so about k times what was in reach over C of them.  A
+// returned, is at or below the k-th of the C encodings that the list held: about k times what was in reach over C of them, and never more
+// than C where the list held more than half of that (2 C less what was in reach, k at least, are then among the nearest C).  A
 // pair of query and stretch of the index a workgroup at a time, one query's tables in LDS.
 //     What this is for: a query that is far from all vectors keeps a bound that lets through eight times what the whole sample's
 //     does, and where the distances to it differ little its list may not hold that.  The exact selection below is one workgroup's nine
