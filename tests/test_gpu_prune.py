@@ -141,15 +141,23 @@ def test_queries_whose_lists_overrun(M, far, k, mm):
 
 
 def test_lists_that_overrun_twice():
-    """1000 neighbours in a list of 2048 out of 30 000: some 15 000 encodings are at or below the second bound."""
+    """1000 neighbours in a list of 2048 out of 30 000: some 15 000 encodings are at or below the second bound, unless the first list happened to hold
+    half of the nearest ones, which it does not for 64 queries in different directions."""
     N, M = 30000, 8
     cb, codes = clusters(N, M)
+    rng = np.random.default_rng(5)
     q = near(cb, codes, 70)
-    q[5] += 20000.0
-    c = context(N, M, device=0, matrix_filter=-1, sample_min=1 << 13, cand_cap=2048)
+    q[:64] += (20000.0 * rng.choice([-1, 1], (64, q.shape[1]))).astype(np.float32)
+    c = context(N, M, device=0, matrix_filter=-1, sample_min=1 << 13, cand_cap=2048, prune_filter=0)
     c.set_stream(torch.cuda.current_stream().cuda_stream)
     c.index_upload()
-    check(c, q[:6], 1000, FOREST, fallback=1)
+    qd = torch.from_numpy(q).cuda()
+    got = c.search(qd, 1000, FOREST)
+    say("exact selections", c.last_fallback_count())
+    assert c.last_fallback_count() > 0 and c.last_kept_encodings() > 0
+    c.set_option("force_fallback", 1)
+    want = c.search(qd, 1000, FOREST)
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
 
 
 def test_beside_the_matrix_filter():
