@@ -13,7 +13,7 @@
 //     Measured (MI355X), 10^6 x 128 in 8 chunks, 64 overlapping clusters, 10 000 queries, k = 100: the filter pass 1.31 -> 0.40 ms (a fifth
 //     of the blocks kept, 220 candidates a query in place of 900), the bound's sample 0.33 -> 0.20 (the first 0.08, the near walk
 //     0.12), k_select 0.165 -> 0.13, against 0.03 for the queries' order, 0.05 and 0.03 for k_prune, 0.03 for the second k_tau and
-//     0.02 for k_units: 1.87 -> 0.94 ms.  10^7 x 128 in 16 chunks, 1024 clusters: 14.9 -> 4.1 to 4.4.
+//     0.01 for k_units: 1.87 -> 0.93 ms.  10^7 x 128 in 16 chunks, 1024 clusters: 14.9 -> 4.1 to 4.4.
 #pragma once
 
 namespace etf {
@@ -433,13 +433,14 @@ __global__ __launch_bounds__(1024) void k_prune(PruneArgs a)
 
 // ------------------------------------------------------------------------------------------------
 // The filter's work: the lists cut into about equal units, a whole number for every sub-tile, as many as give each compute unit one to
-// four.  Bound by the divisions of one workgroup, two for a unit (313 sub-tiles: 16 us, 625: 30 to 35).  grid 1, block 1024.
+// four.  Bound by the latency of one workgroup (313 sub-tiles: 7 us, 625: 11; with a wave for every sub-tile, its count read from memory again and
+// 64-bit divisions 16 and 35, which 10 000 queries on a million vectors paid 1 % for).  grid 1, block 1024.
 // ------------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(1024) void k_units(const uint32_t *__restrict__ count, int subs, int block_items, const uint32_t *__restrict__ done,
                                                 int subs_per_done, uint32_t *__restrict__ state, uint4 *__restrict__ units,
                                                 uint64_t *__restrict__ kept)
 {
-    __shared__ uint32_t wsum[16], first[1024], many[1024];
+    __shared__ uint32_t wsum[16], first[1024], many[1024], has[1024];
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
     auto weight = [&](int i) -> uint32_t { return i < subs && !(done && done[i / subs_per_done] != 0u) ? count[i] : 0u; };
     uint32_t sum = 0u;
@@ -473,12 +474,18 @@ __global__ __launch_bounds__(1024) void k_units(const uint32_t *__restrict__ cou
         }
         first[t] = at;
         many[t] = own;
+        has[t] = n;
+        // part j of the m parts of the n blocks of sub-tile i (m is at most 1025, as most is more than total / 1024: 32 bits do)
+        auto part = [&](uint32_t i, uint32_t n, uint32_t m, uint32_t j) { return make_uint4(i, n * j / m, n * (j + 1u) / m, 0u); };
+        // a few units are written by the sub-tile's thread, more by a wave (few sub-tiles of a large index have a hundred each)
+        constexpr uint32_t FEW = 8;
+        if (own <= FEW)
+            for (uint32_t j = 0; j < own; ++j) units[at + j] = part((uint32_t)i, n, own, j);
         __syncthreads();
-        // a wave a sub-tile, a lane a unit (few sub-tiles of a large index have a hundred units each)
         for (int k = w; k < 1024 && i0 + k < subs; k += 16) {
-            const uint32_t nk = weight(i0 + k), mk = many[k];
-            for (uint32_t j = (uint32_t)lane; j < mk; j += 64u)
-                units[first[k] + j] = make_uint4((uint32_t)(i0 + k), (uint32_t)((uint64_t)nk * j / mk), (uint32_t)((uint64_t)nk * (j + 1u) / mk), 0u);
+            const uint32_t mk = many[k];
+            if (mk <= FEW) continue;
+            for (uint32_t j = (uint32_t)lane; j < mk; j += 64u) units[first[k] + j] = part((uint32_t)(i0 + k), has[k], mk, j);
         }
         __syncthreads();
         base += all;
