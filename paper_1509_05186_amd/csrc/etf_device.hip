@@ -1653,11 +1653,6 @@ static int search_impl(etf_ctx *ctx, const float *queries, int64_t Q, int k, int
         for (int t = 0; t <= ETF_MAX_M; ++t) sa.chunk_begin[t] = 0;
         if (flat) sa.chunk_begin[1] = ix.M;
         else for (int t = 0; t <= ix.T; ++t) sa.chunk_begin[t] = ix.chunk_begin[t];
-        {
-            ProfScope prof(ctx, ETF_K_SELECT);
-            hipLaunchKernelGGL(k_select, dim3((unsigned)nq), dim3(256), select_lds_bytes(k), st, sa);
-        }
-        LAUNCH_CHECK(ctx, "k_select");
         ExactArgs ea;
         memset(&ea, 0, sizeof ea);
         ea.flag = flag;
@@ -1687,24 +1682,28 @@ static int search_impl(etf_ctx *ctx, const float *queries, int64_t Q, int k, int
         ea.out_dist = sa.out_dist;
         ea.perm = sa.perm;
         ea.bm = bm;
-        if (P.prune) {  // (both end at once where no list overran)
-            RefillArgs ra;
-            ra.e = ea;
-            ra.queue = sa.again;
-            ra.tau = tau;
-            ra.cnt = cnt;
-            ra.cand = cand;
-            ra.C = P.C;
-            ra.stretch = 16384;
+        {
             ProfScope prof(ctx, ETF_K_SELECT);
-            hipLaunchKernelGGL(k_refill, dim3(512), dim3(1024), 0, st, ra);
-            LAUNCH_CHECK(ctx, "k_refill");
-            sa.again = nullptr;  // (a list that overruns once more is the exact selection's)
-            sa.fx_margin = 0u;
-            sa.margins = nullptr;
-            sa.fx_first_pass = 0;
-            hipLaunchKernelGGL(k_select_refilled, dim3(256), dim3(256), select_lds_bytes(k), st, sa, ra.queue);
-            LAUNCH_CHECK(ctx, "k_select_refilled");
+            hipLaunchKernelGGL(k_select, dim3((unsigned)nq), dim3(256), select_lds_bytes(k), st, sa);
+            LAUNCH_CHECK(ctx, "k_select");
+            if (P.prune) {  // (both end at once where no list overran)
+                RefillArgs ra;
+                ra.e = ea;
+                ra.queue = sa.again;
+                ra.tau = tau;
+                ra.cnt = cnt;
+                ra.cand = cand;
+                ra.C = P.C;
+                ra.stretch = 16384;
+                hipLaunchKernelGGL(k_refill, dim3(512), dim3(1024), 0, st, ra);
+                LAUNCH_CHECK(ctx, "k_refill");
+                sa.again = nullptr;  // (a list that overruns once more is the exact selection's)
+                sa.fx_margin = 0u;
+                sa.margins = nullptr;
+                sa.fx_first_pass = 0;
+                hipLaunchKernelGGL(k_select_refilled, dim3(256), dim3(256), select_lds_bytes(k), st, sa, ra.queue);
+                LAUNCH_CHECK(ctx, "k_select_refilled");
+            }
         }
         {
             ProfScope prof(ctx, ETF_K_EXACT);
