@@ -28,9 +28,9 @@ HBM_PEAK_GBS = 8000.0          # MI355X HBM3E, published peak
 # Each figure carries the hash of the kernel sources it was measured on (kernel_source_hash below); a run on other
 # sources prints traffic: null.
 MEASURED_TRAFFIC_BYTES = {
-    ("cfg2", "lds16", "lds-resident"): (407.1e6, "a8d19f405551d364"),       # profiles/cfg2_forest_lds_resident.md
-    ("cfg2", "reduce", "register-context"): (9.350e9, "a8d19f405551d364"),  # profiles/cfg2_forest_register_context.md
-    ("cfg4", "lds16", "lds-resident"): (6.742e9, "a8d19f405551d364"),       # profiles/cfg4_forest_lds_resident.md (k_mm16, the class\'s other launch, moves nothing)
+    ("cfg2", "lds16", "lds-resident"): (399.6e6, "acb054feeed85b54"),       # profiles/cfg2_forest_lds_resident.md
+    ("cfg2", "reduce", "register-context"): (9.350e9, "acb054feeed85b54"),  # profiles/cfg2_forest_register_context.md
+    ("cfg4", "lds16", "lds-resident"): (6.636e9, "acb054feeed85b54"),       # profiles/cfg4_forest_lds_resident.md (k_mm16, the other launch of its class, moves nothing)
 }
 # LDS read bandwidth of the chip: 256 compute units x 256 bytes per clock x 2.4 GHz (a conflict-free 16-byte-per-lane
 # wave read, 1 KiB, occupies the LDS pipe for 4 clocks: SQ_LDS_IDX_ACTIVE minus SQ_LDS_BANK_CONFLICT per read)
